@@ -110,9 +110,12 @@ size_t gs_workspace_bytes(const gs_params *p);
 
 /* Tile shapes (valid gs_params.tile values are 1..gs_num_tiles()). The first
  * four select the single-step z-streaming kernel (tblock must be 1); the
- * others select the temporally blocked kernel, which fuses tblock steps per
+ * next five select the temporally blocked kernel, which fuses tblock steps per
  * pass (workgroups of 256 to 1024 lanes; the larger ones fuse fewer steps in
- * FP64, whose registers are twice as many). gs_tile_info reports the output
+ * FP64, whose registers are twice as many); the last three select the block
+ * kernel for small grids, which fuses tblock steps of one block of cells per
+ * workgroup (its planes per workgroup are fixed: zchunk has no effect).
+ * gs_tile_info reports the output
  * tile (tx cells by ty rows) of `tile` for a storage type and tblock, and the
  * largest tblock the tile accepts for that storage type. */
 int32_t gs_num_tiles(void);

@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -53,10 +54,17 @@ bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 // Tile indices: 1..num_tiles() select the single-step z-streaming kernel's
 // shapes; the next num_tb_shapes() indices select the temporally blocked
-// kernel's shapes (any tblock).
-int total_tiles() { return gs::num_tiles() + gs::num_tb_shapes(); }
-bool is_tb_tile(int tile) { return tile > gs::num_tiles(); }
-int tile_max_tblock(int tile, int storage) { return is_tb_tile(tile) ? gs::tb_max_T(tile - gs::num_tiles(), storage) : 1; }
+// kernel's shapes (any tblock), and the last num_blk_shapes() the block
+// kernel's (any tblock; z-chunks do not apply to them).
+int first_blk() { return gs::num_tiles() + gs::num_tb_shapes(); } // block shape s is tile first_blk() + s
+int total_tiles() { return first_blk() + gs::num_blk_shapes(); }
+bool is_blk_tile(int tile) { return tile > first_blk(); }
+bool is_tb_tile(int tile) { return tile > gs::num_tiles() && !is_blk_tile(tile); }
+int tile_max_tblock(int tile, int storage)
+{
+    if (is_blk_tile(tile)) return GS_MAX_TBLOCK;
+    return is_tb_tile(tile) ? gs::tb_max_T(tile - gs::num_tiles(), storage) : 1;
+}
 
 gs_status validate(const gs_params *p)
 {
@@ -249,12 +257,48 @@ gs_status check(gs_sim *s)
 // Smaller grids fuse two steps: in 256-lane workgroups below 4 M cells (more
 // workgroups for 256 CUs), above that in the 768-lane tile for FP64 and the
 // 512-lane one for the others. The single-step kernel (tiles 1..4) runs when
-// asked for.
+// asked for. The smallest and the narrowest grids take the block kernel
+// (default_block).
 double grid_cells(const gs_params &p) { return (double)p.nx * p.ny * p.nz; }
 bool large_grid(const gs_params &p) { return grid_cells(p) >= 64.0 * 1024 * 1024; }
 
+// Block kernel of small grids: shape (0: not taken) and steps per launch.
+// A z-streaming workgroup is a serial chain of planes, two barriers each: on
+// a grid that does not fill the chip a launch takes 8 to 10 us whatever its
+// size. A block is loaded at once, so while there are blocks for about every
+// CU a launch costs its latency and more fused steps pay (us per step, FP64
+// without noise, z-streaming default against the block kernel): 32^3 4.53 ->
+// 1.72 (8x4x4, four steps; 2.16 against 2.09 with noise, where the steps'
+// Philox blocks add up; 40^3, two blocks per CU: 2.23 with three, 2.40 with four), 48^3 4.77 ->
+// 2.41 (16x8x4, three), 64^3 4.89 -> 3.18 (16x8x8, three). With more blocks
+// than that their halos decide: an 80^3 grid still gains (6.49 -> 4.97,
+// 16x8x4, two steps), 88^3 ties, 96^3 loses 8 %, 128 x 106 x 75 15 %. The
+// z-streaming tile is 64 x 10 cells, so what it wastes on narrow rows counts
+// too: 16 x 250 x 250 18.6 -> 7.9, 32 x 200 x 200 11.6 -> 9.5, and
+// 16 x 600 x 600 72 -> 31 (16x8x8, one step), while 24 x 640 x 640 loses 20 %.
+struct BlockChoice {
+    int shape, T;
+};
+BlockChoice default_block(const gs_params &p)
+{
+    auto up = [](int n, int t) { return (double)((n + t - 1) / t); };
+    auto blocks = [&](int shape) {
+        const gs::BlkShape b = gs::blk_shape(shape);
+        return up(p.nx, b.bx) * up(p.ny, b.by) * up(p.nz, b.bz);
+    };
+    if (blocks(1) <= 512) return BlockChoice{1, blocks(1) <= 400 ? 4 : 3};
+    if (blocks(2) <= 256) return BlockChoice{2, 3};
+    if (blocks(3) <= 256) return BlockChoice{3, 3};
+    const double streamed = 64 * up(p.nx, 64) * 10 * up(p.ny, 10) * p.nz; // cells its tiles cover
+    if (grid_cells(p) < 4.0 * 1024 * 1024)
+        return blocks(2) <= 600 || 512 * blocks(2) <= 0.63 * streamed ? BlockChoice{2, 2} : BlockChoice{0, 0};
+    return !large_grid(p) && 1024 * blocks(3) <= 0.3 * streamed ? BlockChoice{3, 1} : BlockChoice{0, 0};
+}
+
 int default_tile(const gs_params &p)
 {
+    const BlockChoice b = default_block(p);
+    if (b.shape) return first_blk() + b.shape;
     const int tb = gs::num_tiles(); // tiles tb + 1 .. tb + 5 are the blocked shapes 1..5
     if (grid_cells(p) < 4.0 * 1024 * 1024) return tb + 1;
     if (!large_grid(p)) return p.storage == GS_F64 ? tb + 4 : tb + 2;
@@ -265,6 +309,8 @@ int default_tile(const gs_params &p)
 int default_tblock(const gs_params &p, int tile)
 {
     if (tile <= gs::num_tiles()) return 1;
+    const BlockChoice b = default_block(p);
+    if (is_blk_tile(tile)) return tile == first_blk() + b.shape ? b.T : 2;
     int T = 2;
     if (large_grid(p) && p.storage == GS_F64) T = 3;
     const int mt = tile_max_tblock(tile, p.storage);
@@ -288,6 +334,7 @@ const int k_zchunks[] = {4, 8, 16, 32, 64, 128, 256, 512};
 // Without the occupancy figures it falls back to fixed chunks.
 int default_zc(const gs_params &p, int tile, int tblock)
 {
+    if (is_blk_tile(tile)) return std::min(gs::blk_shape(tile - first_blk()).bz, p.nz);
     int cus = 0, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -368,7 +415,11 @@ hipError_t enqueue_steps(gs_sim *s, int64_t n, hipStream_t st, const uint64_t *t
         const int q = *parity;
         hipError_t e;
         int done = 1;
-        if (is_tb_tile(s->tile)) {
+        if (is_blk_tile(s->tile)) {
+            done = (int)(left < s->tblock ? left : s->tblock);
+            e = gs::launch_block(s->p.storage, done, s->tile - first_blk(), s->buf[q][0], s->buf[q][1],
+                                 s->buf[q ^ 1][0], s->buf[q ^ 1][1], a, st);
+        } else if (is_tb_tile(s->tile)) {
             done = (int)(left < s->tblock ? left : s->tblock);
             e = gs::launch_tblock(s->p.storage, done, s->tile - gs::num_tiles(), s->buf[q][0], s->buf[q][1],
                                   s->buf[q ^ 1][0], s->buf[q ^ 1][1], a, st);
@@ -414,7 +465,13 @@ gs_status gs_tile_info(int32_t tile, int32_t storage, int32_t tblock, int32_t *t
     if (storage_bytes(storage) == 0) return fail(GS_ERR_INVALID_ARG, "unknown storage type %d", storage);
     const int mt = tile_max_tblock(tile, storage);
     if (tblock < 1 || tblock > mt) return fail(GS_ERR_INVALID_ARG, "tblock %d outside [1, %d] for tile %d", tblock, mt, tile);
-    gs::TileShape t = is_tb_tile(tile) ? gs::tb_shape(tile - gs::num_tiles(), tblock) : gs::tile_shape(tile, storage);
+    gs::TileShape t;
+    if (is_blk_tile(tile)) {
+        const gs::BlkShape b = gs::blk_shape(tile - first_blk());
+        t = gs::TileShape{b.bx, b.by};
+    } else {
+        t = is_tb_tile(tile) ? gs::tb_shape(tile - gs::num_tiles(), tblock) : gs::tile_shape(tile, storage);
+    }
     if (tx) *tx = t.tx;
     if (ty) *ty = t.ty;
     if (max_tblock) *max_tblock = mt;
@@ -611,7 +668,8 @@ gs_status gs_tune(gs_sim *s, int32_t reps, gs_tune_entry *table, int32_t capacit
         for (int T = 1; T <= tile_max_tblock(tile, s->p.storage) && e == hipSuccess; ++T) {
             int last_zc = -1;
             for (int zi = 0; zi < (int)(sizeof k_zchunks / sizeof k_zchunks[0]) && e == hipSuccess; ++zi) {
-                const int zc = zcs[zi] < s->p.nz ? zcs[zi] : s->p.nz;
+                int zc = zcs[zi] < s->p.nz ? zcs[zi] : s->p.nz;
+                if (is_blk_tile(tile)) zc = default_zc(s->p, tile, T); // the block's own planes: one candidate
                 if (zc == last_zc) continue;
                 last_zc = zc;
                 s->tile = tile;
@@ -712,7 +770,7 @@ gs_status gs_step_graph(gs_sim *s, int64_t n_steps)
     if (e != hipSuccess) return hip_fail(e, "step counter");
     e = hipGraphLaunch(g.exec, s->stream);
     if (e != hipSuccess) return hip_fail(e, "graph launch");
-    const int64_t launches = is_tb_tile(s->tile) ? (n_steps + s->tblock - 1) / s->tblock : n_steps;
+    const int64_t launches = (n_steps + s->tblock - 1) / s->tblock; // tblock is 1 for the single-step tiles
     if (launches & 1) end_parity ^= 1;
     s->parity = end_parity;
     s->step += (uint64_t)n_steps;

@@ -98,6 +98,17 @@ int tb_batch_max_T(int shape, int storage);
 hipError_t launch_tblock(int storage, int T, int shape, const void *u, const void *v, void *un, void *vn,
                          const StepArgs &a, hipStream_t st);
 
+// Block sweep of small grids: T <= GS_MAX_TBLOCK steps (u, v) -> (un, vn) in
+// one launch, one block of blk_shape(shape) cells per workgroup, shapes
+// 1..num_blk_shapes().
+struct BlkShape {
+    int bx, by, bz;
+};
+int num_blk_shapes();
+BlkShape blk_shape(int shape);
+hipError_t launch_block(int storage, int T, int shape, const void *u, const void *v, void *un, void *vn,
+                        const StepArgs &a, hipStream_t st);
+
 // Batched sweep over independent simulations (device tables).
 struct SimDesc {
     void *buf[2][2];    // [parity][field] device buffers
