@@ -23,8 +23,10 @@ LIBDIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIBDIR, "libgs.so")
 BUILD = os.path.join(ROOT, "_build")
 
-SOURCES = ["gs_step.hip", "gs_tblock.hip", "gs_block.hip", "gs_aux.hip", "gs_surrogate.hip", "gs_api.cpp", "gs_batch.cpp",
-           "gs_surrogate_api.cpp", "gs_tunecache.cpp", "gs_noalloc.hip"]
+# (a source given as (file, n) is compiled with GS_TB_STORAGE=n: the blocked
+# kernels of one storage type each)
+SOURCES = [*(("gs_tblock.hip", n) for n in range(5)), "gs_step.hip", "gs_block.hip", "gs_aux.hip", "gs_surrogate.hip",
+           "gs_api.cpp", "gs_batch.cpp", "gs_surrogate_api.cpp", "gs_tunecache.cpp", "gs_noalloc.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -38,9 +40,15 @@ def hipcc() -> str:
     return p
 
 
-def _compile(src: str, extra: list[str]) -> str:
+def _object(src) -> str:
+    return os.path.join(BUILD, src + ".o" if isinstance(src, str) else f"{src[0]}.{src[1]}.o")
+
+
+def _compile(src, extra: list[str]) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    obj = os.path.join(BUILD, os.path.basename(src) + ".o")
+    obj = _object(src)
+    if not isinstance(src, str):
+        src, extra = src[0], [*extra, f"-DGS_TB_STORAGE={src[1]}"]
     cmd = [hipcc(), *FLAGS, *extra, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

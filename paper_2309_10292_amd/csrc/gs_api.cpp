@@ -252,8 +252,11 @@ gs_status check(gs_sim *s)
 // temporally blocked kernel at every size. Large grids (>= 64 M cells): FP64
 // fuses three steps in the 512-lane 64 x 22 tile; with noise the other
 // storage types fuse two steps in the same tile (the Philox blocks of deeper
-// fusion cost more than the traffic they save); without noise FP32 fuses two
-// steps in the 1024-lane tile and the 16-bit types two in the 512-lane one.
+// fusion cost more than the traffic they save); without noise the 16-bit types
+// fuse two steps in the 512-lane tile and FP32 three in the 1024-lane one,
+// where two are bound by HBM (1024^3: 1.64 ms per step against 1.80; 640^3 0.46
+// against 0.50), unless its tiles of 50 rows cover the grid worse than those of
+// two steps (512^3: 0.24 against 0.22).
 // Smaller grids fuse two steps: in 256-lane workgroups below 4 M cells (more
 // workgroups for 256 CUs), above that in the 768-lane tile for FP64 and the
 // 512-lane one for the others. The single-step kernel (tiles 1..4) runs when
@@ -313,6 +316,13 @@ int default_tblock(const gs_params &p, int tile)
     if (is_blk_tile(tile)) return tile == first_blk() + b.shape ? b.T : 2;
     int T = 2;
     if (large_grid(p) && p.storage == GS_F64) T = 3;
+    if (large_grid(p) && p.storage == GS_F32 && tile == gs::num_tiles() + 5) {
+        auto rows = [&](int depth) {
+            const int ty = gs::tb_shape(5, depth).ty;
+            return (double)((p.ny + ty - 1) / ty * ty);
+        };
+        if (rows(3) <= 1.05 * rows(2)) T = 3;
+    }
     const int mt = tile_max_tblock(tile, p.storage);
     return T < mt ? T : mt;
 }
@@ -384,12 +394,11 @@ gs::StepArgs make_args(const gs_sim *s)
     a.noise = s->p.noise;
     a.noise_s = std::ldexp(a.noise, -31);
     a.noise_h = std::ldexp(a.noise, -32);
-    a.Du_f = (float)a.Du;
-    a.Dv_f = (float)a.Dv;
+    a.Du6_f = (float)(a.Du / 6.0);
+    a.Dv6_f = (float)(a.Dv / 6.0);
     a.F_f = (float)a.F;
     a.FK_f = (float)a.FK;
     a.dt_f = (float)a.dt;
-    a.noise_f = (float)a.noise;
     a.noise_s_f = (float)a.noise_s;
     a.noise_h_f = (float)a.noise_h;
     a.seed = s->p.seed;

@@ -85,6 +85,7 @@ struct gs_batch {
     int cus;
     int version;
     bool dirty;
+    bool noise_32; // every grid's noise blocks have 32-bit indices
     BGraph graph;
 };
 
@@ -114,10 +115,9 @@ gs::StepArgs shared_coef(const gs_batch *b)
     a.noise = b->base.noise;
     a.noise_s = std::ldexp(a.noise, -31);
     a.noise_h = std::ldexp(a.noise, -32);
-    a.Du_f = (float)a.Du;
-    a.Dv_f = (float)a.Dv;
+    a.Du6_f = (float)(a.Du / 6.0);
+    a.Dv6_f = (float)(a.Dv / 6.0);
     a.dt_f = (float)a.dt;
-    a.noise_f = (float)a.noise;
     a.noise_s_f = (float)a.noise_s;
     a.noise_h_f = (float)a.noise_h;
     return a;
@@ -239,6 +239,7 @@ hipError_t enqueue_batch(gs_batch *b, int64_t n, hipStream_t st, const uint64_t 
             a.parity = par[gi];
             a.t = t_dev ? off : b->step + off;
             a.t_dev = t_dev;
+            a.noise_32 = b->noise_32;
             hipError_t e = gs::launch_tblock_batch(b->base.storage, d, g.shape, a, g.grid[d], st);
             if (e != hipSuccess) return e;
             par[gi] ^= 1;
@@ -342,6 +343,8 @@ gs_status gs_batch_init(const gs_params *base, int32_t n_sims, const int32_t *nx
     b->step = base->step0;
     b->cus = cus > 0 ? cus : 1;
     b->version = 0;
+    b->noise_32 = true;
+    for (int32_t i = 0; i < n_sims; ++i) b->noise_32 = b->noise_32 && gs::noise_fits_32(nx[i], ny[i], nz[i]);
     b->d_desc = (gs::SimDesc *)((char *)workspace + desc_offset());
     b->d_items = (gs::WorkItem *)((char *)workspace + items_offset(n_sims));
     {
@@ -591,6 +594,7 @@ gs_status gs_batch_tune(gs_batch *b, int32_t reps, gs_batch_tune_entry *table, i
                     a.parity = 0;
                     a.t = b->step;
                     a.t_dev = nullptr;
+                    a.noise_32 = b->noise_32;
                     const int grid = std::max(
                         1, std::min(a.n_items, b->cus * gs::tb_batch_occupancy(b->base.storage, T, shape)));
                     if (e == hipSuccess) e = gs::launch_tblock_batch(b->base.storage, T, shape, a, grid, b->stream);

@@ -73,6 +73,7 @@ __global__ __launch_bounds__((BlkGeom<S, BXG, BY, BZ, T, PZ>::NT)) void stencil_
     const int x0 = bx * (4 * BXG), y0 = (int)(rest % (uint32_t)a.nty) * BY, z0 = (int)(rest / (uint32_t)a.nty) * BZ;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const uint64_t t0 = NOISE ? step_index(a) : 0;
+    const CoefF32 kf = coef_f32(a);
 
     // 16-byte vector of half h of x-group (xg, y, z) of field f
     auto vec_at = [&](int f, int h, int z, int y, int xg) { return ((f * G::NH + h) * G::RZ + z) * G::PL + y * G::GX + xg; };
@@ -167,7 +168,7 @@ __global__ __launch_bounds__((BlkGeom<S, BXG, BY, BZ, T, PZ>::NT)) void stencil_
                         if constexpr (sizeof(C) == 8)
                             lap[j][f][e] = lap_f64(cc, xm, xp, ym[e], yp[e], c[f][j][e], c[f][j + 2][e]);
                         else
-                            lap[j][f][e] = lap_f32<S>(cc, xm, xp, ym[e], yp[e], c[f][j][e], c[f][j + 2][e]);
+                            lap[j][f][e] = lap6_f32<S>(cc, xm, xp, ym[e], yp[e], c[f][j][e], c[f][j + 2][e]);
                     }
                 }
             }
@@ -180,14 +181,14 @@ __global__ __launch_bounds__((BlkGeom<S, BXG, BY, BZ, T, PZ>::NT)) void stencil_
                         if constexpr (sizeof(C) == 8)
                             r[e] = __builtin_fma(a.noise_s, (double)(int32_t)wq[k - 1][j][e], a.noise_h);
                         else
-                            r[e] = noise_term_f32(wq[k - 1][j][e], a.noise_s_f, a.noise_h_f);
+                            r[e] = noise_term_f32(wq[k - 1][j][e], kf.ns, kf.nh);
                     }
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     C uo, vo;
                     // dt = 1 needs no variant: the products are exact
-                    cell_update<C, false, NOISE>(a, c[0][j + 1][e], c[1][j + 1][e], lap[j][0][e], lap[j][1][e], r[e], uo, vo);
+                    cell_update<C, false, NOISE>(a, kf, c[0][j + 1][e], c[1][j + 1][e], lap[j][0][e], lap[j][1][e], r[e], uo, vo);
                     res[j][0][e] = fload<S>(0, fstore<S>(0, uo));
                     res[j][1][e] = fload<S>(1, fstore<S>(1, vo));
                 }

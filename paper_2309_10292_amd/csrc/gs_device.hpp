@@ -140,21 +140,41 @@ __device__ __forceinline__ float noise_term_f32(uint32_t w, float s, float h)
     return __builtin_fmaf((float)(int32_t)w, s, h);
 }
 
+// The FP32 step's coefficients, held in vector registers: on gfx950 an FP32
+// add, multiply or fma whose operands are vector registers or constants issues
+// every 2.5 clocks per SIMD, and every 4.3 with a scalar register among them
+// (measured, two or more waves per SIMD).
+struct CoefF32 {
+    float Du6, Dv6, F, FK, dt; // Du / 6, Dv / 6
+    float ns, nh;              // noise 2^-31, noise 2^-32
+};
+__device__ __forceinline__ float in_vgpr(float x)
+{
+    asm volatile("" : "+v"(x)); // no instruction: the value is no longer known to be uniform
+    return x;
+}
+template <typename A> __device__ __forceinline__ CoefF32 coef_f32(const A &a)
+{
+    return CoefF32{in_vgpr(a.Du6_f), in_vgpr(a.Dv6_f), in_vgpr(a.F_f),      in_vgpr(a.FK_f),
+                   in_vgpr(a.dt_f),  in_vgpr(a.noise_s_f), in_vgpr(a.noise_h_f)};
+}
+
 // One Euler step of a cell in FP32 arithmetic (storage other than FP64):
 // Eq. 1a/1b and 2a/2b with the products fused into the sums, so each field
-// takes three operations after u v^2. nr is the noise term n r (NOISE).
-// Every FP32 kernel uses this one sequence, so results do not depend on the
-// kernel, the tile or the fused depth.
+// takes three operations after u v^2. lu6 and lv6 are six times the
+// Laplacians, nr is the noise term n r (NOISE). Every FP32 kernel uses this
+// one sequence, so results do not depend on the kernel, the tile or the fused
+// depth.
 template <bool NOISE>
-__device__ __forceinline__ void euler_f32(float Du, float Dv, float F, float FK, float dt, float uc, float vc,
-                                          float lu, float lv, float nr, float &uo, float &vo)
+__device__ __forceinline__ void euler_f32(const CoefF32 &k, float uc, float vc, float lu6, float lv6, float nr,
+                                          float &uo, float &vo)
 {
     const float uvv = uc * (vc * vc);
-    float du = __builtin_fmaf(F, 1.0f - uc, __builtin_fmaf(Du, lu, -uvv));
+    float du = __builtin_fmaf(k.F, 1.0f - uc, __builtin_fmaf(k.Du6, lu6, -uvv));
     if constexpr (NOISE) du = du + nr;
-    const float dv = __builtin_fmaf(-FK, vc, __builtin_fmaf(Dv, lv, uvv));
-    uo = __builtin_fmaf(du, dt, uc);
-    vo = __builtin_fmaf(dv, dt, vc);
+    const float dv = __builtin_fmaf(-k.FK, vc, __builtin_fmaf(k.Dv6, lv6, uvv));
+    uo = __builtin_fmaf(du, k.dt, uc);
+    vo = __builtin_fmaf(dv, k.dt, vc);
 }
 
 // Noise of the 4 cells idx4 .. idx4+3 (idx4 a multiple of 4) at step t.
@@ -163,6 +183,15 @@ __device__ __forceinline__ Philox4 noise_block(uint64_t idx4, uint64_t t, uint64
     const uint64_t q = idx4 >> 2;
     return philox4x32_10((uint32_t)q, (uint32_t)(q >> 32), (uint32_t)t, (uint32_t)(t >> 32),
                          (uint32_t)seed, (uint32_t)(seed >> 32));
+}
+
+// The same for block q < 2^32 (cells 4 q .. 4 q + 3 of a grid of less than 2^34
+// cells): with the counter's second word 0 and the step words uniform, one of
+// the two products is uniform in each of the first two rounds and runs on the
+// scalar unit (36 instead of 40 vector instructions, and 32-bit indices).
+__device__ __forceinline__ Philox4 noise_block32(uint32_t q, uint64_t t, uint64_t seed)
+{
+    return philox4x32_10(q, 0u, (uint32_t)t, (uint32_t)(t >> 32), (uint32_t)seed, (uint32_t)(seed >> 32));
 }
 
 // ---------------------------------------------------------------- arithmetic
@@ -219,39 +248,64 @@ template <typename S> __device__ __forceinline__ S fstore(int f, typename Traits
     else return Traits<S>::store(c);
 }
 
-// Laplacian in FP32 of values read from 2-byte storage: the six differences
-// summed in three levels without compensation. A difference of two 16-bit
-// values (for the complemented BF16 storage, of their complements) is exact
-// in FP32 whenever their exponents are within 16 of each other (a BF16 or
-// FP16 value has at most 11 significant bits), and the sum errs by at most
-// 3 u sum |d_i| (u = 2^-24): below 2e-7 of the differences, while the state
-// is rounded to 2^-9 (BF16) or 2^-12 (FP16) of itself after every step. The
-// compensated sum buys nothing at this storage and costs 16 more operations
-// per field.
-__device__ __forceinline__ float lap_sum_f32(float c, float xm, float xp, float ym, float yp, float zm, float zp)
+// Four values of field f to storage; BF16 converts them in pairs (one
+// instruction each).
+template <typename S> __device__ __forceinline__ Vec<S, 4> fstore4(int f, const typename Traits<S>::C (&c)[4])
 {
-    const float s = ((xm - c) + (xp - c)) + ((ym - c) + (yp - c)) + ((zm - c) + (zp - c));
-    return s * (1.0f / 6.0f);
+    Vec<S, 4> r;
+    if constexpr (sizeof(S) == 2 && !__is_same(S, f16)) {
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            f2 x = {c[2 * p], c[2 * p + 1]};
+            if constexpr (Complemented<S>::value)
+                if (f == 0) x = f2{1.0f - x[0], 1.0f - x[1]};
+            const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, b2));
+            r.e[2 * p].bits = (uint16_t)w;
+            r.e[2 * p + 1].bits = (uint16_t)(w >> 16);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r.e[e] = fstore<S>(f, c[e]);
+    }
+    return r;
 }
-// Laplacian in FP32 of values read from FP32 storage: the six FP32
-// differences (exact where a neighbour is within a factor 2 of c) summed in
-// FP64, which errs by at most 3 2^-53 sum |d_i|, then rounded once to FP32
-// and scaled. A compensated FP32 sum (Kahan) errs by up to (2u + O(u^2))
-// sum |d_i| (u = 2^-24), which exceeds a rounding of the sum itself wherever
-// the differences cancel, and takes more operations.
-__device__ __forceinline__ float lap_wide_f32(float c, float xm, float xp, float ym, float yp, float zm, float zp)
+
+// Six times the FP32-arithmetic Laplacian (the kernels' coefficients carry the
+// 1/6). 2-byte storage: the neighbour sum less 6 c in FP32. Values of at most
+// 11 significant bits whose exponents lie within 10 of each other (16 - 3 bits
+// for BF16) add without any rounding, the fused 6 c included; beyond that each
+// of the six roundings is within 2^-24 of the partial sum, while the state is
+// rounded to 2^-9 (BF16) or 2^-12 (FP16) of itself after every step. Six
+// operations against eleven for the sum of the differences n_i - c.
+__device__ __forceinline__ float lap6_sum_f32(float c, float xm, float xp, float ym, float yp, float zm, float zp)
 {
-    const double s = (((double)(xm - c) + (double)(xp - c)) + ((double)(ym - c) + (double)(yp - c))) +
-                     ((double)(zm - c) + (double)(zp - c));
-    return (float)s * (1.0f / 6.0f);
+    return __builtin_fmaf(-6.0f, c, ((xm + xp) + (ym + yp)) + (zm + zp));
 }
-// The FP32-arithmetic Laplacian of storage type S: the FP64 sum for FP32
-// storage, the plain sum for 2-byte storage.
+// Complemented BF16 storage: u = 1 - s carries the bits of a small s, which a
+// sum near 6 would round away, so the differences n_i - c (of values near 1,
+// exact) are summed.
+__device__ __forceinline__ float lap6_diff_f32(float c, float xm, float xp, float ym, float yp, float zm, float zp)
+{
+    return ((xm - c) + (xp - c)) + ((ym - c) + (yp - c)) + ((zm - c) + (zp - c));
+}
+// FP32 storage: the sum less 6 c in FP64, which errs by at most 6 2^-53 of the
+// summed magnitudes, rounded once to FP32. Converting each value (a row's cells
+// serve as centre and as x-neighbours) takes 5.5 conversions and 6 operations
+// per cell; converting the six differences took 6 and 11, and rounded each
+// difference to FP32 first.
+__device__ __forceinline__ float lap6_wide_f32(float c, float xm, float xp, float ym, float yp, float zm, float zp)
+{
+    const double s = (((double)xm + (double)xp) + ((double)ym + (double)yp)) + ((double)zm + (double)zp);
+    return (float)__builtin_fma(-6.0, (double)c, s);
+}
 template <typename S>
-__device__ __forceinline__ float lap_f32(float c, float xm, float xp, float ym, float yp, float zm, float zp)
+__device__ __forceinline__ float lap6_f32(float c, float xm, float xp, float ym, float yp, float zm, float zp)
 {
-    if constexpr (sizeof(S) == 2) return lap_sum_f32(c, xm, xp, ym, yp, zm, zp);
-    else return lap_wide_f32(c, xm, xp, ym, yp, zm, zp);
+    if constexpr (Complemented<S>::value) return lap6_diff_f32(c, xm, xp, ym, yp, zm, zp);
+    else if constexpr (sizeof(S) == 2) return lap6_sum_f32(c, xm, xp, ym, yp, zm, zp);
+    else return lap6_wide_f32(c, xm, xp, ym, yp, zm, zp);
 }
 
 // FP64 Laplacian in the canonical order: ((x- + x+) + (y- + y+)) + (z- + z+),

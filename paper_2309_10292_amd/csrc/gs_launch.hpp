@@ -14,7 +14,7 @@ struct StepArgs {
     int ntx, nty;        // tiles per row / column (set by the launcher)
     double Du, Dv, F, FK, dt, noise;   // FK = F + k, rounded once
     double noise_s, noise_h;           // noise 2^-31 and noise 2^-32 (exact: |noise| >= 2^-990 or 0)
-    float Du_f, Dv_f, F_f, FK_f, dt_f, noise_f;
+    float Du6_f, Dv6_f, F_f, FK_f, dt_f; // Du / 6 and Dv / 6 rounded once (gs_device.hpp, CoefF32)
     float noise_s_f, noise_h_f;        // RN(noise 2^-31), RN(noise 2^-32) in FP32
     uint64_t seed;
     uint64_t t;          // global index of the step being taken (noise key)
@@ -23,25 +23,10 @@ struct StepArgs {
     const uint64_t *t_dev;
 };
 
-__host__ __device__ inline uint64_t step_index(const StepArgs &a) { return a.t_dev ? *a.t_dev + a.t : a.t; }
+// Whether every noise block (4 cells) of a grid has an index below 2^32.
+inline bool noise_fits_32(int nx, int ny, int nz) { return (double)nx * ny * nz <= 17179869184.0; }
 
-template <typename C> struct Coef;
-template <> struct Coef<double> {
-    static __host__ __device__ double Du(const StepArgs &a) { return a.Du; }
-    static __host__ __device__ double Dv(const StepArgs &a) { return a.Dv; }
-    static __host__ __device__ double F(const StepArgs &a) { return a.F; }
-    static __host__ __device__ double FK(const StepArgs &a) { return a.FK; }
-    static __host__ __device__ double dt(const StepArgs &a) { return a.dt; }
-    static __host__ __device__ double noise(const StepArgs &a) { return a.noise; }
-};
-template <> struct Coef<float> {
-    static __host__ __device__ float Du(const StepArgs &a) { return a.Du_f; }
-    static __host__ __device__ float Dv(const StepArgs &a) { return a.Dv_f; }
-    static __host__ __device__ float F(const StepArgs &a) { return a.F_f; }
-    static __host__ __device__ float FK(const StepArgs &a) { return a.FK_f; }
-    static __host__ __device__ float dt(const StepArgs &a) { return a.dt_f; }
-    static __host__ __device__ float noise(const StepArgs &a) { return a.noise_f; }
-};
+__host__ __device__ inline uint64_t step_index(const StepArgs &a) { return a.t_dev ? *a.t_dev + a.t : a.t; }
 
 struct TileShape {
     int tx, ty;
@@ -130,6 +115,7 @@ struct BatchArgs {
     int parity;          // buffers holding the current state of every simulation of this launch
     uint64_t t;          // step index of the first fused step (offset when t_dev is set)
     const uint64_t *t_dev;
+    bool noise_32;       // noise_fits_32() holds for every simulation of this launch
 };
 
 hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b, int grid, hipStream_t st);

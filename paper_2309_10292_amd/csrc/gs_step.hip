@@ -141,6 +141,7 @@ __global__ __launch_bounds__(256) void stencil_tile(const S *__restrict__ u, con
     const int ze = min(z0 + a.zc, nz);
     const size_t plane = (size_t)nx * (size_t)ny;
     const LaneMap m = make_lane_map<S, TX, TY, V>(x0, y0, nx, ny);
+    const CoefF32 kf = coef_f32(a);
 
     const S *src[2] = {u, v};
     C zm[NF][V], zc[NF][V], zp[NF][V];
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(256) void stencil_tile(const S *__restrict__ u, con
                         if constexpr (sizeof(C) == 8)
                             r[4 * b + j] = noise_word_f64(w.w[j]);
                         else
-                            r[4 * b + j] = noise_term_f32(w.w[j], a.noise_s_f, a.noise_h_f);
+                            r[4 * b + j] = noise_term_f32(w.w[j], kf.ns, kf.nh);
                     }
                 }
             }
@@ -218,21 +219,20 @@ __global__ __launch_bounds__(256) void stencil_tile(const S *__restrict__ u, con
                     lu = lap_f64(uc, xm[0][i], xp[0][i], ym[0][i], yp[0][i], zm[0][i], zp[0][i]);
                     lv = lap_f64(vc, xm[1][i], xp[1][i], ym[1][i], yp[1][i], zm[1][i], zp[1][i]);
                 } else {
-                    lu = lap_f32<S>(uc, xm[0][i], xp[0][i], ym[0][i], yp[0][i], zm[0][i], zp[0][i]);
-                    lv = lap_f32<S>(vc, xm[1][i], xp[1][i], ym[1][i], yp[1][i], zm[1][i], zp[1][i]);
+                    lu = lap6_f32<S>(uc, xm[0][i], xp[0][i], ym[0][i], yp[0][i], zm[0][i], zp[0][i]);
+                    lv = lap6_f32<S>(vc, xm[1][i], xp[1][i], ym[1][i], yp[1][i], zm[1][i], zp[1][i]);
                 }
                 if constexpr (sizeof(C) == 4) {
                     // the FP32 sequence shared with the blocked kernels; r is n r
                     float uo, vo;
-                    euler_f32<NOISE>(a.Du_f, a.Dv_f, a.F_f, a.FK_f, a.dt_f, uc, vc, lu, lv, r[i], uo, vo);
+                    euler_f32<NOISE>(kf, uc, vc, lu, lv, r[i], uo, vo);
                     ou.e[i] = fstore<S>(0, uo);
                     ov.e[i] = fstore<S>(1, vo);
                 } else {
-                    const C Du = Coef<C>::Du(a), Dv = Coef<C>::Dv(a), F = Coef<C>::F(a);
-                    const C FK = Coef<C>::FK(a), dt = Coef<C>::dt(a);
+                    const C Du = a.Du, Dv = a.Dv, F = a.F, FK = a.FK, dt = a.dt;
                     const C uvv = uc * (vc * vc);
                     C du = (Du * lu - uvv) + F * ((C)1 - uc);
-                    if constexpr (NOISE) du = du + Coef<C>::noise(a) * r[i];
+                    if constexpr (NOISE) du = du + a.noise * r[i];
                     const C dv = (Dv * lv + uvv) - FK * vc;
                     ou.e[i] = Traits<S>::store(uc + du * dt);
                     ov.e[i] = Traits<S>::store(vc + dv * dt);

@@ -38,7 +38,7 @@ namespace gs {
 // barriers of an iteration, where the vector units otherwise wait for the
 // LDS stores: the registers this frees keep its straight-line levels free of
 // spills.
-template <typename S, int T, int NT, bool NOISE, bool BATCH> constexpr bool tb_dma()
+template <typename S, int T, int NT, int NOISE, bool BATCH> constexpr bool tb_dma()
 {
     return sizeof(S) == 8 && NOISE && !BATCH && T == 3 && NT == 512;
 }
@@ -98,7 +98,7 @@ template <typename S, int TXG, int TY, int T, int NT> struct TbGeom {
 // of the first of the T steps. `lds` holds 2 * TbGeom::FIELD elements and
 // `pre_lds` 4 * NT 16-byte slots where tb_dma() holds (else it is unused).
 // Every lane of the workgroup must call it (it contains barriers).
-template <typename S, int TXG, int TY, int T, int NT, bool NOISE, bool BATCH, bool UNIT_DT>
+template <typename S, int TXG, int TY, int T, int NT, int NOISE, bool BATCH, bool UNIT_DT>
 __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__restrict__ v, S *__restrict__ un,
                                         S *__restrict__ vn, const StepArgs &a, int x0, int y0, int z0, int ze,
                                         uint64_t t0, typename Traits<S>::C *__restrict__ lds,
@@ -110,6 +110,7 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
     static_assert(!DMA || 2 * G::FIELD * sizeof(C) + 4 * NT * 16 <= 160 * 1024, "staged planes and prefetch fit");
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const size_t plane = (size_t)nx * (size_t)ny;
+    const CoefF32 kf = coef_f32(a);
 
     // This lane's position (x-group gxs, level-0 row rys) and depth dep
     // (-1: none). Order: the output tile (depth T, row-major), the x-halo
@@ -193,6 +194,12 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
                 o[f][2 * hh + 1] = q.y;
             }
     };
+    // The noise block of this lane's position in plane z at level k.
+    const uint32_t xyq = (uint32_t)(xy >> 2), planeq = (uint32_t)(plane >> 2);
+    auto noise_at = [&](int z, int k) {
+        if constexpr (NOISE == NOISE_32) return noise_block32((uint32_t)z * planeq + xyq, t0 + (uint64_t)(k - 1), a.seed);
+        else return noise_block((size_t)z * plane + xy, t0 + (uint64_t)(k - 1), a.seed);
+    };
     // Philox blocks of the next iteration's levels (tb_dma), made ahead.
     uint32_t wq[T][4];
     auto make_noise = [&](const int i, auto full) {
@@ -200,8 +207,7 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
 #pragma unroll
         for (int k = 1; k <= T; ++k) {
             if (!FULL && !in_level(k)) continue;
-            const size_t idx = (size_t)wrap(i - k + 1, nz) * plane + xy;
-            const Philox4 w = noise_block(idx, t0 + (uint64_t)(k - 1), a.seed);
+            const Philox4 w = noise_at(wrap(i - k + 1, nz), k);
 #pragma unroll
             for (int e = 0; e < 4; ++e) wq[k - 1][e] = w.w[e];
         }
@@ -290,7 +296,7 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
 #pragma unroll
                     for (int e = 0; e < 4; ++e) w.w[e] = wq[k - 1][e];
                 } else {
-                    w = noise_block((size_t)wrap(zk, nz) * plane + xy, t0 + (uint64_t)(k - 1), a.seed);
+                    w = noise_at(wrap(zk, nz), k);
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -300,44 +306,45 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
                     if constexpr (sizeof(C) == 8)
                         r[e] = __builtin_fma(a.noise_s, (double)(int32_t)w.w[e], a.noise_h);
                     else
-                        r[e] = noise_term_f32(w.w[e], a.noise_s_f, a.noise_h_f);
+                        r[e] = noise_term_f32(w.w[e], kf.ns, kf.nh);
                 }
             }
             C res[2][4];
+            C lap[2][4]; // FP64: the Laplacians; FP32: six times them
+            if constexpr (sizeof(C) == 4) {
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        lap[f][e] = lap6_f32<S>(win[k - 1][sc][f][e], xm[f][e], xp[f][e], ym[f][e], yp[f][e],
+                                                win[k - 1][sm][f][e], win[k - 1][sp][f][e]);
+                }
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const C uc = win[k - 1][sc][0][e], vc = win[k - 1][sc][1][e];
-                C lu, lv;
                 if constexpr (sizeof(C) == 8) {
-                    lu = lap_f64(uc, xm[0][e], xp[0][e], ym[0][e], yp[0][e], win[k - 1][sm][0][e], win[k - 1][sp][0][e]);
-                    lv = lap_f64(vc, xm[1][e], xp[1][e], ym[1][e], yp[1][e], win[k - 1][sm][1][e], win[k - 1][sp][1][e]);
-                } else {
-                    lu = lap_f32<S>(uc, xm[0][e], xp[0][e], ym[0][e], yp[0][e], win[k - 1][sm][0][e],
-                                      win[k - 1][sp][0][e]);
-                    lv = lap_f32<S>(vc, xm[1][e], xp[1][e], ym[1][e], yp[1][e], win[k - 1][sm][1][e],
-                                      win[k - 1][sp][1][e]);
+                    lap[0][e] = lap_f64(uc, xm[0][e], xp[0][e], ym[0][e], yp[0][e], win[k - 1][sm][0][e], win[k - 1][sp][0][e]);
+                    lap[1][e] = lap_f64(vc, xm[1][e], xp[1][e], ym[1][e], yp[1][e], win[k - 1][sm][1][e], win[k - 1][sp][1][e]);
                 }
                 C uo, vo;
-                cell_update<C, UNIT_DT, NOISE>(a, uc, vc, lu, lv, r[e], uo, vo);
-                // Intermediate levels carry the stored precision of the state.
-                res[0][e] = fload<S>(0, fstore<S>(0, uo));
-                res[1][e] = fload<S>(1, fstore<S>(1, vo));
+                cell_update<C, UNIT_DT, NOISE != 0>(a, kf, uc, vc, lap[0][e], lap[1][e], r[e], uo, vo);
+                res[0][e] = uo;
+                res[1][e] = vo;
             }
+            // Every level carries the stored precision of the state.
+            Vec<S, 4> st[2];
+#pragma unroll
+            for (int f = 0; f < 2; ++f) st[f] = fstore4<S>(f, res[f]);
             if (k < T) {
 #pragma unroll
                 for (int f = 0; f < 2; ++f)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) win[k][sc][f][e] = res[f][e];
+                    for (int e = 0; e < 4; ++e) win[k][sc][f][e] = fload<S>(f, st[f].e[e]);
             } else if (out_ok && zk >= z0) {
-                Vec<S, 4> ou, ov;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    ou.e[e] = fstore<S>(0, res[0][e]);
-                    ov.e[e] = fstore<S>(1, res[1][e]);
-                }
                 const size_t off = (size_t)zk * plane + xy;
-                NtStore<S>::put(un + off, ou);
-                NtStore<S>::put(vn + off, ov);
+                NtStore<S>::put(un + off, st[0]);
+                NtStore<S>::put(vn + off, st[1]);
             }
         }
         if constexpr (DMA) lds_barrier(); // all reads of the staged planes are done
@@ -368,8 +375,10 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
 
     // The straight-line variant needs more registers; it is used where they
     // fit the budget (up to 512 lanes; FP64 up to 3 levels, and not in the
-    // persistent batched kernel).
-    constexpr bool full_ok = NT <= 512 && (sizeof(C) == 4 || (T <= 3 && !BATCH));
+    // persistent batched kernel; not FP32 storage,
+    // whose FP64 sums would spill 40 registers at two levels in 128: 530 against
+    // 272 us per step at 512^3 with noise).
+    constexpr bool full_ok = NT <= 512 && (sizeof(S) == 2 || (sizeof(S) == 8 && T <= 3 && !BATCH));
     const int wave_depth = __builtin_amdgcn_readfirstlane(dep);
     if (full_ok && wave_depth == T) {
         for (int i = i0; i <= i_end; i += 3) {
@@ -396,7 +405,7 @@ template <typename S, int T, int NT> constexpr int tb_min_waves()
     return (sizeof(typename Traits<S>::C) == 4 && T <= 2 && NT <= 512) ? 4 : 1;
 }
 
-template <typename S, int TXG, int TY, int T, int NT, bool NOISE>
+template <typename S, int TXG, int TY, int T, int NT, int NOISE>
 __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb(const S *__restrict__ u,
                                                                            const S *__restrict__ v,
                                                                            S *__restrict__ un, S *__restrict__ vn,
@@ -436,7 +445,7 @@ __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb(con
 // Persistent sweep over many independent simulations: each workgroup walks
 // the work list (items sorted by decreasing cost) with a stride of the grid
 // size; an item is one tile x z-chunk of one simulation.
-template <typename S, int TXG, int TY, int T, int NT, bool NOISE>
+template <typename S, int TXG, int TY, int T, int NT, int NOISE>
 __global__ __launch_bounds__(NT) void stencil_tb_batch(BatchArgs b)
 {
     typedef TbGeom<S, TXG, TY, T, NT> G;
@@ -482,13 +491,16 @@ static hipError_t launch_tb_t(const void *u, const void *v, void *un, void *vn, 
     const int nzc = (a.nz + a.zc - 1) / a.zc;
     const size_t nb = (size_t)a.ntx * a.nty * nzc;
     if (nb == 0 || nb > 0x7fffffffu) return hipErrorInvalidConfiguration;
-    if (a.noise != 0.0)
-        hipLaunchKernelGGL((stencil_tb<S, TXG, TY, T, NT, true>), dim3((unsigned)nb), dim3(NT), 0, st,
+    auto go = [&](auto mode) {
+        hipLaunchKernelGGL((stencil_tb<S, TXG, TY, T, NT, decltype(mode)::value>), dim3((unsigned)nb), dim3(NT), 0, st,
                            (const S *)u, (const S *)v, (S *)un, (S *)vn, a);
-    else
-        hipLaunchKernelGGL((stencil_tb<S, TXG, TY, T, NT, false>), dim3((unsigned)nb), dim3(NT), 0, st,
-                           (const S *)u, (const S *)v, (S *)un, (S *)vn, a);
-    return hipGetLastError();
+        return hipGetLastError();
+    };
+    if (a.noise == 0.0) return go(Phase<NOISE_OFF>{});
+    if (noise_fits_32(a.nx, a.ny, a.nz)) return go(Phase<NOISE_32>{});
+    // (four FP64 buffers of 2^34 cells are 512 GiB: more than the device holds)
+    if constexpr (sizeof(S) == 8) return hipErrorInvalidConfiguration;
+    else return go(Phase<NOISE_64>{});
 }
 
 // Shapes per T (output x-groups, rows, lanes): the level-0 region
@@ -537,7 +549,7 @@ static hipError_t dispatch_tb_shape(int shape, const void *u, const void *v, voi
 }
 
 template <typename S>
-static hipError_t dispatch_tb_T(int T, int shape, const void *u, const void *v, void *un, void *vn,
+hipError_t dispatch_tb_T(int T, int shape, const void *u, const void *v, void *un, void *vn,
                                 const StepArgs &a, hipStream_t st)
 {
     switch (T) {
@@ -548,6 +560,153 @@ static hipError_t dispatch_tb_T(int T, int shape, const void *u, const void *v, 
     }
     return hipErrorInvalidValue;
 }
+
+template <typename S, int TXG, int TY, int T, int NT>
+static hipError_t launch_tb_batch_t(const BatchArgs &b, int grid, hipStream_t st)
+{
+    if (grid < 1) return hipErrorInvalidConfiguration;
+    auto go = [&](auto mode) {
+        hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value>), dim3(grid), dim3(NT), 0, st, b);
+        return hipGetLastError();
+    };
+    if (b.coef.noise == 0.0) return go(Phase<NOISE_OFF>{});
+    if (b.noise_32) return go(Phase<NOISE_32>{});
+    if constexpr (sizeof(S) == 8) return hipErrorInvalidConfiguration;
+    else return go(Phase<NOISE_64>{});
+}
+
+template <typename S, int T>
+static hipError_t batch_shape(int shape, const BatchArgs &b, int grid, hipStream_t st)
+{
+    switch (shape) {
+    case 1: return launch_tb_batch_t<S, 16, 14 - 2 * T, T, 256>(b, grid, st);
+    case 2: return launch_tb_batch_t<S, 16, 28 - 2 * T, T, 512>(b, grid, st);
+    case 3: return launch_tb_batch_t<S, 32, 14 - 2 * T, T, 512>(b, grid, st);
+    case 4:
+        if constexpr (T <= tb_max_T_of<S, 768, true>()) return launch_tb_batch_t<S, 16, 42 - 2 * T, T, 768>(b, grid, st);
+        break;
+    case 5:
+        if constexpr (T <= tb_max_T_of<S, 1024, true>())
+            return launch_tb_batch_t<S, 16, 56 - 2 * T, T, 1024>(b, grid, st);
+        break;
+    }
+    return hipErrorInvalidValue;
+}
+
+template <typename S>
+hipError_t batch_T(int T, int shape, const BatchArgs &b, int grid, hipStream_t st)
+{
+    switch (T) {
+    case 1: return batch_shape<S, 1>(shape, b, grid, st);
+    case 2: return batch_shape<S, 2>(shape, b, grid, st);
+    case 3: return batch_shape<S, 3>(shape, b, grid, st);
+    case 4: return batch_shape<S, 4>(shape, b, grid, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <typename S, int TXG, int TY, int T, int NT>
+static int occ_t()
+{
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb_batch<S, TXG, TY, T, NT, NOISE_OFF>, NT, 0) != hipSuccess)
+        return 1;
+    return n > 0 ? n : 1;
+}
+
+template <typename S, int T>
+static int occ_shape(int shape)
+{
+    switch (shape) {
+    case 1: return occ_t<S, 16, 14 - 2 * T, T, 256>();
+    case 2: return occ_t<S, 16, 28 - 2 * T, T, 512>();
+    case 3: return occ_t<S, 32, 14 - 2 * T, T, 512>();
+    case 4:
+        if constexpr (T <= tb_max_T_of<S, 768, true>()) return occ_t<S, 16, 42 - 2 * T, T, 768>();
+        break;
+    case 5:
+        if constexpr (T <= tb_max_T_of<S, 1024, true>()) return occ_t<S, 16, 56 - 2 * T, T, 1024>();
+        break;
+    }
+    return 1;
+}
+
+template <typename S>
+int occ_T(int T, int shape)
+{
+    switch (T) {
+    case 1: return occ_shape<S, 1>(shape);
+    case 2: return occ_shape<S, 2>(shape);
+    case 3: return occ_shape<S, 3>(shape);
+    case 4: return occ_shape<S, 4>(shape);
+    }
+    return 1;
+}
+
+template <typename S, int TXG, int TY, int T, int NT>
+static int occ_single_t(bool noise)
+{
+    int n = 0;
+    const hipError_t e = noise
+                             ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb<S, TXG, TY, T, NT, NOISE_32>, NT, 0)
+                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb<S, TXG, TY, T, NT, NOISE_OFF>, NT, 0);
+    return e == hipSuccess && n > 0 ? n : 0;
+}
+
+template <typename S, int T>
+static int occ_single_shape(int shape, bool noise)
+{
+    switch (shape) {
+    case 1: return occ_single_t<S, 16, 14 - 2 * T, T, 256>(noise);
+    case 2: return occ_single_t<S, 16, 28 - 2 * T, T, 512>(noise);
+    case 3: return occ_single_t<S, 32, 14 - 2 * T, T, 512>(noise);
+    case 4:
+        if constexpr (T <= tb_max_T_of<S, 768, false>()) return occ_single_t<S, 16, 42 - 2 * T, T, 768>(noise);
+        break;
+    case 5:
+        if constexpr (T <= tb_max_T_of<S, 1024, false>()) return occ_single_t<S, 16, 56 - 2 * T, T, 1024>(noise);
+        break;
+    }
+    return 0;
+}
+
+template <typename S>
+int occ_single_T(int T, int shape, bool noise)
+{
+    switch (T) {
+    case 1: return occ_single_shape<S, 1>(shape, noise);
+    case 2: return occ_single_shape<S, 2>(shape, noise);
+    case 3: return occ_single_shape<S, 3>(shape, noise);
+    case 4: return occ_single_shape<S, 4>(shape, noise);
+    }
+    return 0;
+}
+
+// The kernels of a storage type are instantiated in an object of their own
+// (GS_TB_STORAGE, set by the build), which the compiler can build side by
+// side; the object of storage 0 also holds the functions below.
+#define GS_TB_TYPE(X, S, BATCHED)                                                                                          \
+    X template hipError_t dispatch_tb_T<S>(int, int, const void *, const void *, void *, void *, const StepArgs &,       \
+                                           hipStream_t);                                                                 \
+    X template int occ_single_T<S>(int, int, bool);                                                                      \
+    BATCHED(X, S)
+#define GS_TB_BATCH(X, S)                                                                                                \
+    X template hipError_t batch_T<S>(int, int, const BatchArgs &, int, hipStream_t);                                     \
+    X template int occ_T<S>(int, int);
+#define GS_TB_SINGLE(X, S)
+#if GS_TB_STORAGE == 1
+GS_TB_TYPE(, float, GS_TB_BATCH)
+#elif GS_TB_STORAGE == 2
+GS_TB_TYPE(, bf16, GS_TB_BATCH)
+#elif GS_TB_STORAGE == 3
+GS_TB_TYPE(, f16, GS_TB_BATCH)
+#elif GS_TB_STORAGE == 4
+GS_TB_TYPE(, bf16c, GS_TB_SINGLE)
+#else
+GS_TB_TYPE(extern, float, GS_TB_BATCH)
+GS_TB_TYPE(extern, bf16, GS_TB_BATCH)
+GS_TB_TYPE(extern, f16, GS_TB_BATCH)
+GS_TB_TYPE(extern, bf16c, GS_TB_SINGLE)
 
 int num_tb_shapes() { return 5; }
 
@@ -579,47 +738,6 @@ template <bool BATCH> static int max_T_for(int shape, int storage)
 int tb_max_T(int shape, int storage) { return max_T_for<false>(shape, storage); }
 int tb_batch_max_T(int shape, int storage) { return max_T_for<true>(shape, storage); }
 
-template <typename S, int TXG, int TY, int T, int NT>
-static hipError_t launch_tb_batch_t(const BatchArgs &b, int grid, hipStream_t st)
-{
-    if (grid < 1) return hipErrorInvalidConfiguration;
-    if (b.coef.noise != 0.0)
-        hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, true>), dim3(grid), dim3(NT), 0, st, b);
-    else
-        hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, false>), dim3(grid), dim3(NT), 0, st, b);
-    return hipGetLastError();
-}
-
-template <typename S, int T>
-static hipError_t batch_shape(int shape, const BatchArgs &b, int grid, hipStream_t st)
-{
-    switch (shape) {
-    case 1: return launch_tb_batch_t<S, 16, 14 - 2 * T, T, 256>(b, grid, st);
-    case 2: return launch_tb_batch_t<S, 16, 28 - 2 * T, T, 512>(b, grid, st);
-    case 3: return launch_tb_batch_t<S, 32, 14 - 2 * T, T, 512>(b, grid, st);
-    case 4:
-        if constexpr (T <= tb_max_T_of<S, 768, true>()) return launch_tb_batch_t<S, 16, 42 - 2 * T, T, 768>(b, grid, st);
-        break;
-    case 5:
-        if constexpr (T <= tb_max_T_of<S, 1024, true>())
-            return launch_tb_batch_t<S, 16, 56 - 2 * T, T, 1024>(b, grid, st);
-        break;
-    }
-    return hipErrorInvalidValue;
-}
-
-template <typename S>
-static hipError_t batch_T(int T, int shape, const BatchArgs &b, int grid, hipStream_t st)
-{
-    switch (T) {
-    case 1: return batch_shape<S, 1>(shape, b, grid, st);
-    case 2: return batch_shape<S, 2>(shape, b, grid, st);
-    case 3: return batch_shape<S, 3>(shape, b, grid, st);
-    case 4: return batch_shape<S, 4>(shape, b, grid, st);
-    }
-    return hipErrorInvalidValue;
-}
-
 hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b, int grid, hipStream_t st)
 {
     switch (storage) {
@@ -632,83 +750,6 @@ hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b
 }
 
 int tb_shape_lanes(int shape) { return shape_lanes(shape); }
-
-template <typename S, int TXG, int TY, int T, int NT>
-static int occ_t()
-{
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb_batch<S, TXG, TY, T, NT, false>, NT, 0) != hipSuccess)
-        return 1;
-    return n > 0 ? n : 1;
-}
-
-template <typename S, int T>
-static int occ_shape(int shape)
-{
-    switch (shape) {
-    case 1: return occ_t<S, 16, 14 - 2 * T, T, 256>();
-    case 2: return occ_t<S, 16, 28 - 2 * T, T, 512>();
-    case 3: return occ_t<S, 32, 14 - 2 * T, T, 512>();
-    case 4:
-        if constexpr (T <= tb_max_T_of<S, 768, true>()) return occ_t<S, 16, 42 - 2 * T, T, 768>();
-        break;
-    case 5:
-        if constexpr (T <= tb_max_T_of<S, 1024, true>()) return occ_t<S, 16, 56 - 2 * T, T, 1024>();
-        break;
-    }
-    return 1;
-}
-
-template <typename S>
-static int occ_T(int T, int shape)
-{
-    switch (T) {
-    case 1: return occ_shape<S, 1>(shape);
-    case 2: return occ_shape<S, 2>(shape);
-    case 3: return occ_shape<S, 3>(shape);
-    case 4: return occ_shape<S, 4>(shape);
-    }
-    return 1;
-}
-
-template <typename S, int TXG, int TY, int T, int NT>
-static int occ_single_t(bool noise)
-{
-    int n = 0;
-    const hipError_t e = noise
-                             ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb<S, TXG, TY, T, NT, true>, NT, 0)
-                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb<S, TXG, TY, T, NT, false>, NT, 0);
-    return e == hipSuccess && n > 0 ? n : 0;
-}
-
-template <typename S, int T>
-static int occ_single_shape(int shape, bool noise)
-{
-    switch (shape) {
-    case 1: return occ_single_t<S, 16, 14 - 2 * T, T, 256>(noise);
-    case 2: return occ_single_t<S, 16, 28 - 2 * T, T, 512>(noise);
-    case 3: return occ_single_t<S, 32, 14 - 2 * T, T, 512>(noise);
-    case 4:
-        if constexpr (T <= tb_max_T_of<S, 768, false>()) return occ_single_t<S, 16, 42 - 2 * T, T, 768>(noise);
-        break;
-    case 5:
-        if constexpr (T <= tb_max_T_of<S, 1024, false>()) return occ_single_t<S, 16, 56 - 2 * T, T, 1024>(noise);
-        break;
-    }
-    return 0;
-}
-
-template <typename S>
-static int occ_single_T(int T, int shape, bool noise)
-{
-    switch (T) {
-    case 1: return occ_single_shape<S, 1>(shape, noise);
-    case 2: return occ_single_shape<S, 2>(shape, noise);
-    case 3: return occ_single_shape<S, 3>(shape, noise);
-    case 4: return occ_single_shape<S, 4>(shape, noise);
-    }
-    return 0;
-}
 
 int tb_occupancy(int storage, int T, int shape, bool noise)
 {
@@ -745,5 +786,7 @@ hipError_t launch_tblock(int storage, int T, int shape, const void *u, const voi
     }
     return hipErrorInvalidValue;
 }
+
+#endif
 
 } // namespace gs

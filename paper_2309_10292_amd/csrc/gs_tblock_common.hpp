@@ -51,6 +51,10 @@ template <> struct NtStore<f16> {
     }
 };
 
+// Noise off, or on with 32-bit block indices (grids of less than 2^34 cells) or
+// 64-bit ones.
+enum { NOISE_OFF = 0, NOISE_32 = 1, NOISE_64 = 2 };
+
 template <int P> struct Phase {
     static constexpr int value = P;
 };
@@ -63,15 +67,16 @@ __host__ __device__ constexpr int slot3(int p) { return ((p % 3) + 3) % 3; }
 // UNIT_DT: dt is exactly 1, so the products du dt and dv dt equal du and dv
 // (bitwise) and are skipped. nr is the noise term n r. FP64 follows the
 // definition's operation order; FP32 arithmetic takes the fused sequence
-// shared by every FP32 kernel.
+// shared by every FP32 kernel (lu, lv are six times the Laplacians there, and
+// its coefficients come from k).
 template <typename C, bool UNIT_DT, bool NOISE>
-__device__ __forceinline__ void cell_update(const StepArgs &a, C uc, C vc, C lu, C lv, C nr, C &uo, C &vo)
+__device__ __forceinline__ void cell_update(const StepArgs &a, const CoefF32 &k, C uc, C vc, C lu, C lv, C nr, C &uo,
+                                            C &vo)
 {
     if constexpr (sizeof(C) == 4) {
-        euler_f32<NOISE>(a.Du_f, a.Dv_f, a.F_f, a.FK_f, a.dt_f, uc, vc, lu, lv, nr, uo, vo);
+        euler_f32<NOISE>(k, uc, vc, lu, lv, nr, uo, vo);
     } else {
-        const C Du = Coef<C>::Du(a), Dv = Coef<C>::Dv(a), F = Coef<C>::F(a);
-        const C FK = Coef<C>::FK(a), dt = Coef<C>::dt(a);
+        const C Du = a.Du, Dv = a.Dv, F = a.F, FK = a.FK, dt = a.dt;
         const C uvv = uc * (vc * vc);
         C du = (Du * lu - uvv) + F * ((C)1 - uc);
         if constexpr (NOISE) du = du + nr;
