@@ -237,11 +237,11 @@ gs_status gs_step_graph(gs_sim *s, int64_t n_steps);
 
 /* ------------------------------------------------------------------ */
 /* Batched sweeps: many independent simulations (own grid and own F, k; shared
- * Du, Dv, dt, noise, storage) advanced together by persistent launches of the
+ * Du, Dv, dt, noise, storage) advanced together by shared launches of the
  * temporally blocked kernel. Simulation i draws its noise with key seed + i.
  * Every simulation has a launch configuration (tile among the temporally
  * blocked tiles, tblock, zchunk >= 8); simulations sharing (tile, tblock) are
- * advanced by one persistent launch per tblock steps. */
+ * advanced by one launch per tblock steps. */
 
 typedef struct gs_batch gs_batch; /* opaque handle */
 
@@ -253,8 +253,7 @@ typedef struct gs_batch_tune_entry {
 } gs_batch_tune_entry;
 
 /* Largest tblock a temporally blocked tile accepts in batched sweeps for a
- * storage type (the persistent kernel needs a few more registers than the
- * single-grid one); 0 when the tile is not available to batches or the
+ * storage type (the larger tiles one step less than in single grids); 0 when the tile is not available to batches or the
  * arguments are invalid. */
 int32_t gs_batch_max_tblock(int32_t tile, int32_t storage);
 

@@ -1,12 +1,11 @@
 // Batched C ABI: many independent Gray-Scott simulations (own grid size, F
-// and k; shared Du, Dv, dt, noise) advanced together by persistent launches
+// and k; shared Du, Dv, dt, noise) advanced together by shared launches
 // of the temporally blocked kernel.
 //
 // Each simulation has a launch configuration (tile shape, fused steps T,
-// z-chunk); simulations with the same (shape, T) form a group that one
-// persistent launch per T steps advances. Work items (one tile x z-chunk of
-// one simulation) are listed per group, longest first, and every workgroup
-// of the persistent grid walks the list with a stride of the grid size.
+// z-chunk); simulations with the same (shape, T) form a group that one launch
+// per T steps advances. Work items (one tile x z-chunk of one simulation) are
+// listed per group, longest first, one workgroup each.
 #include "../../include/gs.h"
 #include "gs_internal.hpp"
 #include "gs_launch.hpp"
@@ -41,7 +40,7 @@ struct BSim {
 struct BGroup {
     int shape, T;
     int parity;
-    int off[GS_MAX_TBLOCK + 1], cnt[GS_MAX_TBLOCK + 1], grid[GS_MAX_TBLOCK + 1];
+    int off[GS_MAX_TBLOCK + 1], cnt[GS_MAX_TBLOCK + 1], slots[GS_MAX_TBLOCK + 1];
 };
 
 struct BGraph {
@@ -123,6 +122,58 @@ gs::StepArgs shared_coef(const gs_batch *b)
     return a;
 }
 
+// Workgroups resident at once, rounded up to the 8 XCDs.
+int batch_slots(const gs_batch *b, int T, int shape)
+{
+    return (b->cus * gs::tb_batch_occupancy(b->base.storage, T, shape) + 7) / 8 * 8;
+}
+
+// Library choice of the steps per launch and the z-chunk, before any tuning.
+// Two steps, except FP64 with work for at least two rounds of workgroups,
+// where T = 2 is bound by HBM and three steps are faster (32 grids of 128^3:
+// 196 against 265 us per step; on 24 grids of 16^3..72^3, less than one round,
+// 31 against 21). FP32 and 16-bit kernels of T = 2 keep two 512-lane
+// workgroups per CU, of T = 3 one (32 x 128^3 without noise: FP32 123 against
+// 148 us per step, BF16 84 against 119 with one step). The chunk is the one
+// with the least estimated makespan of the longest-first list: the items'
+// planes over the resident workgroups, and half the longest item for the last
+// round (the longest item alone if everything is resident at once): 64 planes
+// for 32 x 128^3 in FP64 (196 us; 208 with 32), 32 in FP32 (123; 126 with 64,
+// 128 with 16), 16 for the 24 small grids in FP64 (21; 24 with 8).
+struct BatchChoice {
+    int T, zc;
+};
+BatchChoice default_batch(const gs_batch *b, int shape, int32_t n_sims, const int32_t *nx, const int32_t *ny,
+                          const int32_t *nz)
+{
+    auto columns = [&](int i, int T) {
+        const gs::TileShape ts = gs::tb_shape(shape, T);
+        return (double)tiles_along(nx[i], ts.tx) * tiles_along(ny[i], ts.ty);
+    };
+    const bool f64 = b->base.storage == GS_F64;
+    double items = 0;
+    for (int32_t i = 0; i < n_sims; ++i) items += columns(i, f64 ? 3 : 2) * tiles_along(nz[i], 32);
+    const int T = f64 && items >= 2.0 * batch_slots(b, 3, shape) ? 3 : 2;
+    const double slots = batch_slots(b, T, shape);
+    BatchChoice best = {T, k_min_batch_zc};
+    double best_cost = 1e300;
+    for (int zc = k_min_batch_zc; zc <= 64; zc *= 2) {
+        double n = 0, planes = 0, longest = 0;
+        for (int32_t i = 0; i < n_sims; ++i) {
+            const int len = std::min(zc, nz[i]) + 2 * T;
+            n += columns(i, T) * tiles_along(nz[i], zc);
+            planes += columns(i, T) * (nz[i] + 2.0 * T * tiles_along(nz[i], zc));
+            longest = std::max(longest, (double)len);
+        }
+        const double cost = n <= slots ? longest : planes / slots + 0.5 * longest;
+        if (cost < best_cost) {
+            best_cost = cost;
+            best.zc = zc;
+        }
+    }
+    return best;
+}
+
 void drop_graph(gs_batch *b)
 {
     if (b->graph.exec) (void)hipGraphExecDestroy(b->graph.exec);
@@ -168,7 +219,7 @@ gs_status rebuild(gs_batch *b)
             g.shape = shape;
             g.T = T;
             g.parity = 0;
-            for (int d = 0; d <= GS_MAX_TBLOCK; ++d) g.off[d] = g.cnt[d] = g.grid[d] = 0;
+            for (int d = 0; d <= GS_MAX_TBLOCK; ++d) g.off[d] = g.cnt[d] = g.slots[d] = 0;
             for (int d = 1; d <= T; ++d) {
                 struct Tmp {
                     gs::WorkItem w;
@@ -194,8 +245,7 @@ gs_status rebuild(gs_batch *b)
                                  [](const Tmp &x, const Tmp &y) { return x.len > y.len; });
                 g.off[d] = (int)b->h_items.size();
                 g.cnt[d] = (int)items.size();
-                const int occ = gs::tb_batch_occupancy(b->base.storage, d, shape);
-                g.grid[d] = std::max(1, std::min(g.cnt[d], b->cus * occ));
+                g.slots[d] = batch_slots(b, d, shape);
                 for (const Tmp &t : items) b->h_items.push_back(t.w);
             }
             for (BSim &s : b->sims)
@@ -236,11 +286,12 @@ hipError_t enqueue_batch(gs_batch *b, int64_t n, hipStream_t st, const uint64_t 
             a.sims = b->d_desc;
             a.items = b->d_items + g.off[d];
             a.n_items = g.cnt[d];
+            a.slots = g.slots[d];
             a.parity = par[gi];
             a.t = t_dev ? off : b->step + off;
             a.t_dev = t_dev;
             a.noise_32 = b->noise_32;
-            hipError_t e = gs::launch_tblock_batch(b->base.storage, d, g.shape, a, g.grid[d], st);
+            hipError_t e = gs::launch_tblock_batch(b->base.storage, d, g.shape, a, st);
             if (e != hipSuccess) return e;
             par[gi] ^= 1;
             left -= d;
@@ -355,9 +406,8 @@ gs_status gs_batch_init(const gs_params *base, int32_t n_sims, const int32_t *nx
     }
     const size_t es = storage_bytes(base->storage);
     const int shape = base->tile ? base->tile - gs::num_tiles() : 2;
-    const int T = base->tblock ? base->tblock
-                               : std::min(gs::tb_batch_max_T(shape, base->storage),
-                                          (base->storage == GS_F64 || base->storage == GS_F32) ? 3 : 1);
+    const BatchChoice def = default_batch(b, shape, n_sims, nx, ny, nz);
+    const int T = base->tblock ? base->tblock : std::min(gs::tb_batch_max_T(shape, base->storage), def.T);
     char *p = (char *)arena;
     for (int32_t i = 0; i < n_sims; ++i) {
         BSim s;
@@ -377,7 +427,7 @@ gs_status gs_batch_init(const gs_params *base, int32_t n_sims, const int32_t *nx
         s.group = 0;
         s.shape = shape;
         s.T = T;
-        const int zc = base->zchunk ? base->zchunk : 32;
+        const int zc = base->zchunk ? base->zchunk : def.zc;
         s.zc = std::min(zc, s.nz);
         if (base->tile == 0 && base->tblock == 0 && base->zchunk == 0) {
             // a configuration recorded by gs_batch_tune for this grid class, if any
@@ -595,12 +645,11 @@ gs_status gs_batch_tune(gs_batch *b, int32_t reps, gs_batch_tune_entry *table, i
                     a.t = b->step;
                     a.t_dev = nullptr;
                     a.noise_32 = b->noise_32;
-                    const int grid = std::max(
-                        1, std::min(a.n_items, b->cus * gs::tb_batch_occupancy(b->base.storage, T, shape)));
-                    if (e == hipSuccess) e = gs::launch_tblock_batch(b->base.storage, T, shape, a, grid, b->stream);
+                    a.slots = batch_slots(b, T, shape);
+                    if (e == hipSuccess) e = gs::launch_tblock_batch(b->base.storage, T, shape, a, b->stream);
                     if (e == hipSuccess) e = hipEventRecord(e0, b->stream);
                     for (int r = 0; r < reps && e == hipSuccess; ++r)
-                        e = gs::launch_tblock_batch(b->base.storage, T, shape, a, grid, b->stream);
+                        e = gs::launch_tblock_batch(b->base.storage, T, shape, a, b->stream);
                     if (e == hipSuccess) e = hipEventRecord(e1, b->stream);
                     if (e == hipSuccess) e = hipEventSynchronize(e1);
                     float ms = 0.f;

@@ -76,7 +76,7 @@ int num_tb_shapes();
 TileShape tb_shape(int shape, int T);
 // Largest number of fused steps the temporally blocked shape runs for a
 // storage type (its registers fit the shape's lanes without spills), in the
-// single-grid kernel and in the persistent batched kernel (0: the shape is
+// single-grid kernel and in the batched kernel (0: the shape is
 // not available).
 int tb_max_T(int shape, int storage);
 int tb_batch_max_T(int shape, int storage);
@@ -111,14 +111,15 @@ struct BatchArgs {
     StepArgs coef;       // shared coefficients (Du, Dv, dt, noise); per-sim fields overwritten
     const SimDesc *sims;
     const WorkItem *items;
-    int n_items;
+    int n_items;         // one workgroup each
+    int slots;           // workgroups resident at once (a multiple of 8)
     int parity;          // buffers holding the current state of every simulation of this launch
     uint64_t t;          // step index of the first fused step (offset when t_dev is set)
     const uint64_t *t_dev;
     bool noise_32;       // noise_fits_32() holds for every simulation of this launch
 };
 
-hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b, int grid, hipStream_t st);
+hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b, hipStream_t st);
 int tb_shape_lanes(int shape);
 // Resident workgroups per CU of the batched kernel (at least 1).
 int tb_batch_occupancy(int storage, int T, int shape);

@@ -38,9 +38,9 @@ namespace gs {
 // barriers of an iteration, where the vector units otherwise wait for the
 // LDS stores: the registers this frees keep its straight-line levels free of
 // spills.
-template <typename S, int T, int NT, int NOISE, bool BATCH> constexpr bool tb_dma()
+template <typename S, int T, int NT, int NOISE> constexpr bool tb_dma()
 {
-    return sizeof(S) == 8 && NOISE && !BATCH && T == 3 && NT == 512;
+    return sizeof(S) == 8 && NOISE && T == 3 && NT == 512;
 }
 // A workgroup barrier that waits for the LDS operations only: the LDS-DMA
 // prefetch stays in flight across it (each wave reads only the area its own
@@ -98,7 +98,7 @@ template <typename S, int TXG, int TY, int T, int NT> struct TbGeom {
 // of the first of the T steps. `lds` holds 2 * TbGeom::FIELD elements and
 // `pre_lds` 4 * NT 16-byte slots where tb_dma() holds (else it is unused).
 // Every lane of the workgroup must call it (it contains barriers).
-template <typename S, int TXG, int TY, int T, int NT, int NOISE, bool BATCH, bool UNIT_DT>
+template <typename S, int TXG, int TY, int T, int NT, int NOISE, bool UNIT_DT>
 __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__restrict__ v, S *__restrict__ un,
                                         S *__restrict__ vn, const StepArgs &a, int x0, int y0, int z0, int ze,
                                         uint64_t t0, typename Traits<S>::C *__restrict__ lds,
@@ -106,7 +106,7 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
 {
     typedef TbGeom<S, TXG, TY, T, NT> G;
     typedef typename G::C C;
-    constexpr bool DMA = tb_dma<S, T, NT, NOISE, BATCH>();
+    constexpr bool DMA = tb_dma<S, T, NT, NOISE>();
     static_assert(!DMA || 2 * G::FIELD * sizeof(C) + 4 * NT * 16 <= 160 * 1024, "staged planes and prefetch fit");
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const size_t plane = (size_t)nx * (size_t)ny;
@@ -374,11 +374,10 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
     };
 
     // The straight-line variant needs more registers; it is used where they
-    // fit the budget (up to 512 lanes; FP64 up to 3 levels, and not in the
-    // persistent batched kernel; not FP32 storage,
+    // fit the budget (up to 512 lanes; FP64 up to 3 levels; not FP32 storage,
     // whose FP64 sums would spill 40 registers at two levels in 128: 530 against
     // 272 us per step at 512^3 with noise).
-    constexpr bool full_ok = NT <= 512 && (sizeof(S) == 2 || (sizeof(S) == 8 && T <= 3 && !BATCH));
+    constexpr bool full_ok = NT <= 512 && (sizeof(S) == 2 || (sizeof(S) == 8 && T <= 3));
     const int wave_depth = __builtin_amdgcn_readfirstlane(dep);
     if (full_ok && wave_depth == T) {
         for (int i = i0; i <= i_end; i += 3) {
@@ -405,36 +404,26 @@ template <typename S, int T, int NT> constexpr int tb_min_waves()
     return (sizeof(typename Traits<S>::C) == 4 && T <= 2 && NT <= 512) ? 4 : 1;
 }
 
+// The output tile (bx, by) and chunk bz of the grid in `a` by this workgroup.
 template <typename S, int TXG, int TY, int T, int NT, int NOISE>
-__global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb(const S *__restrict__ u,
-                                                                           const S *__restrict__ v,
-                                                                           S *__restrict__ un, S *__restrict__ vn,
-                                                                           StepArgs a)
+__device__ __forceinline__ void tb_item(const S *__restrict__ u, const S *__restrict__ v, S *__restrict__ un,
+                                        S *__restrict__ vn, const StepArgs &a, int bx, int by, int bz, uint64_t t0)
 {
     typedef TbGeom<S, TXG, TY, T, NT> G;
     __shared__ typename G::C lds[2 * G::FIELD];
-    const uint32_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
-    const int bx = (int)(lb % (uint32_t)a.ntx);
-    const uint32_t rest = lb / (uint32_t)a.ntx;
-    const int by = (int)(rest % (uint32_t)a.nty);
-    const int bz = (int)(rest / (uint32_t)a.nty);
-    const int z0 = bz * a.zc;
-    const uint64_t t0 = NOISE ? step_index(a) : 0;
-    const int ze = min(z0 + a.zc, a.nz);
+    const int z0 = bz * a.zc, ze = min(z0 + a.zc, a.nz);
     auto run = [&](uint4 *pre_lds) {
         // FP64 runs with dt = 1 (the workload of the paper) take the variant
         // without the dt products.
         if constexpr (sizeof(S) == 8) {
             if (a.dt == 1.0) {
-                tb_tile<S, TXG, TY, T, NT, NOISE, false, true>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0,
-                                                               lds, pre_lds);
+                tb_tile<S, TXG, TY, T, NT, NOISE, true>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds, pre_lds);
                 return;
             }
         }
-        tb_tile<S, TXG, TY, T, NT, NOISE, false, false>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds,
-                                                        pre_lds);
+        tb_tile<S, TXG, TY, T, NT, NOISE, false>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds, pre_lds);
     };
-    if constexpr (tb_dma<S, T, NT, NOISE, false>()) {
+    if constexpr (tb_dma<S, T, NT, NOISE>()) {
         __shared__ uint4 pre_lds[4 * NT];
         run(pre_lds);
     } else {
@@ -442,44 +431,43 @@ __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb(con
     }
 }
 
-// Persistent sweep over many independent simulations: each workgroup walks
-// the work list (items sorted by decreasing cost) with a stride of the grid
-// size; an item is one tile x z-chunk of one simulation.
 template <typename S, int TXG, int TY, int T, int NT, int NOISE>
-__global__ __launch_bounds__(NT) void stencil_tb_batch(BatchArgs b)
+__global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb(const S *__restrict__ u,
+                                                                           const S *__restrict__ v,
+                                                                           S *__restrict__ un, S *__restrict__ vn,
+                                                                           StepArgs a)
 {
-    typedef TbGeom<S, TXG, TY, T, NT> G;
-    __shared__ typename G::C lds[2 * G::FIELD];
     const uint32_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
-    const uint64_t t0 = NOISE ? (b.t_dev ? *b.t_dev + b.t : b.t) : 0;
-    for (uint32_t it = lb; it < (uint32_t)b.n_items; it += gridDim.x) {
-        const WorkItem w = b.items[it];
-        const SimDesc &d = b.sims[w.sim];
-        StepArgs a = b.coef;
-        a.nx = d.nx;
-        a.ny = d.ny;
-        a.nz = d.nz;
-        a.F = d.F;
-        a.FK = d.FK;
-        a.F_f = d.F_f;
-        a.FK_f = d.FK_f;
-        a.seed = d.seed;
-        const int z0 = w.bz * d.zc;
-        const S *u = (const S *)d.buf[b.parity][0];
-        const S *v = (const S *)d.buf[b.parity][1];
-        S *un = (S *)d.buf[b.parity ^ 1][0];
-        S *vn = (S *)d.buf[b.parity ^ 1][1];
-        const int ze = min(z0 + d.zc, d.nz);
-        if constexpr (sizeof(S) == 8) {
-            if (a.dt == 1.0) {
-                tb_tile<S, TXG, TY, T, NT, NOISE, true, true>(u, v, un, vn, a, w.bx * (TXG * 4), w.by * TY, z0, ze,
-                                                              t0, lds, nullptr);
-                continue;
-            }
-        }
-        tb_tile<S, TXG, TY, T, NT, NOISE, true, false>(u, v, un, vn, a, w.bx * (TXG * 4), w.by * TY, z0, ze, t0,
-                                                       lds, nullptr);
-    }
+    const uint32_t rest = lb / (uint32_t)a.ntx;
+    tb_item<S, TXG, TY, T, NT, NOISE>(u, v, un, vn, a, (int)(lb % (uint32_t)a.ntx), (int)(rest % (uint32_t)a.nty),
+                                      (int)(rest / (uint32_t)a.nty), NOISE ? step_index(a) : 0);
+}
+
+// Sweep over many independent simulations: one workgroup per work item (one
+// tile x z-chunk of one simulation), items sorted by decreasing cost, so that
+// the places that fall free last are filled with the cheapest ones. Items are
+// dealt to the XCDs in ranges of `slots` (about what is resident at once):
+// neighbouring tiles on one XCD, and every XCD long and short items.
+template <typename S, int TXG, int TY, int T, int NT, int NOISE>
+__global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb_batch(BatchArgs b)
+{
+    const uint32_t r0 = blockIdx.x / (uint32_t)b.slots * (uint32_t)b.slots;
+    const uint32_t lb = r0 + xcd_logical_block(blockIdx.x - r0, min((uint32_t)b.slots, gridDim.x - r0));
+    const WorkItem w = b.items[lb];
+    const SimDesc &d = b.sims[w.sim];
+    StepArgs a = b.coef;
+    a.nx = d.nx;
+    a.ny = d.ny;
+    a.nz = d.nz;
+    a.zc = d.zc;
+    a.F = d.F;
+    a.FK = d.FK;
+    a.F_f = d.F_f;
+    a.FK_f = d.FK_f;
+    a.seed = d.seed;
+    tb_item<S, TXG, TY, T, NT, NOISE>((const S *)d.buf[b.parity][0], (const S *)d.buf[b.parity][1],
+                                      (S *)d.buf[b.parity ^ 1][0], (S *)d.buf[b.parity ^ 1][1], a, w.bx, w.by, w.bz,
+                                      NOISE ? (b.t_dev ? *b.t_dev + b.t : b.t) : 0);
 }
 
 // ------------------------------------------------------------------ launch
@@ -512,8 +500,7 @@ static hipError_t launch_tb_t(const void *u, const void *v, void *un, void *vn, 
 //   shape 5: TXG=16, 1024 lanes, region 18 x 56
 // One workgroup per CU: NT lanes leave 512 / ceil(NT / 256) registers per
 // lane. The deepest fusion whose registers fit that budget without spills
-// (the persistent batched kernel holds a few more registers for its work
-// list):
+// (batched sweeps take the larger shapes one step less deep):
 template <typename S, int NT, bool BATCH> constexpr int tb_max_T_of()
 {
     if (NT <= 512) return 4;
@@ -562,9 +549,10 @@ hipError_t dispatch_tb_T(int T, int shape, const void *u, const void *v, void *u
 }
 
 template <typename S, int TXG, int TY, int T, int NT>
-static hipError_t launch_tb_batch_t(const BatchArgs &b, int grid, hipStream_t st)
+static hipError_t launch_tb_batch_t(const BatchArgs &b, hipStream_t st)
 {
-    if (grid < 1) return hipErrorInvalidConfiguration;
+    const int grid = b.n_items;
+    if (grid < 1 || b.slots < 8) return hipErrorInvalidConfiguration;
     auto go = [&](auto mode) {
         hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value>), dim3(grid), dim3(NT), 0, st, b);
         return hipGetLastError();
@@ -576,31 +564,31 @@ static hipError_t launch_tb_batch_t(const BatchArgs &b, int grid, hipStream_t st
 }
 
 template <typename S, int T>
-static hipError_t batch_shape(int shape, const BatchArgs &b, int grid, hipStream_t st)
+static hipError_t batch_shape(int shape, const BatchArgs &b, hipStream_t st)
 {
     switch (shape) {
-    case 1: return launch_tb_batch_t<S, 16, 14 - 2 * T, T, 256>(b, grid, st);
-    case 2: return launch_tb_batch_t<S, 16, 28 - 2 * T, T, 512>(b, grid, st);
-    case 3: return launch_tb_batch_t<S, 32, 14 - 2 * T, T, 512>(b, grid, st);
+    case 1: return launch_tb_batch_t<S, 16, 14 - 2 * T, T, 256>(b, st);
+    case 2: return launch_tb_batch_t<S, 16, 28 - 2 * T, T, 512>(b, st);
+    case 3: return launch_tb_batch_t<S, 32, 14 - 2 * T, T, 512>(b, st);
     case 4:
-        if constexpr (T <= tb_max_T_of<S, 768, true>()) return launch_tb_batch_t<S, 16, 42 - 2 * T, T, 768>(b, grid, st);
+        if constexpr (T <= tb_max_T_of<S, 768, true>()) return launch_tb_batch_t<S, 16, 42 - 2 * T, T, 768>(b, st);
         break;
     case 5:
         if constexpr (T <= tb_max_T_of<S, 1024, true>())
-            return launch_tb_batch_t<S, 16, 56 - 2 * T, T, 1024>(b, grid, st);
+            return launch_tb_batch_t<S, 16, 56 - 2 * T, T, 1024>(b, st);
         break;
     }
     return hipErrorInvalidValue;
 }
 
 template <typename S>
-hipError_t batch_T(int T, int shape, const BatchArgs &b, int grid, hipStream_t st)
+hipError_t batch_T(int T, int shape, const BatchArgs &b, hipStream_t st)
 {
     switch (T) {
-    case 1: return batch_shape<S, 1>(shape, b, grid, st);
-    case 2: return batch_shape<S, 2>(shape, b, grid, st);
-    case 3: return batch_shape<S, 3>(shape, b, grid, st);
-    case 4: return batch_shape<S, 4>(shape, b, grid, st);
+    case 1: return batch_shape<S, 1>(shape, b, st);
+    case 2: return batch_shape<S, 2>(shape, b, st);
+    case 3: return batch_shape<S, 3>(shape, b, st);
+    case 4: return batch_shape<S, 4>(shape, b, st);
     }
     return hipErrorInvalidValue;
 }
@@ -691,7 +679,7 @@ int occ_single_T(int T, int shape, bool noise)
     X template int occ_single_T<S>(int, int, bool);                                                                      \
     BATCHED(X, S)
 #define GS_TB_BATCH(X, S)                                                                                                \
-    X template hipError_t batch_T<S>(int, int, const BatchArgs &, int, hipStream_t);                                     \
+    X template hipError_t batch_T<S>(int, int, const BatchArgs &, hipStream_t);                                     \
     X template int occ_T<S>(int, int);
 #define GS_TB_SINGLE(X, S)
 #if GS_TB_STORAGE == 1
@@ -738,13 +726,13 @@ template <bool BATCH> static int max_T_for(int shape, int storage)
 int tb_max_T(int shape, int storage) { return max_T_for<false>(shape, storage); }
 int tb_batch_max_T(int shape, int storage) { return max_T_for<true>(shape, storage); }
 
-hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b, int grid, hipStream_t st)
+hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b, hipStream_t st)
 {
     switch (storage) {
-    case 0: return batch_T<double>(T, shape, b, grid, st);
-    case 1: return batch_T<float>(T, shape, b, grid, st);
-    case 2: return batch_T<bf16>(T, shape, b, grid, st);
-    case 3: return batch_T<f16>(T, shape, b, grid, st);
+    case 0: return batch_T<double>(T, shape, b, st);
+    case 1: return batch_T<float>(T, shape, b, st);
+    case 2: return batch_T<bf16>(T, shape, b, st);
+    case 3: return batch_T<f16>(T, shape, b, st);
     }
     return hipErrorInvalidValue;
 }
