@@ -425,11 +425,11 @@ hipError_t enqueue_steps(gs_sim *s, int64_t n, hipStream_t st, const uint64_t *t
         hipError_t e;
         int done = 1;
         if (is_blk_tile(s->tile)) {
-            done = (int)(left < s->tblock ? left : s->tblock);
+            done = gs::next_depth(left, s->tblock);
             e = gs::launch_block(s->p.storage, done, s->tile - first_blk(), s->buf[q][0], s->buf[q][1],
                                  s->buf[q ^ 1][0], s->buf[q ^ 1][1], a, st);
         } else if (is_tb_tile(s->tile)) {
-            done = (int)(left < s->tblock ? left : s->tblock);
+            done = gs::next_depth(left, s->tblock);
             e = gs::launch_tblock(s->p.storage, done, s->tile - gs::num_tiles(), s->buf[q][0], s->buf[q][1],
                                   s->buf[q ^ 1][0], s->buf[q ^ 1][1], a, st);
         } else {

