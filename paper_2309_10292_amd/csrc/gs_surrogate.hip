@@ -62,6 +62,12 @@ __device__ __forceinline__ bf16x8 load8(const u16 *p)
     return __builtin_bit_cast(bf16x8, q);
 }
 
+__device__ __forceinline__ uint4 pack8(const u16 (&v)[8])
+{
+    return uint4{(uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16),
+                 (uint32_t)v[4] | ((uint32_t)v[5] << 16), (uint32_t)v[6] | ((uint32_t)v[7] << 16)};
+}
+
 // ------------------------------------------------------------------ convolution
 // MODE_HIDDEN: z = acc + bias, writes z and GELU(z) (32 channels, BF16).
 // MODE_ACT:    the same, writing GELU(z) only (inference keeps no z).
@@ -78,7 +84,12 @@ __device__ __forceinline__ bf16x8 load8(const u16 *p)
 // while plane z is computed. Every MFMA operand is read from LDS: the ring is
 // stored channel group major so that a fragment read is 256 contiguous bytes
 // per 16 lanes (no bank conflicts), and the K loop keeps its reads a few
-// chunks ahead of the MFMAs that use them.
+// chunks ahead of the MFMAs that use them. The two tiles' output channels are
+// interleaved so that a lane holds 8 consecutive channels and a wavefront
+// stores (and the data gradient reads) whole 1 KB rows in 16-byte accesses: the
+// 8-channel layers, which HBM bounds (1.07 GB each way of a hidden tensor and
+// its pre-activation at 4 x 128^3), took 427 (forward) and 389 us (data
+// gradient) with 8-byte pieces of 32-byte runs and take 345 and 301.
 constexpr int PX = 16, PY = 4;               // patch (x, y)
 constexpr int RX = PX + 2, RY = PY + 2;      // ring plane (x, y)
 constexpr int RCELLS = RX * RY;              // cells per ring plane
@@ -208,52 +219,33 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
                 }
             }
         }
-        // acc[t][j]: output channel 16 t + 4 quad + j of cell (x0 + col, yrow, z).
+        // acc[t][j] with two tiles: output channel 8 quad + 4 t + j of cell
+        // (x0 + col, yrow, z), so a lane holds 8 consecutive channels.
         const size_t r = sbase + (size_t)(x0 + col) + (size_t)g.nx * ((size_t)yrow + (size_t)g.ny * z);
         if (row_ok) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const int co0 = 16 * t + 4 * quad;
-                if constexpr (MODE == MODE_HIDDEN) {
-                    uint2 zq, aq;
-                    u16 zb[4], ab[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float zz = acc[t][j] + a.bias[co0 + j];
-                        zb[j] = f2bf(zz);
-                        ab[j] = f2bf(gelu(zz));
-                    }
-                    zq.x = (uint32_t)zb[0] | ((uint32_t)zb[1] << 16);
-                    zq.y = (uint32_t)zb[2] | ((uint32_t)zb[3] << 16);
-                    aq.x = (uint32_t)ab[0] | ((uint32_t)ab[1] << 16);
-                    aq.y = (uint32_t)ab[2] | ((uint32_t)ab[3] << 16);
-                    *reinterpret_cast<uint2 *>(a.zout + r * 32 + co0) = zq;
-                    *reinterpret_cast<uint2 *>(a.aout + r * 32 + co0) = aq;
-                } else if constexpr (MODE == MODE_ACT) {
-                    u16 ab[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) ab[j] = f2bf(gelu(acc[t][j] + a.bias[co0 + j]));
-                    *reinterpret_cast<uint2 *>(a.aout + r * 32 + co0) =
-                        uint2{(uint32_t)ab[0] | ((uint32_t)ab[1] << 16), (uint32_t)ab[2] | ((uint32_t)ab[3] << 16)};
-                } else if constexpr (MODE == MODE_OUT) {
-                    if (quad == 0) {
-                        // r = s * ncell + cell indexes the planar (sample, cell) fields
-                        const IO *ru = (const IO *)a.res_u, *rv = (const IO *)a.res_v;
-                        ((IO *)a.out_u)[r] = ru[r] + (IO)(acc[t][0] + a.bias[0]);
-                        ((IO *)a.out_v)[r] = rv[r] + (IO)(acc[t][1] + a.bias[1]);
-                    }
-                } else {
-                    const uint2 zq = *reinterpret_cast<const uint2 *>(a.zprev + r * 32 + co0);
-                    const float zp[4] = {bf2f((u16)(zq.x & 0xffffu)), bf2f((u16)(zq.x >> 16)),
-                                         bf2f((u16)(zq.y & 0xffffu)), bf2f((u16)(zq.y >> 16))};
-                    u16 gb[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) gb[j] = f2bf(acc[t][j] * gelu_grad(zp[j]));
-                    uint2 gq;
-                    gq.x = (uint32_t)gb[0] | ((uint32_t)gb[1] << 16);
-                    gq.y = (uint32_t)gb[2] | ((uint32_t)gb[3] << 16);
-                    *reinterpret_cast<uint2 *>(a.aout + r * 32 + co0) = gq;
+            if constexpr (MODE == MODE_OUT) {
+                if (quad == 0) {
+                    // r = s * ncell + cell indexes the planar (sample, cell) fields
+                    const IO *ru = (const IO *)a.res_u, *rv = (const IO *)a.res_v;
+                    ((IO *)a.out_u)[r] = ru[r] + (IO)(acc[0][0] + a.bias[0]);
+                    ((IO *)a.out_v)[r] = rv[r] + (IO)(acc[0][1] + a.bias[1]);
                 }
+            } else if constexpr (MODE == MODE_DGRAD) {
+                const bf16x8 zp = load8(a.zprev + r * 32 + 8 * quad);
+                u16 gb[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) gb[c] = f2bf(acc[c / 4][c % 4] * gelu_grad((float)zp[c]));
+                *reinterpret_cast<uint4 *>(a.aout + r * 32 + 8 * quad) = pack8(gb);
+            } else {
+                u16 zb[8], ab[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const float zz = acc[c / 4][c % 4] + a.bias[8 * quad + c];
+                    zb[c] = f2bf(zz);
+                    ab[c] = f2bf(gelu(zz));
+                }
+                if constexpr (MODE == MODE_HIDDEN) *reinterpret_cast<uint4 *>(a.zout + r * 32 + 8 * quad) = pack8(zb);
+                *reinterpret_cast<uint4 *>(a.aout + r * 32 + 8 * quad) = pack8(ab);
             }
         }
         __syncthreads(); // every read of plane z-1's slot is done
@@ -363,7 +355,7 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) bias_r[t][j] = a.bias[16 * t + 4 * quad + j];
+            for (int j = 0; j < 4; ++j) bias_r[t][j] = a.bias[8 * quad + 4 * t + j];
     }
     auto cell_of = [&](int r, int z) __attribute__((always_inline)) {
         const int yrow = min(yw + r, g.ny - 1);
@@ -376,13 +368,10 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
     auto plane_step = [&](auto prev, int z, f32x4 (&acc)[RW][NT], const f32x4 (&accp)[RW][NT], u32x4 (&pre)[LOADS]) __attribute__((always_inline)) {
         constexpr bool PREV = decltype(prev)::value;
         load_plane(z + 2, pre);
-        uint2 zq[RW][NT];
+        bf16x8 zq[RW];
         if constexpr (PREV && MODE == MODE_DGRAD) {
 #pragma unroll
-            for (int r = 0; r < RW; ++r)
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    zq[r][t] = *reinterpret_cast<const uint2 *>(a.zprev + cell_of(r, z - 1) * 32 + 16 * t + 4 * quad);
+            for (int r = 0; r < RW; ++r) zq[r] = load8(a.zprev + cell_of(r, z - 1) * 32 + 8 * quad);
         }
 #pragma unroll
         for (int r = 0; r < RW; ++r)
@@ -402,7 +391,7 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
         };
 #pragma unroll
         for (int c = 0; c < KD; ++c) frag(c, c);
-        u16 e1[RW][NT][4], e2[RW][NT][4];
+        u16 e1[RW][8], e2[RW][8]; // 8 consecutive channels per lane and row
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             const int sl = c % KD;
@@ -422,18 +411,16 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
                         float zz = accp[r][t][j] + bias_r[t][j];
                         float gz = gelu(zz);
                         asm volatile("" : "+v"(zz), "+v"(gz));
-                        e1[r][t][j] = f2bf(zz);
-                        e2[r][t][j] = f2bf(gz);
+                        e1[r][4 * t + j] = f2bf(zz);
+                        e2[r][4 * t + j] = f2bf(gz);
                     } else if constexpr (MODE == MODE_ACT) {
                         float gz = gelu(accp[r][t][j] + bias_r[t][j]);
                         asm volatile("" : "+v"(gz));
-                        e1[r][t][j] = f2bf(gz);
+                        e1[r][4 * t + j] = f2bf(gz);
                     } else {
-                        const uint32_t w = j < 2 ? zq[r][t].x : zq[r][t].y;
-                        const float zp = bf2f((u16)((j & 1) ? (w >> 16) : (w & 0xffffu)));
-                        float gd = accp[r][t][j] * gelu_grad(zp);
+                        float gd = accp[r][t][j] * gelu_grad((float)zq[r][4 * t + j]);
                         asm volatile("" : "+v"(gd));
-                        e1[r][t][j] = f2bf(gd);
+                        e1[r][4 * t + j] = f2bf(gd);
                     }
                 }
             }
@@ -447,20 +434,12 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
             // clamped onto row 0's cell, whose own store then follows it
 #pragma unroll
             for (int r = RW - 1; r >= 0; --r) {
-                const size_t cell = cell_of(r, z - 1);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const int co0 = 16 * t + 4 * quad;
-                    const uint2 q1{(uint32_t)e1[r][t][0] | ((uint32_t)e1[r][t][1] << 16),
-                                   (uint32_t)e1[r][t][2] | ((uint32_t)e1[r][t][3] << 16)};
-                    if constexpr (MODE == MODE_HIDDEN) {
-                        const uint2 q2{(uint32_t)e2[r][t][0] | ((uint32_t)e2[r][t][1] << 16),
-                                       (uint32_t)e2[r][t][2] | ((uint32_t)e2[r][t][3] << 16)};
-                        *reinterpret_cast<uint2 *>(a.zout + cell * 32 + co0) = q1;
-                        *reinterpret_cast<uint2 *>(a.aout + cell * 32 + co0) = q2;
-                    } else {
-                        *reinterpret_cast<uint2 *>(a.aout + cell * 32 + co0) = q1;
-                    }
+                const size_t o = cell_of(r, z - 1) * 32 + 8 * quad;
+                if constexpr (MODE == MODE_HIDDEN) {
+                    *reinterpret_cast<uint4 *>(a.zout + o) = pack8(e1[r]);
+                    *reinterpret_cast<uint4 *>(a.aout + o) = pack8(e2[r]);
+                } else {
+                    *reinterpret_cast<uint4 *>(a.aout + o) = pack8(e1[r]);
                 }
             }
         }
@@ -469,37 +448,23 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
     auto last_epilogue = [&](int z, const f32x4 (&accp)[RW][NT]) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = RW - 1; r >= 0; --r) {
-            const size_t cell = cell_of(r, z);
+            const size_t o = cell_of(r, z) * 32 + 8 * quad;
+            u16 e1[8], e2[8];
+            bf16x8 zp = {};
+            if constexpr (MODE == MODE_DGRAD) zp = load8(a.zprev + o);
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const int co0 = 16 * t + 4 * quad;
-                u16 e1[4], e2[4];
-                if constexpr (MODE == MODE_HIDDEN) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float zz = accp[r][t][j] + bias_r[t][j];
-                        e1[j] = f2bf(zz);
-                        e2[j] = f2bf(gelu(zz));
-                    }
-                    *reinterpret_cast<uint2 *>(a.zout + cell * 32 + co0) =
-                        uint2{(uint32_t)e1[0] | ((uint32_t)e1[1] << 16), (uint32_t)e1[2] | ((uint32_t)e1[3] << 16)};
-                    *reinterpret_cast<uint2 *>(a.aout + cell * 32 + co0) =
-                        uint2{(uint32_t)e2[0] | ((uint32_t)e2[1] << 16), (uint32_t)e2[2] | ((uint32_t)e2[3] << 16)};
-                } else if constexpr (MODE == MODE_ACT) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) e1[j] = f2bf(gelu(accp[r][t][j] + bias_r[t][j]));
-                    *reinterpret_cast<uint2 *>(a.aout + cell * 32 + co0) =
-                        uint2{(uint32_t)e1[0] | ((uint32_t)e1[1] << 16), (uint32_t)e1[2] | ((uint32_t)e1[3] << 16)};
+            for (int c = 0; c < 8; ++c) {
+                const float acc = accp[r][c / 4][c % 4];
+                if constexpr (MODE == MODE_DGRAD) {
+                    e1[c] = f2bf(acc * gelu_grad((float)zp[c]));
                 } else {
-                    const uint2 zq = *reinterpret_cast<const uint2 *>(a.zprev + cell * 32 + co0);
-                    const float zp[4] = {bf2f((u16)(zq.x & 0xffffu)), bf2f((u16)(zq.x >> 16)),
-                                         bf2f((u16)(zq.y & 0xffffu)), bf2f((u16)(zq.y >> 16))};
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) e1[j] = f2bf(accp[r][t][j] * gelu_grad(zp[j]));
-                    *reinterpret_cast<uint2 *>(a.aout + cell * 32 + co0) =
-                        uint2{(uint32_t)e1[0] | ((uint32_t)e1[1] << 16), (uint32_t)e1[2] | ((uint32_t)e1[3] << 16)};
+                    const float zz = acc + bias_r[c / 4][c % 4];
+                    e1[c] = f2bf(MODE == MODE_HIDDEN ? zz : gelu(zz));
+                    if constexpr (MODE == MODE_HIDDEN) e2[c] = f2bf(gelu(zz));
                 }
             }
+            *reinterpret_cast<uint4 *>((MODE == MODE_HIDDEN ? a.zout : a.aout) + o) = pack8(e1);
+            if constexpr (MODE == MODE_HIDDEN) *reinterpret_cast<uint4 *>(a.aout + o) = pack8(e2);
         }
     };
 
@@ -965,7 +930,10 @@ __global__ __launch_bounds__(256) void repack(const float *__restrict__ W, int c
     for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
         const int j = e % 8, lane = (e / 8) % 64, t = (e / 512) % nt, c = e / (512 * nt);
         const int k = 32 * c + 8 * (lane / 16) + j;
-        const int d = k / cins, kc = k % cins, n = 16 * t + lane % 16;
+        // two tiles: row m of tile t is output channel 8 (m / 4) + 4 t + m % 4, so
+        // that a lane's accumulators of both tiles are 8 consecutive channels
+        const int m = lane % 16;
+        const int d = k / cins, kc = k % cins, n = nt == 2 ? 8 * (m / 4) + 4 * t + m % 4 : m;
         float w = 0.f;
         if (d < 27) {
             if (!dgrad) {
