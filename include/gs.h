@@ -338,7 +338,7 @@ gs_status gs_surrogate_get_params(gs_surrogate *s, float *params);
 
 /* Prediction of nsamp <= max_batch samples; io_storage is GS_F64 or GS_F32
  * for u, v, u_out, v_out (device, must not alias); F and k are host arrays of
- * nsamp values. Asynchronous after the upload of F and k. */
+ * nsamp values, read before the call returns. Asynchronous. */
 gs_status gs_surrogate_predict(gs_surrogate *s, int32_t nsamp, int32_t io_storage, const void *u, const void *v,
                                const double *F, const double *k, void *u_out, void *v_out);
 

@@ -857,8 +857,7 @@ __global__ __launch_bounds__(1024) void colsum_reduce(const float *__restrict__ 
 // ------------------------------------------------------------------ input, loss, optimiser
 template <typename IO>
 __global__ __launch_bounds__(256) void pack_input(const IO *__restrict__ u, const IO *__restrict__ v,
-                                                  const float *__restrict__ fk, int nsamp, int ncell,
-                                                  u16 *__restrict__ x)
+                                                  FkArgs fk, int nsamp, int ncell, u16 *__restrict__ x)
 {
     const size_t rows = (size_t)nsamp * ncell;
     for (size_t r = (size_t)blockIdx.x * blockDim.x + threadIdx.x; r < rows; r += (size_t)gridDim.x * blockDim.x) {
@@ -870,7 +869,7 @@ __global__ __launch_bounds__(256) void pack_input(const IO *__restrict__ u, cons
         const u16 ul = f2bf(uf - bf2f(uh)), vl = f2bf(vf - bf2f(vh));
         uint4 q;
         q.x = (uint32_t)uh | ((uint32_t)vh << 16);
-        q.y = (uint32_t)f2bf((fk[2 * s] - F_CENTER) / F_SCALE) | ((uint32_t)f2bf((fk[2 * s + 1] - K_CENTER) / K_SCALE) << 16);
+        q.y = (uint32_t)f2bf((fk.f[s] - F_CENTER) / F_SCALE) | ((uint32_t)f2bf((fk.k[s] - K_CENTER) / K_SCALE) << 16);
         q.z = (uint32_t)ul | ((uint32_t)vl << 16);
         q.w = 0u;
         *reinterpret_cast<uint4 *>(x + r * 8) = q;
@@ -1019,7 +1018,7 @@ hipError_t launch_bias_reduce(const float *bpart, int cout, float *gb, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_pack_input(int io_f64, const void *u, const void *v, const float *fk, int nsamp, int ncell,
+hipError_t launch_pack_input(int io_f64, const void *u, const void *v, const FkArgs &fk, int nsamp, int ncell,
                              uint16_t *x, hipStream_t st)
 {
     const int grid = grid_cap((size_t)nsamp * ncell, 256, 65536);

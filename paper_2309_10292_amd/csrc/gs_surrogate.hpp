@@ -48,7 +48,13 @@ hipError_t launch_wgrad(int cin, int couts, const WgradArgs &a, hipStream_t st);
 hipError_t launch_wgrad_reduce(const float *part, int pco, int pci, int cout, int cin, int lo_pairs, float *gW,
                                hipStream_t st);
 hipError_t launch_bias_reduce(const float *bpart, int cout, float *gb, hipStream_t st);
-hipError_t launch_pack_input(int io_f64, const void *u, const void *v, const float *fk, int nsamp, int ncell,
+// The samples' (F, k) go with the launch, up to FK_PER_LAUNCH samples at once:
+// no device copy of them to wait for (a prediction at 128^3 lost 35 us to it).
+constexpr int FK_PER_LAUNCH = 64;
+struct FkArgs {
+    float f[FK_PER_LAUNCH], k[FK_PER_LAUNCH];
+};
+hipError_t launch_pack_input(int io_f64, const void *u, const void *v, const FkArgs &fk, int nsamp, int ncell,
                              uint16_t *x, hipStream_t st);
 int loss_blocks();
 hipError_t launch_loss_grad(const float *pu, const float *pv, const float *tu, const float *tv, size_t rows,

@@ -29,7 +29,7 @@ int nchunks(int cins) { return (27 * cins + 31) / 32; }
 size_t a256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct Layout {
-    size_t x0, z[3], a[3], pu, pv, dz[3], dz4, par, grad, m, v, wf[4], wd[4], wpart, cpart, lpart, fk, total;
+    size_t x0, z[3], a[3], pu, pv, dz[3], dz4, par, grad, m, v, wf[4], wd[4], wpart, cpart, lpart, total;
 };
 
 Layout layout(size_t cells, int B)
@@ -63,7 +63,6 @@ Layout layout(size_t cells, int B)
     L.wpart = take((size_t)gs::nn::wgrad_blocks() * 27 * 32 * 32 * 4);
     L.cpart = take((size_t)gs::nn::wgrad_blocks() * 32 * 4);
     L.lpart = take((size_t)gs::nn::loss_blocks() * 8);
-    L.fk = take((size_t)B * 2 * 4);
     L.total = o;
     return L;
 }
@@ -127,17 +126,11 @@ hipError_t repack_all(gs_surrogate *s)
     return e;
 }
 
-gs_status upload_fk(gs_surrogate *s, int32_t nsamp, const double *F, const double *k)
+gs_status check_fk(int32_t nsamp, const double *F, const double *k)
 {
-    std::vector<float> fk(2 * (size_t)nsamp);
-    for (int i = 0; i < nsamp; ++i) {
+    for (int i = 0; i < nsamp; ++i)
         if (!std::isfinite(F[i]) || !std::isfinite(k[i])) return fail(GS_ERR_INVALID_ARG, "F/k of sample %d not finite", i);
-        fk[2 * i] = (float)F[i];
-        fk[2 * i + 1] = (float)k[i];
-    }
-    hipError_t e = hipMemcpyAsync(at<float>(s, s->L.fk), fk.data(), fk.size() * 4, hipMemcpyHostToDevice, s->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(s->stream); // fk is a stack vector
-    return e == hipSuccess ? GS_OK : hip_fail(e, "F/k upload");
+    return GS_OK;
 }
 
 // Planes per workgroup chunk of the convolutions for a batch of nsamp
@@ -156,12 +149,23 @@ int conv_zc(const gs_surrogate *s, int nsamp)
 // Forward pass of nsamp samples; keeps the activations, and the
 // pre-activations too when keep_pre (the backward pass needs them; a
 // prediction does not, and skips their stores).
-hipError_t forward(gs_surrogate *s, int32_t nsamp, int io_f64, const void *u, const void *v, void *uo, void *vo,
-                   bool keep_pre)
+hipError_t forward(gs_surrogate *s, int32_t nsamp, int io_f64, const void *u, const void *v, const double *F,
+                   const double *k, void *uo, void *vo, bool keep_pre)
 {
     using namespace gs::nn;
-    hipError_t e = launch_pack_input(io_f64, u, v, at<float>(s, s->L.fk), nsamp, s->geo.ncell,
-                                     at<uint16_t>(s, s->L.x0), s->stream);
+    hipError_t e = hipSuccess;
+    const size_t es = io_f64 ? 8 : 4;
+    for (int32_t i0 = 0; i0 < nsamp && e == hipSuccess; i0 += FK_PER_LAUNCH) {
+        const int32_t n = nsamp - i0 < FK_PER_LAUNCH ? nsamp - i0 : FK_PER_LAUNCH;
+        const size_t row = (size_t)i0 * s->geo.ncell;
+        FkArgs fk = {};
+        for (int32_t i = 0; i < n; ++i) {
+            fk.f[i] = (float)F[i0 + i];
+            fk.k[i] = (float)k[i0 + i];
+        }
+        e = launch_pack_input(io_f64, (const char *)u + row * es, (const char *)v + row * es, fk, n, s->geo.ncell,
+                              at<uint16_t>(s, s->L.x0) + row * 8, s->stream);
+    }
     const float *P = at<float>(s, s->L.par);
     const uint16_t *in = at<uint16_t>(s, s->L.x0);
     for (int l = 0; l < 3 && e == hipSuccess; ++l) {
@@ -275,8 +279,8 @@ gs_status gs_surrogate_predict(gs_surrogate *s, int32_t nsamp, int32_t io_storag
     if (io_storage != GS_F64 && io_storage != GS_F32) return fail(GS_ERR_UNSUPPORTED, "surrogate I/O is FP64 or FP32");
     if (!u || !v || !u_out || !v_out || !F || !k) return fail(GS_ERR_INVALID_ARG, "NULL pointer");
     if (u_out == u || v_out == v || u_out == v || v_out == u) return fail(GS_ERR_INVALID_ARG, "outputs must not alias inputs");
-    if ((st = upload_fk(s, nsamp, F, k)) != GS_OK) return st;
-    hipError_t e = forward(s, nsamp, io_storage == GS_F64, u, v, u_out, v_out, false);
+    if ((st = check_fk(nsamp, F, k)) != GS_OK) return st;
+    hipError_t e = forward(s, nsamp, io_storage == GS_F64, u, v, F, k, u_out, v_out, false);
     if (e != hipSuccess) return hip_fail(e, "surrogate forward");
     s->last_fwd = nsamp;
     s->last_fwd_loss = false; // the stored data gradients no longer match the activations
@@ -292,10 +296,10 @@ gs_status gs_surrogate_loss_grad(gs_surrogate *s, int32_t nsamp, const float *u,
     if (st != GS_OK) return st;
     if (nsamp < 1 || nsamp > s->max_batch) return fail(GS_ERR_INVALID_ARG, "nsamp %d outside [1, %d]", nsamp, s->max_batch);
     if (!u || !v || !u_target || !v_target || !F || !k) return fail(GS_ERR_INVALID_ARG, "NULL pointer");
-    if ((st = upload_fk(s, nsamp, F, k)) != GS_OK) return st;
+    if ((st = check_fk(nsamp, F, k)) != GS_OK) return st;
     const size_t rows = (size_t)nsamp * s->geo.ncell;
     float *pu = at<float>(s, s->L.pu), *pv = at<float>(s, s->L.pv);
-    hipError_t e = forward(s, nsamp, 0, u, v, pu, pv, true);
+    hipError_t e = forward(s, nsamp, 0, u, v, F, k, pu, pv, true);
     const double n_terms = 2.0 * (double)rows;
     uint16_t *dz4 = at<uint16_t>(s, s->L.dz4);
     if (e == hipSuccess)

@@ -427,3 +427,18 @@ def test_trained_surrogate_gain_l128(torch):
     if os.environ.get("GS_REPORT_DIR"):
         with open(os.path.join(os.environ["GS_REPORT_DIR"], "surrogate_gain_l128.json"), "w") as f:
             json.dump(report, f, indent=1)
+
+
+def test_predict_more_samples_than_one_launch_packs(torch):
+    """(F, k) travel with the input packing's launches, 64 samples each: 70 samples equal the samples one by one."""
+    from paper_2309_10292_amd.surrogate import Surrogate
+    n, shape = 70, (4, 8, 16)
+    rng = np.random.default_rng(1)
+    u = torch.from_numpy(rng.uniform(0.2, 1.0, (n,) + shape).astype(np.float32)).cuda()
+    v = torch.from_numpy(rng.uniform(0.0, 0.5, (n,) + shape).astype(np.float32)).cuda()
+    F, k = rng.uniform(0.01, 0.06, n), rng.uniform(0.04, 0.07, n)
+    with Surrogate(16, 8, 4, max_batch=n) as m:
+        ou, ov = m.predict(u, v, F, k)
+        for i in (0, 1, 63, 64, 65, 69):
+            su, sv = m.predict(u[i], v[i], F[i], k[i])
+            assert torch.equal(su, ou[i]) and torch.equal(sv, ov[i]), i
