@@ -68,6 +68,16 @@ __device__ __forceinline__ uint4 pack8(const u16 (&v)[8])
                  (uint32_t)v[4] | ((uint32_t)v[5] << 16), (uint32_t)v[6] | ((uint32_t)v[7] << 16)};
 }
 
+// Workgroup barrier that waits for the wave's LDS operations only: global
+// loads in flight (the next planes' staging) stay in flight across it.
+__device__ __forceinline__ void wg_lds_barrier()
+{
+    __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0); vmcnt and expcnt not waited
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_barrier();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // ------------------------------------------------------------------ convolution
 // MODE_HIDDEN: z = acc + bias, writes z and GELU(z) (32 channels, BF16).
 // MODE_ACT:    the same, writing GELU(z) only (inference keeps no z).
@@ -90,13 +100,17 @@ __device__ __forceinline__ uint4 pack8(const u16 (&v)[8])
 // 8-channel layers, which HBM bounds (1.07 GB each way of a hidden tensor and
 // its pre-activation at 4 x 128^3), took 427 (forward) and 389 us (data
 // gradient) with 8-byte pieces of 32-byte runs and take 345 and 301.
+template <int N> struct IntC {
+    static constexpr int value = N;
+};
 constexpr int PX = 16, PY = 4;               // patch (x, y)
 constexpr int RX = PX + 2, RY = PY + 2;      // ring plane (x, y)
 constexpr int RCELLS = RX * RY;              // cells per ring plane
 
-template <int CIN, int NT, int MODE, typename IO>
+template <int MODE>
 __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
 {
+    constexpr int CIN = 8, NT = 2;
     constexpr int NCH = (27 * CIN + 31) / 32;
     constexpr int VPC = CIN / 8;              // 16-byte vectors per cell
     // Ring layout: channel group major, cells contiguous within a group, so
@@ -145,16 +159,6 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
     }
     __syncthreads();
 
-    // One output-channel tile with 32 input channels (the output layer): its
-    // 27 weight fragments stay in registers, so the K loop reads only the
-    // activation fragments from LDS.
-    constexpr bool WREG = CIN == 32 && NT == 1;
-    bf16x8 wreg[WREG ? 27 : 1];
-    if constexpr (WREG) {
-#pragma unroll
-        for (int c = 0; c < 27; ++c) wreg[c] = __builtin_bit_cast(bf16x8, wl[c * 64 + lane]);
-    }
-
     const int yrow = y0 + wave;
     const bool row_ok = yrow < g.ny;
     for (int z = z0; z < ze; ++z) {
@@ -170,67 +174,30 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
         // A = weights (rows: output channels), B = activations (columns:
         // cells), so a lane's accumulators are 4 consecutive output channels
         // of one cell.
-        if constexpr (CIN == 32) {
-            // K chunk c is offset d = c with all 32 input channels. The 27
-            // chunks are unrolled with the fragments of the next KD chunks in
-            // flight (a register ring), so each MFMA's LDS reads were issued
-            // KD chunks earlier.
-            constexpr int KD = 3;
-            bf16x8 avr[KD], wvr[KD][NT];
-            auto load = [&](int c, int sl) {
-                const int dz = c / 9, dy = (c / 3) % 3, dx = c % 3;
-                const uint4 *rs = ring + ((z + dz + 2) % 3) * PLANE_V; // slot of plane z + dz - 1
-                avr[sl] = __builtin_bit_cast(bf16x8, rs[quad * GCELLS + (wave + dy) * RX + col + dx]);
-                if constexpr (!WREG) {
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) wvr[sl][t] = __builtin_bit_cast(bf16x8, wl[(c * NT + t) * 64 + lane]);
-                }
-            };
-#pragma unroll
-            for (int c = 0; c < KD; ++c) load(c, c);
-#pragma unroll
-            for (int c = 0; c < 27; ++c) {
-                const int sl = c % KD;
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(WREG ? wreg[c] : wvr[sl][t], avr[sl], acc[t], 0, 0, 0);
-                if (c + KD < 27) load(c + KD, sl);
-                // keep the reads KD chunks ahead of their MFMAs
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
 #pragma unroll 9
-            for (int c = 0; c < NCH; ++c) {
-                const int k0 = 32 * c + 8 * quad;
-                const int d = k0 / CIN, ci0 = k0 % CIN;
-                bf16x8 av;
-                if (d < 27) {
-                    const int dz = d / 9, dy = (d / 3) % 3, dx = d % 3;
-                    const int slot = (((z + dz - 1) % 3) + 3) % 3;
-                    const int cell = (wave + dy) * RX + col + dx;
-                    av = __builtin_bit_cast(bf16x8, ring[slot * PLANE_V + (ci0 / 8) * GCELLS + cell]);
-                } else {
-                    av = __builtin_bit_cast(bf16x8, uint4{0u, 0u, 0u, 0u});
-                }
+        for (int c = 0; c < NCH; ++c) {
+            const int k0 = 32 * c + 8 * quad;
+            const int d = k0 / CIN, ci0 = k0 % CIN;
+            bf16x8 av;
+            if (d < 27) {
+                const int dz = d / 9, dy = (d / 3) % 3, dx = d % 3;
+                const int slot = (((z + dz - 1) % 3) + 3) % 3;
+                const int cell = (wave + dy) * RX + col + dx;
+                av = __builtin_bit_cast(bf16x8, ring[slot * PLANE_V + (ci0 / 8) * GCELLS + cell]);
+            } else {
+                av = __builtin_bit_cast(bf16x8, uint4{0u, 0u, 0u, 0u});
+            }
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const bf16x8 wv = __builtin_bit_cast(bf16x8, wl[(c * NT + t) * 64 + lane]);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, av, acc[t], 0, 0, 0);
-                }
+            for (int t = 0; t < NT; ++t) {
+                const bf16x8 wv = __builtin_bit_cast(bf16x8, wl[(c * NT + t) * 64 + lane]);
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, av, acc[t], 0, 0, 0);
             }
         }
         // acc[t][j] with two tiles: output channel 8 quad + 4 t + j of cell
         // (x0 + col, yrow, z), so a lane holds 8 consecutive channels.
         const size_t r = sbase + (size_t)(x0 + col) + (size_t)g.nx * ((size_t)yrow + (size_t)g.ny * z);
         if (row_ok) {
-            if constexpr (MODE == MODE_OUT) {
-                if (quad == 0) {
-                    // r = s * ncell + cell indexes the planar (sample, cell) fields
-                    const IO *ru = (const IO *)a.res_u, *rv = (const IO *)a.res_v;
-                    ((IO *)a.out_u)[r] = ru[r] + (IO)(acc[0][0] + a.bias[0]);
-                    ((IO *)a.out_v)[r] = rv[r] + (IO)(acc[0][1] + a.bias[1]);
-                }
-            } else if constexpr (MODE == MODE_DGRAD) {
+            if constexpr (MODE == MODE_DGRAD) {
                 const bf16x8 zp = load8(a.zprev + r * 32 + 8 * quad);
                 u16 gb[8];
 #pragma unroll
@@ -256,6 +223,172 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
         }
         __syncthreads();
     }
+}
+
+// Output layer (32 -> 2 channels, residual added). As an implicit GEMM over the
+// 27 offsets its 2 output channels fill 2 of an MFMA tile's 16 rows. Here the
+// rows are the 9 (y, x) offsets of both channels instead (18 rows, two tiles),
+// and K runs over the 32 channels and the three z offsets:
+//   Q[dy, dx, o](x, y, z) = sum over dz, c of W[o][c][dz, dy, dx] a(x, y, z + dz, c),
+//   out[o](x, y, z) = sum over dy, dx of Q[dy, dx, o](x + dx, y + dy, z),
+// six MFMAs per 16 cells instead of 27 and every activation fragment read once,
+// straight from memory (16 cells x 64 bytes are contiguous). The nine shifted
+// terms of an output are added from LDS, 144 bytes of traffic per cell instead
+// of 1.7 KB of fragments.
+//
+// A workgroup of eight wavefronts owns OUT_TY output rows of up to OUT_NG
+// 16-cell groups (a whole row when it fits, else OUT_NG - 2 output groups
+// between two halo groups) of one sample and marches through a chunk of z
+// planes; wavefront w computes Q of region row y0 - 1 + w. Planes z - 1, z and
+// z + 1 sit in registers (five slots, planes z + 2 and z + 3 on their way), Q in
+// one of two LDS buffers, so there is one barrier per plane, which waits for LDS
+// operations only.
+// What bounds it: the read of the activations (0.54 GB at 4 x 128^3, 0.11 ms at
+// the rate of a large copy; a third more with the rows two workgroups read).
+// 4 x 128^3: 176 us (363 as an implicit GEMM over 27 offsets). The prefetch has
+// to stay in flight: waits are in order, so with the residual inputs loaded
+// after it, or the addresses in spilled registers, a plane cost 250 us' worth of
+// exposed latency.
+constexpr int OUT_TY = 6, OUT_NG = 8, OUT_COLS = 16 * OUT_NG;
+constexpr int OUT_PLANE = (OUT_TY + 2) * OUT_COLS + 8; // float2 per (dy, dx); the pad spreads the quads' writes over the banks
+// FULL: rows of at least OUT_NG groups, so that every load is unconditional (the
+// compiler's waits then count the loads in flight; behind conditions they drain
+// them).
+template <typename IO, bool FULL>
+__global__ __launch_bounds__(512) void conv_out_kernel(ConvArgs a)
+{
+    __shared__ float2 q_l[2][9 * OUT_PLANE];
+    const Geo g = a.geo;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int col = lane & 15, quad = lane >> 4;
+    const int ng = g.nx / 16;
+    const bool whole = ng <= OUT_NG;                // the tile is the whole row (periodic in itself)
+    const int tg = whole ? ng : OUT_NG - 2;         // output groups of a tile
+    const int rg = whole ? ng : OUT_NG;             // groups computed
+    const int tx = (ng + tg - 1) / tg, ty = (g.ny + OUT_TY - 1) / OUT_TY, tzc = (g.nz + a.zc - 1) / a.zc;
+    int b = blockIdx.x;
+    const int bx = b % tx;
+    b /= tx;
+    const int by = b % ty;
+    b /= ty;
+    const int bz = b % tzc;
+    const int s = b / tzc;
+    const int g0 = bx * tg, y0 = by * OUT_TY, z0 = bz * a.zc, ze = min(z0 + a.zc, g.nz);
+    const size_t sbase = (size_t)s * g.ncell, plane = (size_t)g.nx * g.ny;
+
+    bf16x8 w[3][2];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) w[d][t] = load8(a.wpack + ((d * 2 + t) * 64 + lane) * 8);
+
+    // Every address is a wavefront's base plus this lane's bytes. Group i of
+    // region row `wave` starts at cell row + gcell[i] of a plane; a lane reads 8
+    // channels of its cell.
+    const size_t row = sbase + (size_t)((y0 - 1 + wave + g.ny) % g.ny) * g.nx;
+    int gcell[OUT_NG];
+#pragma unroll
+    for (int i = 0; i < OUT_NG; ++i) gcell[i] = 16 * ((g0 + (whole ? min(i, ng - 1) : i - 1) + ng) % ng);
+    const uint32_t lane_b = col * 64 + quad * 16;
+    bf16x8 f[5][OUT_NG]; // plane z in slot (z - z0 + 1) mod 5
+    auto load_plane = [&](int z, bf16x8 (&o)[OUT_NG]) __attribute__((always_inline)) {
+        const u16 *base = a.in + (row + (size_t)wrapc(z, g.nz) * plane) * 32;
+#pragma unroll
+        for (int i = 0; i < OUT_NG; ++i)
+            if (FULL || i < rg)
+                o[i] = load8(reinterpret_cast<const u16 *>(reinterpret_cast<const char *>(base + (size_t)gcell[i] * 32) + lane_b));
+    };
+    const float2 bias = {a.bias[0], a.bias[1]};
+    // This lane's outputs: column x of rows wave / 2 and 4 more.
+    const int xw = (wave & 1) * 64, x = xw + lane, row0 = wave >> 1;
+    const int c = (whole ? 0 : 16) + x; // its column in the region
+    const int cl = whole && c == 0 ? g.nx - 1 : c - 1, cr = whole && c == g.nx - 1 ? 0 : c + 1;
+    const int ncol = min(16 * tg, g.nx - 16 * g0);
+    const bool x_ok = x < ncol;
+    bool row_ok[2];
+    size_t out_row[2]; // (rows without outputs load a valid residual, as do lanes past the tile)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        row_ok[h] = row0 + 4 * h < OUT_TY && y0 + row0 + 4 * h < g.ny;
+        out_row[h] = sbase + (row_ok[h] ? (size_t)(y0 + row0 + 4 * h) * g.nx + 16 * g0 : 0);
+    }
+    const uint32_t out_b = (uint32_t)min(x, ncol - 1) * (uint32_t)sizeof(IO);
+    auto io_at = [&](const void *p, size_t e) __attribute__((always_inline)) {
+        return reinterpret_cast<IO *>(const_cast<char *>(static_cast<const char *>(p)) + e * sizeof(IO) + out_b);
+    };
+    auto step = [&](int z, auto phase) __attribute__((always_inline)) {
+        constexpr int P = decltype(phase)::value; // (z - z0) mod 5
+        // The residual inputs are loaded before the prefetch: loads complete in
+        // order, and waiting for them must not wait for it.
+        IO res[2][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const size_t r = out_row[h] + (size_t)z * plane;
+            res[h][0] = *io_at(a.res_u, r);
+            res[h][1] = *io_at(a.res_v, r);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        load_plane(min(z + 3, ze), f[(P + 4) % 5]);
+        float2 *q = q_l[(z - z0) & 1];
+#pragma unroll
+        for (int i = 0; i < OUT_NG; ++i) {
+            if (!FULL && i >= rg) break;
+            f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[d][t], f[(P + d) % 5][i], acc[t], 0, 0, 0);
+            // acc[t][j]: row 16 t + 4 quad + j = 2 (3 dy + dx) + o of cell (16 i + col)
+            float2 *dst = q + wave * OUT_COLS + 16 * i + col;
+            dst[(2 * quad) * OUT_PLANE] = float2{acc[0][0], acc[0][1]};
+            dst[(2 * quad + 1) * OUT_PLANE] = float2{acc[0][2], acc[0][3]};
+            if (quad == 0) dst[8 * OUT_PLANE] = float2{acc[1][0], acc[1][1]};
+            if (i & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        wg_lds_barrier();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (!(row_ok[h] && x_ok)) continue;
+            float2 sum = bias;
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                const float2 *p = q + 3 * dy * OUT_PLANE + (row0 + 4 * h + dy) * OUT_COLS;
+                const float2 l = p[cl], m = p[OUT_PLANE + c], r = p[2 * OUT_PLANE + cr];
+                sum.x += (l.x + m.x) + r.x;
+                sum.y += (l.y + m.y) + r.y;
+            }
+            const size_t r = out_row[h] + (size_t)z * plane;
+            *io_at(a.out_u, r) = res[h][0] + (IO)sum.x;
+            *io_at(a.out_v, r) = res[h][1] + (IO)sum.y;
+        }
+    };
+#pragma unroll
+    for (int p = 0; p < 4; ++p) load_plane(z0 - 1 + p, f[p]);
+    for (int z = z0; z < ze; z += 5) {
+        step(z, IntC<0>{});
+        if (z + 1 < ze) step(z + 1, IntC<1>{});
+        if (z + 2 < ze) step(z + 2, IntC<2>{});
+        if (z + 3 < ze) step(z + 3, IntC<3>{});
+        if (z + 4 < ze) step(z + 4, IntC<4>{});
+    }
+}
+// Planes per workgroup of conv_out_kernel, one workgroup per CU: the chunk with
+// the fewest plane times, rounds of workgroups times its planes and the two
+// extra ones it reads.
+static int conv_out_zc(const Geo &g, size_t cols)
+{
+    int best = 1;
+    size_t cost = ~(size_t)0;
+    for (int n = 1; n <= g.nz && n <= 64; ++n) {
+        const int zc = (g.nz + n - 1) / n;
+        const size_t blocks = cols * ((g.nz + zc - 1) / zc), c = (blocks + 255) / 256 * (zc + 2);
+        if (c < cost) {
+            cost = c;
+            best = zc;
+        }
+    }
+    return best;
 }
 
 // 32 -> 32 convolutions of the forward hidden layer (with or without the
@@ -569,15 +702,6 @@ __device__ __forceinline__ bf16x8 frag_tr(const u16 *row, int cell0, int c0, int
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// Workgroup barrier that waits for the wave's LDS operations only: global
-// loads in flight (the next planes' staging) stay in flight across it.
-__device__ __forceinline__ void wg_lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0); vmcnt and expcnt not waited
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
 template <int CIN, int COUTS, int MT, int NT, int TR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void wgrad_kernel(WgradArgs a)
 {
@@ -947,6 +1071,18 @@ __global__ __launch_bounds__(256) void repack(const float *__restrict__ W, int c
     }
 }
 
+// Weights of the output layer for conv_out_kernel: fragment 2 dz + t, row m of
+// tile t is offset (16 t + m) / 2 of the nine (dy, dx) and output channel m % 2
+// (rows past 17 are zero), 8 consecutive input channels per lane.
+__global__ __launch_bounds__(256) void repack_out(const float *__restrict__ W, u16 *__restrict__ out)
+{
+    const int e = blockIdx.x * 256 + threadIdx.x; // 6 x 64 x 8
+    const int j = e % 8, lane = e / 8 % 64, t = e / 512 % 2, dz = e / 1024;
+    if (dz >= 3) return;
+    const int r = 16 * t + lane % 16, ci = 8 * (lane / 16) + j;
+    out[e] = r < 18 ? f2bf(W[((size_t)(r % 2) * 32 + ci) * 27 + 9 * dz + r / 2]) : (u16)0;
+}
+
 // ------------------------------------------------------------------ launchers
 static int grid_cap(size_t work, int per_block, int cap)
 {
@@ -973,17 +1109,28 @@ hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a,
             hipLaunchKernelGGL(conv32p_kernel<MODE_DGRAD>, dim3((unsigned)nb), dim3(64 * C32_WAVES), 0, st, b);
         return hipGetLastError();
     }
+    if (cin == 32 && nt == 1 && mode == MODE_OUT) {
+        ConvArgs b = a;
+        const int ng = a.geo.nx / 16, tg = ng <= OUT_NG ? ng : OUT_NG - 2;
+        const size_t cols = (size_t)((ng + tg - 1) / tg) * ((a.geo.ny + OUT_TY - 1) / OUT_TY) * a.nsamp;
+        b.zc = conv_out_zc(a.geo, cols);
+        const size_t nb = cols * ((a.geo.nz + b.zc - 1) / b.zc);
+        if (nb == 0 || nb > 0x7fffffffu) return hipErrorInvalidConfiguration;
+        auto go = [&](auto full) {
+            if (io_f64) hipLaunchKernelGGL((conv_out_kernel<double, decltype(full)::value>), dim3((unsigned)nb), dim3(512), 0, st, b);
+            else hipLaunchKernelGGL((conv_out_kernel<float, decltype(full)::value>), dim3((unsigned)nb), dim3(512), 0, st, b);
+            return hipGetLastError();
+        };
+        return ng >= OUT_NG ? go(BoolC<true>{}) : go(BoolC<false>{});
+    }
     const size_t blocks = (size_t)(a.geo.nx / PX) * ((a.geo.ny + PY - 1) / PY) * ((a.geo.nz + a.zc - 1) / a.zc) * a.nsamp;
     if (blocks == 0 || blocks > 0x7fffffffu) return hipErrorInvalidConfiguration;
     const int grid = (int)blocks;
-#define GS_CONV(CI, N, M, IO) hipLaunchKernelGGL((conv_kernel<CI, N, M, IO>), dim3(grid), dim3(256), 0, st, a)
-    if (cin == 8 && nt == 2 && mode == MODE_HIDDEN) GS_CONV(8, 2, MODE_HIDDEN, float);
-    else if (cin == 8 && nt == 2 && mode == MODE_ACT) GS_CONV(8, 2, MODE_ACT, float);
-    else if (cin == 32 && nt == 1 && mode == MODE_OUT && io_f64) GS_CONV(32, 1, MODE_OUT, double);
-    else if (cin == 32 && nt == 1 && mode == MODE_OUT) GS_CONV(32, 1, MODE_OUT, float);
-    else if (cin == 8 && nt == 2 && mode == MODE_DGRAD) GS_CONV(8, 2, MODE_DGRAD, float);
+    if (cin != 8 || nt != 2) return hipErrorInvalidValue;
+    if (mode == MODE_HIDDEN) hipLaunchKernelGGL(conv_kernel<MODE_HIDDEN>, dim3(grid), dim3(256), 0, st, a);
+    else if (mode == MODE_ACT) hipLaunchKernelGGL(conv_kernel<MODE_ACT>, dim3(grid), dim3(256), 0, st, a);
+    else if (mode == MODE_DGRAD) hipLaunchKernelGGL(conv_kernel<MODE_DGRAD>, dim3(grid), dim3(256), 0, st, a);
     else return hipErrorInvalidValue;
-#undef GS_CONV
     return hipGetLastError();
 }
 
@@ -1045,6 +1192,12 @@ hipError_t launch_adam(float *p, const float *g, float *m, float *v, int n, floa
 {
     hipLaunchKernelGGL(adam_kernel, dim3(grid_cap(n, 256, 1024)), dim3(256), 0, st, p, g, m, v, n, lr, b1, b2, eps,
                        c1, c2);
+    return hipGetLastError();
+}
+
+hipError_t launch_repack_out(const float *W, uint16_t *out, hipStream_t st)
+{
+    hipLaunchKernelGGL(repack_out, dim3(12), dim3(256), 0, st, W, out);
     return hipGetLastError();
 }
 

@@ -61,6 +61,8 @@ hipError_t launch_loss_grad(const float *pu, const float *pv, const float *tu, c
                             float scale, uint16_t *dz4, double *part, hipStream_t st);
 hipError_t launch_adam(float *p, const float *g, float *m, float *v, int n, float lr, float b1, float b2, float eps,
                        float c1, float c2, hipStream_t st);
+// The output layer's forward weights (conv_out_kernel's order, 6 x 512 values).
+hipError_t launch_repack_out(const float *W, uint16_t *out, hipStream_t st);
 hipError_t launch_repack(const float *W, int cout, int cin, int cins, int nt, int nch, int dgrad, int lo_pairs,
                          uint16_t *out, hipStream_t st);
 

@@ -115,9 +115,10 @@ hipError_t repack_all(gs_surrogate *s)
 {
     const float *P = at<float>(s, s->L.par);
     hipError_t e = hipSuccess;
-    for (int l = 0; l < 4 && e == hipSuccess; ++l)
+    for (int l = 0; l < 3 && e == hipSuccess; ++l)
         e = gs::nn::launch_repack(P + w_off(l), k_chan[l + 1], k_chan[l], k_cins[l], k_nt[l], nchunks(k_cins[l]), 0,
                                   l == 0 ? k_lo_pairs : 0, at<uint16_t>(s, s->L.wf[l]), s->stream);
+    if (e == hipSuccess) e = gs::nn::launch_repack_out(P + w_off(3), at<uint16_t>(s, s->L.wf[3]), s->stream);
     for (int l = 1; l < 4 && e == hipSuccess; ++l) {
         const int cins = l == 3 ? 8 : 32;
         e = gs::nn::launch_repack(P + w_off(l), k_chan[l + 1], k_chan[l], cins, 2, nchunks(cins), 1, 0,

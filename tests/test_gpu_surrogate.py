@@ -429,6 +429,49 @@ def test_trained_surrogate_gain_l128(torch):
             json.dump(report, f, indent=1)
 
 
+# grids at the edges of the output layer's tiles: the narrowest, a whole row of 8 16-cell groups, one and 7 groups more
+# (tiles between halo groups, the last with 1 or 3 groups), rows not a multiple of 6, a single z-plane chunk
+@pytest.mark.parametrize("shape", [(4, 4, 16), (5, 8, 128), (4, 7, 144), (4, 6, 240)])
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+def test_output_layer_tiles(torch, shape, dtype):
+    """predict()'s output layer against the FP64 layer applied to the GPU's own activations: residual plus the FP32
+    accumulation of 3 MFMAs (dz), 32 roundings each, and at most 12 for the bias and the 9 shifted partial sums.
+    FP32 outputs are rounded once more, and their correction is added to an FP32 residual."""
+    from paper_2309_10292_amd.surrogate import Surrogate
+    from synth import surrogate_init
+    nz, ny, nx = shape
+    rng = np.random.default_rng(sum(shape))
+    p = surrogate_init(3)
+    p[w_off_out():] *= 10  # the correction as large as the other layers' outputs
+    u = rng.uniform(0.2, 1.0, (2,) + shape)
+    v = rng.uniform(0.0, 0.5, (2,) + shape)
+    with Surrogate(nx, ny, nz, max_batch=2, params=p) as m:
+        tu, tv = (torch.from_numpy(a.astype(dtype)).cuda() for a in (u, v))
+        ou, ov = m.predict(tu, tv, [0.02, 0.05], [0.05, 0.06])
+        act = m.read_tensor(m.ACT, 2, 2).astype(np.float64)
+    W = p[w_off_out():w_off_out() + 2 * 32 * 27].astype(np.float32)
+    W = ((W.view(np.uint32) + 0x7FFF + ((W.view(np.uint32) >> 16) & 1)) & 0xFFFF0000).astype(np.uint32).view(np.float32)
+    W = W.astype(np.float64).reshape(2, 32, 27)
+    b = p[w_off_out() + 2 * 32 * 27:].astype(np.float64)
+    corr = np.zeros((2,) + shape + (2,))
+    mag = np.zeros_like(corr)
+    for d in range(27):
+        s = np.roll(act, (1 - d // 9, 1 - d // 3 % 3, 1 - d % 3), (1, 2, 3))
+        corr += s @ W[:, :, d].T
+        mag += np.abs(s) @ np.abs(W[:, :, d].T)
+    for got, res, o in ((ou, tu, 0), (ov, tv, 1)):
+        ref = res.double().cpu().numpy() + (corr[..., o] + b[o])
+        bound = 2.0 ** -24 * (32 * 3 + 12) * (mag[..., o] + abs(b[o]))
+        if dtype == "float32":
+            bound = bound + 2.0 ** -23 * np.abs(ref)
+        assert np.all(np.abs(got.double().cpu().numpy() - ref) <= bound), float(np.max(np.abs(got.double().cpu().numpy() - ref) / bound))
+
+
+def w_off_out():
+    """Offset of the output layer's weights in the flat parameter vector."""
+    return (32 * 4 * 27 + 32) + 2 * (32 * 32 * 27 + 32)
+
+
 def test_predict_more_samples_than_one_launch_packs(torch):
     """(F, k) travel with the input packing's launches, 64 samples each: 70 samples equal the samples one by one."""
     from paper_2309_10292_amd.surrogate import Surrogate
