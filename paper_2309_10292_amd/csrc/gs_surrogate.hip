@@ -14,6 +14,8 @@
 #include "gs_device.hpp"
 #include "gs_surrogate.hpp"
 
+#include <algorithm>
+
 namespace gs {
 namespace nn {
 
@@ -373,24 +375,6 @@ __global__ __launch_bounds__(512) void conv_out_kernel(ConvArgs a)
         if (z + 4 < ze) step(z + 4, IntC<4>{});
     }
 }
-// Planes per workgroup of conv_out_kernel, one workgroup per CU: the chunk with
-// the fewest plane times, rounds of workgroups times its planes and the two
-// extra ones it reads.
-static int conv_out_zc(const Geo &g, size_t cols)
-{
-    int best = 1;
-    size_t cost = ~(size_t)0;
-    for (int n = 1; n <= g.nz && n <= 64; ++n) {
-        const int zc = (g.nz + n - 1) / n;
-        const size_t blocks = cols * ((g.nz + zc - 1) / zc), c = (blocks + 255) / 256 * (zc + 2);
-        if (c < cost) {
-            cost = c;
-            best = zc;
-        }
-    }
-    return best;
-}
-
 // 32 -> 32 convolutions of the forward hidden layer (with or without the
 // pre-activation's store) and the data gradient. A wavefront owns RW rows of
 // 16 cells and both 16-channel N tiles (four accumulator chains) of one
@@ -643,46 +627,33 @@ int conv32p_zc(const Geo &g, int nsamp)
 // over 32 cells (two rows of 16).
 //
 // The workgroups are persistent: each walks work items (a patch of 16 x-cells
-// by TR y-rows of one sample, through a chunk of WG_ZC planes) and keeps its
-// sums in registers. TR is 8 for the layers with 32 input channels, whose
-// staging of 32-channel activation planes costs the most: 8 rows load 10
-// activation rows per 8 instead of 6 per 4 (the 32 -> 8 layer then runs one
-// workgroup per CU, for its registers); the 8 -> 32 layer keeps 4. Act plane p
-// meets dz planes p + 1, p and p - 1 (z offsets -1, 0, +1), so the loop runs
-// over act planes: while plane p is in LDS, the dz fragments of the three
-// planes it meets are held in registers, and every B fragment read from LDS
-// feeds three MFMAs, one per z offset (a third of the LDS reads of a loop that
-// takes the offsets one by one). For each offset the planes are still added in
-// increasing z. Both operands stay channels-last in LDS, as in memory (16-byte
-// chunks, no transposes on the way in): a fragment (8 cells of one channel per
-// lane) is two transposing LDS reads. Cells 8 .. 15 of every 16 have their
-// channel halves swapped (rows of 32 channels) or are moved 4 cells over (rows
-// of 16), so that the two 16-lane groups of a half-wave read distinct banks.
+// by TR = 8 y-rows of one sample, through a chunk of WG_ZC planes; 8 rows load 10
+// activation rows per 8 where 4 would load 6 per 4) and keeps its sums in
+// registers. Act plane p meets dz planes p + 1, p and p - 1 (z offsets -1, 0,
+// +1), so the loop runs over act planes: while plane p is in LDS, the dz
+// fragments of the three planes it meets are held in registers, and every B
+// fragment read from LDS feeds three MFMAs, one per z offset (a third of the LDS
+// reads of a loop that takes the offsets one by one). For each offset the planes
+// are still added in increasing z. Both operands stay channels-last in LDS, as in
+// memory (16-byte chunks, no transposes on the way in): a fragment (8 cells of
+// one channel per lane) is two transposing LDS reads. Cells 8 .. 15 of every 16
+// have their channel halves swapped, so that the two 16-lane groups of a
+// half-wave read distinct banks.
 //
-// Wave w owns one 16 x 16 output tile (co x ci) for all 27 offsets: with four
-// tiles (32 -> 32) for all K chunks of a plane (two rows of 16 cells each),
-// with two tiles two waves share a tile, split the K chunks, and add their sums
-// at the end. Staging is double-buffered with one barrier per plane: act plane
-// p + 2 and dz plane p + 3 are loaded into registers while plane p is
-// multiplied and stored into the free buffers at the start of the next plane.
-// The bias gradient (the sum of dz over cells) is accumulated while dz is
-// staged. Each workgroup writes its partial sums (padded 16*MT x 16*NT per
-// offset, and 32 bias sums) once.
+// Wave w owns one 16 x 16 output tile (co x ci) for all 27 offsets and all K
+// chunks of a plane (two rows of 16 cells each). Staging is double-buffered with
+// one barrier per plane: act plane p + 2 and dz plane p + 3 are loaded into
+// registers while plane p is multiplied and stored into the free buffers at the
+// start of the next plane. The bias gradient (the sum of dz over cells) is
+// accumulated while dz is staged. Each workgroup writes its partial sums (32 x 32
+// per offset, and 32 bias sums) once.
 constexpr int WG_ZC = 64;
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 
 // Offset (16-bit units) of channel ch of cell `cell` in an LDS row of
-// channels-last cells of NC channels, with the bank swizzle described above.
-template <int NC>
-__device__ __forceinline__ int wg_pos(int cell, int ch)
-{
-    static_assert(NC == 16 || NC == 32, "rows of 16 or 32 channels");
-    if constexpr (NC == 32)
-        return cell * 32 + (ch ^ ((cell & 8) << 1));
-    else
-        return (cell ^ ((cell >> 1) & 4)) * 16 + ch;
-}
+// channels-last cells of 32 channels, with the bank swizzle described above.
+__device__ __forceinline__ int wg_pos(int cell, int ch) { return cell * 32 + (ch ^ ((cell & 8) << 1)); }
 
 // MFMA operand of cells cell0 .. cell0 + 7 and channels c0 .. c0 + 15 (one per
 // lane of a 16-lane group) from an LDS row. In each group of 16 lanes the
@@ -691,26 +662,22 @@ __device__ __forceinline__ int wg_pos(int cell, int ch)
 // X[t + 32] and X[t + 48]; so lane L addresses cell L / 4 (then 4 + L / 4)
 // at channels c0 + 4 (L % 4) .. + 3, and receives channel c0 + L of the
 // 8 cells.
-template <int NC>
 __device__ __forceinline__ bf16x8 frag_tr(const u16 *row, int cell0, int c0, int lane16)
 {
     const int cell = cell0 + (lane16 >> 2), ch = c0 + 4 * (lane16 & 3);
     typedef __attribute__((address_space(3))) v4s *lds_v4s;
-    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(row + wg_pos<NC>(cell, ch)));
-    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(row + wg_pos<NC>(cell + 4, ch)));
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(row + wg_pos(cell, ch)));
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(row + wg_pos(cell + 4, ch)));
     const v4s v[2] = {lo, hi};
     return __builtin_bit_cast(bf16x8, v);
 }
 
-template <int CIN, int COUTS, int MT, int NT, int TR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void wgrad_kernel(WgradArgs a)
 {
+    constexpr int CIN = 32, COUTS = 32, MT = 2, NT = 2, TR = 8;
     constexpr int NCI = 16 * NT, NCO = 16 * MT;
     constexpr int NCG = CIN / 8, NCGZ = COUTS / 8;
-    constexpr int KS = MT * NT == 4 ? 1 : 2; // waves per output tile (splitting the K chunks)
-    constexpr int NKC = TR / 2 / KS;         // K chunks (two rows of 16 cells) per wave and plane
-    static_assert(TR % (2 * KS) == 0, "whole K chunks per wave");
-    static_assert(MT * NT * KS == 4, "four waves");
+    constexpr int NKC = TR / 2;              // K chunks (two rows of 16 cells) per wave and plane
     constexpr int AROW = (18 * NCI * 2 + 255) / 256 * 256 / 2; // u16 per act row: cells x0 - 1 .. x0 + 16
     constexpr int APL = (TR + 2) * AROW;                        // act rows y0 - 1 .. y0 + TR
     constexpr int DROW = 16 * NCO, DPL = TR * DROW;             // dz rows y0 .. y0 + TR - 1
@@ -721,14 +688,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ __align__(16) u16 act_l[2 * APL];
     __shared__ __align__(16) u16 dz_l[2 * DPL];
     __shared__ float bsum_l[TDL][8];
-    __shared__ float red_l[KS == 2 ? 2 * 27 * 4 * 64 : 1];
     const Geo g = a.geo;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, quad = lane >> 4;
-    const int tile = KS == 1 ? wave : (wave & 1);
-    const int mw = MT == 1 ? 0 : (NT == 1 ? tile : tile >> 1);
-    const int nw = NT == 1 ? 0 : (MT == 1 ? tile : tile & 1);
-    const int kc0 = KS == 1 ? 0 : (wave >> 1) * NKC;
+    const int mw = wave >> 1, nw = wave & 1; // the wave's output tile
 
     // Channels past CIN / COUTS stay zero.
     for (int e = tid; e < 2 * APL; e += 256) act_l[e] = 0;
@@ -771,7 +734,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const int cg = v % NCG, cell = (v / NCG) % 18, row = v / (18 * NCG);
             const int x = wrapc(x0 + cell - 1, g.nx), y = wrapc(y0 + row - 1, g.ny);
             goff_a[k] = ((size_t)y * g.nx + x) * CIN + 8 * cg;
-            loff_a[k] = row * AROW + wg_pos<NCI>(cell, 8 * cg);
+            loff_a[k] = row * AROW + wg_pos(cell, 8 * cg);
         }
         // lanes with nothing to stage load a valid chunk of the plane and keep zero
         bool dz_lane[RD], dz_in[RD];
@@ -784,7 +747,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             dz_lane[r] = t < T_DZ;
             dz_in[r] = dz_lane[r] && y0 + drow < g.ny;
             goff_d[r] = dz_in[r] ? ((size_t)(y0 + drow) * g.nx + x0 + dcell) * COUTS + 8 * dcg : (size_t)x0 * COUTS;
-            loff_d[r] = drow * DROW + wg_pos<NCO>(dcell, 8 * dcg);
+            loff_d[r] = drow * DROW + wg_pos(dcell, 8 * dcg);
         }
 
         uint4 qa[RA], qd[RD];
@@ -816,7 +779,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     *reinterpret_cast<uint4 *>(dz_l + (z & 1) * DPL + loff_d[r]) = qd[r];
                 }
         };
-        // dz fragments (K chunk kc0 + c) of planes p - 1, p, p + 1
+        // dz fragments (K chunk c) of planes p - 1, p, p + 1
         bf16x8 am[NKC], a0[NKC], ap[NKC];
 #pragma unroll
         for (int c = 0; c < NKC; ++c) am[c] = a0[c] = ap[c] = bf16x8{};
@@ -831,7 +794,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const int dyo = e / 3 - 1, dxo = e % 3 - 1;
 #pragma unroll
                 for (int c = 0; c < NKC; ++c)
-                    b[c] = frag_tr<NCI>(pl + (2 * (kc0 + c) + (quad >> 1) + dyo + 1) * AROW, 8 * (quad & 1) + dxo + 1, 16 * nw, col);
+                    b[c] = frag_tr(pl + (2 * c + (quad >> 1) + dyo + 1) * AROW, 8 * (quad & 1) + dxo + 1, 16 * nw, col);
             };
             // the reads of offset pair e + LA are issued before the MFMAs of
             // pair e, and no earlier: LA + 1 pairs of B fragments are live
@@ -873,7 +836,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const u16 *dl = dz_l + ((p + 1) & 1) * DPL;
 #pragma unroll
                 for (int c = 0; c < NKC; ++c)
-                    ap[c] = frag_tr<NCO>(dl + (2 * (kc0 + c) + (quad >> 1)) * DROW, 8 * (quad & 1), 16 * mw, col);
+                    ap[c] = frag_tr(dl + (2 * c + (quad >> 1)) * DROW, 8 * (quad & 1), 16 * mw, col);
             } else {
 #pragma unroll
                 for (int c = 0; c < NKC; ++c) ap[c] = bf16x8{};
@@ -896,26 +859,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (tid < TDL)
 #pragma unroll
         for (int c = 0; c < 8; ++c) bsum_l[tid][c] = bs[c];
-    if constexpr (KS == 2) {
-        // the waves of the second K chunk hand their sums to those of the first
-        if (wave >= 2)
-#pragma unroll
-            for (int d = 0; d < 27; ++d)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) red_l[(((wave & 1) * 27 + d) * 4 + j) * 64 + lane] = acc[d][j];
-    }
     __syncthreads();
     if (tid < COUTS) {
         float t = 0.f;
         for (int l = tid / 8; l < TDL; l += NCGZ) t += bsum_l[l][tid % 8];
         a.bpart[(size_t)blockIdx.x * 32 + tid] = t;
-    }
-    if (KS == 2 && wave >= 2) return;
-    if constexpr (KS == 2) {
-#pragma unroll
-        for (int d = 0; d < 27; ++d)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[d][j] += red_l[(((wave & 1) * 27 + d) * 4 + j) * 64 + lane];
     }
     // acc[d][j]: co = 16 mw + 4 quad + j, ci = 16 nw + col
     constexpr int PCO = 16 * MT, PCI = 16 * NT;
@@ -926,37 +874,294 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int j = 0; j < 4; ++j) part[((size_t)d * PCO + 16 * mw + 4 * quad + j) * PCI + 16 * nw + col] = acc[d][j];
 }
 
-// grad[W(co, ci, d)] = sum over workgroups of the partials; the first
-// lo_pairs input channels add the partials of their low parts (stored
-// channels cin ..). A workgroup handles 64 outputs (input channel fastest, so
-// the loads of a wave are contiguous) with 4 slices each: slice j sums the
-// workgroups b = j, j + 4, ... in order, and the 4 slice sums are added in
-// a fixed order: the result does not depend on scheduling.
-__global__ __launch_bounds__(256) void wgrad_reduce(const float *__restrict__ part, int nblk, int pco, int pci,
-                                                    int cout, int cin, int lo_pairs, float *__restrict__ gW)
+// Weight gradients of the first layer (8 -> 32 stored channels) and of the last
+// (32 -> 8, two of them real). One side has few channels, and as a product per
+// offset (wgrad_kernel) they fill little of an MFMA tile. Here the rows of the
+// product are the pairs (offset, channel) of the narrow side, shifted, and the
+// columns the 32 channels of the wide side, unshifted:
+//   last layer:  rows 2 d + co, dz[p - d][co] against act[p][ci];
+//   first layer: rows 4 d + s,  x[c + d][s] against dz[c][co], s the high and low
+//                parts of u and v; the (F, k) channels are constant over a
+//                sample, so their gradient is the same for every offset: two
+//                rows of constants, and a row of ones gives the bias gradient.
+// 4 (last) or 7 (first) row tiles by two column tiles per K = 32 cells: 8 and 14
+// MFMAs where the offset-by-offset kernel takes 54, and the wide tensor, which is
+// not shifted, is read once and without a halo.
+//
+// Every wavefront works alone (no barriers until its sums are folded): it owns
+// patches of 16 x-cells by 4 rows through a chunk of planes, stages the wide
+// tensor's plane channels-last in LDS (read back as fragments of 8 cells per
+// channel, frag_tr), and the narrow one planar, in three copies shifted by one
+// cell, so that a row's fragment is one aligned 16-byte read. Loads run a plane
+// ahead. What bounds it: the read of the wide tensor (0.54 GB at 4 x 128^3, with
+// the 0.13 GB of the narrow one 0.13 ms at the rate of a large copy). 4 x 128^3:
+// last layer 430 -> 157 us, first layer 268 -> 140 (its narrow side is read at
+// four of its eight channels, with 45 KB of LDS per workgroup three per CU).
+constexpr int WS_RT = 4;      // rows of a patch
+constexpr int WS_WAVES = 4;   // wavefronts of a workgroup
+template <bool FIRST> struct WsGeom {
+    static constexpr int NS = FIRST ? 4 : 2;                 // shifted channels
+    static constexpr int CONST0 = 27 * NS;                   // first layer: rows of ones, F, k; last: bias rows
+    static constexpr int MT = (CONST0 + (FIRST ? 3 : 0) + 15) / 16;
+    static constexpr int ROWS = 16 * MT;                     // rows of a partial (x 32 columns)
+    static constexpr int U16 = WS_RT * 16 * 32;              // wide plane (16-bit units)
+    static constexpr int SROW = NS * 3 * 16;                 // narrow plane: [row][channel][copy][cell]
+    static constexpr int SLOT = (WS_RT + 2) * SROW + (FIRST ? 48 : 0); // a plane slot, with the constant rows
+    static constexpr int WAVE16 = U16 + 3 * SLOT;
+};
+template <bool FIRST>
+__global__ __launch_bounds__(64 * WS_WAVES) void wgrad_shift_kernel(WgradArgs a)
+{
+    typedef WsGeom<FIRST> G;
+    constexpr int NS = G::NS, MT = G::MT;
+    __shared__ __align__(16) u16 lds[WS_WAVES * G::WAVE16];
+    static_assert(sizeof(lds) >= 2 * MT * 2 * 256 * 4, "two wavefronts' sums fit");
+    const Geo g = a.geo;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int col = lane & 15, quad = lane >> 4;
+    u16 *ul = lds + wave * G::WAVE16, *sl = ul + G::U16;
+    const u16 *wide = FIRST ? a.dz : a.act, *narrow = FIRST ? a.act : a.dz;
+
+    f32x4 acc[MT][2];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float bs[2] = {0.f, 0.f}; // last layer: the lane's sums of dz
+
+    // Row 16 t + col of the product: its place in a narrow slot (without the
+    // cell group and the patch row) and its plane offset plus one.
+    int srow[MT], soz[MT], sky[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        const int r = 16 * t + col;
+        const int d = min(r / NS, 26), ch = r % NS;
+        const int dz = d / 9, dy = d / 3 % 3, dx = d % 3;
+        const int ox = FIRST ? dx - 1 : 1 - dx, oy = FIRST ? dy - 1 : 1 - dy, oz = FIRST ? dz - 1 : 1 - dz;
+        const bool con = FIRST && r >= G::CONST0;
+        srow[t] = con ? (WS_RT + 2) * G::SROW + min(r - G::CONST0, 2) * 16 : ((oy + 1) * NS + ch) * 48 + (ox + 1) * 16;
+        soz[t] = oz + 1;
+        sky[t] = con ? 0 : G::SROW; // the step per patch row
+    }
+    const int ntx = g.nx / 16, nty = (g.ny + WS_RT - 1) / WS_RT, ntz = (g.nz + a.zc - 1) / a.zc;
+    const int nitems = ntx * nty * ntz * a.nsamp;
+    for (int it = blockIdx.x * WS_WAVES + wave; it < nitems; it += gridDim.x * WS_WAVES) {
+        int r = it;
+        const int tx = r % ntx;
+        r /= ntx;
+        const int ty = r % nty;
+        r /= nty;
+        const int tz = r % ntz, smp = r / ntz;
+        const int x0 = 16 * tx, y0 = WS_RT * ty, z0 = tz * a.zc, ze = min(z0 + a.zc, g.nz);
+        const size_t sbase = (size_t)smp * g.ncell, plane = (size_t)g.nx * g.ny;
+
+        // Wide: load k is patch row k, lane = cell 4 (lane / 4) .. of 16-byte
+        // chunks (rows past ny read a valid row and count as zero).
+        size_t uoff[WS_RT];
+#pragma unroll
+        for (int k = 0; k < WS_RT; ++k) uoff[k] = ((size_t)min(y0 + k, g.ny - 1) * g.nx + x0) * 32 + lane * 8;
+        const int upos = wg_pos(lane >> 2, 8 * (lane & 3));
+        // Narrow: load k is cell v = lane + 64 k of the 18 x 6 cells around the patch.
+        size_t soff[2];
+        int srx[2], sry[2];
+        bool inner[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int v = min(lane + 64 * k, 18 * (WS_RT + 2) - 1);
+            srx[k] = v % 18;
+            sry[k] = v / 18;
+            int y = y0 + sry[k] - 1;
+            y = y < 0 ? y + g.ny : y;
+            while (y >= g.ny) y -= g.ny;
+            soff[k] = ((size_t)y * g.nx + wrapc(x0 + srx[k] - 1, g.nx)) * 8;
+            inner[k] = lane + 64 * k < 18 * (WS_RT + 2) && srx[k] >= 1 && srx[k] <= 16 && sry[k] >= 1 && sry[k] <= WS_RT &&
+                       y0 + sry[k] - 1 < g.ny;
+        }
+        uint4 qu[WS_RT], qs[2];
+        auto load_u = [&](int z) __attribute__((always_inline)) {
+            const u16 *p = wide + (sbase + (size_t)z * plane) * 32;
+#pragma unroll
+            for (int k = 0; k < WS_RT; ++k) qu[k] = *reinterpret_cast<const uint4 *>(p + uoff[k]);
+        };
+        auto load_s = [&](int z) __attribute__((always_inline)) {
+            const u16 *p = narrow + (sbase + (size_t)wrapc(z, g.nz) * plane) * 8;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) qs[k] = *reinterpret_cast<const uint4 *>(p + soff[k]);
+        };
+        auto store_u = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < WS_RT; ++k)
+                *reinterpret_cast<uint4 *>(ul + k * 512 + upos) = y0 + k < g.ny ? qu[k] : uint4{0u, 0u, 0u, 0u};
+        };
+        // Narrow plane z into slot `slot`; copy c holds cell x0 + i + c - 1 at i.
+        auto store_s = [&](int slot, bool own) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const u16 ch[4] = {(u16)(qs[k].x & 0xffffu), (u16)(qs[k].x >> 16), (u16)(qs[k].z & 0xffffu), (u16)(qs[k].z >> 16)};
+                u16 *dst = sl + slot * G::SLOT + sry[k] * G::SROW;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const int i = srx[k] - c;
+                    if (i >= 0 && i < 16 && lane + 64 * k < 18 * (WS_RT + 2))
+#pragma unroll
+                        for (int s = 0; s < NS; ++s) dst[(s * 3 + c) * 16 + i] = ch[s];
+                }
+                if (!FIRST && own && inner[k]) {
+                    bs[0] += bf2f(ch[0]);
+                    bs[1] += bf2f(ch[1]);
+                }
+            }
+        };
+        // slots: plane z in ((z - z0) + 3) mod 3
+        load_s(z0 - 1);
+        if constexpr (FIRST) {
+            // constant rows of every slot: ones, F, k (channels 2 and 3 of any cell of the sample)
+            const uint32_t fk = __shfl(qs[0].y, 0, 64);
+            if (lane < 48) {
+                const u16 v = lane < 16 ? (u16)0x3F80 : lane < 32 ? (u16)(fk & 0xffffu) : (u16)(fk >> 16);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) sl[p * G::SLOT + (WS_RT + 2) * G::SROW + lane] = v;
+            }
+        }
+        store_s(2, false);
+        load_s(z0);
+        store_s(0, true);
+        load_u(z0);
+        load_s(z0 + 1);
+        int ph = 0; // (z - z0) mod 3
+        for (int z = z0; z < ze; ++z) {
+            store_u();
+            store_s(ph == 2 ? 0 : ph + 1, z + 1 < ze);
+            __builtin_amdgcn_wave_barrier(); // the fragment reads below follow the stores (LDS keeps a wavefront's order)
+            load_u(min(z + 1, ze - 1));
+            load_s(min(z + 2, ze));
+#pragma unroll
+            for (int c = 0; c < WS_RT / 2; ++c) {
+                const int prow = 2 * c + (quad >> 1), cell0 = 8 * (quad & 1);
+                bf16x8 b[2];
+#pragma unroll
+                for (int n = 0; n < 2; ++n) b[n] = frag_tr(ul + prow * 512, cell0, 16 * n, col);
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    // slot of plane z + soz - 1
+                    int q = ph + soz[t] + 2;
+                    q = q >= 3 ? q - 3 : q;
+                    q = q >= 3 ? q - 3 : q;
+                    const bf16x8 av = load8(sl + q * G::SLOT + srow[t] + prow * sky[t] + cell0);
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, b[n], acc[t][n], 0, 0, 0);
+                }
+            }
+            ph = ph == 2 ? 0 : ph + 1;
+        }
+    }
+
+    // Fold the wavefronts' sums: 2 and 3 into 0 and 1, then 1 into 0; wavefront 0
+    // writes the workgroup's partial. acc[t][n][j]: row 16 t + 4 quad + j, column
+    // 16 n + col.
+    float *red = reinterpret_cast<float *>(lds);
+#pragma unroll
+    for (int h = 2; h >= 1; h /= 2) {
+        __syncthreads();
+        if (wave >= h && wave < 2 * h)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+                    *reinterpret_cast<f32x4 *>(red + (((wave - h) * MT + t) * 2 + n) * 256 + lane * 4) = acc[t][n];
+        __syncthreads();
+        if (wave < h)
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int n = 0; n < 2; ++n) acc[t][n] += *reinterpret_cast<const f32x4 *>(red + ((wave * MT + t) * 2 + n) * 256 + lane * 4);
+    }
+    float *part = a.part + (size_t)blockIdx.x * G::ROWS * 32;
+    if constexpr (!FIRST) {
+        // bias sums into the spare rows 54 and 55, column 0: lanes in order, then wavefronts
+        __syncthreads();
+        red[2 * threadIdx.x] = bs[0];
+        red[2 * threadIdx.x + 1] = bs[1];
+        __syncthreads();
+    }
+    if (wave == 0) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int n = 0; n < 2; ++n)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = 16 * t + 4 * quad + j;
+                    if (FIRST || r < G::CONST0) part[r * 32 + 16 * n + col] = acc[t][n][j];
+                }
+        if (!FIRST && lane < 2) {
+            float s = 0.f;
+            for (int i = 0; i < 64 * WS_WAVES; ++i) s += red[2 * i + lane];
+            part[(G::CONST0 + lane) * 32] = s;
+        }
+    }
+}
+
+// Gradients of the first or last layer from wgrad_shift_kernel's partials: one
+// workgroup per output row of 32 columns, 8 slices of the partials summed in
+// FP64 and folded in a fixed order.
+// FIRST: blocks 0 .. 53: (offset, u or v), the high and the low part's rows;
+// 54, 55: F and k (one row each, the same for every offset); 56: the bias.
+// Last: blocks 0 .. 53: row 2 d + co; 54, 55: the bias of channel 0, 1.
+template <bool FIRST>
+__global__ __launch_bounds__(256) void wgrad_shift_reduce(const float *__restrict__ part, int nblk, float *__restrict__ gW,
+                                                          float *__restrict__ gb)
+{
+    typedef WsGeom<FIRST> G;
+    __shared__ double red[8][32];
+    const int c = threadIdx.x & 31, j = threadIdx.x >> 5, o = blockIdx.x;
+    const int d = o / 2, ch = o % 2;
+    const int row = !FIRST ? (o < 54 ? o : G::CONST0 + ch) : o < 54 ? 4 * d + ch : o < 56 ? G::CONST0 + 1 + ch : G::CONST0;
+    double s = 0.0;
+    const float *p = part + (size_t)row * 32 + c;
+    // unrolled so that eight loads are in flight; the adds keep their order
+#pragma unroll 8
+    for (int b = j; b < nblk; b += 8) s += p[(size_t)b * (G::ROWS * 32)];
+    if (FIRST && o < 54)
+#pragma unroll 8
+        for (int b = j; b < nblk; b += 8) s += p[(size_t)b * (G::ROWS * 32) + 2 * 32];
+    red[j][c] = s;
+    __syncthreads();
+    if (j != 0) return;
+    double t = 0.0;
+    for (int i = 0; i < 8; ++i) t += red[i][c];
+    const float v = (float)t;
+    if constexpr (FIRST) {
+        // W[co = c][ci][d], 4 input channels
+        if (o < 54) gW[(c * 4 + ch) * 27 + d] = v;
+        else if (o < 56)
+            for (int e = 0; e < 27; ++e) gW[(c * 4 + 2 + ch) * 27 + e] = v;
+        else gb[c] = v;
+    } else {
+        // W[co = ch][ci = c][d]
+        if (o < 54) gW[(ch * 32 + c) * 27 + d] = v;
+        else if (c == 0) gb[ch] = v;
+    }
+}
+
+// grad[W(co, ci, d)] of a 32 -> 32 layer = sum over workgroups of the partials.
+// A workgroup handles 64 outputs (input channel fastest, so the loads of a wave
+// are contiguous) with 4 slices each: slice j sums the workgroups b = j, j + 4,
+// ... in order, and the 4 slice sums are added in a fixed order: the result does
+// not depend on scheduling.
+__global__ __launch_bounds__(256) void wgrad_reduce(const float *__restrict__ part, int nblk, float *__restrict__ gW)
 {
     __shared__ double red[4][64];
-    const int n = cout * cin * 27;
     const int o = threadIdx.x & 63, j = threadIdx.x >> 6;
-    const int e = blockIdx.x * 64 + o;
+    const int e = blockIdx.x * 64 + o; // (d, co, ci)
     double s = 0.0;
-    int ci = 0, co = 0, d = 0;
-    if (e < n) {
-        ci = e % cin;
-        co = (e / cin) % cout;
-        d = e / (cin * cout);
-        const size_t stride = (size_t)27 * pco * pci;
-        const float *p = part + ((size_t)d * pco + co) * pci;
-        // unrolled so that eight loads are in flight; the adds keep their order
+    // unrolled so that eight loads are in flight; the adds keep their order
 #pragma unroll 8
-        for (int b = j; b < nblk; b += 4) s += p[(size_t)b * stride + ci];
-        if (ci < lo_pairs)
-#pragma unroll 8
-            for (int b = j; b < nblk; b += 4) s += p[(size_t)b * stride + cin + ci];
-    }
+    for (int b = j; b < nblk; b += 4) s += part[(size_t)b * (27 * 32 * 32) + e];
     red[j][o] = s;
     __syncthreads();
-    if (j == 0 && e < n) gW[((size_t)co * cin + ci) * 27 + d] = (float)((red[0][o] + red[1][o]) + (red[2][o] + red[3][o]));
+    const int ci = e % 32, co = e / 32 % 32, d = e / 1024;
+    if (j == 0) gW[(co * 32 + ci) * 27 + d] = (float)((red[0][o] + red[1][o]) + (red[2][o] + red[3][o]));
 }
 
 // Bias gradient: fixed-order fold of the per-workgroup channel sums; 32
@@ -1092,6 +1297,24 @@ static int grid_cap(size_t work, int per_block, int cap)
     return (int)b;
 }
 
+// The chunk of planes with the fewest plane times for `cols` columns of work on
+// `slots` places: rounds of chunks times a chunk's planes and the two more it
+// reads.
+static int balanced_zc(int nz, size_t cols, size_t slots)
+{
+    int best = 1;
+    size_t cost = ~(size_t)0;
+    for (int n = 1; n <= nz && n <= 64; ++n) {
+        const int zc = (nz + n - 1) / n;
+        const size_t items = cols * ((nz + zc - 1) / zc), c = (items + slots - 1) / slots * (zc + 2);
+        if (c < cost) {
+            cost = c;
+            best = zc;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a, hipStream_t st)
 {
     if (a.zc < 1 || a.geo.nx % PX != 0) return hipErrorInvalidValue;
@@ -1113,7 +1336,7 @@ hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a,
         ConvArgs b = a;
         const int ng = a.geo.nx / 16, tg = ng <= OUT_NG ? ng : OUT_NG - 2;
         const size_t cols = (size_t)((ng + tg - 1) / tg) * ((a.geo.ny + OUT_TY - 1) / OUT_TY) * a.nsamp;
-        b.zc = conv_out_zc(a.geo, cols);
+        b.zc = balanced_zc(a.geo.nz, cols, 256); // one workgroup per CU
         const size_t nb = cols * ((a.geo.nz + b.zc - 1) / b.zc);
         if (nb == 0 || nb > 0x7fffffffu) return hipErrorInvalidConfiguration;
         auto go = [&](auto full) {
@@ -1136,26 +1359,35 @@ hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a,
 
 int wgrad_blocks() { return 512; }
 
-hipError_t launch_wgrad(int cin, int couts, const WgradArgs &a, hipStream_t st)
+hipError_t launch_wgrad_edge(bool first, const WgradArgs &a, float *gW, float *gb, hipStream_t st)
 {
-    const int grid = wgrad_blocks();
-    if (cin == 32 && couts == 32)
-        hipLaunchKernelGGL((wgrad_kernel<32, 32, 2, 2, 8>), dim3(grid), dim3(256), 0, st, a);
-    else if (cin == 32 && couts == 8)
-        hipLaunchKernelGGL((wgrad_kernel<32, 8, 1, 2, 8>), dim3(grid), dim3(256), 0, st, a);
-    else if (cin == 8 && couts == 32)
-        hipLaunchKernelGGL((wgrad_kernel<8, 32, 2, 1, 4>), dim3(grid), dim3(256), 0, st, a);
-    else
-        return hipErrorInvalidValue;
+    // resident at once on 256 CUs: 3 workgroups per CU (LDS), or 4
+    const size_t slots = first ? 768 : 1024;
+    const size_t cols = (size_t)(a.geo.nx / 16) * ((a.geo.ny + WS_RT - 1) / WS_RT) * a.nsamp;
+    WgradArgs b = a;
+    b.zc = balanced_zc(a.geo.nz, cols, slots * WS_WAVES);
+    const size_t items = cols * ((a.geo.nz + b.zc - 1) / b.zc);
+    if (items == 0 || items > 0x7fffffffu) return hipErrorInvalidConfiguration;
+    const int grid = (int)std::min<size_t>(slots, (items + WS_WAVES - 1) / WS_WAVES);
+    if (first) {
+        hipLaunchKernelGGL(wgrad_shift_kernel<true>, dim3(grid), dim3(64 * WS_WAVES), 0, st, b);
+        hipLaunchKernelGGL(wgrad_shift_reduce<true>, dim3(57), dim3(256), 0, st, b.part, grid, gW, gb);
+    } else {
+        hipLaunchKernelGGL(wgrad_shift_kernel<false>, dim3(grid), dim3(64 * WS_WAVES), 0, st, b);
+        hipLaunchKernelGGL(wgrad_shift_reduce<false>, dim3(56), dim3(256), 0, st, b.part, grid, gW, gb);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_wgrad_reduce(const float *part, int pco, int pci, int cout, int cin, int lo_pairs, float *gW,
-                               hipStream_t st)
+hipError_t launch_wgrad(const WgradArgs &a, hipStream_t st)
 {
-    const int n = cout * cin * 27;
-    hipLaunchKernelGGL(wgrad_reduce, dim3((n + 63) / 64), dim3(256), 0, st, part, wgrad_blocks(), pco, pci, cout, cin,
-                       lo_pairs, gW);
+    hipLaunchKernelGGL(wgrad_kernel, dim3(wgrad_blocks()), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_wgrad_reduce(const float *part, float *gW, hipStream_t st)
+{
+    hipLaunchKernelGGL(wgrad_reduce, dim3(32 * 32 * 27 / 64), dim3(256), 0, st, part, wgrad_blocks(), gW);
     return hipGetLastError();
 }
 

@@ -38,15 +38,18 @@ struct WgradArgs {
     int nsamp;
     const uint16_t *dz;  // output gradient, COUTS channels
     const uint16_t *act; // layer input, CIN channels
-    float *part;         // wgrad_blocks() x 27 x (16 MT) x (16 NT) partial sums
+    int zc;              // first and last layers: planes per work item (set by the launcher)
+    float *part;         // wgrad_blocks() x 27 x (16 MT) x (16 NT) partial sums (at least 1024 x 112 x 32 values)
     float *bpart;        // wgrad_blocks() x 32 partial sums of dz (bias gradient)
 };
 
 hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a, hipStream_t st);
 int wgrad_blocks();
-hipError_t launch_wgrad(int cin, int couts, const WgradArgs &a, hipStream_t st);
-hipError_t launch_wgrad_reduce(const float *part, int pco, int pci, int cout, int cin, int lo_pairs, float *gW,
-                               hipStream_t st);
+hipError_t launch_wgrad(const WgradArgs &a, hipStream_t st); // 32 -> 32 layers
+// Weight and bias gradients of the first layer (8 stored input channels) or the
+// last (8 stored output channels), from the tensors in `a`.
+hipError_t launch_wgrad_edge(bool first, const WgradArgs &a, float *gW, float *gb, hipStream_t st);
+hipError_t launch_wgrad_reduce(const float *part, float *gW, hipStream_t st);
 hipError_t launch_bias_reduce(const float *bpart, int cout, float *gb, hipStream_t st);
 // The samples' (F, k) go with the launch, up to FK_PER_LAUNCH samples at once:
 // no device copy of them to wait for (a prediction at 128^3 lost 35 us to it).

@@ -321,11 +321,13 @@ gs_status gs_surrogate_loss_grad(gs_surrogate *s, int32_t nsamp, const float *u,
         w.act = act_in[l];
         w.part = wpart;
         w.bpart = cpart;
-        e = launch_wgrad(k_cins[l], couts, w, s->stream);
-        if (e == hipSuccess)
-            e = launch_wgrad_reduce(wpart, couts == 8 ? 16 : 32, k_cins[l] == 8 ? 16 : 32, k_chan[l + 1], k_chan[l],
-                                    l == 0 ? k_lo_pairs : 0, G + w_off(l), s->stream);
-        if (e == hipSuccess) e = launch_bias_reduce(cpart, k_chan[l + 1], G + b_off(l), s->stream);
+        if (l == 0 || l == 3) {
+            e = launch_wgrad_edge(l == 0, w, G + w_off(l), G + b_off(l), s->stream);
+        } else {
+            e = launch_wgrad(w, s->stream);
+            if (e == hipSuccess) e = launch_wgrad_reduce(wpart, G + w_off(l), s->stream);
+            if (e == hipSuccess) e = launch_bias_reduce(cpart, k_chan[l + 1], G + b_off(l), s->stream);
+        }
         if (l == 0 || e != hipSuccess) break;
         ConvArgs a = {};
         a.geo = s->geo;

@@ -485,3 +485,38 @@ def test_predict_more_samples_than_one_launch_packs(torch):
         for i in (0, 1, 63, 64, 65, 69):
             su, sv = m.predict(u[i], v[i], F[i], k[i])
             assert torch.equal(su, ou[i]) and torch.equal(sv, ov[i]), i
+
+
+# the smallest grid, and one with more work items than wavefronts at once (5000 columns of 16 x 4 cells) and rows that
+# are no multiple of a patch's
+@pytest.mark.parametrize("nz, ny, nx, n", [(4, 4, 16, 2), (5, 998, 320, 1)], ids=["4x4x16x2", "5x998x320x1"])
+def test_edge_layer_weight_gradients(torch, nz, ny, nx, n):
+    """First and last layer's weight and bias gradients against FP64 sums of the GPU's own stored tensors: FP32 sums
+    of at most 32 roundings per MFMA over a wavefront's items (two K chunks per plane) and two folds, summed in FP64
+    and rounded once; the last layer's bias adds lane by lane."""
+    from paper_2309_10292_amd.surrogate import Surrogate
+    u, v = _fields((nz, ny, nx), n, 4)
+    rng = np.random.default_rng(5)
+    ut, vt = u + 0.02 * rng.normal(size=u.shape), v + 0.02 * rng.normal(size=v.shape)
+    F, k = np.array([0.025, 0.05])[:n], np.array([0.045, 0.065])[:n]
+    T = lambda a: torch.from_numpy(a.astype(np.float32)).cuda().contiguous()
+    with Surrogate(nx, ny, nz, max_batch=n, params=_params(21)) as m:
+        _, g = m.loss_grad(T(u), T(v), T(ut), T(vt), F, k, want_grad=True)
+        D = lambda t, l: torch.from_numpy(m.read_tensor(t, l, n)).cuda().double()
+        X, A2, D0, D4 = D(m.INPUT, 0), D(m.ACT, 2), D(m.DPRE, 0), D(m.DOUT, 3)[..., :2]
+    G = S.unflatten(g.astype(np.float64))
+    xin = torch.stack([X[..., 0] + X[..., 4], X[..., 1] + X[..., 5], X[..., 2], X[..., 3]], -1)
+    xabs = torch.stack([X[..., 0].abs() + X[..., 4].abs(), X[..., 1].abs() + X[..., 5].abs(), X[..., 2].abs(), X[..., 3].abs()], -1)
+    items = -(-(nx // 16) * -(-ny // 4) * n * nz // 3072)  # items of at least one plane per wavefront, at most
+    gam = (32 * 2 * (items + 2 * nz) + 4 * 64) * U
+    for name, l, dz, a, a_abs in (("first", 0, D0, xin, xabs), ("last", 3, D4, A2, A2.abs())):
+        co, ci = dz.shape[-1], a.shape[-1]
+        for d in range(27):
+            sh = (1 - d // 9, 1 - d // 3 % 3, 1 - d % 3)
+            s, sa = torch.roll(a, sh, (1, 2, 3)).reshape(-1, ci), torch.roll(a_abs, sh, (1, 2, 3)).reshape(-1, ci)
+            z = dz.reshape(-1, co)
+            ref, mag = (z.t().contiguous() @ s).cpu().numpy(), (z.abs().t().contiguous() @ sa).cpu().numpy()
+            got = G[l][0].reshape(co, ci, 27)[:, :, d]
+            assert np.all(np.abs(got - ref) <= gam * mag + 2 * U * np.abs(ref) + 1e-38), (name, d)
+        ref, mag = dz.reshape(-1, co).sum(0).cpu().numpy(), dz.abs().reshape(-1, co).sum(0).cpu().numpy()
+        assert np.all(np.abs(G[l][1] - ref) <= gam * mag + 2 * U * np.abs(ref) + 1e-38), name
