@@ -257,28 +257,28 @@ gs_status check(gs_sim *s)
 // where two are bound by HBM (1024^3: 1.64 ms per step against 1.80; 640^3 0.46
 // against 0.50), unless its tiles of 50 rows cover the grid worse than those of
 // two steps (512^3: 0.24 against 0.22).
-// Smaller grids fuse two steps: in 256-lane workgroups below 4 M cells (more
-// workgroups for 256 CUs), above that in the 768-lane tile for FP64 and the
-// 512-lane one for the others. The single-step kernel (tiles 1..4) runs when
-// asked for. The smallest and the narrowest grids take the block kernel
-// (default_block).
+// Smaller grids take the launch that default_stream estimates fastest (where
+// gs_params sets a part of it, two steps in 256-lane workgroups below 4 M cells
+// and above that in the 768-lane tile for FP64 and the 512-lane one for the
+// others). The single-step kernel (tiles 1..4) runs when asked for. The smallest
+// and the narrowest grids take the block kernel (default_block).
 double grid_cells(const gs_params &p) { return (double)p.nx * p.ny * p.nz; }
 bool large_grid(const gs_params &p) { return grid_cells(p) >= 64.0 * 1024 * 1024; }
 
 // Block kernel of small grids: shape (0: not taken) and steps per launch.
-// A z-streaming workgroup is a serial chain of planes, two barriers each: on
-// a grid that does not fill the chip a launch takes 8 to 10 us whatever its
-// size. A block is loaded at once, so while there are blocks for about every
-// CU a launch costs its latency and more fused steps pay (us per step, FP64
-// without noise, z-streaming default against the block kernel): 32^3 4.53 ->
-// 1.72 (8x4x4, four steps; 2.16 against 2.09 with noise, where the steps'
-// Philox blocks add up; 40^3, two blocks per CU: 2.23 with three, 2.40 with four), 48^3 4.77 ->
-// 2.41 (16x8x4, three), 64^3 4.89 -> 3.18 (16x8x8, three). With more blocks
-// than that their halos decide: an 80^3 grid still gains (6.49 -> 4.97,
-// 16x8x4, two steps), 88^3 ties, 96^3 loses 8 %, 128 x 106 x 75 15 %. The
-// z-streaming tile is 64 x 10 cells, so what it wastes on narrow rows counts
-// too: 16 x 250 x 250 18.6 -> 7.9, 32 x 200 x 200 11.6 -> 9.5, and
-// 16 x 600 x 600 72 -> 31 (16x8x8, one step), while 24 x 640 x 640 loses 20 %.
+// A z-streaming workgroup is a serial chain of planes, two barriers each: on a
+// grid that does not fill the chip a launch takes 8 to 10 us whatever its size.
+// A block is loaded at once, so while there are blocks for about every CU a
+// launch costs its latency and more fused steps pay (us per step, FP64 without
+// noise, z-streaming against the block kernel): 32^3 4.53 -> 1.72 (8x4x4, four
+// steps; with noise, whose Philox blocks add up, 2.16 against 2.09 with three;
+// 40^3, two blocks per CU: 2.40 with four, 2.23 with three), 48^3 4.77 -> 2.41
+// (16x8x4, three), 64^3 4.89 -> 3.18 (16x8x8, three). With more blocks than that
+// their halos decide: 72^3 7.17 -> 4.73 and 80^3 6.49 -> 4.97 (16x8x4, two
+// steps), while 88^3 ties and 128 x 106 x 75 loses 15 %. The z-streaming tile is
+// 64 x 10 cells, so what it wastes on narrow rows counts too: 16 x 250 x 250
+// 18.6 -> 7.9 and 16 x 600 x 600 72 -> 31 (16x8x8, one step); 32 x 150 x 200 gains
+// 6 % in FP64 and loses 5 % in BF16 with noise, 24 x 640 x 640 loses 20 %.
 struct BlockChoice {
     int shape, T;
 };
@@ -294,7 +294,8 @@ BlockChoice default_block(const gs_params &p)
     if (blocks(3) <= 256) return BlockChoice{3, 3};
     const double streamed = 64 * up(p.nx, 64) * 10 * up(p.ny, 10) * p.nz; // cells its tiles cover
     if (grid_cells(p) < 4.0 * 1024 * 1024)
-        return blocks(2) <= 600 || 512 * blocks(2) <= 0.63 * streamed ? BlockChoice{2, 2} : BlockChoice{0, 0};
+        return blocks(2) <= 600 || 512 * blocks(2) <= (grid_cells(p) < 600e3 ? 0.63 : 0.45) * streamed ? BlockChoice{2, 2}
+                                                                                                      : BlockChoice{0, 0};
     return !large_grid(p) && 1024 * blocks(3) <= 0.3 * streamed ? BlockChoice{3, 1} : BlockChoice{0, 0};
 }
 
@@ -377,6 +378,58 @@ int default_zc(const gs_params &p, int tile, int tblock)
     if (large_grid(p))
         z = tile <= gs::num_tiles() ? 32 : p.storage == GS_F64 ? 128 : p.storage == GS_F32 ? 32 : 64;
     return p.nz < z ? p.nz : z;
+}
+
+// Launch of grids between the block kernel's and 64 M cells when gs_params leaves
+// all of it to the library: the blocked shape, depth and z-chunk of least
+// estimated time per step. A launch of nb workgroups on 256 CUs that hold occ each
+// runs nb / (256 occ) full rounds and a part of one; a round takes
+// (zc + 2T - 1) plane times (the chunk, the planes its levels run ahead and one
+// for its start), and a plane of a CU with n workgroups fixed + n each, in us.
+// The constants are least-squares fits over 25 grids of 0.4 to 57 M cells and 14
+// chunks each (10 % standard deviation); over those grids, six storage and noise
+// cases, the choice takes 0.9 % longer than the best measured launch and is
+// 15 % faster than fixed shapes with power-of-two chunks: FP64 192^3 39.8 ->
+// 27.7 us per step, 320^3 143 -> 103, 128^3 14.6 -> 12.5, FP32 256^3 39.1 -> 34.6,
+// BF16 320 x 100 x 200 15.6 -> 11.9.
+struct StreamCost {
+    int shape, T, occ;
+    double fixed[2], each[2]; // without and with noise
+};
+struct StreamChoice {
+    int shape, T, zc;
+};
+StreamChoice default_stream(const gs_params &p)
+{
+    static const StreamCost f64[] = {{1, 2, 2, {0.70, 0.84}, {0.55, 0.57}},
+                                     {2, 2, 1, {0.96, 1.10}, {0.96, 1.10}},
+                                     {2, 3, 1, {1.22, 1.51}, {1.23, 1.51}}};
+    static const StreamCost f32[] = {{1, 2, 4, {0.75, 0.90}, {0.29, 0.33}},
+                                     {2, 2, 2, {0.89, 1.11}, {0.59, 0.65}},
+                                     {5, 2, 1, {1.16, 1.40}, {1.16, 1.40}}};
+    static const StreamCost b16[] = {{1, 2, 4, {0.68, 0.84}, {0.17, 0.19}},
+                                     {2, 2, 2, {0.73, 0.99}, {0.38, 0.39}},
+                                     {5, 2, 1, {0.84, 1.05}, {0.84, 1.05}}};
+    const StreamCost *table = p.storage == GS_F64 ? f64 : p.storage == GS_F32 ? f32 : b16;
+    const int noise = p.noise != 0.0;
+    StreamChoice best = {1, 2, 4};
+    double best_us = 1e300;
+    for (int i = 0; i < 3; ++i) {
+        const StreamCost &c = table[i];
+        const gs::TileShape t = gs::tb_shape(c.shape, c.T);
+        const int64_t tiles = (int64_t)((p.nx + t.tx - 1) / t.tx) * ((p.ny + t.ty - 1) / t.ty);
+        for (int z = 3; z <= 64 && z <= p.nz; ++z) {
+            const int64_t nb = tiles * ((p.nz + z - 1) / z), full = nb / (256 * c.occ), rest = nb % (256 * c.occ);
+            double plane = full * (c.fixed[noise] + c.occ * c.each[noise]);
+            if (rest) plane += c.fixed[noise] + (double)((rest + 255) / 256) * c.each[noise];
+            const double us = (2.5 + (z + 2 * c.T - 1) * plane) / c.T; // 2.5: a launch
+            if (us <= best_us) {
+                best_us = us;
+                best = StreamChoice{c.shape, c.T, z};
+            }
+        }
+    }
+    return best;
 }
 
 gs::StepArgs make_args(const gs_sim *s)
@@ -521,6 +574,12 @@ gs_status gs_init(const gs_params *p, void *u0, void *v0, void *u1, void *v1, vo
     s->tblock = p->tblock ? p->tblock : default_tblock(*p, s->tile);
     s->zc = p->zchunk ? (p->zchunk < p->nz ? p->zchunk : p->nz) : default_zc(*p, s->tile, s->tblock);
     if (p->tile == 0 && p->tblock == 0 && p->zchunk == 0) {
+        if (!large_grid(*p) && !default_block(*p).shape) {
+            const StreamChoice c = default_stream(*p);
+            s->tile = gs::num_tiles() + c.shape;
+            s->tblock = c.T;
+            s->zc = c.zc;
+        }
         // a configuration recorded by gs_tune for this grid class, if any
         TuneVal v;
         const TuneKey key = {TUNE_SINGLE, p->storage, p->nx, p->ny, p->nz, p->noise != 0.0};
