@@ -377,51 +377,73 @@ __global__ __launch_bounds__(512) void conv_out_kernel(ConvArgs a)
 }
 // 32 -> 32 convolutions of the forward hidden layer (with or without the
 // pre-activation's store) and the data gradient. A wavefront owns RW rows of
-// 16 cells and both 16-channel N tiles (four accumulator chains) of one
-// sample and marches through a chunk of z planes with a private LDS ring of
-// three input planes (rows y-1 .. y+RW, cells x-1 .. x+16, channel group
-// major), so the wavefronts of a workgroup meet at one barrier only, after
-// the weights are staged. The weight fragments of the first C32_CR K chunks
-// sit in registers and the other chunks' in LDS (shared by the workgroup's
-// eight wavefronts), which leaves room for two wavefronts per SIMD: one
+// 16 cells and both 16-channel N tiles of one sample and marches through a chunk
+// of z planes. Input plane p adds to the outputs of planes p + 1, p and p - 1 (z
+// offsets -1, 0, +1), which sit in three sets of accumulators, so an activation
+// fragment is read from LDS once for all z offsets and for the rows it is a
+// neighbour of: 12 reads per plane where a loop over the 27 offsets takes 54. The
+// plane in work and the next one sit in a private LDS ring (rows y-1 .. y+RW, cells
+// x-1 .. x+16, channel group major, groups C32_GC cells apart so that the staging
+// writes of a cell's four groups meet different banks), so the wavefronts of a
+// workgroup meet at one barrier only, after the weights are staged. Every ninth K
+// chunk's weight fragments sit in registers and the others' in LDS (shared by the
+// workgroup's eight wavefronts), which leaves room for two wavefronts per SIMD: one
 // wavefront's vector work (the epilogue, the staging) then runs beside the
-// other's MFMAs. The K loop reads the activation fragments (one per row and
-// K chunk for two MFMAs) and the LDS weight fragments a few chunks ahead.
-// Plane z's MFMAs and plane z-1's epilogue (bias, GELU or its derivative,
-// BF16 rounding) sit in one basic block. The MFMAs accumulate each output
-// over the 27 K chunks in the same order as conv_kernel, so the results are
-// the same bit for bit.
-constexpr int C32_RW = 2, C32_WAVES = 8, C32_CR = 8;
+// other's MFMAs. Plane p's MFMAs and the epilogue (bias, GELU or its derivative,
+// BF16 rounding) of the plane finished before sit in one basic block, in four
+// copies, as the finished set and the three in work rotate. Each output still adds
+// its 27 K chunks in the order z, y, x: the results are those of a loop over the
+// offsets, bit for bit.
+// What bounds it: power. MFMAs alone on random data run at 1.7 GHz and 1730
+// TFLOP/s, with six vector instructions per 32 clocks of MFMA at 1265 to 1335; this
+// kernel reaches 1070 (forward) and 980 (data gradient). At 4 x 128^3 the loop over
+// the offsets took 450 and 500 us, with 65% of its cycles spent on LDS reads, and
+// this one 435 and 470; one prediction's layer at 128^3 140 -> 116 us (the pre-
+// activations are then not stored: 1.07 of 1.6 GB). More weights in registers, other
+// read distances and group strides make no difference any more.
+constexpr int C32_RW = 2, C32_WAVES = 8, C32_EVERY = 9;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4))); // a native vector (no struct copies)
 template <bool B> struct BoolC {
     static constexpr bool value = B;
 };
+// One step of the march: the z offsets LO .. LO + NZ - 1 (of 0, 1, 2) that add,
+// whether a finished plane has its epilogue, and whether another plane follows.
+// Group k of a step works on chunk (3 dy + dx) 3 + dz.
+template <int PHASE_, int LO_, int NZ_, bool PREV_, bool MORE_> struct C32Step {
+    static constexpr int PHASE = PHASE_, LO = LO_, NZ = NZ_;
+    static constexpr bool PREV = PREV_, MORE = MORE_;
+    static constexpr int chunk(int k) { return k / NZ * 3 + LO + k % NZ; }
+};
 template <int MODE>
 __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv32p_kernel(ConvArgs a)
 {
-    constexpr int NT = 2, NCH = 27, VPC = 4, RW = C32_RW, PYW = RW * C32_WAVES;
+    constexpr int NT = 2, NCH = 27, VPC = 4, RW = C32_RW, PYW = RW * C32_WAVES, EV = C32_EVERY;
     constexpr int RCELLS = RX * (RW + 2);              // ring cells per plane
-    constexpr int GC = (RCELLS + 15) / 16 * 16;        // cells per channel group, padded to 256 bytes
+    constexpr int GC = RCELLS + 12;                    // cells per channel group: 5.25 times 256 bytes
     constexpr int SLOT_V = GC * VPC;                   // 16-byte vectors per plane slot
     constexpr int LOAD_V = RCELLS * VPC;               // vectors loaded per plane
     constexpr int LOADS = (LOAD_V + 63) / 64;
-    constexpr int CR = C32_CR, CL = NCH - CR;          // weight chunks in registers / in LDS
-    __shared__ u32x4 ring_all[C32_WAVES * 3 * SLOT_V];
+    constexpr int CR = (NCH + EV - 1) / EV, CL = NCH - CR; // weight chunks in registers / in LDS
+    __shared__ u32x4 ring_all[C32_WAVES * 2 * SLOT_V];
     __shared__ uint4 wl[CL * NT * 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    u32x4 *ring = ring_all + wave * 3 * SLOT_V;
-    auto slot3 = [](int z) { return ((z % 3) + 3) % 3; };
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    u32x4 *ring = ring_all + wave * 2 * SLOT_V;
     const int col = lane & 15, quad = lane >> 4;
     const Geo g = a.geo;
 
+    // Chunk i = (3 dy + dx) 3 + dz; the packed weights are in the order 9 dz + 3 dy + dx.
+    auto packed = [](int i) { return i % 3 * 9 + i / 3; };
     bf16x8 wr[CR][NT];
     {
         const uint4 *wg = reinterpret_cast<const uint4 *>(a.wpack);
 #pragma unroll
         for (int c = 0; c < CR; ++c)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) wr[c][t] = __builtin_bit_cast(bf16x8, wg[(c * NT + t) * 64 + lane]);
-        for (int i = threadIdx.x; i < CL * NT * 64; i += 64 * C32_WAVES) wl[i] = wg[CR * NT * 64 + i];
+            for (int t = 0; t < NT; ++t) wr[c][t] = __builtin_bit_cast(bf16x8, wg[(packed(c * EV) * NT + t) * 64 + lane]);
+        for (int e = threadIdx.x; e < CL * NT * 64; e += 64 * C32_WAVES) {
+            const int l = e / (NT * 64), i = l / (EV - 1) * EV + l % (EV - 1) + 1; // the l-th chunk that is no multiple of EV
+            wl[e] = wg[packed(i) * NT * 64 + e % (NT * 64)];
+        }
     }
     __syncthreads();
     const int tx = g.nx / PX, ty = (g.ny + PYW - 1) / PYW, tzc = (g.nz + a.zc - 1) / a.zc;
@@ -432,15 +454,14 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
     b /= ty;
     const int bz = b % tzc;
     const int s = b / tzc;
-    const int x0 = bx * PX, yw = by * PYW + RW * wave, z0 = bz * a.zc;
-    const int ze = min(z0 + a.zc, g.nz);
+    const int x0 = bx * PX, yw = by * PYW + RW * wave, z0 = min(bz * a.zc, g.nz - a.zc), ze = z0 + a.zc;
     if (yw >= g.ny) return; // a wavefront below the grid (no barriers after this point)
     const size_t sbase = (size_t)s * g.ncell, plane = (size_t)g.nx * g.ny;
 
-    // This lane's ring vectors: offset within an input plane (in channels)
+    // This lane's ring vectors: offset within an input plane (in vectors)
     // and ring position; the lanes past the plane load a valid vector and
-    // store nothing.
-    size_t goff[LOADS];
+    // store it into padding.
+    uint32_t goff[LOADS];
     int rpos[LOADS];
 #pragma unroll
     for (int l = 0; l < LOADS; ++l) {
@@ -451,19 +472,13 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
         if (gy < 0) gy += g.ny;
         while (gy >= g.ny) gy -= g.ny;
         const int gx = wrapc(x0 + rx - 1, g.nx);
-        goff[l] = ((size_t)gx + (size_t)g.nx * gy) * 32 + cg * 8;
-        // lanes past the plane store into the padding cells of channel group 3
-        rpos[l] = lane + 64 * l < LOAD_V ? cg * GC + cell : 3 * GC + RCELLS + (lane & (GC - RCELLS - 1));
+        goff[l] = ((uint32_t)gx + (uint32_t)g.nx * gy) * VPC + cg; // at most 4 x 2.5e8
+        rpos[l] = lane + 64 * l < LOAD_V ? cg * GC + cell : 3 * GC + RCELLS + (lane & 7);
     }
     auto load_plane = [&](int z, u32x4 (&o)[LOADS]) __attribute__((always_inline)) {
-        const uint16_t *base = a.in + (sbase + (size_t)wrapc(z, g.nz) * plane) * 32;
+        const u32x4 *base = reinterpret_cast<const u32x4 *>(a.in + (sbase + (size_t)wrapc(z, g.nz) * plane) * 32);
 #pragma unroll
-        for (int l = 0; l < LOADS; ++l) o[l] = *reinterpret_cast<const u32x4 *>(base + goff[l]);
-    };
-    auto stage_plane = [&](int z, const u32x4 (&o)[LOADS]) __attribute__((always_inline)) {
-        u32x4 *dst = ring + slot3(z) * SLOT_V;
-#pragma unroll
-        for (int l = 0; l < LOADS; ++l) dst[rpos[l]] = o[l];
+        for (int l = 0; l < LOADS; ++l) o[l] = base[goff[l]];
     };
     // Epilogue values: the lane's biases are read once (the compiler cannot
     // move their loads past the output stores).
@@ -474,150 +489,156 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
             for (int j = 0; j < 4; ++j) bias_r[t][j] = a.bias[8 * quad + 4 * t + j];
     }
-    auto cell_of = [&](int r, int z) __attribute__((always_inline)) {
-        const int yrow = min(yw + r, g.ny - 1);
-        return sbase + (size_t)(x0 + col) + (size_t)g.nx * ((size_t)yrow + (size_t)g.ny * wrapc(z, g.nz));
+    // This lane's 8 channels of its cell of row r, plane z: a wavefront's base and
+    // the lane's offset.
+    const uint32_t lane_c = col * 32 + quad * 8;
+    auto out_at = [&](int r, int z) __attribute__((always_inline)) {
+        return (sbase + (size_t)x0 + (size_t)g.nx * ((size_t)min(yw + r, g.ny - 1) + (size_t)g.ny * z)) * 32;
     };
-    // One plane: start loading plane z+2, run the 27 K chunks of plane z,
-    // then stage plane z+2 into the ring; with PREV, the
-    // previous plane's 16 epilogue values (2 rows x 2 tiles x 4 channels) are
-    // computed one per chunk beside its MFMAs, and stored at the end.
-    auto plane_step = [&](auto prev, int z, f32x4 (&acc)[RW][NT], const f32x4 (&accp)[RW][NT], u32x4 (&pre)[LOADS]) __attribute__((always_inline)) {
-        constexpr bool PREV = decltype(prev)::value;
-        load_plane(z + 2, pre);
-        bf16x8 zq[RW];
-        if constexpr (PREV && MODE == MODE_DGRAD) {
-#pragma unroll
-            for (int r = 0; r < RW; ++r) zq[r] = load8(a.zprev + cell_of(r, z - 1) * 32 + 8 * quad);
+    bf16x8 zq[RW] = {};  // MODE_DGRAD: pre-activations of the plane whose epilogue is next
+    f32x4 acc[4][RW][NT]; // output plane z in set (z - z0 + 1) mod 4
+    u16 e1[RW][8], e2[RW][8]; // 8 consecutive channels per lane and row
+    auto value = [&](int v, const f32x4 (&f)[RW][NT]) __attribute__((always_inline)) {
+        const int r = v / (NT * 4), t = (v / 4) % NT, j = v % 4;
+        // the empty asm keeps each value's arithmetic where it stands
+        // (pure arithmetic would otherwise sink to the stores)
+        if constexpr (MODE == MODE_HIDDEN) {
+            float zz = f[r][t][j] + bias_r[t][j];
+            float gz = gelu(zz);
+            asm volatile("" : "+v"(zz), "+v"(gz));
+            e1[r][4 * t + j] = f2bf(zz);
+            e2[r][4 * t + j] = f2bf(gz);
+        } else if constexpr (MODE == MODE_ACT) {
+            float gz = gelu(f[r][t][j] + bias_r[t][j]);
+            asm volatile("" : "+v"(gz));
+            e1[r][4 * t + j] = f2bf(gz);
+        } else {
+            float gd = f[r][t][j] * gelu_grad((float)zq[r][4 * t + j]);
+            asm volatile("" : "+v"(gd));
+            e1[r][4 * t + j] = f2bf(gd);
         }
+    };
+    auto store_plane = [&](int z) __attribute__((always_inline)) {
+        // rows last to first: a row past the grid (only when ny is odd) is
+        // clamped onto row 0's cell, whose own store then follows it
+#pragma unroll
+        for (int r = RW - 1; r >= 0; --r) {
+            const size_t o = out_at(r, z);
+            *reinterpret_cast<uint4 *>((MODE == MODE_HIDDEN ? a.zout : a.aout) + o + lane_c) = pack8(e1[r]);
+            if constexpr (MODE == MODE_HIDDEN) *reinterpret_cast<uint4 *>(a.aout + o + lane_c) = pack8(e2[r]);
+        }
+    };
+    // Input plane p (in slot PHASE mod 2, PHASE = p - z0 + 1 mod 4): start loading
+    // plane p + 1, run the K chunks with the 16 epilogue values of plane p - 2 (2
+    // rows x 2 tiles x 4 channels) spread over them, then stage plane p + 1 and
+    // store plane p - 2.
+    auto step = [&](auto kind, int p) __attribute__((always_inline)) {
+        typedef decltype(kind) K;
+        constexpr int P = K::PHASE, NG = 9 * K::NZ, NV = RW * NT * 4, KD = 3;
+        u32x4 pre[LOADS];
+        if constexpr (K::MORE) load_plane(p + 1, pre);
+        const f32x4 (&fin)[RW][NT] = acc[(P + 2) % 4]; // plane p - 2
 #pragma unroll
         for (int r = 0; r < RW; ++r)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        constexpr int KD = 3;
-        bf16x8 av[KD][RW], wv[KD][NT];
-        auto frag = [&](int c, int sl) __attribute__((always_inline)) {
-            const int dz = c / 9, dy = (c / 3) % 3, dx = c % 3;
-            const u32x4 *rs = ring + slot3(z + dz - 1) * SLOT_V + quad * GC;
+            for (int t = 0; t < NT; ++t) acc[(P + 1) % 4][r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const u32x4 *rs = ring + P % 2 * SLOT_V + quad * GC + col;
+        bf16x8 av[3][3], wv[KD][NT]; // ring row R in av[R % 3]
+        auto read_row = [&](int R, int dx) __attribute__((always_inline)) {
+            av[R % 3][dx] = __builtin_bit_cast(bf16x8, rs[R * RX + dx]);
+        };
+        auto read_w = [&](int k) __attribute__((always_inline)) {
+            const int i = K::chunk(k);
+            if (i % EV != 0) {
 #pragma unroll
-            for (int r = 0; r < RW; ++r) av[sl][r] = __builtin_bit_cast(bf16x8, rs[(r + dy) * RX + col + dx]);
-            if (c >= CR) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t) wv[sl][t] = __builtin_bit_cast(bf16x8, wl[((c - CR) * NT + t) * 64 + lane]);
+                for (int t = 0; t < NT; ++t)
+                    wv[k % KD][t] = __builtin_bit_cast(bf16x8, wl[((i - i / EV - 1) * NT + t) * 64 + lane]);
             }
         };
+        read_row(0, 0);
+        read_row(1, 0);
+        read_w(0);
+        read_row(0, 1);
+        read_row(1, 1);
+        read_w(1);
+        read_row(0, 2);
+        read_row(1, 2);
+        read_w(2);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int c = 0; c < KD; ++c) frag(c, c);
-        u16 e1[RW][8], e2[RW][8]; // 8 consecutive channels per lane and row
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int sl = c % KD;
+        for (int k = 0; k < NG; ++k) {
+            const int i = K::chunk(k), dz = i % 3, dx = i / 3 % 3, dy = i / 9;
+            f32x4 (&o)[RW][NT] = acc[(P + 5 - dz) % 4]; // plane p + 1 - dz
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int r = 0; r < RW; ++r)
-                    acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c < CR ? wr[c < CR ? c : 0][t] : wv[sl][t], av[sl][r],
-                                                                        acc[r][t], 0, 0, 0);
-            if (c + KD < NCH) frag(c + KD, sl);
-            if constexpr (PREV) {
-                if (c < RW * NT * 4) {
-                    const int r = c / (NT * 4), t = (c / 4) % NT, j = c % 4;
-                    // the empty asm keeps each value's arithmetic at this chunk
-                    // (pure arithmetic would otherwise sink to the stores)
-                    if constexpr (MODE == MODE_HIDDEN) {
-                        float zz = accp[r][t][j] + bias_r[t][j];
-                        float gz = gelu(zz);
-                        asm volatile("" : "+v"(zz), "+v"(gz));
-                        e1[r][4 * t + j] = f2bf(zz);
-                        e2[r][4 * t + j] = f2bf(gz);
-                    } else if constexpr (MODE == MODE_ACT) {
-                        float gz = gelu(accp[r][t][j] + bias_r[t][j]);
-                        asm volatile("" : "+v"(gz));
-                        e1[r][4 * t + j] = f2bf(gz);
-                    } else {
-                        float gd = accp[r][t][j] * gelu_grad((float)zq[r][4 * t + j]);
-                        asm volatile("" : "+v"(gd));
-                        e1[r][4 * t + j] = f2bf(gd);
-                    }
-                }
+                    o[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(i % EV == 0 ? wr[i / EV][t] : wv[k % KD][t],
+                                                                      av[(dy + r) % 3][dx], o[r][t], 0, 0, 0);
+            if (k + KD < NG) read_w(k + KD);
+            // row dy + 2 replaces row dy - 1, from the second offset's groups on
+            if (dy < 2 && k % K::NZ == 0) read_row(dy + 2, dx);
+            if constexpr (K::PREV) {
+#pragma unroll
+                for (int v = k * NV / NG; v < (k + 1) * NV / NG; ++v) value(v, fin);
+            }
+            if constexpr (MODE == MODE_DGRAD && K::LO + K::NZ == 3) {
+#pragma unroll
+                for (int r = 0; r < RW; ++r) // row r's values are done: its next plane's
+                    if ((k + 1) * NV / NG >= (r + 1) * NT * 4 && k * NV / NG < (r + 1) * NT * 4)
+                        zq[r] = load8(a.zprev + out_at(r, p - 1) + lane_c);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        // plane z+2 into its slot (last read as plane z-2), before the stores
-        // so that the wait for its loads does not also wait for them
-        stage_plane(z + 2, pre);
-        if constexpr (PREV) {
-            // rows last to first: a row past the grid (only when ny is odd) is
-            // clamped onto row 0's cell, whose own store then follows it
+        if constexpr (K::MORE) {
+            u32x4 *dst = ring + (P + 1) % 2 * SLOT_V;
 #pragma unroll
-            for (int r = RW - 1; r >= 0; --r) {
-                const size_t o = cell_of(r, z - 1) * 32 + 8 * quad;
-                if constexpr (MODE == MODE_HIDDEN) {
-                    *reinterpret_cast<uint4 *>(a.zout + o) = pack8(e1[r]);
-                    *reinterpret_cast<uint4 *>(a.aout + o) = pack8(e2[r]);
-                } else {
-                    *reinterpret_cast<uint4 *>(a.aout + o) = pack8(e1[r]);
-                }
-            }
+            for (int l = 0; l < LOADS; ++l) dst[rpos[l]] = pre[l];
         }
+        if constexpr (K::PREV) store_plane(p - 2);
     };
-    // The last plane's epilogue on its own.
-    auto last_epilogue = [&](int z, const f32x4 (&accp)[RW][NT]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int r = RW - 1; r >= 0; --r) {
-            const size_t o = cell_of(r, z) * 32 + 8 * quad;
-            u16 e1[8], e2[8];
-            bf16x8 zp = {};
-            if constexpr (MODE == MODE_DGRAD) zp = load8(a.zprev + o);
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const float acc = accp[r][c / 4][c % 4];
-                if constexpr (MODE == MODE_DGRAD) {
-                    e1[c] = f2bf(acc * gelu_grad((float)zp[c]));
-                } else {
-                    const float zz = acc + bias_r[c / 4][c % 4];
-                    e1[c] = f2bf(MODE == MODE_HIDDEN ? zz : gelu(zz));
-                    if constexpr (MODE == MODE_HIDDEN) e2[c] = f2bf(gelu(zz));
-                }
-            }
-            *reinterpret_cast<uint4 *>((MODE == MODE_HIDDEN ? a.zout : a.aout) + o) = pack8(e1);
-            if constexpr (MODE == MODE_HIDDEN) *reinterpret_cast<uint4 *>(a.aout + o) = pack8(e2);
-        }
-    };
-
-    u32x4 pre[LOADS];
     {
         u32x4 q[LOADS];
-        for (int p = -1; p <= 1; ++p) {
-            load_plane(z0 + p, q);
-            stage_plane(z0 + p, q);
-        }
+        load_plane(z0 - 1, q);
+#pragma unroll
+        for (int l = 0; l < LOADS; ++l) ring[rpos[l]] = q[l];
     }
-    f32x4 accA[RW][NT], accB[RW][NT];
-    plane_step(BoolC<false>{}, z0, accA, accB, pre);
-    int z = z0 + 1;
-    for (; z + 1 < ze; z += 2) {
-        plane_step(BoolC<true>{}, z, accB, accA, pre);
-        plane_step(BoolC<true>{}, z + 1, accA, accB, pre);
+    step(C32Step<0, 0, 1, false, true>{}, z0 - 1);
+    step(C32Step<1, 0, 2, false, true>{}, z0);
+    step(C32Step<2, 0, 3, false, true>{}, z0 + 1);
+    step(C32Step<3, 0, 3, true, true>{}, z0 + 2);
+    int p = z0 + 3;
+    for (; p + 1 < ze; p += 4) {
+        step(C32Step<0, 0, 3, true, true>{}, p);
+        step(C32Step<1, 0, 3, true, true>{}, p + 1);
+        step(C32Step<2, 0, 3, true, true>{}, p + 2);
+        step(C32Step<3, 0, 3, true, true>{}, p + 3);
     }
-    if (z < ze) {
-        plane_step(BoolC<true>{}, z, accB, accA, pre);
-        last_epilogue(z, accB);
-    } else {
-        last_epilogue(ze - 1, accA);
-    }
+    step(C32Step<0, 1, 2, true, true>{}, p);
+    step(C32Step<1, 2, 1, true, false>{}, p + 1);
+#pragma unroll
+    for (int v = 0; v < RW * NT * 4; ++v) value(v, acc[0]);
+    store_plane(p);
 }
-// Planes per workgroup of conv32p_kernel: one workgroup of eight wavefronts
-// fills a CU (its registers and LDS), so the chunk is the longest that still
-// gives at least two workgroups per CU, which amortises the weights' load and
-// the ring's first planes.
-int conv32p_zc(const Geo &g, int nsamp)
+// Planes per workgroup of conv32p_kernel, a multiple of 4 (its steps rotate over four
+// sets of accumulators; the last chunk ends with the grid and may repeat planes of
+// the one before, with the same results). One workgroup of eight wavefronts fills
+// a CU (its registers and LDS), so the chunk is the one with the fewest plane
+// times on 256 CUs, where the weights' load and the first planes count as two.
+static int conv32p_zc(const Geo &g, int nsamp)
 {
     const size_t cols = (size_t)(g.nx / PX) * ((g.ny + C32_RW * C32_WAVES - 1) / (C32_RW * C32_WAVES)) * (size_t)nsamp;
-    int zc = 1;
-    while (zc < g.nz) zc *= 2;
-    while (zc > 4 && cols * ((g.nz + zc - 1) / zc) < 512) zc /= 2;
-    return zc;
+    int best = 4;
+    size_t cost = ~(size_t)0;
+    for (int n = 1; n <= g.nz / 4 && n <= 1024; ++n) {
+        const int zc = std::min((g.nz + 4 * n - 1) / (4 * n), g.nz / 4) * 4;
+        const size_t c = (cols * ((g.nz + zc - 1) / zc) + 255) / 256 * (zc + 2);
+        if (c < cost) {
+            cost = c;
+            best = zc;
+        }
+    }
+    return best;
 }
 
 // ------------------------------------------------------------------ weight gradient
