@@ -26,7 +26,8 @@ BUILD = os.path.join(ROOT, "_build")
 # (a source given as (file, n) is compiled with GS_TB_STORAGE=n: the blocked
 # kernels of one storage type each)
 SOURCES = [*(("gs_tblock.hip", n) for n in range(5)), "gs_step.hip", "gs_block.hip", "gs_aux.hip", "gs_surrogate.hip",
-           "gs_api.cpp", "gs_batch.cpp", "gs_surrogate_api.cpp", "gs_tunecache.cpp", "gs_noalloc.hip"]
+           "gs_api.cpp", "gs_batch.cpp", "gs_surrogate_api.cpp", "gs_tunecache.cpp", "gs_hostio.cpp",
+           "gs_noalloc.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

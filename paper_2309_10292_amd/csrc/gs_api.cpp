@@ -119,46 +119,6 @@ uint16_t host_bf16(float f)
     u += 0x7fffu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
 }
-float host_from_bf16(uint16_t b)
-{
-    uint32_t u = (uint32_t)b << 16;
-    float f;
-    std::memcpy(&f, &u, 4);
-    return f;
-}
-
-// field: 0 = u, 1 = v (GS_BF16C stores 1 - u).
-gs_status read_field(const void *dev, int32_t storage, size_t n, double *host, hipStream_t st, int field)
-{
-    const size_t es = storage_bytes(storage);
-    if (storage == GS_F64) {
-        hipError_t e = hipMemcpyAsync(host, dev, n * 8, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        return e == hipSuccess ? GS_OK : hip_fail(e, "device-to-host copy");
-    }
-    std::vector<unsigned char> stage(n * es);
-    hipError_t e = hipMemcpyAsync(stage.data(), dev, n * es, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return hip_fail(e, "device-to-host copy");
-    if (storage == GS_F32) {
-        const float *x = (const float *)stage.data();
-        for (size_t i = 0; i < n; ++i) host[i] = x[i];
-    } else if (storage == GS_BF16) {
-        const uint16_t *x = (const uint16_t *)stage.data();
-        for (size_t i = 0; i < n; ++i) host[i] = host_from_bf16(x[i]);
-    } else if (storage == GS_BF16C) {
-        const uint16_t *x = (const uint16_t *)stage.data();
-        if (field == 0)
-            for (size_t i = 0; i < n; ++i) host[i] = 1.0 - (double)host_from_bf16(x[i]);
-        else
-            for (size_t i = 0; i < n; ++i) host[i] = host_from_bf16(x[i]);
-    } else {
-        const _Float16 *x = (const _Float16 *)stage.data();
-        for (size_t i = 0; i < n; ++i) host[i] = (double)(float)x[i];
-    }
-    return GS_OK;
-}
-
 gs_status write_field(void *dev, int32_t storage, size_t n, const double *host, hipStream_t st, int field)
 {
     const size_t es = storage_bytes(storage);
@@ -237,6 +197,7 @@ struct gs_sim {
     size_t n;
     GraphCache graph;
     hipStream_t capture_stream;
+    ReadStage reads;
 };
 
 namespace {
@@ -625,11 +586,8 @@ gs_status gs_read(gs_sim *s, double *u_host, double *v_host)
     gs_status st = check(s);
     if (st != GS_OK) return st;
     double *dst[2] = {u_host, v_host};
-    for (int f = 0; f < 2; ++f) {
-        if (!dst[f]) continue;
-        st = read_field(s->buf[s->parity][f], s->p.storage, s->n, dst[f], s->stream, f);
-        if (st != GS_OK) return st;
-    }
+    st = read_fields(s->reads, s->buf[s->parity], s->p.storage, s->n, dst, s->stream);
+    if (st != GS_OK) return st;
     hipError_t e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_fail(e, "gs_read sync");
     return GS_OK;

@@ -86,6 +86,7 @@ struct gs_batch {
     bool dirty;
     bool noise_32; // every grid's noise blocks have 32-bit indices
     BGraph graph;
+    ReadStage reads;
 };
 
 namespace {
@@ -721,10 +722,7 @@ gs_status gs_batch_read(gs_batch *b, int32_t sim, double *u_host, double *v_host
     if ((st = sim_index(b, sim)) != GS_OK) return st;
     const BSim &s = b->sims[sim];
     double *dst[2] = {u_host, v_host};
-    for (int f = 0; f < 2; ++f) {
-        if (!dst[f]) continue;
-        if ((st = read_field(s.buf[s.parity][f], b->base.storage, s.n, dst[f], b->stream, f)) != GS_OK) return st;
-    }
+    if ((st = read_fields(b->reads, s.buf[s.parity], b->base.storage, s.n, dst, b->stream)) != GS_OK) return st;
     hipError_t e = hipStreamSynchronize(b->stream);
     return e == hipSuccess ? GS_OK : hip_fail(e, "gs_batch_read sync");
 }

@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <mutex>
+
 namespace gsapi {
 
 gs_status fail(gs_status s, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
@@ -15,8 +17,24 @@ size_t storage_bytes(int32_t storage);
 bool aligned(const void *p, size_t a);
 // Validates a problem statement (grid, coefficients, init, tiling fields).
 gs_status validate(const gs_params *p);
-// Synchronising copies between a device field of `storage` type and host FP64.
-gs_status read_field(const void *dev, int32_t storage, size_t n, double *host, hipStream_t st, int field);
+// Pinned staging of a handle's reads: a ring that the first large read makes and the
+// handle gives back. Reads of one handle from several threads take turns.
+struct ReadStage {
+    static constexpr int SLOTS = 4; // of 2 MB
+    std::mutex mu;
+    unsigned char *ring = nullptr;
+    int device = -1;
+    hipEvent_t arrived[SLOTS] = {};
+    ReadStage() = default;
+    ReadStage(const ReadStage &) = delete;
+    ReadStage &operator=(const ReadStage &) = delete;
+    ~ReadStage();
+    bool prepare(hipStream_t st);
+};
+// Synchronising copies between device fields of `storage` type (u, v) and host FP64;
+// a NULL host skips the field.
+gs_status read_fields(ReadStage &stage, const void *const dev[2], int32_t storage, size_t n, double *const host[2],
+                      hipStream_t st);
 gs_status write_field(void *dev, int32_t storage, size_t n, const double *host, hipStream_t st, int field);
 // Synchronising diagnostics of a (u, v) pair using the workspace's partials.
 gs_status diagnostics(int32_t storage, const void *u, const void *v, size_t n, void *ws, hipStream_t st,

@@ -539,3 +539,44 @@ def test_block_kernel_default_launch(torch, shape, tile, T):
         u, v = s.read()
     ue, ve = O.run(u0, v0, T + 2, **p)
     assert np.array_equal(u, ue) and np.array_equal(v, ve), f"{max_abs(u, ue)} {max_abs(v, ve)}"
+
+
+# the smallest grid that is read through the ring and one plane less, a last chunk of a few values, and enough chunks
+# to go round the ring
+@pytest.mark.parametrize("shape", [(56, 64, 128), (55, 64, 128), (257, 64, 64), (129, 129, 136)])
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16", "f16", "bf16c"])
+def test_large_reads(torch, shape, storage):
+    """read() equals the device fields widened by torch, value for value: both fields, one of them, from two threads
+    at once, and of a batch's simulation."""
+    import ctypes
+    import threading
+    from paper_2309_10292_amd import gs
+    nz, ny, nx = shape
+    g = torch.Generator(device="cuda").manual_seed(nz)
+    with gs.Sim(nx, ny, nz, storage=storage, init="none", F=0.03, k=0.06) as s:
+        du, dv, _ = s.current()
+        du.copy_(torch.rand(shape, generator=g, device="cuda"))
+        dv.copy_(torch.rand(shape, generator=g, device="cuda"))
+        want = du.double().cpu().numpy(), dv.double().cpu().numpy()
+        if storage == "bf16c":
+            want = 1.0 - want[0], want[1]
+        got = [None, None]
+        def read(i):
+            got[i] = s.read()
+        ts = [threading.Thread(target=read, args=(i,)) for i in range(2)]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+        for u, v in got + [s.read()]:
+            assert np.array_equal(u, want[0]) and np.array_equal(v, want[1])
+        one = np.full(shape, np.nan)
+        gs.check(gs.load().gs_read(s.h, None, one.ctypes.data_as(ctypes.POINTER(ctypes.c_double))))
+        assert np.array_equal(one, want[1])
+    if storage == "bf16c":
+        return
+    with gs.Batch([dict(nx=16, ny=8, nz=8, F=0.03, k=0.06), dict(nx=nx, ny=ny, nz=nz, F=0.03, k=0.06)],
+                  storage=storage, init="none") as b:
+        b.write(1, *want)
+        u, v = b.read(1)
+        assert np.array_equal(u, want[0]) and np.array_equal(v, want[1])
