@@ -21,39 +21,41 @@ namespace nn {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4))); // a native vector (no struct copies)
 typedef uint16_t u16;
 
 __device__ __forceinline__ float bf2f(u16 b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ __forceinline__ u16 f2bf(float f) { return bf16_rne(f).bits; }
 
-// erf by Abramowitz and Stegun 7.1.26 (Hastings' rational approximation,
-// |error| <= 1.5e-7, far below the BF16 rounding of the activations),
-// without branches; e receives exp(-x^2), which the GELU's derivative reuses.
-__device__ __forceinline__ float erf_as(float x, float &e)
+// erf(x) / 2 by Abramowitz and Stegun 7.1.26 (Hastings' rational approximation, here
+// with half its coefficients; |error of erf| <= 1.5e-7, far below the BF16 rounding
+// of the activations), without branches; e receives exp(-x^2), which the GELU's
+// derivative reuses.
+__device__ __forceinline__ float half_erf(float x, float &e)
 {
     const float ax = fabsf(x);
     const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f, ax, 1.0f));
-    float p = __builtin_fmaf(1.061405429f, t, -1.453152027f);
-    p = __builtin_fmaf(p, t, 1.421413741f);
-    p = __builtin_fmaf(p, t, -0.284496736f);
-    p = __builtin_fmaf(p, t, 0.254829592f);
+    float p = __builtin_fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
+    p = __builtin_fmaf(p, t, 0.5f * 1.421413741f);
+    p = __builtin_fmaf(p, t, 0.5f * -0.284496736f);
+    p = __builtin_fmaf(p, t, 0.5f * 0.254829592f);
     p *= t;
     e = __expf(-ax * ax);
-    return copysignf(__builtin_fmaf(-p, e, 1.0f), x);
+    return copysignf(__builtin_fmaf(-p, e, 0.5f), x);
 }
 
-// GELU(z) = z Phi(z) = z (1 + erf(z / sqrt 2)) / 2 and its derivative
+// GELU(z) = z Phi(z) = z (1/2 + erf(z / sqrt 2) / 2) and its derivative
 // Phi(z) + z phi(z), phi(z) = exp(-z^2 / 2) / sqrt(2 pi).
 __device__ __forceinline__ float gelu(float z)
 {
     float e;
-    return 0.5f * z * (1.0f + erf_as(z * 0.70710678118654752f, e));
+    return z * (0.5f + half_erf(z * 0.70710678118654752f, e));
 }
 __device__ __forceinline__ float gelu_grad(float z)
 {
     float e;
-    const float er = erf_as(z * 0.70710678118654752f, e);
-    return __builtin_fmaf(0.5f, 1.0f + er, z * e * 0.39894228040143268f);
+    const float er = half_erf(z * 0.70710678118654752f, e);
+    return (0.5f + er) + z * e * 0.39894228040143268f;
 }
 
 __device__ __forceinline__ int wrapc(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
@@ -86,55 +88,52 @@ __device__ __forceinline__ void wg_lds_barrier()
 // MODE_OUT:    pred = residual input + acc + bias for output channels 0, 1.
 // MODE_DGRAD:  writes acc * GELU'(zprev) (the gradient of the layer below's
 //              pre-activation, 32 channels, BF16).
-//
-// A workgroup (4 wavefronts) owns a patch of 16 x-cells by 4 y-rows of one
-// sample and marches through a chunk of z planes; wavefront w computes row w
-// (one 16-cell M tile per plane). The input planes z-1, z, z+1 of the patch
-// with a one-cell ring (18 x 6 cells) sit in an LDS ring of three planes next
-// to the packed weights, so every input value is fetched from L2 once per
-// chunk instead of once per offset; the plane z+2 is loaded into registers
-// while plane z is computed. Every MFMA operand is read from LDS: the ring is
-// stored channel group major so that a fragment read is 256 contiguous bytes
-// per 16 lanes (no bank conflicts), and the K loop keeps its reads a few
-// chunks ahead of the MFMAs that use them. The two tiles' output channels are
-// interleaved so that a lane holds 8 consecutive channels and a wavefront
-// stores (and the data gradient reads) whole 1 KB rows in 16-byte accesses: the
-// 8-channel layers, which HBM bounds (1.07 GB each way of a hidden tensor and
-// its pre-activation at 4 x 128^3), took 427 (forward) and 389 us (data
-// gradient) with 8-byte pieces of 32-byte runs and take 345 and 301.
 template <int N> struct IntC {
     static constexpr int value = N;
 };
-constexpr int PX = 16, PY = 4;               // patch (x, y)
-constexpr int RX = PX + 2, RY = PY + 2;      // ring plane (x, y)
-constexpr int RCELLS = RX * RY;              // cells per ring plane
+constexpr int PX = 16;      // cells of a patch in x
+constexpr int RX = PX + 2;  // with the ring around it
 
+// 8 -> 32 convolutions (the first layer, and the data gradient of the last): as
+// conv32p_kernel below, a wavefront owns RW rows of 16 cells and both 16-channel N
+// tiles of one sample and marches through a chunk of z planes with a private LDS
+// ring, here of the three planes that a K chunk (four neighbour cells) may reach
+// into; no barriers. All 14 weight fragments sit in registers. The two tiles'
+// output channels are interleaved so that a lane holds 8 consecutive channels and a
+// wavefront stores (and the data gradient reads) whole 1 KB rows in 16-byte
+// accesses. Loads run a plane ahead; the chunk's planes are a multiple of three, the
+// ring's phases.
+// What bounds it: the stores of a hidden layer's two tensors (1.07 GB at 4 x 128^3,
+// 3.4 TB/s), the data gradient's 1.2 GB (the rate of a large copy), and for a
+// prediction the GELU's 16 vector operations a value. With workgroups sharing a ring
+// behind two barriers a plane, and the weights in LDS: forward 346 -> 320 us, data
+// gradient 302 -> 238, one prediction's layer at 128^3 74 -> 65. Four rows a
+// wavefront, or four wavefronts a SIMD, are no faster.
+constexpr int C8_RW = 2, C8_WAVES = 4;
 template <int MODE>
-__global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
+__global__ __launch_bounds__(64 * C8_WAVES) __attribute__((amdgpu_waves_per_eu(3, 3))) void conv8_kernel(ConvArgs a)
 {
-    constexpr int CIN = 8, NT = 2;
-    constexpr int NCH = (27 * CIN + 31) / 32;
-    constexpr int VPC = CIN / 8;              // 16-byte vectors per cell
-    // Ring layout: channel group major, cells contiguous within a group, so
-    // the 16 lanes of a channel group read 16 consecutive cells (256
-    // contiguous bytes, free of bank conflicts); each group's cells are padded
-    // to a multiple of 16 vectors (256 bytes).
-    constexpr int GCELLS = (RCELLS + 15) / 16 * 16;
-    constexpr int PLANE_V = GCELLS * VPC;     // 16-byte vectors per ring plane
-    constexpr int LOAD_V = RCELLS * VPC;      // vectors loaded per plane
-    constexpr int LOADS = (LOAD_V + 255) / 256;
-    // ring position of loaded vector v (cell v / VPC, channel group v % VPC)
-    auto ring_pos = [](int v) { return (v % VPC) * GCELLS + v / VPC; };
-    __shared__ uint4 wl[NCH * NT * 64];
-    __shared__ uint4 ring[3 * PLANE_V];
-    const uint4 *wg = reinterpret_cast<const uint4 *>(a.wpack);
-    for (int i = threadIdx.x; i < NCH * NT * 64; i += 256) wl[i] = wg[i];
-
-    const Geo g = a.geo;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    constexpr int NT = 2, NCH = 7, RW = C8_RW, PYW = RW * C8_WAVES;
+    constexpr int RCELLS = RX * (RW + 2);             // ring cells per plane, a 16-byte vector each
+    constexpr int SLOT_V = (RCELLS + 15) / 16 * 16;
+    constexpr int LOADS = (RCELLS + 63) / 64;
+    // behind the rings RW rows of zeros: the last chunk has 27 - 24 = 3 cells
+    constexpr int ZERO = C8_WAVES * 3 * SLOT_V;
+    __shared__ u32x4 ring_all[ZERO + (RW - 1) * RX + 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int col = lane & 15, quad = lane >> 4;
-    const int tx = g.nx / PX, ty = (g.ny + PY - 1) / PY, tzc = (g.nz + a.zc - 1) / a.zc;
+    const Geo g = a.geo;
+    const int ring0 = wave * 3 * SLOT_V;
+
+    bf16x8 w[NCH][NT];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) w[c][t] = load8(a.wpack + ((c * NT + t) * 64 + lane) * 8);
+    if ((int)threadIdx.x < (RW - 1) * RX + 1) ring_all[ZERO + threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+
+    const int tx = g.nx / PX, ty = (g.ny + PYW - 1) / PYW, tzc = (g.nz + a.zc - 1) / a.zc;
     int b = blockIdx.x;
     const int bx = b % tx;
     b /= tx;
@@ -142,88 +141,119 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a)
     b /= ty;
     const int bz = b % tzc;
     const int s = b / tzc;
-    const int x0 = bx * PX, y0 = by * PY, z0 = bz * a.zc;
-    const int ze = min(z0 + a.zc, g.nz);
-    const size_t sbase = (size_t)s * g.ncell;
+    const int x0 = bx * PX, yw = by * PYW + RW * wave, z0 = min(bz * a.zc, g.nz - a.zc), ze = z0 + a.zc;
+    if (yw >= g.ny) return; // a wavefront below the grid (no barriers after this point)
+    const size_t sbase = (size_t)s * g.ncell, plane = (size_t)g.nx * g.ny;
 
-    // global address of ring vector v (cell (rx, ry) of plane z, channel group cg)
-    auto ring_src = [&](int v, int z) -> const uint4 * {
-        const int cell = v / VPC, cg = v % VPC;
-        const int rx = cell % RX, ry = cell / RX;
-        const int gx = wrapc(x0 + rx - 1, g.nx), gy = wrapc(y0 + ry - 1, g.ny), gz = wrapc(z, g.nz);
-        const size_t row = sbase + (size_t)gx + (size_t)g.nx * ((size_t)gy + (size_t)g.ny * gz);
-        return reinterpret_cast<const uint4 *>(a.in + row * CIN) + cg;
-    };
-    for (int p = 0; p < 3; ++p) {
-        const int z = z0 - 1 + p; // ring slot of plane z is (z mod 3)
-        const int slot = ((z % 3) + 3) % 3;
-        for (int v = threadIdx.x; v < LOAD_V; v += 256) ring[slot * PLANE_V + ring_pos(v)] = *ring_src(v, z);
+    // This lane's ring vectors (cells; lanes past the plane repeat the last one).
+    uint32_t goff[LOADS];
+    int rpos[LOADS];
+#pragma unroll
+    for (int l = 0; l < LOADS; ++l) {
+        rpos[l] = min(lane + 64 * l, RCELLS - 1);
+        int gy = yw + rpos[l] / RX - 1;
+        if (gy < 0) gy += g.ny;
+        while (gy >= g.ny) gy -= g.ny;
+        goff[l] = (uint32_t)wrapc(x0 + rpos[l] % RX - 1, g.nx) + (uint32_t)g.nx * gy;
     }
-    __syncthreads();
-
-    const int yrow = y0 + wave;
-    const bool row_ok = yrow < g.ny;
-    for (int z = z0; z < ze; ++z) {
-        // prefetch plane z+2 (needed from the next plane on); every lane loads
-        // an in-range vector (indices clamped) and only the LDS store is masked
-        const bool more = z + 1 < ze;
-        static_assert(LOADS <= 2, "a ring plane is at most two vectors per lane");
-        const uint4 pre0 = *ring_src(min((int)threadIdx.x, LOAD_V - 1), z + 2);
-        const uint4 pre1 = LOADS > 1 ? *ring_src(min((int)threadIdx.x + 256, LOAD_V - 1), z + 2) : pre0;
-        f32x4 acc[NT];
+    auto load_plane = [&](int z, u32x4 (&o)[LOADS]) __attribute__((always_inline)) {
+        const u32x4 *base = reinterpret_cast<const u32x4 *>(a.in) + sbase + (size_t)wrapc(z, g.nz) * plane;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // A = weights (rows: output channels), B = activations (columns:
-        // cells), so a lane's accumulators are 4 consecutive output channels
-        // of one cell.
-#pragma unroll 9
+        for (int l = 0; l < LOADS; ++l) o[l] = base[goff[l]];
+    };
+    auto stage_plane = [&](int slot, const u32x4 (&o)[LOADS]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int l = 0; l < LOADS; ++l) ring_all[ring0 + slot * SLOT_V + rpos[l]] = o[l];
+    };
+    // Chunk c's cell of this lane (offset 4 c + quad) in phase P, where plane z + dz - 1
+    // sits in slot (P + dz) mod 3.
+    int at0[NCH], at1[NCH], at2[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const int d = 4 * c + quad, cell = ring0 + d / 3 % 3 * RX + d % 3 + col;
+        at0[c] = d < 27 ? cell + d / 9 * SLOT_V : ZERO;
+        at1[c] = d < 27 ? cell + (d / 9 + 1) % 3 * SLOT_V : ZERO;
+        at2[c] = d < 27 ? cell + (d / 9 + 2) % 3 * SLOT_V : ZERO;
+    }
+    float bias_r[8] = {};
+    if constexpr (MODE != MODE_DGRAD) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) bias_r[c] = a.bias[8 * quad + c];
+    }
+    const uint32_t lane_c = col * 32 + quad * 8;
+    auto out_at = [&](int r, int z) __attribute__((always_inline)) {
+        return (sbase + (size_t)x0 + (size_t)g.nx * ((size_t)min(yw + r, g.ny - 1) + (size_t)g.ny * z)) * 32;
+    };
+    bf16x8 zq[RW] = {}; // MODE_DGRAD: this plane's pre-activations
+    auto load_zq = [&](int r, int z) __attribute__((always_inline)) {
+        if constexpr (MODE == MODE_DGRAD) zq[r] = load8(a.zprev + out_at(r, z) + lane_c);
+    };
+    auto step = [&](auto phase, int z) __attribute__((always_inline)) {
+        constexpr int P = decltype(phase)::value;
+        u32x4 pre[LOADS];
+        load_plane(z + 2, pre);
+        f32x4 acc[RW][NT];
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        constexpr int KD = 2; // fragments are read KD chunks ahead of their MFMAs
+        bf16x8 av[KD][RW];
+        auto frag = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r) av[c % KD][r] = __builtin_bit_cast(bf16x8, ring_all[(P == 0 ? at0[c] : P == 1 ? at1[c] : at2[c]) + r * RX]);
+        };
+#pragma unroll
+        for (int c = 0; c < KD; ++c) frag(c);
+#pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            const int k0 = 32 * c + 8 * quad;
-            const int d = k0 / CIN, ci0 = k0 % CIN;
-            bf16x8 av;
-            if (d < 27) {
-                const int dz = d / 9, dy = (d / 3) % 3, dx = d % 3;
-                const int slot = (((z + dz - 1) % 3) + 3) % 3;
-                const int cell = (wave + dy) * RX + col + dx;
-                av = __builtin_bit_cast(bf16x8, ring[slot * PLANE_V + (ci0 / 8) * GCELLS + cell]);
-            } else {
-                av = __builtin_bit_cast(bf16x8, uint4{0u, 0u, 0u, 0u});
-            }
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const bf16x8 wv = __builtin_bit_cast(bf16x8, wl[(c * NT + t) * 64 + lane]);
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, av, acc[t], 0, 0, 0);
-            }
+            for (int r = 0; r < RW; ++r)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[c][t], av[c % KD][r], acc[r][t], 0, 0, 0);
+            if (c + KD < NCH) frag(c + KD);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        // acc[t][j] with two tiles: output channel 8 quad + 4 t + j of cell
-        // (x0 + col, yrow, z), so a lane holds 8 consecutive channels.
-        const size_t r = sbase + (size_t)(x0 + col) + (size_t)g.nx * ((size_t)yrow + (size_t)g.ny * z);
-        if (row_ok) {
-            if constexpr (MODE == MODE_DGRAD) {
-                const bf16x8 zp = load8(a.zprev + r * 32 + 8 * quad);
-                u16 gb[8];
+        // acc[r][t][j]: output channel 8 quad + 4 t + j of cell (x0 + col, yw + r, z).
+        u16 e1[RW][8], e2[RW][8];
 #pragma unroll
-                for (int c = 0; c < 8; ++c) gb[c] = f2bf(acc[c / 4][c % 4] * gelu_grad((float)zp[c]));
-                *reinterpret_cast<uint4 *>(a.aout + r * 32 + 8 * quad) = pack8(gb);
-            } else {
-                u16 zb[8], ab[8];
+        for (int r = 0; r < RW; ++r) {
 #pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const float zz = acc[c / 4][c % 4] + a.bias[8 * quad + c];
-                    zb[c] = f2bf(zz);
-                    ab[c] = f2bf(gelu(zz));
+            for (int c = 0; c < 8; ++c) {
+                const float v = acc[r][c / 4][c % 4];
+                if constexpr (MODE == MODE_DGRAD) {
+                    e1[r][c] = f2bf(v * gelu_grad((float)zq[r][c]));
+                } else {
+                    const float zz = v + bias_r[c];
+                    e1[r][c] = f2bf(MODE == MODE_HIDDEN ? zz : gelu(zz));
+                    if constexpr (MODE == MODE_HIDDEN) e2[r][c] = f2bf(gelu(zz));
                 }
-                if constexpr (MODE == MODE_HIDDEN) *reinterpret_cast<uint4 *>(a.zout + r * 32 + 8 * quad) = pack8(zb);
-                *reinterpret_cast<uint4 *>(a.aout + r * 32 + 8 * quad) = pack8(ab);
             }
+            load_zq(r, min(z + 1, ze - 1));
         }
-        __syncthreads(); // every read of plane z-1's slot is done
-        if (more) {
-            const int slot = ((z + 2) % 3 + 3) % 3;
-            if ((int)threadIdx.x < LOAD_V) ring[slot * PLANE_V + ring_pos(threadIdx.x)] = pre0;
-            if (LOADS > 1 && (int)threadIdx.x + 256 < LOAD_V) ring[slot * PLANE_V + ring_pos(threadIdx.x + 256)] = pre1;
+        stage_plane((P + 3) % 3, pre); // plane z + 2 replaces z - 1
+        // rows last to first: a row past the grid (only when ny is odd) is
+        // clamped onto row 0's cell, whose own store then follows it
+#pragma unroll
+        for (int r = RW - 1; r >= 0; --r) {
+            const size_t o = out_at(r, z);
+            *reinterpret_cast<uint4 *>((MODE == MODE_HIDDEN ? a.zout : a.aout) + o + lane_c) = pack8(e1[r]);
+            if constexpr (MODE == MODE_HIDDEN) *reinterpret_cast<uint4 *>(a.aout + o + lane_c) = pack8(e2[r]);
         }
-        __syncthreads();
+    };
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        u32x4 q[LOADS];
+        load_plane(z0 - 1 + p, q);
+        stage_plane(p, q);
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) load_zq(r, z0);
+    for (int z = z0; z < ze; z += 3) {
+        step(IntC<0>{}, z);
+        step(IntC<1>{}, z + 1);
+        step(IntC<2>{}, z + 2);
     }
 }
 
@@ -402,7 +432,6 @@ __global__ __launch_bounds__(512) void conv_out_kernel(ConvArgs a)
 // activations are then not stored: 1.07 of 1.6 GB). More weights in registers, other
 // read distances and group strides make no difference any more.
 constexpr int C32_RW = 2, C32_WAVES = 8, C32_EVERY = 9;
-typedef unsigned u32x4 __attribute__((ext_vector_type(4))); // a native vector (no struct copies)
 template <bool B> struct BoolC {
     static constexpr bool value = B;
 };
@@ -620,27 +649,6 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
     for (int v = 0; v < RW * NT * 4; ++v) value(v, acc[0]);
     store_plane(p);
 }
-// Planes per workgroup of conv32p_kernel, a multiple of 4 (its steps rotate over four
-// sets of accumulators; the last chunk ends with the grid and may repeat planes of
-// the one before, with the same results). One workgroup of eight wavefronts fills
-// a CU (its registers and LDS), so the chunk is the one with the fewest plane
-// times on 256 CUs, where the weights' load and the first planes count as two.
-static int conv32p_zc(const Geo &g, int nsamp)
-{
-    const size_t cols = (size_t)(g.nx / PX) * ((g.ny + C32_RW * C32_WAVES - 1) / (C32_RW * C32_WAVES)) * (size_t)nsamp;
-    int best = 4;
-    size_t cost = ~(size_t)0;
-    for (int n = 1; n <= g.nz / 4 && n <= 1024; ++n) {
-        const int zc = std::min((g.nz + 4 * n - 1) / (4 * n), g.nz / 4) * 4;
-        const size_t c = (cols * ((g.nz + zc - 1) / zc) + 255) / 256 * (zc + 2);
-        if (c < cost) {
-            cost = c;
-            best = zc;
-        }
-    }
-    return best;
-}
-
 // ------------------------------------------------------------------ weight gradient
 // dW[d][co][ci] = sum over cells of dz[cell][co] * act[cell + d][ci]: for each
 // of the 27 offsets d a product A B with A = dz^T (rows co, K = cells) and
@@ -1336,22 +1344,45 @@ static int balanced_zc(int nz, size_t cols, size_t slots)
     return best;
 }
 
+// Planes per workgroup of conv8_kernel and conv32p_kernel, a multiple of `unit` (the
+// phases their steps rotate over); the last chunk ends with the grid and may repeat
+// planes of the one before, with the same results. The chunk is the one with the
+// fewest plane times on `slots` places, where the weights' load and the first planes
+// count as two.
+static int chunk_planes(int nz, size_t cols, size_t slots, int unit)
+{
+    int best = unit;
+    size_t cost = ~(size_t)0;
+    for (int n = 1; n <= nz / unit && n <= 1024; ++n) {
+        const int zc = std::min((nz + unit * n - 1) / (unit * n), nz / unit) * unit;
+        const size_t c = (cols * ((nz + zc - 1) / zc) + slots - 1) / slots * (zc + 2);
+        if (c < cost) {
+            cost = c;
+            best = zc;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a, hipStream_t st)
 {
-    if (a.zc < 1 || a.geo.nx % PX != 0) return hipErrorInvalidValue;
-    if (cin == 32 && nt == 2 && mode != MODE_OUT) {
+    if (a.geo.nx % PX != 0 || a.geo.nz < 4) return hipErrorInvalidValue;
+    if (nt == 2 && mode != MODE_OUT && (cin == 8 || cin == 32)) {
         ConvArgs b = a;
-        b.zc = conv32p_zc(a.geo, a.nsamp);
-        const int py = C32_RW * C32_WAVES;
-        const size_t nb = (size_t)(a.geo.nx / PX) * ((a.geo.ny + py - 1) / py) * ((a.geo.nz + b.zc - 1) / b.zc) * a.nsamp;
+        const int waves = cin == 8 ? C8_WAVES : C32_WAVES, py = waves * (cin == 8 ? C8_RW : C32_RW);
+        const size_t cols = (size_t)(a.geo.nx / PX) * ((a.geo.ny + py - 1) / py) * a.nsamp;
+        // workgroups at once on 256 CUs: three of conv8_kernel a CU (registers), one of
+        // conv32p_kernel (registers and LDS)
+        b.zc = cin == 8 ? chunk_planes(a.geo.nz, cols, 768, 3) : chunk_planes(a.geo.nz, cols, 256, 4);
+        const size_t nb = cols * ((a.geo.nz + b.zc - 1) / b.zc);
         if (nb == 0 || nb > 0x7fffffffu) return hipErrorInvalidConfiguration;
-        if (mode == MODE_HIDDEN)
-            hipLaunchKernelGGL(conv32p_kernel<MODE_HIDDEN>, dim3((unsigned)nb), dim3(64 * C32_WAVES), 0, st, b);
-        else if (mode == MODE_ACT)
-            hipLaunchKernelGGL(conv32p_kernel<MODE_ACT>, dim3((unsigned)nb), dim3(64 * C32_WAVES), 0, st, b);
-        else
-            hipLaunchKernelGGL(conv32p_kernel<MODE_DGRAD>, dim3((unsigned)nb), dim3(64 * C32_WAVES), 0, st, b);
-        return hipGetLastError();
+        auto go = [&](auto m) {
+            constexpr int M = decltype(m)::value;
+            if (cin == 8) hipLaunchKernelGGL(conv8_kernel<M>, dim3((unsigned)nb), dim3(64 * waves), 0, st, b);
+            else hipLaunchKernelGGL(conv32p_kernel<M>, dim3((unsigned)nb), dim3(64 * waves), 0, st, b);
+            return hipGetLastError();
+        };
+        return mode == MODE_HIDDEN ? go(IntC<MODE_HIDDEN>{}) : mode == MODE_ACT ? go(IntC<MODE_ACT>{}) : go(IntC<MODE_DGRAD>{});
     }
     if (cin == 32 && nt == 1 && mode == MODE_OUT) {
         ConvArgs b = a;
@@ -1367,15 +1398,7 @@ hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a,
         };
         return ng >= OUT_NG ? go(BoolC<true>{}) : go(BoolC<false>{});
     }
-    const size_t blocks = (size_t)(a.geo.nx / PX) * ((a.geo.ny + PY - 1) / PY) * ((a.geo.nz + a.zc - 1) / a.zc) * a.nsamp;
-    if (blocks == 0 || blocks > 0x7fffffffu) return hipErrorInvalidConfiguration;
-    const int grid = (int)blocks;
-    if (cin != 8 || nt != 2) return hipErrorInvalidValue;
-    if (mode == MODE_HIDDEN) hipLaunchKernelGGL(conv_kernel<MODE_HIDDEN>, dim3(grid), dim3(256), 0, st, a);
-    else if (mode == MODE_ACT) hipLaunchKernelGGL(conv_kernel<MODE_ACT>, dim3(grid), dim3(256), 0, st, a);
-    else if (mode == MODE_DGRAD) hipLaunchKernelGGL(conv_kernel<MODE_DGRAD>, dim3(grid), dim3(256), 0, st, a);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 int wgrad_blocks() { return 512; }

@@ -134,19 +134,6 @@ gs_status check_fk(int32_t nsamp, const double *F, const double *k)
     return GS_OK;
 }
 
-// Planes per workgroup chunk of the convolutions for a batch of nsamp
-// samples: long chunks amortise the two extra ring planes (at 4 x 128^3 the
-// 32 -> 32 forward takes 0.757, 0.721 and 0.699 ms with 16, 32 and 64
-// planes), shorter ones keep at least 2048 workgroups (eight per CU) in flight
-// on small grids and batches.
-int conv_zc(const gs_surrogate *s, int nsamp)
-{
-    const size_t patches = (size_t)(s->geo.nx / 16) * ((s->geo.ny + 3) / 4) * (size_t)nsamp;
-    int zc = 64;
-    while (zc > 4 && patches * ((s->geo.nz + zc - 1) / zc) < 2048) zc /= 2;
-    return zc < s->geo.nz ? zc : s->geo.nz;
-}
-
 // Forward pass of nsamp samples; keeps the activations, and the
 // pre-activations too when keep_pre (the backward pass needs them; a
 // prediction does not, and skips their stores).
@@ -173,7 +160,6 @@ hipError_t forward(gs_surrogate *s, int32_t nsamp, int io_f64, const void *u, co
         ConvArgs a = {};
         a.geo = s->geo;
         a.nsamp = nsamp;
-        a.zc = conv_zc(s, nsamp);
         a.in = in;
         a.wpack = at<uint16_t>(s, s->L.wf[l]);
         a.bias = P + b_off(l);
@@ -186,7 +172,6 @@ hipError_t forward(gs_surrogate *s, int32_t nsamp, int io_f64, const void *u, co
         ConvArgs a = {};
         a.geo = s->geo;
         a.nsamp = nsamp;
-        a.zc = conv_zc(s, nsamp);
         a.in = in;
         a.wpack = at<uint16_t>(s, s->L.wf[3]);
         a.bias = P + b_off(3);
@@ -332,7 +317,6 @@ gs_status gs_surrogate_loss_grad(gs_surrogate *s, int32_t nsamp, const float *u,
         ConvArgs a = {};
         a.geo = s->geo;
         a.nsamp = nsamp;
-        a.zc = conv_zc(s, nsamp);
         a.in = dz;
         a.wpack = at<uint16_t>(s, s->L.wd[l]);
         a.zprev = at<uint16_t>(s, s->L.z[l - 1]);

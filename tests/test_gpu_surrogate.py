@@ -522,8 +522,8 @@ def test_edge_layer_weight_gradients(torch, nz, ny, nx, n):
         assert np.all(np.abs(G[l][1] - ref) <= gam * mag + 2 * U * np.abs(ref) + 1e-38), name
 
 
-# hidden-layer launches of 12 (the second repeats planes of the first) and 16 planes per workgroup, the second with an
-# odd number of rows; the small grids' launches take 4
+# hidden-layer launches of 12 (the second repeats planes of the first) and 16 planes per workgroup, 9 and 12 in the
+# 8-channel layers, the second with an odd number of rows; the small grids' launches take 8, and 6 and 3
 @pytest.mark.parametrize("nz, ny, nx, reps", [(22, 16, 64, 32), (30, 15, 128, 32)], ids=["22x16x64", "30x15x128"])
 def test_hidden_layers_same_for_every_chunk(torch, nz, ny, nx, reps):
     """A grid repeated along x holds the small grid's tensors again, bit for bit (the loss gradient scaled by the
@@ -537,7 +537,7 @@ def test_hidden_layers_same_for_every_chunk(torch, nz, ny, nx, reps):
         T = lambda a: torch.from_numpy(np.tile(a, (1, 1, 1, r)).astype(np.float32)).cuda()
         with Surrogate(nx * r, ny, nz, params=_params(22)) as m:
             m.loss_grad(T(u), T(v), T(ut), T(vt), [0.03], [0.055], want_grad=True)
-            got.append([m.read_tensor(t, l, 1)[0] for t, l in ((m.PRE, 1), (m.ACT, 1), (m.PRE, 2), (m.ACT, 2), (m.DPRE, 1), (m.DPRE, 0))])
+            got.append([m.read_tensor(t, l, 1)[0] for t, l in ([(t, l) for l in range(3) for t in (m.PRE, m.ACT)] + [(m.DPRE, l) for l in range(3)])])
     for i, (small, large) in enumerate(zip(*got)):
-        small = small / reps if i >= 4 else small
+        small = small / reps if i >= 6 else small
         assert np.array_equal(large.reshape(nz, ny, reps, nx, 32), np.broadcast_to(small[:, :, None], (nz, ny, reps, nx, 32))), i
