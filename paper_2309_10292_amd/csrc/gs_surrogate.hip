@@ -670,12 +670,17 @@ __global__ __launch_bounds__(64 * C32_WAVES) __attribute__((amdgpu_waves_per_eu(
 // half-wave read distinct banks.
 //
 // Wave w owns one 16 x 16 output tile (co x ci) for all 27 offsets and all K
-// chunks of a plane (two rows of 16 cells each). Staging is double-buffered with
-// one barrier per plane: act plane p + 2 and dz plane p + 3 are loaded into
-// registers while plane p is multiplied and stored into the free buffers at the
-// start of the next plane. The bias gradient (the sum of dz over cells) is
-// accumulated while dz is staged. Each workgroup writes its partial sums (32 x 32
-// per offset, and 32 bias sums) once.
+// chunks of a plane (two rows of 16 cells each). Act plane p + 2 and dz plane p + 3
+// are stored into the third of three LDS slots half way through plane p, behind the
+// plane's one barrier, and loaded a step before; the B fragments are read a few
+// MFMAs ahead across the planes, so no wavefront starts a plane waiting for LDS or
+// for the others. The bias gradient (the sum of dz over cells) is accumulated while
+// dz is staged. Each workgroup writes its partial sums (32 x 32 per offset, and 32
+// bias sums) once.
+// What bounds it: the matrix units at the clock that the card's power allows (1300
+// TFLOP/s; MFMAs with their LDS reads alone 1540 to 1660). 4 x 128^3: 452 -> 355 us
+// against two slots with the barrier between planes and the staged vectors as
+// structs, which the compiler kept in LDS, waiting for each load where it was issued.
 constexpr int WG_ZC = 64;
 
 typedef short v4s __attribute__((ext_vector_type(4)));
@@ -712,20 +717,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr int DROW = 16 * NCO, DPL = TR * DROW;             // dz rows y0 .. y0 + TR - 1
     constexpr int T_ACT = (TR + 2) * 18 * NCG, RA = (T_ACT + 255) / 256; // 16-byte chunks of an act plane
     constexpr int T_DZ = TR * 16 * NCGZ;                                  // and of a dz plane
-    constexpr int RD = (T_DZ + 255) / 256, TDL = T_DZ < 256 ? T_DZ : 256; // dz chunks per lane, lanes staging dz
-    static_assert(T_DZ <= 256 || T_DZ % 256 == 0, "whole dz rounds");
-    __shared__ __align__(16) u16 act_l[2 * APL];
-    __shared__ __align__(16) u16 dz_l[2 * DPL];
-    __shared__ float bsum_l[TDL][8];
+    constexpr int RD = T_DZ / 256;              // dz chunks per lane
+    static_assert(T_DZ % 256 == 0, "whole dz rounds");
+    __shared__ __align__(16) u16 act_l[3 * APL];
+    __shared__ __align__(16) u16 dz_l[3 * DPL];
+    __shared__ float bsum_l[256][8];
     const Geo g = a.geo;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, quad = lane >> 4;
     const int mw = wave >> 1, nw = wave & 1; // the wave's output tile
 
-    // Channels past CIN / COUTS stay zero.
-    for (int e = tid; e < 2 * APL; e += 256) act_l[e] = 0;
-    for (int e = tid; e < 2 * DPL; e += 256) dz_l[e] = 0;
-    __syncthreads();
 
     f32x4 acc[27];
 #pragma unroll
@@ -755,143 +756,132 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // t / (16 NCGZ) (rows past ny contribute zero). Plane p goes to buffer p & 1.
         const size_t plane_a = (size_t)g.ny * g.nx * CIN, plane_d = (size_t)g.ny * g.nx * COUTS;
         const u16 *act_s = a.act + sbase * CIN, *dz_s = a.dz + sbase * COUTS;
-        size_t goff_a[RA];
+        uint32_t goff_a[RA]; // in 16-byte chunks
         int loff_a[RA];
 #pragma unroll
         for (int k = 0; k < RA; ++k) {
             const int v = min(tid + 256 * k, T_ACT - 1);
             const int cg = v % NCG, cell = (v / NCG) % 18, row = v / (18 * NCG);
             const int x = wrapc(x0 + cell - 1, g.nx), y = wrapc(y0 + row - 1, g.ny);
-            goff_a[k] = ((size_t)y * g.nx + x) * CIN + 8 * cg;
+            goff_a[k] = ((uint32_t)y * g.nx + x) * NCG + cg;
             loff_a[k] = row * AROW + wg_pos(cell, 8 * cg);
         }
-        // lanes with nothing to stage load a valid chunk of the plane and keep zero
-        bool dz_lane[RD], dz_in[RD];
-        size_t goff_d[RD];
+        // rows past ny load a valid chunk of the plane and store zero
+        bool dz_in[RD];
+        uint32_t goff_d[RD];
         int loff_d[RD];
 #pragma unroll
         for (int r = 0; r < RD; ++r) {
             const int t = tid + 256 * r;
             const int dcg = t % NCGZ, dcell = (t / NCGZ) % 16, drow = t / (16 * NCGZ);
-            dz_lane[r] = t < T_DZ;
-            dz_in[r] = dz_lane[r] && y0 + drow < g.ny;
-            goff_d[r] = dz_in[r] ? ((size_t)(y0 + drow) * g.nx + x0 + dcell) * COUTS + 8 * dcg : (size_t)x0 * COUTS;
+            dz_in[r] = y0 + drow < g.ny;
+            goff_d[r] = ((uint32_t)(dz_in[r] ? y0 + drow : 0) * g.nx + x0 + dcell) * NCGZ + dcg;
             loff_d[r] = drow * DROW + wg_pos(dcell, 8 * dcg);
         }
 
-        uint4 qa[RA], qd[RD];
-        auto load_act = [&](int p) {
-            const u16 *src = act_s + (size_t)wrapc(p, g.nz) * plane_a;
+        // Act plane q and dz plane q + 1 travel together; qa and qd hold the pair
+        // for one step between its loads and its stores. Every step issues the same
+        // loads and stores (plane indices clamped to the chunk; dz planes outside it are
+        // stored as zeros), and nothing touches the loaded values before the stores,
+        // so that the loads stay in flight.
+        u32x4 qa[RA], qd[RD];
+        auto load = [&](int q) __attribute__((always_inline)) {
+            const u32x4 *pa = reinterpret_cast<const u32x4 *>(act_s + (size_t)wrapc(min(q, ze), g.nz) * plane_a);
 #pragma unroll
-            for (int k = 0; k < RA; ++k) qa[k] = *reinterpret_cast<const uint4 *>(src + goff_a[k]);
+            for (int k = 0; k < RA; ++k) qa[k] = pa[goff_a[k]];
+            const u32x4 *pd = reinterpret_cast<const u32x4 *>(dz_s + (size_t)min(q + 1, ze - 1) * plane_d);
+#pragma unroll
+            for (int r = 0; r < RD; ++r) qd[r] = pd[goff_d[r]];
         };
-        auto store_act = [&](int p) {
-            u16 *pl = act_l + (p & 1) * APL;
+        auto store = [&](int q, int slot) __attribute__((always_inline)) {
 #pragma unroll
-            for (int k = 0; k < RA; ++k)
-                if (tid + 256 * k < T_ACT) *reinterpret_cast<uint4 *>(pl + loff_a[k]) = qa[k];
-        };
-        auto load_dz = [&](int z) {
+            for (int k = 0; k < RA; ++k) *reinterpret_cast<u32x4 *>(act_l + slot * APL + loff_a[k]) = qa[k];
 #pragma unroll
-            for (int r = 0; r < RD; ++r) {
-                const uint4 t = *reinterpret_cast<const uint4 *>(dz_s + (size_t)z * plane_d + goff_d[r]);
-                qd[r] = dz_in[r] ? t : uint4{0u, 0u, 0u, 0u};
+            for (int r = 0; r < RD; ++r) { // chunk r of this lane: channel group tid % NCGZ, as every r
+                const u32x4 w = dz_in[r] && q + 1 < ze ? qd[r] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int c = 0; c < 8; ++c) bs[c] += bf2f((u16)((c & 1) ? (w[c >> 1] >> 16) : (w[c >> 1] & 0xffffu)));
+                *reinterpret_cast<u32x4 *>(dz_l + slot * DPL + loff_d[r]) = w;
             }
         };
-        auto store_dz = [&](int z) {
+        // dz fragments (K chunk c) of plane p in f[(p - z0 + 1) mod 3]
+        bf16x8 f[3][NKC];
 #pragma unroll
-            for (int r = 0; r < RD; ++r)
-                if (dz_lane[r]) { // chunk r of this lane: channel group tid % NCGZ, as every r
-                    const uint32_t *w = reinterpret_cast<const uint32_t *>(&qd[r]);
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) bs[c] += bf2f((u16)((c & 1) ? (w[c >> 1] >> 16) : (w[c >> 1] & 0xffffu)));
-                    *reinterpret_cast<uint4 *>(dz_l + (z & 1) * DPL + loff_d[r]) = qd[r];
-                }
-        };
-        // dz fragments (K chunk c) of planes p - 1, p, p + 1
-        bf16x8 am[NKC], a0[NKC], ap[NKC];
-#pragma unroll
-        for (int c = 0; c < NKC; ++c) am[c] = a0[c] = ap[c] = bf16x8{};
+        for (int c = 0; c < NKC; ++c) f[0][c] = f[1][c] = f[2][c] = bf16x8{};
 
-        // B fragments of offset (dyo, dxo) from act plane p meet dz planes
-        // p + 1 (z offset -1), p (0) and p - 1 (+1); the fragments of planes
-        // outside [z0, ze) are zero (one code path: the two planes around a
-        // chunk cost 2 / WG_ZC more MFMAs, adding exact zeros).
-        auto mult = [&](int p) {
-            const u16 *pl = act_l + (p & 1) * APL;
-            auto read_b = [&](int e, bf16x8 *b) {
-                const int dyo = e / 3 - 1, dxo = e % 3 - 1;
+        // B fragment k = e NKC + c of a plane: offset pair e (y, x), K chunk c, from the
+        // act plane in `slot`, into a window of NB fragments.
+        constexpr int NB = 6, NK = 9 * NKC;
+        static_assert(NKC == 4 && NK % NB == 0, "the window's positions repeat every plane");
+        bf16x8 b[NB];
+        auto read_b = [&](int slot, int k) __attribute__((always_inline)) {
+            const int e = k / NKC, c = k % NKC, dyo = e / 3 - 1, dxo = e % 3 - 1;
+            b[k % NB] = frag_tr(act_l + slot * APL + (2 * c + (quad >> 1) + dyo + 1) * AROW, 8 * (quad & 1) + dxo + 1, 16 * nw, col);
+        };
+        // Step J of three (slots, fragment sets): act plane p, in slot J, meets dz planes
+        // p + 1 (z offset -1), p (0) and p - 1 (+1); the fragments of planes outside
+        // [z0, ze) are zero (one code path: the planes around a chunk cost MFMAs that
+        // add exact zeros). A B fragment is read five fragments, 15 MFMAs, ahead of its
+        // own, the next plane's first ones in this step; plane p + 1's dz fragments are
+        // read here and meet the first offset pair last. Half way every wavefront has
+        // left plane p - 1: the planes p + 2 take its slot.
+        auto step = [&](auto j, int p) __attribute__((always_inline)) {
+            constexpr int J = decltype(j)::value, J1 = (J + 1) % 3, J2 = (J + 2) % 3;
 #pragma unroll
-                for (int c = 0; c < NKC; ++c)
-                    b[c] = frag_tr(pl + (2 * c + (quad >> 1) + dyo + 1) * AROW, 8 * (quad & 1) + dxo + 1, 16 * nw, col);
-            };
-            // the reads of offset pair e + LA are issued before the MFMAs of
-            // pair e, and no earlier: LA + 1 pairs of B fragments are live
-            // (fewer where a wave takes more K chunks, for the registers)
-            constexpr int LA = NKC == 1 ? 3 : NKC == 2 ? 2 : 1;
-            bf16x8 b[LA + 1][NKC];
+            for (int c = 0; c < NKC; ++c) f[J1][c] = frag_tr(dz_l + J * DPL + (2 * c + (quad >> 1)) * DROW, 8 * (quad & 1), 16 * mw, col);
+            read_b(J, 5);
 #pragma unroll
-            for (int e = 0; e < LA; ++e) read_b(e, b[e]);
+            for (int c = 0; c < NKC; ++c) {
+                acc[9] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[J][c], b[c], acc[9], 0, 0, 0);
+                acc[18] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[J2][c], b[c], acc[18], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int e = 0; e < 9; ++e) {
-                if (e + LA < 9) read_b(e + LA, b[(e + LA) % (LA + 1)]);
+            for (int c = 0; c < NKC; ++c) acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[J1][c], b[c], acc[0], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int c = 0; c < NKC; ++c) {
-                    const bf16x8 bv = b[e % (LA + 1)][c];
-                    acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[c], bv, acc[e], 0, 0, 0);
-                    acc[9 + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[c], bv, acc[9 + e], 0, 0, 0);
-                    acc[18 + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[c], bv, acc[18 + e], 0, 0, 0);
+            for (int k = NKC; k < NK; ++k) {
+                const int e = k / NKC, c = k % NKC;
+#pragma unroll
+                for (int n = k == NKC ? 6 : k + 5; n <= k + 5; ++n)
+                    if (n < NK) read_b(J, n);
+                    else read_b(J1, n - NK);
+                acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[J1][c], b[k % NB], acc[e], 0, 0, 0);
+                acc[9 + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[J][c], b[k % NB], acc[9 + e], 0, 0, 0);
+                acc[18 + e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[J2][c], b[k % NB], acc[18 + e], 0, 0, 0);
+                if (k == NK / 2) {
+                    wg_lds_barrier();
+                    store(p + 2, J2);
+                    load(p + 3);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
 
-        // When plane p is multiplied the registers hold act plane p + 1 and
-        // dz plane p + 2, loaded during plane p - 1. Every plane issues the
-        // same loads (plane indices clamped to the chunk) and the barrier
-        // waits for LDS operations only, so the loads stay in flight across
-        // it until their stores.
-        load_act(z0 - 1);
-        load_dz(z0);
-        store_act(z0 - 1);
-        store_dz(z0);
-        load_act(z0);
-        load_dz(min(z0 + 1, ze - 1));
+        load(z0 - 1);
+        store(z0 - 1, 0);
+        load(z0);
+        store(z0, 1);
+        load(z0 + 1);
         __syncthreads();
-        for (int p = z0 - 1; p <= ze; ++p) {
-            if (p + 1 <= ze) store_act(p + 1);
-            if (p + 2 < ze) store_dz(p + 2);
-            if (p + 1 < ze) {
-                const u16 *dl = dz_l + ((p + 1) & 1) * DPL;
 #pragma unroll
-                for (int c = 0; c < NKC; ++c)
-                    ap[c] = frag_tr(dl + (2 * c + (quad >> 1)) * DROW, 8 * (quad & 1), 16 * mw, col);
-            } else {
-#pragma unroll
-                for (int c = 0; c < NKC; ++c) ap[c] = bf16x8{};
-            }
-            load_act(min(p + 2, ze));
-            load_dz(min(p + 3, ze - 1));
-            mult(p);
-            wg_lds_barrier();
-#pragma unroll
-            for (int c = 0; c < NKC; ++c) {
-                am[c] = a0[c];
-                a0[c] = ap[c];
-            }
+        for (int k = 0; k < 5; ++k) read_b(0, k);
+        for (int p = z0 - 1; p <= ze; p += 3) { // (a chunk's planes and two, rounded up to three)
+            step(IntC<0>{}, p);
+            step(IntC<1>{}, p + 1);
+            step(IntC<2>{}, p + 2);
         }
-        __syncthreads(); // the loads issued past the chunk's end have landed
+        __syncthreads(); // the slots are free
     }
 
     // Bias partials: dz staging lane t summed channels 8 (t % NCGZ) + c (of
     // every chunk it stages); fold the lanes of each channel in lane order.
-    if (tid < TDL)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) bsum_l[tid][c] = bs[c];
+    for (int c = 0; c < 8; ++c) bsum_l[tid][c] = bs[c];
     __syncthreads();
     if (tid < COUTS) {
         float t = 0.f;
-        for (int l = tid / 8; l < TDL; l += NCGZ) t += bsum_l[l][tid % 8];
+        for (int l = tid / 8; l < 256; l += NCGZ) t += bsum_l[l][tid % 8];
         a.bpart[(size_t)blockIdx.x * 32 + tid] = t;
     }
     // acc[d][j]: co = 16 mw + 4 quad + j, ci = 16 nw + col
