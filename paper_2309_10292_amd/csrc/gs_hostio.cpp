@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <atomic>
 #include <exception>
+#include <memory>
 #include <new>
 #include <thread>
 #include <vector>
@@ -28,6 +29,21 @@ float from_bf16(uint16_t b)
 {
     const uint32_t w = (uint32_t)b << 16;
     float f;
+    memcpy(&f, &w, 4);
+    return f;
+}
+
+// IEEE half: the mantissa and exponent bits in place in an FP32 word are the value
+// times 2^-112, subnormals included; the largest exponent (infinities, NaN) stays it.
+float from_f16(uint16_t b)
+{
+    uint32_t w = (uint32_t)(b & 0x7fffu) << 13;
+    float f;
+    memcpy(&f, &w, 4);
+    f *= 0x1p112f;
+    memcpy(&w, &f, 4);
+    w = (b & 0x7c00u) == 0x7c00u ? 0x7f800000u | (uint32_t)(b & 0x3ffu) << 13 : w;
+    w |= (uint32_t)(b & 0x8000u) << 16;
     memcpy(&f, &w, 4);
     return f;
 }
@@ -47,8 +63,8 @@ void widen(int32_t storage, int field, const void *src, double *__restrict__ dst
         const uint16_t *x = (const uint16_t *)src;
         for (size_t i = 0; i < n; ++i) dst[i] = 1.0 - (double)from_bf16(x[i]);
     } else {
-        const _Float16 *x = (const _Float16 *)src;
-        for (size_t i = 0; i < n; ++i) dst[i] = (double)(float)x[i];
+        const uint16_t *x = (const uint16_t *)src;
+        for (size_t i = 0; i < n; ++i) dst[i] = from_f16(x[i]);
     }
 }
 
@@ -81,15 +97,12 @@ constexpr size_t k_min = 448 << 10;          // values of a field from which the
 // One field in a plain copy.
 gs_status read_plain(const void *dev, int32_t storage, size_t n, double *host, hipStream_t st, int field)
 {
-    std::vector<unsigned char> tmp;
+    std::unique_ptr<unsigned char[]> tmp; // (not cleared)
     void *to = host;
     if (storage != GS_F64) {
-        try {
-            tmp.resize(n * storage_bytes(storage));
-        } catch (const std::bad_alloc &) {
-            return fail(GS_ERR_INVALID_ARG, "out of host memory");
-        }
-        to = tmp.data();
+        tmp.reset(new (std::nothrow) unsigned char[n * storage_bytes(storage)]);
+        if (!tmp) return fail(GS_ERR_INVALID_ARG, "out of host memory");
+        to = tmp.get();
     }
     hipError_t e = hipMemcpyAsync(to, dev, n * storage_bytes(storage), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);

@@ -580,3 +580,20 @@ def test_large_reads(torch, shape, storage):
         b.write(1, *want)
         u, v = b.read(1)
         assert np.array_equal(u, want[0]) and np.array_equal(v, want[1])
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16"])
+def test_reads_of_every_16_bit_value(torch, storage):
+    """All 65536 patterns (subnormals, infinities, NaN): read() widens them exactly."""
+    from paper_2309_10292_amd import gs
+    bits = torch.arange(65536, device="cuda").to(torch.int16).view(32, 32, 64)
+    with gs.Sim(64, 32, 32, storage=storage, init="none", F=0.03, k=0.06) as s:
+        du, dv, _ = s.current()
+        du.view(torch.int16).copy_(bits)
+        dv.view(torch.int16).copy_(bits.flip(0))
+        u, v = s.read()
+        wu, wv = du.cpu().double().numpy(), dv.cpu().double().numpy()
+    for got, want in ((u, wu), (v, wv)):
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        ok = ~np.isnan(want)
+        assert np.array_equal(got[ok].view(np.int64), want[ok].view(np.int64))
