@@ -54,16 +54,20 @@ bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 // Tile indices: 1..num_tiles() select the single-step z-streaming kernel's
 // shapes; the next num_tb_shapes() indices select the temporally blocked
-// kernel's shapes (any tblock), and the last num_blk_shapes() the block
-// kernel's (any tblock; z-chunks do not apply to them).
+// kernel's shapes (any tblock), the next num_blk_shapes() the block
+// kernel's (any tblock; z-chunks do not apply to them), and the last
+// num_tb_narrow() the temporally blocked kernel's narrow shapes.
 int first_blk() { return gs::num_tiles() + gs::num_tb_shapes(); } // block shape s is tile first_blk() + s
-int total_tiles() { return first_blk() + gs::num_blk_shapes(); }
-bool is_blk_tile(int tile) { return tile > first_blk(); }
+int last_blk() { return first_blk() + gs::num_blk_shapes(); }
+int total_tiles() { return last_blk() + gs::num_tb_narrow(); }
+bool is_blk_tile(int tile) { return tile > first_blk() && tile <= last_blk(); }
 bool is_tb_tile(int tile) { return tile > gs::num_tiles() && !is_blk_tile(tile); }
+int tb_shape_of(int tile) { return tile <= first_blk() ? tile - gs::num_tiles() : tile - last_blk() + gs::num_tb_shapes(); }
+int tb_tile_of(int shape) { return shape <= gs::num_tb_shapes() ? gs::num_tiles() + shape : last_blk() + shape - gs::num_tb_shapes(); }
 int tile_max_tblock(int tile, int storage)
 {
     if (is_blk_tile(tile)) return GS_MAX_TBLOCK;
-    return is_tb_tile(tile) ? gs::tb_max_T(tile - gs::num_tiles(), storage) : 1;
+    return is_tb_tile(tile) ? gs::tb_max_T(tb_shape_of(tile), storage) : 1;
 }
 
 gs_status validate(const gs_params *p)
@@ -312,9 +316,9 @@ int default_zc(const gs_params &p, int tile, int tblock)
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 0;
     const bool tb = is_tb_tile(tile);
-    const int occ = tb ? gs::tb_occupancy(p.storage, tblock, tile - gs::num_tiles(), p.noise != 0.0)
+    const int occ = tb ? gs::tb_occupancy(p.storage, tblock, tb_shape_of(tile), p.noise != 0.0)
                        : gs::step_occupancy(p.storage, tile, p.noise != 0.0);
-    const gs::TileShape t = tb ? gs::tb_shape(tile - gs::num_tiles(), tblock) : gs::tile_shape(tile, p.storage);
+    const gs::TileShape t = tb ? gs::tb_shape(tb_shape_of(tile), tblock) : gs::tile_shape(tile, p.storage);
     if (cus > 0 && occ > 0 && t.tx > 0 && t.ty > 0) {
         const double slots = (double)cus * occ;
         const double tiles = (double)((p.nx + t.tx - 1) / t.tx) * (double)((p.ny + t.ty - 1) / t.ty);
@@ -353,6 +357,12 @@ int default_zc(const gs_params &p, int tile, int tblock)
 // 15 % faster than fixed shapes with power-of-two chunks: FP64 192^3 39.8 ->
 // 27.7 us per step, 320^3 143 -> 103, 128^3 14.6 -> 12.5, FP32 256^3 39.1 -> 34.6,
 // BF16 320 x 100 x 200 15.6 -> 11.9.
+// The narrow shapes cost what shape 2 does, and up to a fifth more where the tiles are
+// as many (448 x 159 x 300 BF16 28.6 against 33.8, 184 x 250 x 100 FP64 19.2 against
+// 22.4): they have to look 10% faster. Over 42 grids, six cases each, 60 launches
+// change and take 0.85 of their time: 24 x 640 x 640 FP64 75.3 -> 40.7 and BF16 32.4 ->
+// 18.9, 72 x 300 x 300 FP32 22.4 -> 18.7, 272^3 FP64 84.0 -> 75.4; at worst 184 x
+// 250 x 100 FP64 with noise 21.8 -> 23.2.
 struct StreamCost {
     int shape, T, occ;
     double fixed[2], each[2]; // without and with noise
@@ -364,18 +374,26 @@ StreamChoice default_stream(const gs_params &p)
 {
     static const StreamCost f64[] = {{1, 2, 2, {0.70, 0.84}, {0.55, 0.57}},
                                      {2, 2, 1, {0.96, 1.10}, {0.96, 1.10}},
-                                     {2, 3, 1, {1.22, 1.51}, {1.23, 1.51}}};
+                                     {2, 3, 1, {1.22, 1.51}, {1.23, 1.51}},
+                                     {6, 2, 1, {0.96, 1.10}, {0.96, 1.10}},
+                                     {6, 3, 1, {1.22, 1.51}, {1.23, 1.51}},
+                                     {7, 2, 1, {0.96, 1.10}, {0.96, 1.10}},
+                                     {7, 3, 1, {1.22, 1.51}, {1.23, 1.51}}};
     static const StreamCost f32[] = {{1, 2, 4, {0.75, 0.90}, {0.29, 0.33}},
                                      {2, 2, 2, {0.89, 1.11}, {0.59, 0.65}},
-                                     {5, 2, 1, {1.16, 1.40}, {1.16, 1.40}}};
+                                     {5, 2, 1, {1.16, 1.40}, {1.16, 1.40}},
+                                     {6, 2, 2, {0.89, 1.11}, {0.59, 0.65}},
+                                     {7, 2, 2, {0.89, 1.11}, {0.59, 0.65}}};
     static const StreamCost b16[] = {{1, 2, 4, {0.68, 0.84}, {0.17, 0.19}},
                                      {2, 2, 2, {0.73, 0.99}, {0.38, 0.39}},
-                                     {5, 2, 1, {0.84, 1.05}, {0.84, 1.05}}};
+                                     {5, 2, 1, {0.84, 1.05}, {0.84, 1.05}},
+                                     {6, 2, 2, {0.73, 0.99}, {0.38, 0.39}},
+                                     {7, 2, 2, {0.73, 0.99}, {0.38, 0.39}}};
     const StreamCost *table = p.storage == GS_F64 ? f64 : p.storage == GS_F32 ? f32 : b16;
     const int noise = p.noise != 0.0;
     StreamChoice best = {1, 2, 4};
     double best_us = 1e300;
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < (p.storage == GS_F64 ? 7 : 5); ++i) {
         const StreamCost &c = table[i];
         const gs::TileShape t = gs::tb_shape(c.shape, c.T);
         const int64_t tiles = (int64_t)((p.nx + t.tx - 1) / t.tx) * ((p.ny + t.ty - 1) / t.ty);
@@ -383,7 +401,8 @@ StreamChoice default_stream(const gs_params &p)
             const int64_t nb = tiles * ((p.nz + z - 1) / z), full = nb / (256 * c.occ), rest = nb % (256 * c.occ);
             double plane = full * (c.fixed[noise] + c.occ * c.each[noise]);
             if (rest) plane += c.fixed[noise] + (double)((rest + 255) / 256) * c.each[noise];
-            const double us = (2.5 + (z + 2 * c.T - 1) * plane) / c.T; // 2.5: a launch
+            double us = (2.5 + (z + 2 * c.T - 1) * plane) / c.T; // 2.5: a launch
+            if (c.shape > gs::num_tb_shapes()) us *= 1.1;
             if (us <= best_us) {
                 best_us = us;
                 best = StreamChoice{c.shape, c.T, z};
@@ -444,7 +463,7 @@ hipError_t enqueue_steps(gs_sim *s, int64_t n, hipStream_t st, const uint64_t *t
                                  s->buf[q ^ 1][0], s->buf[q ^ 1][1], a, st);
         } else if (is_tb_tile(s->tile)) {
             done = gs::next_depth(left, s->tblock);
-            e = gs::launch_tblock(s->p.storage, done, s->tile - gs::num_tiles(), s->buf[q][0], s->buf[q][1],
+            e = gs::launch_tblock(s->p.storage, done, tb_shape_of(s->tile), s->buf[q][0], s->buf[q][1],
                                   s->buf[q ^ 1][0], s->buf[q ^ 1][1], a, st);
         } else {
             e = gs::launch_step(s->p.storage, s->tile, s->buf[q][0], s->buf[q][1], s->buf[q ^ 1][0],
@@ -493,7 +512,7 @@ gs_status gs_tile_info(int32_t tile, int32_t storage, int32_t tblock, int32_t *t
         const gs::BlkShape b = gs::blk_shape(tile - first_blk());
         t = gs::TileShape{b.bx, b.by};
     } else {
-        t = is_tb_tile(tile) ? gs::tb_shape(tile - gs::num_tiles(), tblock) : gs::tile_shape(tile, storage);
+        t = is_tb_tile(tile) ? gs::tb_shape(tb_shape_of(tile), tblock) : gs::tile_shape(tile, storage);
     }
     if (tx) *tx = t.tx;
     if (ty) *ty = t.ty;
@@ -537,7 +556,7 @@ gs_status gs_init(const gs_params *p, void *u0, void *v0, void *u1, void *v1, vo
     if (p->tile == 0 && p->tblock == 0 && p->zchunk == 0) {
         if (!large_grid(*p) && !default_block(*p).shape) {
             const StreamChoice c = default_stream(*p);
-            s->tile = gs::num_tiles() + c.shape;
+            s->tile = tb_tile_of(c.shape);
             s->tblock = c.T;
             s->zc = c.zc;
         }

@@ -71,13 +71,15 @@ template <typename S, int TXG, int TY, int T, int NT> struct TbGeom {
     static constexpr bool SPLIT = sizeof(C) == 8;
     static constexpr int HS = 2 * (GX + 2);     // half-row length
     static constexpr int RS_MIN = SPLIT ? 2 * HS : RW + 2 * H;
-    // A wave holds several rows of 16 lanes; their 16-byte reads are free of
-    // bank conflicts on gfx950 only when the rows start a multiple of 256
-    // bytes apart (measured with the LDS counters; 640- and 320-byte strides
-    // conflict two ways). Rows are padded to that where the padded planes fit
-    // the LDS of a CU.
-    static constexpr int RS_PAD = (int)((RS_MIN * sizeof(C) + 255) / 256 * 256 / sizeof(C));
-    static constexpr int RS = 2 * LDS_ROWS * RS_PAD * sizeof(C) <= 160 * 1024 ? RS_PAD : RS_MIN; // row stride
+    // A wave holds several rows of TXG lanes; their 16-byte reads are free of bank
+    // conflicts on gfx950 only when each row goes on where the one before ends,
+    // modulo 256 bytes (measured with the LDS counters for 16 lanes: 640- and
+    // 320-byte strides conflict two ways). Rows are padded to that where the padded
+    // planes (and the FP64 kernel's prefetch area) fit the LDS of a CU.
+    static constexpr int RS_MIN_B = RS_MIN * (int)sizeof(C);
+    static constexpr int RS_PAD_B = RS_MIN_B + (TXG * 16 - RS_MIN_B % 256 + 512) % 256;
+    static constexpr int DMA_B = SPLIT && T == 3 && NT == 512 ? 4 * NT * 16 : 0;
+    static constexpr int RS = (2 * LDS_ROWS * RS_PAD_B + DMA_B <= 160 * 1024 ? RS_PAD_B : RS_MIN_B) / (int)sizeof(C); // row stride
     // Offset within a row of column 4 gx + e of the region (e = -1 .. 4):
     // a per-lane base plus a constant, so every access of a lane shares one
     // address register.
@@ -498,6 +500,8 @@ static hipError_t launch_tb_t(const void *u, const void *v, void *un, void *vn, 
 //   shape 3: TXG=32,  512 lanes, region 34 x 14
 //   shape 4: TXG=16,  768 lanes, region 18 x 42
 //   shape 5: TXG=16, 1024 lanes, region 18 x 56
+//   shape 6: TXG=8,   512 lanes, region 10 x 51 \\ one to three steps, single grids: for
+//   shape 7: TXG=12,  512 lanes, region 14 x 36 / rows that 64 cells cover badly
 // One workgroup per CU: NT lanes leave 512 / ceil(NT / 256) registers per
 // lane. The deepest fusion whose registers fit that budget without spills
 // (batched sweeps take the larger shapes one step less deep):
@@ -507,12 +511,13 @@ template <typename S, int NT, bool BATCH> constexpr int tb_max_T_of()
     if (NT <= 768) return sizeof(S) == 8 ? (BATCH ? 1 : 2) : (BATCH ? 3 : 4);
     return sizeof(S) == 8 ? (BATCH ? 0 : 1) : (BATCH ? 2 : 3);
 }
-constexpr int shape_lanes(int shape) { return shape == 1 ? 256 : shape <= 3 ? 512 : shape == 4 ? 768 : 1024; }
+constexpr int shape_lanes(int shape) { return shape == 1 ? 256 : shape == 4 ? 768 : shape == 5 ? 1024 : 512; }
 template <typename S, bool BATCH> constexpr int tb_max_T_shape(int shape)
 {
     return shape <= 3   ? tb_max_T_of<S, 512, BATCH>()
            : shape == 4 ? tb_max_T_of<S, 768, BATCH>()
-                        : tb_max_T_of<S, 1024, BATCH>();
+           : shape == 5 ? tb_max_T_of<S, 1024, BATCH>()
+                        : (BATCH ? 0 : 3);
 }
 
 template <typename S, int T>
@@ -530,6 +535,12 @@ static hipError_t dispatch_tb_shape(int shape, const void *u, const void *v, voi
     case 5:
         if constexpr (T <= tb_max_T_of<S, 1024, false>())
             return launch_tb_t<S, 16, 56 - 2 * T, T, 1024>(u, v, un, vn, a, st);
+        break;
+    case 6:
+        if constexpr (T <= 3) return launch_tb_t<S, 8, 51 - 2 * T, T, 512>(u, v, un, vn, a, st);
+        break;
+    case 7:
+        if constexpr (T <= 3) return launch_tb_t<S, 12, 36 - 2 * T, T, 512>(u, v, un, vn, a, st);
         break;
     }
     return hipErrorInvalidValue;
@@ -654,6 +665,12 @@ static int occ_single_shape(int shape, bool noise)
     case 5:
         if constexpr (T <= tb_max_T_of<S, 1024, false>()) return occ_single_t<S, 16, 56 - 2 * T, T, 1024>(noise);
         break;
+    case 6:
+        if constexpr (T <= 3) return occ_single_t<S, 8, 51 - 2 * T, T, 512>(noise);
+        break;
+    case 7:
+        if constexpr (T <= 3) return occ_single_t<S, 12, 36 - 2 * T, T, 512>(noise);
+        break;
     }
     return 0;
 }
@@ -697,6 +714,7 @@ GS_TB_TYPE(extern, f16, GS_TB_BATCH)
 GS_TB_TYPE(extern, bf16c, GS_TB_SINGLE)
 
 int num_tb_shapes() { return 5; }
+int num_tb_narrow() { return 2; }
 
 TileShape tb_shape(int shape, int T)
 {
@@ -706,13 +724,15 @@ TileShape tb_shape(int shape, int T)
     case 3: return TileShape{128, 14 - 2 * T};
     case 4: return TileShape{64, 42 - 2 * T};
     case 5: return TileShape{64, 56 - 2 * T};
+    case 6: return TileShape{32, 51 - 2 * T};
+    case 7: return TileShape{48, 36 - 2 * T};
     }
     return TileShape{0, 0};
 }
 
 template <bool BATCH> static int max_T_for(int shape, int storage)
 {
-    if (shape < 1 || shape > 5) return 0;
+    if (shape < 1 || shape > num_tb_shapes() + (BATCH ? 0 : num_tb_narrow())) return 0;
     switch (storage) {
     case 0: return tb_max_T_shape<double, BATCH>(shape);
     case 1: return tb_max_T_shape<float, BATCH>(shape);

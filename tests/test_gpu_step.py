@@ -522,7 +522,8 @@ def test_tune_cache_roundtrip(torch, tmp_path, monkeypatch):
 BLOCK_RULE = [((4, 4, 8), 10, 4), ((32, 32, 32), 10, 4), ((40, 40, 32), 10, 4), ((41, 40, 32), 10, 3),
               ((32, 64, 32), 10, 3), ((33, 64, 32), 11, 3), ((64, 32, 64), 11, 3), ((65, 32, 64), 12, 3),
               ((64, 64, 64), 12, 3), ((72, 72, 72), 11, 2), ((61, 57, 72), 5, 2), ((70, 200, 16), 12, 3),
-              ((150, 200, 16), 11, 2), ((96, 96, 96), 6, 2), ((192, 96, 64), 6, 2), ((513, 513, 16), 12, 1)]
+              ((150, 200, 16), 11, 2), ((96, 96, 96), 6, 2), ((192, 96, 64), 6, 2), ((513, 513, 16), 12, 1),
+              ((100, 320, 24), 13, 2), ((61, 201, 96), 14, 2)]
 
 
 @pytest.mark.parametrize("shape, tile, T", BLOCK_RULE, ids=lambda x: str(x).replace(" ", ""))
