@@ -45,7 +45,7 @@ typedef enum gs_status {
 
 /* Storage type of the fields in device memory. GS_F64 computes in FP64 and
  * reproduces the FP64 definition of the step bit for bit; the other types
- * compute in FP32 (Laplacian neighbour sum compensated) and round each stored
+ * compute in FP32 (FP32 storage sums the Laplacian in FP64) and round each stored
  * value to nearest-even. GS_BF16C is BF16 storage that keeps 1 - u in place
  * of u (v as it is): where u is near 1, most of a Gray-Scott state, 1 - u is
  * small and BF16 keeps eight significant bits of it, where plain BF16 steps

@@ -7,8 +7,8 @@
 // implicit GEMM (8 consecutive channels of one neighbour cell) is one 16-byte
 // load. Convolutions are implicit GEMMs with M = cells (tiles of 16 cells of
 // one x-row), N = output channels (tiles of 16) and K = 27 offsets x input
-// channels, walked in chunks of 32 with v_mfma_f32_16x16x32_bf16; the packed
-// weights of a layer sit in LDS. The data gradient is the same convolution
+// channels, walked in chunks of 32 with v_mfma_f32_16x16x32_bf16 (the output
+// layer has its own form); the packed weights of a layer sit in registers or LDS. The data gradient is the same convolution
 // with the weights transposed and the offsets mirrored; the weight gradient
 // is a GEMM with K = cells, reduced per workgroup into FP32 partials.
 #include "gs_device.hpp"

@@ -6,7 +6,7 @@ JSON record (and writing it to --out):
              oracle are measured by the GPU tests).
   batched    256 independent simulations (F ~ U[0.01, 0.06], k ~ U[0.04,
              0.07], L ~ U{32, 48, ..., 192}), cube start, 500 steps, FP64:
-             one persistent batched sweep (default and autotuned, graph
+             one batched sweep (default and autotuned, graph
              replay) against the same simulations run one after another.
   small      the L=64 parity workload (FP64, 100 steps): eager launches
              against one captured HIP graph replayed. Its 8 MB of state stay

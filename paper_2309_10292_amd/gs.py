@@ -320,7 +320,7 @@ class Sim:
 
 
 class Batch:
-    """Many independent simulations advanced by persistent launches.
+    """Many independent simulations advanced by shared launches.
 
     `sims` is a list of dicts {nx, ny, nz, F, k} (or {L, F, k} for cubes);
     the remaining keyword arguments are the shared gs_params (storage, Du, Dv,

@@ -115,7 +115,7 @@ class Surrogate:
 
 
 def generate_pairs(L, blobs, steps_total, pair_every, warm=0, storage="f32", device="cuda"):
-    """Training pairs from stencil trajectories (batched persistent sweeps).
+    """Training pairs from stencil trajectories (batched sweeps).
 
     `blobs` (synth.random_blobs) gives one trajectory each: a random cube of
     (0.25, 0.33) in a (1, 0) background and its own (F, k). After `warm`
