@@ -242,8 +242,9 @@ gs_status gs_step_graph(gs_sim *s, int64_t n_steps);
  * Du, Dv, dt, noise, storage) advanced together by shared launches of the
  * temporally blocked kernel. Simulation i draws its noise with key seed + i.
  * Every simulation has a launch configuration (tile among the temporally
- * blocked tiles, tblock, zchunk >= 8); simulations sharing (tile, tblock) are
- * advanced by one launch per tblock steps. */
+ * blocked tiles 5..9, tblock, zchunk >= 8); simulations sharing (tile, tblock) are
+ * advanced by one launch per tblock steps. Up to three steps, tile 6 covers a grid
+ * with tiles of 32 or 48 cells where it takes fewer of them. */
 
 typedef struct gs_batch gs_batch; /* opaque handle */
 

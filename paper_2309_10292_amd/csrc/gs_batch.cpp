@@ -41,6 +41,7 @@ struct BGroup {
     int shape, T;
     int parity;
     int off[GS_MAX_TBLOCK + 1], cnt[GS_MAX_TBLOCK + 1], slots[GS_MAX_TBLOCK + 1];
+    bool narrow[GS_MAX_TBLOCK + 1]; // some items of that depth have narrow tiles
 };
 
 struct BGraph {
@@ -129,6 +130,28 @@ int batch_slots(const gs_batch *b, int T, int shape)
     return (b->cus * gs::tb_batch_occupancy(b->base.storage, T, shape) + 7) / 8 * 8;
 }
 
+// Tiles of a grid's plane in `shape`'s launches at depth T: the 64-cell shape of 512
+// lanes covers a grid with its narrow forms where they are 10% fewer (they cost up
+// to that more each).
+struct Cover {
+    int width, ntx, nty;
+};
+Cover cover(int shape, int T, int nx, int ny)
+{
+    const gs::TileShape t = gs::tb_shape(shape, T);
+    Cover best = {0, tiles_along(nx, t.tx), tiles_along(ny, t.ty)};
+    double cost = (double)best.ntx * best.nty;
+    for (int w = 1; shape == 2 && T <= 3 && w <= gs::num_tb_narrow(); ++w) {
+        const gs::TileShape n = gs::tb_shape(gs::num_tb_shapes() + w, T);
+        const Cover c = {w, tiles_along(nx, n.tx), tiles_along(ny, n.ty)};
+        if (1.1 * c.ntx * c.nty <= cost) {
+            best = c;
+            cost = 1.1 * c.ntx * c.nty;
+        }
+    }
+    return best;
+}
+
 // Library choice of the steps per launch and the z-chunk, before any tuning.
 // Two steps, except FP64 with work for at least two rounds of workgroups,
 // where T = 2 is bound by HBM and three steps are faster (32 grids of 128^3:
@@ -148,8 +171,8 @@ BatchChoice default_batch(const gs_batch *b, int shape, int32_t n_sims, const in
                           const int32_t *nz)
 {
     auto columns = [&](int i, int T) {
-        const gs::TileShape ts = gs::tb_shape(shape, T);
-        return (double)tiles_along(nx[i], ts.tx) * tiles_along(ny[i], ts.ty);
+        const Cover c = cover(shape, T, nx[i], ny[i]);
+        return (double)c.ntx * c.nty;
     };
     const bool f64 = b->base.storage == GS_F64;
     double items = 0;
@@ -220,24 +243,24 @@ gs_status rebuild(gs_batch *b)
             g.shape = shape;
             g.T = T;
             g.parity = 0;
-            for (int d = 0; d <= GS_MAX_TBLOCK; ++d) g.off[d] = g.cnt[d] = g.slots[d] = 0;
+            for (int d = 0; d <= GS_MAX_TBLOCK; ++d) g.off[d] = g.cnt[d] = g.slots[d] = 0, g.narrow[d] = false;
             for (int d = 1; d <= T; ++d) {
                 struct Tmp {
                     gs::WorkItem w;
                     int len;
                 };
                 std::vector<Tmp> items;
-                const gs::TileShape ts = gs::tb_shape(shape, d);
                 for (size_t i = 0; i < b->sims.size(); ++i) {
                     const BSim &s = b->sims[i];
                     if (s.shape != shape || s.T != T) continue;
-                    const int ntx = tiles_along(s.nx, ts.tx), nty = tiles_along(s.ny, ts.ty);
+                    const Cover c = cover(shape, d, s.nx, s.ny);
+                    g.narrow[d] = g.narrow[d] || c.width != 0;
                     const int nzc = tiles_along(s.nz, s.zc);
                     for (int bz = 0; bz < nzc; ++bz) {
                         const int len = std::min(s.zc, s.nz - bz * s.zc) + 2 * d - 2;
-                        for (int by = 0; by < nty; ++by)
-                            for (int bx = 0; bx < ntx; ++bx)
-                                items.push_back(Tmp{gs::WorkItem{(int)i, bx, by, bz}, len});
+                        for (int by = 0; by < c.nty; ++by)
+                            for (int bx = 0; bx < c.ntx; ++bx)
+                                items.push_back(Tmp{gs::WorkItem{(int)i, bx, by, bz | c.width << gs::ITEM_BZ_BITS}, len});
                     }
                 }
                 // Longest chunks first; ties keep simulation-major order, so a
@@ -292,6 +315,7 @@ hipError_t enqueue_batch(gs_batch *b, int64_t n, hipStream_t st, const uint64_t 
             a.t = t_dev ? off : b->step + off;
             a.t_dev = t_dev;
             a.noise_32 = b->noise_32;
+            a.narrow = g.narrow[d];
             hipError_t e = gs::launch_tblock_batch(b->base.storage, d, g.shape, a, st);
             if (e != hipSuccess) return e;
             par[gi] ^= 1;
@@ -623,13 +647,14 @@ gs_status gs_batch_tune(gs_batch *b, int32_t reps, gs_batch_tune_entry *table, i
                     if (zc == last) continue;
                     last = zc;
                     items.clear();
-                    const gs::TileShape ts = gs::tb_shape(shape, T);
+                    const Cover c = cover(shape, T, k.nx, k.ny);
                     for (int i : members) {
                         desc[i].zc = zc;
-                        const int ntx = tiles_along(k.nx, ts.tx), nty = tiles_along(k.ny, ts.ty), nzc = tiles_along(k.nz, zc);
+                        const int nzc = tiles_along(k.nz, zc);
                         for (int z = 0; z < nzc; ++z)
-                            for (int y = 0; y < nty; ++y)
-                                for (int x = 0; x < ntx; ++x) items.push_back(gs::WorkItem{i, x, y, z});
+                            for (int y = 0; y < c.nty; ++y)
+                                for (int x = 0; x < c.ntx; ++x)
+                                    items.push_back(gs::WorkItem{i, x, y, z | c.width << gs::ITEM_BZ_BITS});
                     }
                     e = hipMemcpyAsync(b->d_desc, desc.data(), desc.size() * sizeof(gs::SimDesc),
                                        hipMemcpyHostToDevice, b->stream);
@@ -646,6 +671,7 @@ gs_status gs_batch_tune(gs_batch *b, int32_t reps, gs_batch_tune_entry *table, i
                     a.t = b->step;
                     a.t_dev = nullptr;
                     a.noise_32 = b->noise_32;
+                    a.narrow = c.width != 0;
                     a.slots = batch_slots(b, T, shape);
                     if (e == hipSuccess) e = gs::launch_tblock_batch(b->base.storage, T, shape, a, b->stream);
                     if (e == hipSuccess) e = hipEventRecord(e0, b->stream);

@@ -115,9 +115,14 @@ struct SimDesc {
     uint64_t seed;
 };
 
+// Tile (bx, by) of chunk bz; the top bits of bz hold the tile's width: 0 the shape's
+// own, w the narrow shape num_tb_shapes() + w.
 struct WorkItem {
     int sim, bx, by, bz;
 };
+constexpr int ITEM_BZ_BITS = 28;
+__host__ __device__ inline int item_bz(const WorkItem &w) { return w.bz & ((1 << ITEM_BZ_BITS) - 1); }
+__host__ __device__ inline int item_width(const WorkItem &w) { return w.bz >> ITEM_BZ_BITS; }
 
 struct BatchArgs {
     StepArgs coef;       // shared coefficients (Du, Dv, dt, noise); per-sim fields overwritten
@@ -129,6 +134,7 @@ struct BatchArgs {
     uint64_t t;          // step index of the first fused step (offset when t_dev is set)
     const uint64_t *t_dev;
     bool noise_32;       // noise_fits_32() holds for every simulation of this launch
+    bool narrow;         // some items have a width of their own
 };
 
 hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b, hipStream_t st);

@@ -406,32 +406,27 @@ template <typename S, int T, int NT> constexpr int tb_min_waves()
     return (sizeof(typename Traits<S>::C) == 4 && T <= 2 && NT <= 512) ? 4 : 1;
 }
 
-// The output tile (bx, by) and chunk bz of the grid in `a` by this workgroup.
+// The output tile (bx, by) and chunk bz of the grid in `a` by this workgroup;
+// `lds` and `pre_lds` as tb_tile takes them.
 template <typename S, int TXG, int TY, int T, int NT, int NOISE>
 __device__ __forceinline__ void tb_item(const S *__restrict__ u, const S *__restrict__ v, S *__restrict__ un,
-                                        S *__restrict__ vn, const StepArgs &a, int bx, int by, int bz, uint64_t t0)
+                                        S *__restrict__ vn, const StepArgs &a, int bx, int by, int bz, uint64_t t0,
+                                        typename Traits<S>::C *lds, uint4 *pre_lds)
 {
-    typedef TbGeom<S, TXG, TY, T, NT> G;
-    __shared__ typename G::C lds[2 * G::FIELD];
     const int z0 = bz * a.zc, ze = min(z0 + a.zc, a.nz);
-    auto run = [&](uint4 *pre_lds) {
-        // FP64 runs with dt = 1 (the workload of the paper) take the variant
-        // without the dt products.
-        if constexpr (sizeof(S) == 8) {
-            if (a.dt == 1.0) {
-                tb_tile<S, TXG, TY, T, NT, NOISE, true>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds, pre_lds);
-                return;
-            }
+    // FP64 runs with dt = 1 (the workload of the paper) take the variant
+    // without the dt products.
+    if constexpr (sizeof(S) == 8) {
+        if (a.dt == 1.0) {
+            tb_tile<S, TXG, TY, T, NT, NOISE, true>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds, pre_lds);
+            return;
         }
-        tb_tile<S, TXG, TY, T, NT, NOISE, false>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds, pre_lds);
-    };
-    if constexpr (tb_dma<S, T, NT, NOISE>()) {
-        __shared__ uint4 pre_lds[4 * NT];
-        run(pre_lds);
-    } else {
-        run(nullptr);
     }
+    tb_tile<S, TXG, TY, T, NT, NOISE, false>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds, pre_lds);
 }
+
+// LDS-DMA prefetch area of a workgroup (tb_dma), in 16-byte slots.
+template <typename S, int T, int NT, int NOISE> constexpr int tb_pre_slots() { return tb_dma<S, T, NT, NOISE>() ? 4 * NT : 1; }
 
 template <typename S, int TXG, int TY, int T, int NT, int NOISE>
 __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb(const S *__restrict__ u,
@@ -439,20 +434,33 @@ __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb(con
                                                                            S *__restrict__ un, S *__restrict__ vn,
                                                                            StepArgs a)
 {
+    __shared__ typename Traits<S>::C lds[2 * TbGeom<S, TXG, TY, T, NT>::FIELD];
+    __shared__ uint4 pre_lds[tb_pre_slots<S, T, NT, NOISE>()];
     const uint32_t lb = xcd_logical_block(blockIdx.x, gridDim.x);
     const uint32_t rest = lb / (uint32_t)a.ntx;
     tb_item<S, TXG, TY, T, NT, NOISE>(u, v, un, vn, a, (int)(lb % (uint32_t)a.ntx), (int)(rest % (uint32_t)a.nty),
-                                      (int)(rest / (uint32_t)a.nty), NOISE ? step_index(a) : 0);
+                                      (int)(rest / (uint32_t)a.nty), NOISE ? step_index(a) : 0, lds, pre_lds);
 }
 
 // Sweep over many independent simulations: one workgroup per work item (one
 // tile x z-chunk of one simulation), items sorted by decreasing cost, so that
 // the places that fall free last are filled with the cheapest ones. Items are
 // dealt to the XCDs in ranges of `slots` (about what is resident at once):
-// neighbouring tiles on one XCD, and every XCD long and short items.
-template <typename S, int TXG, int TY, int T, int NT, int NOISE>
+// neighbouring tiles on one XCD, and every XCD long and short items. WIDTHS: an item
+// of the 64-cell shape of 512 lanes may be of the narrow shapes' tiles instead (the
+// host picks a grid's width), so that one launch covers grids of 80 cells with six
+// tiles and grids of 128 with twelve: 32 grids of 32^3 to 192^3 in FP64, 12 steps,
+// 2.18 -> 2.03 ms. A launch without such items takes the kernel without them (32 x
+// 128^3 FP32 with it: 1.97 -> 2.00 ms).
+template <typename S, int TXG, int TY, int T, int NT, int NOISE, bool WIDTHS>
 __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb_batch(BatchArgs b)
 {
+    constexpr int TY6 = 51 - 2 * T, TY7 = 36 - 2 * T;
+    constexpr int F0 = TbGeom<S, TXG, TY, T, NT>::FIELD;
+    constexpr int F6 = WIDTHS ? TbGeom<S, 8, WIDTHS ? TY6 : 4, WIDTHS ? T : 1, 512>::FIELD : 0;
+    constexpr int F7 = WIDTHS ? TbGeom<S, 12, WIDTHS ? TY7 : 4, WIDTHS ? T : 1, 512>::FIELD : 0;
+    __shared__ typename Traits<S>::C lds[2 * (F0 > F6 ? (F0 > F7 ? F0 : F7) : (F6 > F7 ? F6 : F7))];
+    __shared__ uint4 pre_lds[tb_pre_slots<S, T, NT, NOISE>()];
     const uint32_t r0 = blockIdx.x / (uint32_t)b.slots * (uint32_t)b.slots;
     const uint32_t lb = r0 + xcd_logical_block(blockIdx.x - r0, min((uint32_t)b.slots, gridDim.x - r0));
     const WorkItem w = b.items[lb];
@@ -467,9 +475,15 @@ __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb_bat
     a.F_f = d.F_f;
     a.FK_f = d.FK_f;
     a.seed = d.seed;
-    tb_item<S, TXG, TY, T, NT, NOISE>((const S *)d.buf[b.parity][0], (const S *)d.buf[b.parity][1],
-                                      (S *)d.buf[b.parity ^ 1][0], (S *)d.buf[b.parity ^ 1][1], a, w.bx, w.by, w.bz,
-                                      NOISE ? (b.t_dev ? *b.t_dev + b.t : b.t) : 0);
+    const S *u = (const S *)d.buf[b.parity][0], *v = (const S *)d.buf[b.parity][1];
+    S *un = (S *)d.buf[b.parity ^ 1][0], *vn = (S *)d.buf[b.parity ^ 1][1];
+    const uint64_t t0 = NOISE ? (b.t_dev ? *b.t_dev + b.t : b.t) : 0;
+    if constexpr (WIDTHS) {
+        const int width = item_width(w);
+        if (width == 1) return tb_item<S, 8, TY6, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, item_bz(w), t0, lds, pre_lds);
+        if (width == 2) return tb_item<S, 12, TY7, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, item_bz(w), t0, lds, pre_lds);
+    }
+    tb_item<S, TXG, TY, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, WIDTHS ? item_bz(w) : w.bz, t0, lds, pre_lds);
 }
 
 // ------------------------------------------------------------------ launch
@@ -565,7 +579,13 @@ static hipError_t launch_tb_batch_t(const BatchArgs &b, hipStream_t st)
     const int grid = b.n_items;
     if (grid < 1 || b.slots < 8) return hipErrorInvalidConfiguration;
     auto go = [&](auto mode) {
-        hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value>), dim3(grid), dim3(NT), 0, st, b);
+        if constexpr (TXG == 16 && NT == 512 && T <= 3) {
+            if (b.narrow) {
+                hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value, true>), dim3(grid), dim3(NT), 0, st, b);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value, false>), dim3(grid), dim3(NT), 0, st, b);
         return hipGetLastError();
     };
     if (b.coef.noise == 0.0) return go(Phase<NOISE_OFF>{});
@@ -608,7 +628,7 @@ template <typename S, int TXG, int TY, int T, int NT>
 static int occ_t()
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb_batch<S, TXG, TY, T, NT, NOISE_OFF>, NT, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb_batch<S, TXG, TY, T, NT, NOISE_OFF, false>, NT, 0) != hipSuccess)
         return 1;
     return n > 0 ? n : 1;
 }

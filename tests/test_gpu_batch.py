@@ -78,3 +78,23 @@ def test_batch_sweep_sample_bitwise(torch):
         d = b.diagnostics(3)
         e = O.diagnostics(*_oracle(sims[3], 3, 10))
         assert abs(d["sum_u"] - e["sum_u"]) <= 1e-13 * abs(e["sum_u"])
+
+
+# tile 6 takes 64-, 48- and 32-cell tiles in one launch: grids of all three widths, ragged rows, chunks that do not
+# divide them, and step counts split over launches of two depths
+@pytest.mark.parametrize("T", [1, 2, 3])
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16", "f16"])
+def test_batch_tile_widths(torch, storage, T):
+    """Every simulation equals the same one alone (single-grid results do not depend on the launch), bit for bit."""
+    from paper_2309_10292_amd import gs
+    sims = [dict(nx=80, ny=80, nz=20, F=0.03, k=0.06), dict(nx=48, ny=61, nz=18, F=0.035, k=0.06),
+            dict(nx=24, ny=100, nz=17, F=0.02, k=0.05), dict(nx=128, ny=50, nz=19, F=0.04, k=0.06),
+            dict(nx=72, ny=96, nz=9, F=0.012, k=0.045)]
+    shared = dict(noise=1e-3, storage=storage, cube_side=8, **SHARED)
+    with gs.Batch(sims, seed=50, tile=6, tblock=T, zchunk=8, **shared) as b:
+        b.step(7)
+        for i, sm in enumerate(sims):
+            with gs.Sim(sm["nx"], sm["ny"], sm["nz"], F=sm["F"], k=sm["k"], seed=50 + i, **shared) as s:
+                s.step(7)
+                for got, want in zip(b.read(i), s.read()):
+                    assert np.array_equal(got, want), (i, max_abs(got, want))
