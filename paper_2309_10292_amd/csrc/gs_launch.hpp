@@ -84,7 +84,7 @@ namespace gs {
 // Temporally blocked sweep: T steps (u, v) -> (un, vn) in one launch with
 // tile shape 1..num_tb_shapes().
 int num_tb_shapes();
-int num_tb_narrow(); // shapes num_tb_shapes() + 1 .., single grids only
+int num_tb_narrow(); // shapes num_tb_shapes() + 1 .., for batches as a width of shape 2's items
 TileShape tb_shape(int shape, int T);
 // Largest number of fused steps the temporally blocked shape runs for a
 // storage type (its registers fit the shape's lanes without spills), in the
