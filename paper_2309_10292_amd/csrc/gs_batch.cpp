@@ -152,8 +152,7 @@ Cover cover(int shape, int T, int nx, int ny)
     return best;
 }
 
-// Library choice of the steps per launch and the z-chunk, before any tuning.
-// Two steps, except FP64 with work for at least two rounds of workgroups,
+// Steps per launch and z-chunk of one tile. Two steps, except FP64 with work for at least two rounds of workgroups,
 // where T = 2 is bound by HBM and three steps are faster (32 grids of 128^3:
 // 196 against 265 us per step; on 24 grids of 16^3..72^3, less than one round,
 // 31 against 21). FP32 and 16-bit kernels of T = 2 keep two 512-lane
@@ -165,9 +164,9 @@ Cover cover(int shape, int T, int nx, int ny)
 // for 32 x 128^3 in FP64 (196 us; 208 with 32), 32 in FP32 (123; 126 with 64,
 // 128 with 16), 16 for the 24 small grids in FP64 (21; 24 with 8).
 struct BatchChoice {
-    int T, zc;
+    int shape, T, zc;
 };
-BatchChoice default_batch(const gs_batch *b, int shape, int32_t n_sims, const int32_t *nx, const int32_t *ny,
+BatchChoice shape_batch(const gs_batch *b, int shape, int32_t n_sims, const int32_t *nx, const int32_t *ny,
                           const int32_t *nz)
 {
     auto columns = [&](int i, int T) {
@@ -179,7 +178,7 @@ BatchChoice default_batch(const gs_batch *b, int shape, int32_t n_sims, const in
     for (int32_t i = 0; i < n_sims; ++i) items += columns(i, f64 ? 3 : 2) * tiles_along(nz[i], 32);
     const int T = f64 && items >= 2.0 * batch_slots(b, 3, shape) ? 3 : 2;
     const double slots = batch_slots(b, T, shape);
-    BatchChoice best = {T, k_min_batch_zc};
+    BatchChoice best = {shape, T, k_min_batch_zc};
     double best_cost = 1e300;
     for (int zc = k_min_batch_zc; zc <= 64; zc *= 2) {
         double n = 0, planes = 0, longest = 0;
@@ -196,6 +195,81 @@ BatchChoice default_batch(const gs_batch *b, int shape, int32_t n_sims, const in
         }
     }
     return best;
+}
+
+// Library choice of tile, steps per launch and z-chunk, before any tuning: the least
+// estimated time per step, for all simulations together so that they share their
+// launches. A launch's items stream (chunk + 2T - 1) planes each, the longest first;
+// n of them on 256 CUs of up to occ workgroups take the longest item if all are
+// resident at once, else their planes over the places and 0.3 of the longest item for
+// the last round, and a plane of a CU with k workgroups takes fixed + k each, in us.
+// The constants are least-squares fits over 48 batches of 4 to 32 grids of 16^3 to
+// 192^3 and ten chunks each (3 to 16 % standard deviation). Because of that deviation
+// shape_batch's launch of the 64-cell tile of 512 lanes stays unless another looks 6 %
+// faster: of the 48 batches 6 were slower without that (19 grids of 56^3..120^3 FP64
+// with noise 70 -> 75 us per step), none with it. The choice takes 1.7 % longer than the
+// best measured launch and 0.89 of shape_batch's time, us per step: 27 x 40^3 FP64 25.5
+// -> 15.0 (256 lanes, chunks of 10), 10 grids of 24^3..40^3 FP64 10.6 -> 7.3 (256 lanes,
+// three steps), 31 of 64^3..112^3 FP64 with noise 129 -> 102 (two steps for three), 12
+// of 72^3..88^3 FP32 27.8 -> 22.2. Three steps in 256 lanes with noise are left out in
+// 16 bits, where the estimate is worst (12 %): 4 grids of 32^3..80^3 FP16 took 9.4 with
+// them against 8.4, 8 of 24^3 and 32^3 only 6.3 against 6.5 with two.
+struct BatchCost {
+    int shape, T, occ;
+    double fixed[2], each[2]; // without and with noise
+};
+BatchChoice default_batch(const gs_batch *b, int32_t n_sims, const int32_t *nx, const int32_t *ny, const int32_t *nz)
+{
+    static const BatchCost f64[] = {{1, 2, 2, {0.45, 0.70}, {0.74, 0.67}},
+                                    {1, 3, 2, {0.08, 0.24}, {1.43, 1.64}},
+                                    {2, 2, 1, {1.59, 1.81}, {0.51, 0.50}},
+                                    {2, 3, 1, {2.22, 2.70}, {0.59, 0.65}}};
+    static const BatchCost f32[] = {{1, 2, 4, {0.61, 0.68}, {0.34, 0.46}},
+                                    {1, 3, 2, {1.07, 1.24}, {0.21, 0.36}},
+                                    {2, 2, 2, {0.62, 0.69}, {0.79, 1.04}},
+                                    {2, 3, 1, {1.50, 1.92}, {0.48, 0.52}}};
+    static const BatchCost b16[] = {{1, 2, 4, {0.56, 0.71}, {0.20, 0.25}},
+                                    {1, 3, 2, {0.94, 1.20}, {0.07, 0.05}},
+                                    {2, 2, 2, {0.53, 0.62}, {0.49, 0.65}},
+                                    {2, 3, 1, {1.00, 1.38}, {0.46, 0.50}}};
+    static const int chunks[] = {8, 10, 12, 16, 20, 24, 32, 40, 48, 64};
+    const BatchCost *table = b->base.storage == GS_F64 ? f64 : b->base.storage == GS_F32 ? f32 : b16;
+    const int noise = b->base.noise != 0.0;
+    BatchChoice best = shape_batch(b, 2, n_sims, nx, ny, nz);
+    if (b->base.zchunk) best.zc = b->base.zchunk;
+    const BatchChoice first = best;
+    double best_us = 1e300, first_us = 1e300;
+    for (int i = 0; i < 4; ++i) {
+        const BatchCost &c = table[i];
+        if (c.T > gs::tb_batch_max_T(c.shape, b->base.storage)) continue;
+        if (table == b16 && noise && c.shape == 1 && c.T == 3) continue;
+        std::vector<double> tiles((size_t)n_sims);
+        for (int32_t j = 0; j < n_sims; ++j) {
+            const Cover v = cover(c.shape, c.T, nx[j], ny[j]);
+            tiles[(size_t)j] = (double)v.ntx * v.nty;
+        }
+        for (int chunk : chunks) {
+            const int zc = b->base.zchunk ? b->base.zchunk : chunk;
+            double n = 0, planes = 0;
+            int longest = 0;
+            for (int32_t j = 0; j < n_sims; ++j) {
+                const double parts = tiles_along(nz[j], zc);
+                n += tiles[(size_t)j] * parts;
+                planes += tiles[(size_t)j] * (nz[j] + (2 * c.T - 1) * parts);
+                longest = std::max(longest, std::min(zc, nz[j]) + 2 * c.T - 1);
+            }
+            const double k = std::min((double)c.occ, std::ceil(n / 256));
+            const double span = n <= 256 * k ? longest : std::max((double)longest, planes / (256 * k) + 0.3 * longest);
+            const double us = (2.5 + span * (c.fixed[noise] + k * c.each[noise])) / c.T; // 2.5: a launch
+            if (c.shape == first.shape && c.T == first.T && zc == first.zc) first_us = us;
+            if (us < best_us) {
+                best_us = us;
+                best = BatchChoice{c.shape, c.T, zc};
+            }
+            if (b->base.zchunk) break;
+        }
+    }
+    return best_us <= 0.94 * first_us ? best : first;
 }
 
 void drop_graph(gs_batch *b)
@@ -430,8 +504,10 @@ gs_status gs_batch_init(const gs_params *base, int32_t n_sims, const int32_t *nx
         b->scratch_items = b->item_capacity;
     }
     const size_t es = storage_bytes(base->storage);
-    const int shape = base->tile ? base->tile - gs::num_tiles() : 2;
-    const BatchChoice def = default_batch(b, shape, n_sims, nx, ny, nz);
+    const BatchChoice def = base->tile || base->tblock
+                                ? shape_batch(b, base->tile ? base->tile - gs::num_tiles() : 2, n_sims, nx, ny, nz)
+                                : default_batch(b, n_sims, nx, ny, nz);
+    const int shape = def.shape;
     const int T = base->tblock ? base->tblock : std::min(gs::tb_batch_max_T(shape, base->storage), def.T);
     char *p = (char *)arena;
     for (int32_t i = 0; i < n_sims; ++i) {

@@ -98,3 +98,29 @@ def test_batch_tile_widths(torch, storage, T):
                 s.step(7)
                 for got, want in zip(b.read(i), s.read()):
                     assert np.array_equal(got, want), (i, max_abs(got, want))
+
+
+# the library's choice: every tile and depth it takes, chunks that do not divide the grids, grids of one chunk, and a
+# chunk that the caller sets
+@pytest.mark.parametrize("n,dims,storage,noise,zchunk,want", [
+    (6, (32, 32, 32), "f64", 1e-3, 0, (5, 2)), (27, (40, 40, 40), "f64", 0.0, 0, (5, 2)),
+    (32, (128, 128, 48), "f64", 0.0, 0, (6, 3)), (16, (80, 80, 80), "f32", 0.0, 0, (6, 2)),
+    (7, (48, 40, 30), "f32", 1e-3, 0, (5, 2)), (20, (104, 90, 60), "bf16", 0.0, 0, (6, 2)),
+    (5, (64, 64, 24), "f16", 0.0, 0, (5, 3)), (5, (64, 64, 24), "f16", 1e-3, 0, (5, 2)), (3, (24, 9, 5), "f32", 1e-3, 0, None),
+    (4, (136, 31, 70), "f64", 1e-3, 11, None)])
+def test_batch_library_choice(torch, n, dims, storage, noise, zchunk, want):
+    """The tile and depth of the least estimated time, and the first and the last simulation bit for bit as alone."""
+    from paper_2309_10292_amd import gs
+    nx, ny, nz = dims
+    sims = [dict(nx=nx, ny=ny, nz=nz, F=0.02 + 0.001 * i, k=0.055) for i in range(n)]
+    shared = dict(noise=noise, storage=storage, cube_side=5, **SHARED)
+    with gs.Batch(sims, seed=9, zchunk=zchunk, **shared) as b:
+        c = b.config(0)
+        assert want is None or (c["tile"], c["tblock"]) == want, c
+        assert not zchunk or c["zchunk"] == zchunk
+        b.step(8)
+        for i in (0, n - 1):
+            with gs.Sim(nx, ny, nz, F=sims[i]["F"], k=sims[i]["k"], seed=9 + i, **shared) as s:
+                s.step(8)
+                for got, one in zip(b.read(i), s.read()):
+                    assert np.array_equal(got, one), (i, max_abs(got, one))
