@@ -33,17 +33,19 @@ float from_bf16(uint16_t b)
     return f;
 }
 
-// IEEE half: the mantissa and exponent bits in place in an FP32 word are the value
-// times 2^-112, subnormals included; the largest exponent (infinities, NaN) stays it.
+// IEEE half, with integer operations and normal FP32 operands alone, so that the
+// calling thread's treatment of denormals does not matter: a normal half is its bits in
+// place with the exponent rebiased by 127 - 15, a subnormal one its mantissa times 2^-24,
+// and the largest exponent (infinities, NaN) stays the largest.
 float from_f16(uint16_t b)
 {
-    uint32_t w = (uint32_t)(b & 0x7fffu) << 13;
-    float f;
-    memcpy(&f, &w, 4);
-    f *= 0x1p112f;
-    memcpy(&w, &f, 4);
-    w = (b & 0x7c00u) == 0x7c00u ? 0x7f800000u | (uint32_t)(b & 0x3ffu) << 13 : w;
+    const uint32_t m = b & 0x3ffu, e = b & 0x7c00u;
+    const float small = (float)(int32_t)m * 0x1p-24f;
+    uint32_t w;
+    memcpy(&w, &small, 4);
+    w = e ? ((uint32_t)(b & 0x7fffu) << 13) + (e == 0x7c00u ? 224u << 23 : 112u << 23) : w;
     w |= (uint32_t)(b & 0x8000u) << 16;
+    float f;
     memcpy(&f, &w, 4);
     return f;
 }

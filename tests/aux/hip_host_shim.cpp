@@ -1,0 +1,65 @@
+// Stand-ins for the HIP runtime calls of the library's host code, so that its launch
+// rules and its reads run on a machine without a GPU: "device" memory is host memory,
+// streams are synchronous. Loaded with global symbols before libgs.so. No kernel may be
+// launched.
+#include <hip/hip_runtime_api.h>
+
+#include <atomic>
+#include <stdlib.h>
+#include <string.h>
+#include <xmmintrin.h>
+
+static int g_cus = 256, g_lanes = 1024; // compute units; lanes that one of them holds
+static std::atomic<int> g_pinned{0}, g_events{0};
+
+extern "C" {
+
+void shim_device(int cus, int lanes) { g_cus = cus, g_lanes = lanes; }
+int shim_pinned() { return g_pinned; } // pinned allocations alive
+int shim_events() { return g_events; } // events alive
+// Denormals are zero and flushed to zero in the calling thread (and those it starts).
+void shim_flush_denormals(int on) { _mm_setcsr(on ? _mm_getcsr() | 0x8040 : _mm_getcsr() & ~0x8040u); }
+
+hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t a, int)
+{
+    if (a != hipDeviceAttributeMultiprocessorCount) return hipErrorInvalidValue;
+    return *v = g_cus, hipSuccess;
+}
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int block, size_t)
+{
+    return *n = g_lanes >= block ? g_lanes / block : 1, hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
+{
+    memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t, hipDevice_t *d) { return *d = 0, hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned)
+{
+    *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
+    return *p ? ++g_pinned, hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipHostFree(void *p)
+{
+    free(p);
+    return --g_pinned, hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned)
+{
+    *e = (hipEvent_t)malloc(1);
+    return ++g_events, hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t e)
+{
+    free(e);
+    return --g_events, hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *, const void *) { return hipErrorInvalidValue; }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+}

@@ -1,0 +1,79 @@
+"""The library's host code without a GPU: reads, and the launch that a problem statement
+leaves to the library. Each test runs in a process of its own, where stand-ins for the HIP
+runtime calls (aux/hip_host_shim.cpp) are loaded before the library."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, sys
+import numpy as np
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+from paper_2309_10292_amd import gs
+L = gs.load()
+DP = ctypes.POINTER(ctypes.c_double)
+
+def aligned(nbytes):
+    raw = np.zeros(nbytes + 256, np.uint8)
+    o = -raw.ctypes.data % 256
+    return raw[o:o + nbytes]
+
+class HostSim:
+    "A simulation over host memory (no steps)."
+    def __init__(self, nx, ny, nz, buffers=None, **kw):
+        self.p = gs.make_params(nx, ny, nz, init="none", **kw)
+        self.fields = buffers or [aligned(256) for _ in range(4)]
+        self.ws = aligned(256)
+        self.h = ctypes.c_void_p()
+        gs.check(L.gs_init(ctypes.byref(self.p), *[f.ctypes.data for f in self.fields], self.ws.ctypes.data, None,
+                           ctypes.byref(self.h)))
+    def config(self):
+        c = [ctypes.c_int32() for _ in range(3)]
+        gs.check(L.gs_get_config(self.h, *[ctypes.byref(x) for x in c]))
+        return tuple(x.value for x in c)
+    def read(self, u, v):
+        gs.check(L.gs_read(self.h, u.ctypes.data_as(DP), v.ctypes.data_as(DP)))
+    def close(self):
+        gs.check(L.gs_destroy(self.h))
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("shim") / "shim.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(ROOT, "tests", "aux", "hip_host_shim.cpp"), "-o", so], check=True)
+
+    def go(body):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), so], cwd=ROOT, capture_output=True,
+                           text=True, timeout=120)
+        assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+    return go
+
+
+@pytest.mark.parametrize("flush", [0, 1])
+@pytest.mark.parametrize("times", [1, 8])
+def test_half_precision_reads_in_either_denormal_mode(run, times, flush):
+    """All 65536 FP16 patterns, in a plain copy and through the ring, whatever the calling
+    thread does with denormals: every half is a normal FP32 number."""
+    run(f"""
+    bits = np.tile(np.arange(65536, dtype=np.uint16), {times})
+    want = bits.view(np.float16).astype(np.float64)
+    fields = [aligned(bits.nbytes) for _ in range(4)]
+    fields[0][:] = bits.view(np.uint8)
+    fields[1][:] = bits[::-1].copy().view(np.uint8)
+    s = HostSim(64, 32, 32 * {times}, fields, storage="f16")
+    u, v = np.empty(bits.size), np.empty(bits.size)
+    shim.shim_flush_denormals({flush})
+    s.read(u, v)
+    shim.shim_flush_denormals(0)
+    for got, w in ((u, want), (v, want[::-1])):
+        assert np.array_equal(np.isnan(got), np.isnan(w))
+        ok = ~np.isnan(w)
+        assert np.array_equal(got[ok].view(np.int64), w[ok].view(np.int64))
+    """)
