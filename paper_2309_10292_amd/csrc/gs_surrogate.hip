@@ -751,9 +751,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // Per item, each lane's staging chunks sit at fixed offsets within a
         // plane (global) and within a buffer (LDS); a plane adds its offset.
         // Chunk v of an act plane: channel group v % NCG of cell (v / NCG) % 18
-        // (x0 - 1 + cell) in row v / (18 NCG) (y0 - 1 + row); chunk t of a dz
-        // plane (lanes t < T_DZ): group t % NCGZ, cell (t / NCGZ) % 16, row
-        // t / (16 NCGZ) (rows past ny contribute zero). Plane p goes to buffer p & 1.
+        // (x0 - 1 + cell) in row v / (18 NCG) (y0 - 1 + row, which wraps more than
+        // once where ny < TR + 1); chunk t of a dz plane, RD of them per lane: group
+        // t % NCGZ, cell (t / NCGZ) % 16, row t / (16 NCGZ) (rows past ny contribute
+        // zero). Act plane p and dz plane p + 1 go to slot (p - z0 + 1) mod 3.
         const size_t plane_a = (size_t)g.ny * g.nx * CIN, plane_d = (size_t)g.ny * g.nx * COUTS;
         const u16 *act_s = a.act + sbase * CIN, *dz_s = a.dz + sbase * COUTS;
         uint32_t goff_a[RA]; // in 16-byte chunks
@@ -762,7 +763,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int k = 0; k < RA; ++k) {
             const int v = min(tid + 256 * k, T_ACT - 1);
             const int cg = v % NCG, cell = (v / NCG) % 18, row = v / (18 * NCG);
-            const int x = wrapc(x0 + cell - 1, g.nx), y = wrapc(y0 + row - 1, g.ny);
+            const int x = wrapc(x0 + cell - 1, g.nx);
+            int y = y0 + row - 1;
+            if (y < 0) y += g.ny;
+            while (y >= g.ny) y -= g.ny;
             goff_a[k] = ((uint32_t)y * g.nx + x) * NCG + cg;
             loff_a[k] = row * AROW + wg_pos(cell, 8 * cg);
         }

@@ -541,3 +541,20 @@ def test_hidden_layers_same_for_every_chunk(torch, nz, ny, nx, reps):
     for i, (small, large) in enumerate(zip(*got)):
         small = small / reps if i >= 6 else small
         assert np.array_equal(large.reshape(nz, ny, reps, nx, 32), np.broadcast_to(small[:, :, None], (nz, ny, reps, nx, 32))), i
+
+
+@pytest.mark.parametrize("ny", [4, 5, 9])
+def test_gradients_do_not_read_other_samples(torch, ny):
+    """Gradients of one sample in a workspace for two, whose unused half holds NaN: bit for bit those of a workspace
+    for one. A patch of the hidden layers' weight gradients takes 10 activation rows, which wrap around the grid
+    twice where it has 4."""
+    from paper_2309_10292_amd.surrogate import Surrogate
+    u, v = _fields((8, ny, 16), 1, 10)
+    T = lambda a: torch.from_numpy(a.astype(np.float32)).cuda()
+    got = []
+    for batch in (1, 2):
+        with Surrogate(16, ny, 8, max_batch=batch, params=_params(23)) as m:
+            m.workspace.fill_(255)
+            m.set_params(_params(23))
+            got.append(m.loss_grad(T(u), T(v), T(u * 0.98), T(v + 0.01), [0.03], [0.055], want_grad=True))
+    assert np.all(np.isfinite(got[0][1])) and got[0][0] == got[1][0] and np.array_equal(got[0][1], got[1][1])
