@@ -270,9 +270,11 @@ int default_tile(const gs_params &p)
     if (b.shape) return first_blk() + b.shape;
     const int tb = gs::num_tiles(); // tiles tb + 1 .. tb + 5 are the blocked shapes 1..5
     if (grid_cells(p) < 4.0 * 1024 * 1024) return tb + 1;
-    if (!large_grid(p)) return p.storage == GS_F64 ? tb + 4 : tb + 2;
-    if (p.storage == GS_F32 && p.noise == 0.0) return tb + 5;
-    return tb + 2;
+    int tile = tb + 2;
+    if (!large_grid(p) && p.storage == GS_F64) tile = tb + 4;
+    if (large_grid(p) && p.storage == GS_F32 && p.noise == 0.0) tile = tb + 5;
+    // a caller's tblock may be more than the larger tiles fuse; the 512-lane one fuses any
+    return p.tblock <= tile_max_tblock(tile, p.storage) ? tile : tb + 2;
 }
 
 int default_tblock(const gs_params &p, int tile)

@@ -598,3 +598,18 @@ def test_reads_of_every_16_bit_value(torch, storage):
         assert np.array_equal(np.isnan(got), np.isnan(want))
         ok = ~np.isnan(want)
         assert np.array_equal(got[ok].view(np.int64), want[ok].view(np.int64))
+
+
+@pytest.mark.parametrize("storage, tblock", [("f64", 3), ("f64", 4), ("f32", 4)])
+def test_callers_depth_with_the_librarys_tile(torch, storage, tblock):
+    """tile = 0 and a depth that the library's larger tiles do not fuse: the steps run, bit for bit those of the
+    single-step kernel (FP64 between 4 and 64 M cells, FP32 without noise above)."""
+    from paper_2309_10292_amd import gs
+    nx, ny, nz = (168, 162, 160) if storage == "f64" else (512, 512, 256)
+    got = []
+    for kw in (dict(tblock=tblock), dict(tile=2)):
+        with gs.Sim(nx, ny, nz, storage=storage, cube_side=60, **kw) as s:
+            s.step(tblock + 1)
+            u, v, _ = s.current()
+            got.append((u.clone(), v.clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])

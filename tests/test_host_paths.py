@@ -77,3 +77,16 @@ def test_half_precision_reads_in_either_denormal_mode(run, times, flush):
         ok = ~np.isnan(w)
         assert np.array_equal(got[ok].view(np.int64), w[ok].view(np.int64))
     """)
+
+
+def test_library_tile_fuses_the_callers_steps(run):
+    """tile = 0 with tblock set: the library's tile runs that depth in every size class and storage type."""
+    run("""
+    for shape in [(32, 32, 32), (64, 64, 64), (88, 88, 88), (16, 600, 600), (168, 168, 168), (512, 512, 512)]:
+        for storage in ("f64", "f32", "bf16", "f16", "bf16c"):
+            for noise in (0.0, 1e-3):
+                for tblock in (0, 1, 2, 3, 4):
+                    tile, depth, _ = HostSim(*shape, storage=storage, noise=noise, tblock=tblock).config()
+                    assert (depth == tblock or not tblock) and 1 <= depth <= gs.max_tblock(tile, storage), \
+                        (shape, storage, noise, tblock, tile, depth)
+    """)
