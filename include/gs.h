@@ -114,8 +114,8 @@ size_t gs_workspace_bytes(const gs_params *p);
  * pass (workgroups of 256 to 1024 lanes; the larger ones fuse fewer steps in
  * FP64, whose registers are twice as many); the next three select the block
  * kernel for small grids, which fuses tblock steps of one block of cells per
- * workgroup (its planes per workgroup are fixed: zchunk has no effect); the last
- * two are narrower tiles of the temporally blocked kernel (32 and 48 cells, up to
+ * workgroup (its planes per workgroup are fixed: zchunk has no effect, and with
+ * zchunk set the library's choice is never one of these); the last two are narrower tiles of the temporally blocked kernel (32 and 48 cells, up to
  * three steps, not for batches).
  * gs_tile_info reports the output
  * tile (tx cells by ty rows) of `tile` for a storage type and tblock, and the

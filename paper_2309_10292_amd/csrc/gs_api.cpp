@@ -226,7 +226,8 @@ gs_status check(gs_sim *s)
 // gs_params sets a part of it, two steps in 256-lane workgroups below 4 M cells
 // and above that in the 768-lane tile for FP64 and the 512-lane one for the
 // others). The single-step kernel (tiles 1..4) runs when asked for. The smallest
-// and the narrowest grids take the block kernel (default_block).
+// and the narrowest grids take the block kernel (default_block), unless gs_params
+// sets the z-chunk.
 double grid_cells(const gs_params &p) { return (double)p.nx * p.ny * p.nz; }
 bool large_grid(const gs_params &p) { return grid_cells(p) >= 64.0 * 1024 * 1024; }
 
@@ -249,6 +250,7 @@ struct BlockChoice {
 };
 BlockChoice default_block(const gs_params &p)
 {
+    if (p.zchunk) return BlockChoice{0, 0}; // the caller's z-chunk has no meaning for blocks
     auto up = [](int n, int t) { return (double)((n + t - 1) / t); };
     auto blocks = [&](int shape) {
         const gs::BlkShape b = gs::blk_shape(shape);

@@ -90,3 +90,17 @@ def test_library_tile_fuses_the_callers_steps(run):
                     assert (depth == tblock or not tblock) and 1 <= depth <= gs.max_tblock(tile, storage), \
                         (shape, storage, noise, tblock, tile, depth)
     """)
+
+
+def test_callers_z_chunk_is_used(run):
+    """tile = 0 with zchunk set: a kernel that streams along z, with that chunk, also on the grids that the block
+    kernel takes otherwise (tiles 10 to 12, which have planes of their own)."""
+    run("""
+    for shape in [(16, 20, 24), (32, 32, 32), (48, 48, 48), (64, 64, 64), (80, 80, 80), (16, 600, 600), (192, 192, 192)]:
+        for storage in ("f64", "f32", "bf16c"):
+            for tblock in (0, 1, 4):
+                tile, depth, zchunk = HostSim(*shape, storage=storage, tblock=tblock, zchunk=9).config()
+                assert not 10 <= tile <= 12 and zchunk == 9, (shape, storage, tblock, tile, zchunk)
+                assert 1 <= depth <= gs.max_tblock(tile, storage)
+    assert 10 <= HostSim(32, 32, 32).config()[0] <= 12
+    """)
