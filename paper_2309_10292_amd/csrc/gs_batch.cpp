@@ -152,10 +152,10 @@ Cover cover(int shape, int T, int nx, int ny)
     return best;
 }
 
-// Steps per launch and z-chunk of one tile. Two steps, except FP64 with work for at least two rounds of workgroups,
-// where T = 2 is bound by HBM and three steps are faster (32 grids of 128^3:
-// 196 against 265 us per step; on 24 grids of 16^3..72^3, less than one round,
-// 31 against 21). FP32 and 16-bit kernels of T = 2 keep two 512-lane
+// Steps per launch and z-chunk of one tile. `tblock` steps if the caller sets them, else two (or what the tile
+// fuses, if that is less), except FP64 with work for at least two rounds of workgroups, where T = 2 is bound by
+// HBM and three steps are faster (32 grids of 128^3: 196 against 265 us per step; on 24 grids of 16^3..72^3, less
+// than one round, 31 against 21). FP32 and 16-bit kernels of T = 2 keep two 512-lane
 // workgroups per CU, of T = 3 one (32 x 128^3 without noise: FP32 123 against
 // 148 us per step, BF16 84 against 119 with one step). The chunk is the one
 // with the least estimated makespan of the longest-first list: the items'
@@ -166,8 +166,8 @@ Cover cover(int shape, int T, int nx, int ny)
 struct BatchChoice {
     int shape, T, zc;
 };
-BatchChoice shape_batch(const gs_batch *b, int shape, int32_t n_sims, const int32_t *nx, const int32_t *ny,
-                          const int32_t *nz)
+BatchChoice shape_batch(const gs_batch *b, int shape, int tblock, int32_t n_sims, const int32_t *nx,
+                        const int32_t *ny, const int32_t *nz)
 {
     auto columns = [&](int i, int T) {
         const Cover c = cover(shape, T, nx[i], ny[i]);
@@ -176,7 +176,8 @@ BatchChoice shape_batch(const gs_batch *b, int shape, int32_t n_sims, const int3
     const bool f64 = b->base.storage == GS_F64;
     double items = 0;
     for (int32_t i = 0; i < n_sims; ++i) items += columns(i, f64 ? 3 : 2) * tiles_along(nz[i], 32);
-    const int T = f64 && items >= 2.0 * batch_slots(b, 3, shape) ? 3 : 2;
+    const int deep = f64 && items >= 2.0 * batch_slots(b, 3, shape) ? 3 : 2;
+    const int T = tblock ? tblock : std::min(gs::tb_batch_max_T(shape, b->base.storage), deep);
     const double slots = batch_slots(b, T, shape);
     BatchChoice best = {shape, T, k_min_batch_zc};
     double best_cost = 1e300;
@@ -235,7 +236,7 @@ BatchChoice default_batch(const gs_batch *b, int32_t n_sims, const int32_t *nx, 
     static const int chunks[] = {8, 10, 12, 16, 20, 24, 32, 40, 48, 64};
     const BatchCost *table = b->base.storage == GS_F64 ? f64 : b->base.storage == GS_F32 ? f32 : b16;
     const int noise = b->base.noise != 0.0;
-    BatchChoice best = shape_batch(b, 2, n_sims, nx, ny, nz);
+    BatchChoice best = shape_batch(b, 2, 0, n_sims, nx, ny, nz);
     if (b->base.zchunk) best.zc = b->base.zchunk;
     const BatchChoice first = best;
     double best_us = 1e300, first_us = 1e300;
@@ -505,10 +506,10 @@ gs_status gs_batch_init(const gs_params *base, int32_t n_sims, const int32_t *nx
     }
     const size_t es = storage_bytes(base->storage);
     const BatchChoice def = base->tile || base->tblock
-                                ? shape_batch(b, base->tile ? base->tile - gs::num_tiles() : 2, n_sims, nx, ny, nz)
+                                ? shape_batch(b, base->tile ? base->tile - gs::num_tiles() : 2, base->tblock, n_sims, nx,
+                                              ny, nz)
                                 : default_batch(b, n_sims, nx, ny, nz);
-    const int shape = def.shape;
-    const int T = base->tblock ? base->tblock : std::min(gs::tb_batch_max_T(shape, base->storage), def.T);
+    const int shape = def.shape, T = def.T;
     char *p = (char *)arena;
     for (int32_t i = 0; i < n_sims; ++i) {
         BSim s;

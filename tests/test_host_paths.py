@@ -40,6 +40,20 @@ class HostSim:
         gs.check(L.gs_read(self.h, u.ctypes.data_as(DP), v.ctypes.data_as(DP)))
     def close(self):
         gs.check(L.gs_destroy(self.h))
+
+class HostBatch:
+    "A batch of cubes (no steps, and no fields: the library does not touch them)."
+    def __init__(self, sides, **kw):
+        p, n = gs.make_params(8, 8, 8, init="none", **kw), len(sides)
+        d, r = (ctypes.c_int32 * n)(*sides), (ctypes.c_double * n)(*[0.03] * n)
+        nbytes = int(L.gs_batch_workspace_bytes(n, d, d, d))
+        self.ws, self.h = aligned(nbytes), ctypes.c_void_p()
+        gs.check(L.gs_batch_init(ctypes.byref(p), n, d, d, d, r, r, 1 << 40, 1 << 60, self.ws.ctypes.data, nbytes, None,
+                                 ctypes.byref(self.h)))
+    def config(self, i=0):
+        c = [ctypes.c_int32() for _ in range(3)]
+        gs.check(L.gs_batch_get_config(self.h, i, *[ctypes.byref(x) for x in c]))
+        return tuple(x.value for x in c)
 """
 
 
@@ -103,4 +117,33 @@ def test_callers_z_chunk_is_used(run):
                 assert not 10 <= tile <= 12 and zchunk == 9, (shape, storage, tblock, tile, zchunk)
                 assert 1 <= depth <= gs.max_tblock(tile, storage)
     assert 10 <= HostSim(32, 32, 32).config()[0] <= 12
+    """)
+
+
+@pytest.mark.parametrize("tile, tblock", [(0, 1), (0, 4), (6, 4), (7, 3), (8, 0)])
+def test_batch_chunk_for_the_callers_depth(run, tile, tblock):
+    """A batch with tile or tblock set and no zchunk: the chunk of least estimated makespan at that depth (FP64, one
+    workgroup of more than 256 lanes per CU)."""
+    run(f"""
+    shim.shim_device(256, 512)
+    for sides in ([72, 88, 96, 96, 104, 112, 120, 120], [24] * 24, [128] * 32, [64, 192] * 8):
+        t, T, zchunk = HostBatch(sides, tile={tile}, tblock={tblock}).config()
+        assert t == ({tile} or 6) and T == ({tblock} or 1), (t, T)
+        tx, ty = gs.tile_info(t, "f64", T)
+        def cost(zc):
+            n = planes = longest = 0
+            for L in sides:
+                cols = -(-L // tx) * -(-L // ty)
+                if t == 6 and T <= 3: # narrow tiles where they are 10 % fewer
+                    c = cols
+                    for wx, wy in ((32, 51 - 2 * T), (48, 36 - 2 * T)):
+                        k = 1.1 * -(-L // wx) * -(-L // wy)
+                        if k <= c: c, cols = k, -(-L // wx) * -(-L // wy)
+                n += cols * -(-L // zc)
+                planes += cols * (L + 2 * T * -(-L // zc))
+                longest = max(longest, min(zc, L) + 2 * T)
+            return longest if n <= 256 else planes / 256 + 0.5 * longest
+        # configurations report chunks cut to the grid
+        want = min((8, 16, 32, 64), key=cost)
+        assert zchunk == min(want, sides[0]), (sides, zchunk, want)
     """)
