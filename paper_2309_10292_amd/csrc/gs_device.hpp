@@ -153,6 +153,12 @@ __device__ __forceinline__ float in_vgpr(float x)
     asm volatile("" : "+v"(x)); // no instruction: the value is no longer known to be uniform
     return x;
 }
+// In scalar registers, for kernels that the number of their wavefronts or their
+// spills bind more than the issue rate.
+template <typename A> __device__ __forceinline__ CoefF32 coef_f32_scalar(const A &a)
+{
+    return CoefF32{a.Du6_f, a.Dv6_f, a.F_f, a.FK_f, a.dt_f, a.noise_s_f, a.noise_h_f};
+}
 template <typename A> __device__ __forceinline__ CoefF32 coef_f32(const A &a)
 {
     return CoefF32{in_vgpr(a.Du6_f), in_vgpr(a.Dv6_f), in_vgpr(a.F_f),      in_vgpr(a.FK_f),

@@ -121,11 +121,20 @@ __device__ __forceinline__ void widen(int f, const Vec<S, V> &a, C (&out)[V])
     for (int i = 0; i < V; ++i) out[i] = fload<S>(f, a.e[i]);
 }
 
+// Waves per SIMD to fit the registers for: four where that takes no spills (FP16
+// would take 132 registers, and three waves, by itself).
+template <typename S, bool NOISE> constexpr int tile_min_waves()
+{
+    return sizeof(S) == 2 && !NOISE && !Complemented<S>::value ? 4 : 1;
+}
+
 // NF = 2: the Gray-Scott step on (u, v). NF = 1 with LAPLACE: out = lap(f)
 // of a single FP64 field (calibration kernel).
 template <typename S, int TX, int TY, int V, int NF, bool NOISE, bool LAPLACE>
-__global__ __launch_bounds__(256) void stencil_tile(const S *__restrict__ u, const S *__restrict__ v,
-                                                    S *__restrict__ un, S *__restrict__ vn, StepArgs a)
+__global__ __launch_bounds__(256, (tile_min_waves<S, NOISE>())) void stencil_tile(const S *__restrict__ u,
+                                                                               const S *__restrict__ v,
+                                                                               S *__restrict__ un, S *__restrict__ vn,
+                                                                               StepArgs a)
 {
     typedef Geom<S, TX, TY, V> G;
     typedef typename G::C C;
@@ -141,7 +150,11 @@ __global__ __launch_bounds__(256) void stencil_tile(const S *__restrict__ u, con
     const int ze = min(z0 + a.zc, nz);
     const size_t plane = (size_t)nx * (size_t)ny;
     const LaneMap m = make_lane_map<S, TX, TY, V>(x0, y0, nx, ny);
-    const CoefF32 kf = coef_f32(a);
+    // Without noise the loads in flight bind, and vector registers for the coefficients
+    // cost a wave per SIMD: 320 x 320 x 256, 64-cell tiles, us per step with scalar ones
+    // FP16 75 -> 46 (chunks of 16 planes) and 54 -> 46 (4), BF16 65 -> 42 and 50 -> 46,
+    // FP32 99 -> 103 and 106 -> 98. With noise both take as many waves.
+    const CoefF32 kf = NOISE ? coef_f32(a) : coef_f32_scalar(a);
 
     const S *src[2] = {u, v};
     C zm[NF][V], zc[NF][V], zp[NF][V];

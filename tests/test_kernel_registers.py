@@ -1,0 +1,47 @@
+"""Registers of the built kernels, from the code objects' own metadata: kernels whose speed
+depends on how many wavefronts or workgroups a CU holds, or on not spilling."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2309_10292_amd import gs
+
+LLVM = "/opt/rocm/llvm/bin/"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{symbol: (vector registers, spilled vector registers)} of every kernel in libgs.so."""
+    d = tmp_path_factory.mktemp("code")
+    fat = str(d / "fat")
+    subprocess.run([LLVM + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, gs.LIB_PATH, os.devnull], check=True)
+    blob, out, pos = open(fat, "rb").read(), {}, 0
+    while (pos := blob.find(b"\x7fELF", pos)) >= 0:
+        shoff, = struct.unpack_from("<Q", blob, pos + 0x28)
+        shnum, = struct.unpack_from("<H", blob, pos + 0x3C)
+        obj = d / "object"
+        obj.write_bytes(blob[pos:pos + shoff + 64 * shnum])
+        notes = subprocess.run([LLVM + "llvm-readelf", "--notes", str(obj)], check=True, capture_output=True, text=True).stdout
+        for k in notes.split("- .agpr_count:")[1:]:
+            f = {n: v for n, v in re.findall(r"\.(symbol|vgpr_count|vgpr_spill_count):\s+'?([^\s']+)", k)}
+            out[f["symbol"]] = (int(f["vgpr_count"]), int(f["vgpr_spill_count"]))
+        pos += 64
+    assert out
+    return out
+
+
+# symbols, largest number of registers (512 a SIMD lane slot: 128 let 4 wavefronts in, 96 let 5), largest number spilled
+@pytest.mark.parametrize("symbol, vgprs, spilled", [
+    # the single-step kernel streams: its loads in flight are its wavefronts (FP16 tiles of up to 39 KB of LDS)
+    (r"stencil_tileIDF16_Li(128ELi16|64ELi32)ELi8ELi2ELb0ELb0E", 128, 0),
+    (r"stencil_tileINS_4bf16E\w+ELi2ELb0ELb0E", 128, 0),
+    (r"stencil_tileIfLi\d+ELi\d+ELi4ELi2ELb0ELb0E", 96, 0),
+])
+def test_registers(kernels, symbol, vgprs, spilled):
+    found = {k: v for k, v in kernels.items() if re.search(symbol, k)}
+    assert found
+    for k, (n, s) in found.items():
+        assert n <= vgprs and s <= spilled, (k, n, s)
