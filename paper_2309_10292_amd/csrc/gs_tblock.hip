@@ -42,6 +42,12 @@ template <typename S, int T, int NT, int NOISE> constexpr bool tb_dma()
 {
     return sizeof(S) == 8 && NOISE && T == 3 && NT == 512;
 }
+// FP64 kernels whose noise has 64-bit block indices on every grid: those that the
+// registers bind most, where the 32-bit ones' few more cost spills or their places (320 x
+// 320 x 256 with noise, chunks of 4 planes, us per step: 1024 lanes 222 -> 203, 768
+// lanes at two steps 142 -> 137, 512 lanes at four 232 -> 217; 512 lanes at three,
+// chunks of 16, keep the 32-bit ones, 107 against 111).
+template <typename S, int T, int NT> constexpr bool tb_noise_64() { return sizeof(S) == 8 && (NT > 512 || (NT == 512 && T == 4)); }
 // A workgroup barrier that waits for the LDS operations only: the LDS-DMA
 // prefetch stays in flight across it (each wave reads only the area its own
 // loads fill, after waiting for them).
@@ -501,9 +507,10 @@ static hipError_t launch_tb_t(const void *u, const void *v, void *un, void *vn, 
         return hipGetLastError();
     };
     if (a.noise == 0.0) return go(Phase<NOISE_OFF>{});
-    if (noise_fits_32(a.nx, a.ny, a.nz)) return go(Phase<NOISE_32>{});
+    if constexpr (tb_noise_64<S, T, NT>()) return go(Phase<NOISE_64>{});
+    else if (noise_fits_32(a.nx, a.ny, a.nz)) return go(Phase<NOISE_32>{});
     // (four FP64 buffers of 2^34 cells are 512 GiB: more than the device holds)
-    if constexpr (sizeof(S) == 8) return hipErrorInvalidConfiguration;
+    else if constexpr (sizeof(S) == 8) return hipErrorInvalidConfiguration;
     else return go(Phase<NOISE_64>{});
 }
 
@@ -589,8 +596,9 @@ static hipError_t launch_tb_batch_t(const BatchArgs &b, hipStream_t st)
         return hipGetLastError();
     };
     if (b.coef.noise == 0.0) return go(Phase<NOISE_OFF>{});
-    if (b.noise_32) return go(Phase<NOISE_32>{});
-    if constexpr (sizeof(S) == 8) return hipErrorInvalidConfiguration;
+    if constexpr (tb_noise_64<S, T, NT>()) return go(Phase<NOISE_64>{});
+    else if (b.noise_32) return go(Phase<NOISE_32>{});
+    else if constexpr (sizeof(S) == 8) return hipErrorInvalidConfiguration;
     else return go(Phase<NOISE_64>{});
 }
 
@@ -667,7 +675,7 @@ static int occ_single_t(bool noise)
 {
     int n = 0;
     const hipError_t e = noise
-                             ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb<S, TXG, TY, T, NT, NOISE_32>, NT, 0)
+                             ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb<S, TXG, TY, T, NT, tb_noise_64<S, T, NT>() ? NOISE_64 : NOISE_32>, NT, 0)
                              : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb<S, TXG, TY, T, NT, NOISE_OFF>, NT, 0);
     return e == hipSuccess && n > 0 ? n : 0;
 }

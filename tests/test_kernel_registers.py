@@ -39,6 +39,9 @@ def kernels(tmp_path_factory):
     (r"stencil_tileIDF16_Li(128ELi16|64ELi32)ELi8ELi2ELb0ELb0E", 128, 0),
     (r"stencil_tileINS_4bf16E\w+ELi2ELb0ELb0E", 128, 0),
     (r"stencil_tileIfLi\d+ELi\d+ELi4ELi2ELb0ELb0E", 96, 0),
+    # the FP64 kernels of 768 and 1024 lanes with noise, which leave no register
+    (r"10stencil_tbIdLi16ELi38ELi2ELi768ELi[12]E", 168, 0),
+    (r"10stencil_tbIdLi16ELi54ELi1ELi1024ELi[12]E", 128, 2),
 ])
 def test_registers(kernels, symbol, vgprs, spilled):
     found = {k: v for k, v in kernels.items() if re.search(symbol, k)}
