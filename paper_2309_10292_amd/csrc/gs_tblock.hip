@@ -47,7 +47,19 @@ template <typename S, int T, int NT, int NOISE> constexpr bool tb_dma()
 // 320 x 256 with noise, chunks of 4 planes, us per step: 1024 lanes 222 -> 203, 768
 // lanes at two steps 142 -> 137, 512 lanes at four 232 -> 217; 512 lanes at three,
 // chunks of 16, keep the 32-bit ones, 107 against 111).
-template <typename S, int T, int NT> constexpr bool tb_noise_64() { return sizeof(S) == 8 && (NT > 512 || (NT == 512 && T == 4)); }
+// FP32's three steps in 1024 lanes spill nothing then (14 otherwise), and its single step
+// in 768 takes the 80 registers that let two workgroups share a CU.
+template <typename S, int T, int NT> constexpr bool tb_noise_64()
+{
+    return sizeof(S) == 8   ? NT > 512 || (NT == 512 && T == 4)
+           : sizeof(S) == 4 ? (NT == 768 && T == 1) || (NT == 1024 && T == 3)
+                            : false;
+}
+// FP32 kernels whose coefficients stay in scalar registers: those of 768 and 1024 lanes,
+// where vector ones made them spill (three steps in 1024 lanes, 320 x 320 x 256 with
+// noise, chunks of 16 planes: 102 -> 86 us per step; without noise 67.7 -> 65.8) or lose
+// a workgroup per CU (one step in 768 lanes with noise, chunks of 4: 108 -> 94).
+template <typename S, int NT> constexpr bool tb_coef_scalar() { return sizeof(S) == 4 && NT > 512; }
 // A workgroup barrier that waits for the LDS operations only: the LDS-DMA
 // prefetch stays in flight across it (each wave reads only the area its own
 // loads fill, after waiting for them).
@@ -118,7 +130,7 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
     static_assert(!DMA || 2 * G::FIELD * sizeof(C) + 4 * NT * 16 <= 160 * 1024, "staged planes and prefetch fit");
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const size_t plane = (size_t)nx * (size_t)ny;
-    const CoefF32 kf = coef_f32(a);
+    const CoefF32 kf = tb_coef_scalar<S, NT>() ? coef_f32_scalar(a) : coef_f32(a);
 
     // This lane's position (x-group gxs, level-0 row rys) and depth dep
     // (-1: none). Order: the output tile (depth T, row-major), the x-halo

@@ -42,6 +42,9 @@ def kernels(tmp_path_factory):
     # the FP64 kernels of 768 and 1024 lanes with noise, which leave no register
     (r"10stencil_tbIdLi16ELi38ELi2ELi768ELi[12]E", 168, 0),
     (r"10stencil_tbIdLi16ELi54ELi1ELi1024ELi[12]E", 128, 2),
+    # FP32: three steps in 1024 lanes; one in 768, two workgroups of which share a CU at 80 registers
+    (r"10stencil_tbIfLi16ELi50ELi3ELi1024E", 128, 0),
+    (r"10stencil_tbIfLi16ELi40ELi1ELi768E", 80, 0),
 ])
 def test_registers(kernels, symbol, vgprs, spilled):
     found = {k: v for k, v in kernels.items() if re.search(symbol, k)}
