@@ -60,6 +60,16 @@ template <typename S, int T, int NT> constexpr bool tb_noise_64()
 // noise, chunks of 16 planes: 102 -> 86 us per step; without noise 67.7 -> 65.8) or lose
 // a workgroup per CU (one step in 768 lanes with noise, chunks of 4: 108 -> 94).
 template <typename S, int NT> constexpr bool tb_coef_scalar() { return sizeof(S) == 4 && NT > 512; }
+// Complemented BF16 without noise: the kernels that round a cell as soon as it is done
+// instead of all four in pairs. The paired rounding takes fewer instructions, and longer
+// where one workgroup of 768 or 1024 lanes fills a CU or 512 lanes keep four levels (320 x
+// 320 x 256, chunks of 16 planes, us per step: 768 lanes 52.5 -> 48.4 at two steps and
+// 53.6 -> 48.9 at three, 1024 lanes 56.2 -> 54.3 and 61.8 -> 58.0, 128-cell tile at four
+// 131 -> 116; 256 lanes at four would lose a fifth).
+template <typename S, int T, int NT, int NOISE> constexpr bool tb_round_cells()
+{
+    return Complemented<S>::value && !NOISE && T >= 2 && (NT > 512 || (NT == 512 && T == 4));
+}
 // A workgroup barrier that waits for the LDS operations only: the LDS-DMA
 // prefetch stays in flight across it (each wave reads only the area its own
 // loads fill, after waiting for them).
@@ -127,6 +137,7 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
     typedef TbGeom<S, TXG, TY, T, NT> G;
     typedef typename G::C C;
     constexpr bool DMA = tb_dma<S, T, NT, NOISE>();
+    constexpr bool CELLS = tb_round_cells<S, T, NT, NOISE>();
     static_assert(!DMA || 2 * G::FIELD * sizeof(C) + 4 * NT * 16 <= 160 * 1024, "staged planes and prefetch fit");
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const size_t plane = (size_t)nx * (size_t)ny;
@@ -349,18 +360,25 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
                 }
                 C uo, vo;
                 cell_update<C, UNIT_DT, NOISE != 0>(a, kf, uc, vc, lap[0][e], lap[1][e], r[e], uo, vo);
-                res[0][e] = uo;
-                res[1][e] = vo;
+                res[0][e] = CELLS ? fload<S>(0, fstore<S>(0, uo)) : uo;
+                res[1][e] = CELLS ? fload<S>(1, fstore<S>(1, vo)) : vo;
             }
             // Every level carries the stored precision of the state.
             Vec<S, 4> st[2];
 #pragma unroll
-            for (int f = 0; f < 2; ++f) st[f] = fstore4<S>(f, res[f]);
+            for (int f = 0; f < 2; ++f) {
+                if constexpr (CELLS) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) st[f].e[e] = fstore<S>(f, res[f][e]); // exact
+                } else {
+                    st[f] = fstore4<S>(f, res[f]);
+                }
+            }
             if (k < T) {
 #pragma unroll
                 for (int f = 0; f < 2; ++f)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) win[k][sc][f][e] = fload<S>(f, st[f].e[e]);
+                    for (int e = 0; e < 4; ++e) win[k][sc][f][e] = CELLS ? res[f][e] : fload<S>(f, st[f].e[e]);
             } else if (out_ok && zk >= z0) {
                 const size_t off = (size_t)zk * plane + xy;
                 NtStore<S>::put(un + off, st[0]);

@@ -613,3 +613,19 @@ def test_callers_depth_with_the_librarys_tile(torch, storage, tblock):
             u, v, _ = s.current()
             got.append((u.clone(), v.clone()))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16", "bf16c"])
+def test_tblock_without_noise_equals_single_step(torch, storage):
+    """The same without noise, whose kernels round and keep their coefficients in other ways: every tile and depth,
+    on a grid with ragged tiles, bit for bit the single steps."""
+    shape, p = (24, 57, 72), dict(P0, noise=0.0)
+    with _sim(shape, storage=storage, tile=1, cube_side=10, **p) as s:
+        s.step(9)
+        ref = [t.clone() for t in s.current()[:2]]
+    for tile in tb_tiles():
+        for T in range(1, max_T(tile, storage) + 1):
+            with _sim(shape, storage=storage, tile=tile, tblock=T, cube_side=10, **p) as s:
+                s.step(9)
+                u, v, _ = s.current()
+                assert torch.equal(u, ref[0]) and torch.equal(v, ref[1]), (storage, tile, T)
