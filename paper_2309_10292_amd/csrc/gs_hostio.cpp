@@ -155,6 +155,14 @@ ReadStage::~ReadStage()
 gs_status read_fields(ReadStage &stage, const void *const dev[2], int32_t storage, size_t n, double *const host[2],
                       hipStream_t st)
 {
+    if (host[0] && host[1]) {
+        const uintptr_t u = (uintptr_t)host[0], v = (uintptr_t)host[1];
+        if ((u < v ? v - u : u - v) < n * sizeof(double)) { // overlapping arrays: all of u, then all of v
+            double *const one[2] = {host[0], nullptr}, *const other[2] = {nullptr, host[1]};
+            const gs_status r = read_fields(stage, dev, storage, n, one, st);
+            return r != GS_OK ? r : read_fields(stage, dev, storage, n, other, st);
+        }
+    }
     const size_t es = storage_bytes(storage), bytes = n * es;
     const size_t chunks = (bytes + k_slot - 1) / k_slot; // of a field
     int field[2], nf = 0;

@@ -147,3 +147,30 @@ def test_batch_chunk_for_the_callers_depth(run, tile, tblock):
         want = min((8, 16, 32, 64), key=cost)
         assert zchunk == min(want, sides[0]), (sides, zchunk, want)
     """)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16"])
+def test_reads_into_one_array(run, storage):
+    """u and v read into the same or overlapping arrays: u first, then v, at every size."""
+    run(f"""
+    ny, nz = 64, 128
+    n = 64 * ny * nz
+    dtype = dict(f64=np.float64, f32=np.float32, bf16=np.uint16)["{storage}"]
+    bits = [(np.arange(n) % 251 + 251 * f).astype(np.float32) for f in range(2)]
+    want = [(b.view(np.uint32) >> 16 << 16).view(np.float32).astype(np.float64) if "{storage}" == "bf16" else b.astype(np.float64) for b in bits]
+    fields = [aligned(n * dtype().itemsize) for _ in range(4)]
+    for f in range(2):
+        x = (bits[f].view(np.uint32) >> 16).astype(np.uint16) if "{storage}" == "bf16" else bits[f].astype(dtype)
+        fields[f][:] = x.view(np.uint8)
+    s = HostSim(64, ny, nz, fields, storage="{storage}")
+    for shift in (0, 100, n // 2):
+        for first in (0, 1): # which of the two arrays begins earlier
+            for _ in range(20):
+                got = np.full(n + shift, -1.0)
+                at = [shift, 0] if first else [0, shift]
+                s.read(got[at[0]:], got[at[1]:])
+                model = np.full(n + shift, -1.0)
+                for f in range(2):
+                    model[at[f]:at[f] + n] = want[f]
+                assert np.array_equal(got, model), (shift, first, np.flatnonzero(got != model)[:4])
+    """)
