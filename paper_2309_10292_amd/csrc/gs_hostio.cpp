@@ -170,9 +170,11 @@ gs_status read_fields(ReadStage &stage, const void *const dev[2], int32_t storag
         if (host[f]) field[nf++] = f;
     // Below 3.5 MB of FP64 a first read would lose more to making the ring (0.7 ms) than
     // it gains (72^3 FP64 0.36 -> 1.13 ms; 80^3 1.84 -> 1.19, FP32 1.35 -> 0.88), and
-    // later ones gain little. FP64 into the caller's own pinned memory needs no staging.
+    // later ones gain little. FP64 into memory that the runtime knows needs no staging.
     std::unique_lock<std::mutex> lock(stage.mu, std::defer_lock);
-    bool ringed = nf > 0 && n >= k_min && !(storage == GS_F64 && !pageable(host[field[0]]));
+    bool ringed = nf > 0 && n >= k_min;
+    if (storage == GS_F64)
+        for (int i = 0; i < nf; ++i) ringed = ringed && pageable(host[field[i]]);
     if (ringed) {
         lock.lock();
         ringed = stage.prepare(st);

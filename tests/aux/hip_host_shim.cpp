@@ -10,11 +10,13 @@
 #include <xmmintrin.h>
 
 static int g_cus = 256, g_lanes = 1024; // compute units; lanes that one of them holds
+static const void *g_known;              // memory of the runtime's own
 static std::atomic<int> g_pinned{0}, g_events{0};
 
 extern "C" {
 
 void shim_device(int cus, int lanes) { g_cus = cus, g_lanes = lanes; }
+void shim_known(const void *p) { g_known = p; }
 int shim_pinned() { return g_pinned; } // pinned allocations alive
 int shim_events() { return g_events; } // events alive
 // Denormals are zero and flushed to zero in the calling thread (and those it starts).
@@ -59,7 +61,11 @@ hipError_t hipEventDestroy(hipEvent_t e)
 }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipPointerGetAttributes(hipPointerAttribute_t *, const void *) { return hipErrorInvalidValue; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
+{
+    if (p != g_known) return hipErrorInvalidValue;
+    return a->type = hipMemoryTypeDevice, hipSuccess;
+}
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 }

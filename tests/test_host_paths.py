@@ -174,3 +174,23 @@ def test_reads_into_one_array(run, storage):
                     model[at[f]:at[f] + n] = want[f]
                 assert np.array_equal(got, model), (shift, first, np.flatnonzero(got != model)[:4])
     """)
+
+
+@pytest.mark.parametrize("known", [0, 1])
+def test_fp64_reads_into_memory_of_the_runtime(run, known):
+    """FP64 goes to memory that the runtime knows (pinned, managed, a device's) in plain copies, whichever of the two
+    arrays that is."""
+    run(f"""
+    n = 64 * 64 * 128
+    fields = [aligned(8 * n) for _ in range(4)]
+    for f in range(2):
+        fields[f].view(np.float64)[:] = np.arange(n) + f
+    s = HostSim(64, 64, 128, fields)
+    out = [np.empty(n), np.empty(n)]
+    shim.shim_known(ctypes.c_void_p(out[{known}].ctypes.data))
+    s.read(*out)
+    assert shim.shim_pinned() == 0 and all(np.array_equal(out[f], np.arange(n) + f) for f in range(2))
+    shim.shim_known(None)
+    s.read(*out)
+    assert shim.shim_pinned() == 1 and all(np.array_equal(out[f], np.arange(n) + f) for f in range(2))
+    """)
