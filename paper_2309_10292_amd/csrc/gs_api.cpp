@@ -728,6 +728,10 @@ gs_status gs_tune(gs_sim *s, int32_t reps, gs_tune_entry *table, int32_t capacit
                 // and the step index are left unchanged.
                 int par = s->parity;
                 e = enqueue_steps(s, T, s->stream, nullptr, &par); // warm-up
+                if (e == hipErrorInvalidConfiguration) { // more workgroups than a launch takes: no candidate
+                    e = hipSuccess;
+                    continue;
+                }
                 if (e == hipSuccess) e = hipEventRecord(e0, s->stream);
                 for (int r = 0; r < reps && e == hipSuccess; ++r) {
                     par = s->parity;

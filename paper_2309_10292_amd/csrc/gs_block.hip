@@ -242,8 +242,8 @@ static hipError_t launch_blk_t(const void *u, const void *v, void *un, void *vn,
     a.ntx = (a.nx + 4 * BXG - 1) / (4 * BXG);
     a.nty = (a.ny + BY - 1) / BY;
     const size_t nb = (size_t)a.ntx * a.nty * ((a.nz + BZ - 1) / BZ);
-    if (nb == 0 || nb > 0x7fffffffu) return hipErrorInvalidConfiguration;
     const int nt = BlkGeom<S, BXG, BY, BZ, T, PZ>::NT;
+    if (!grid_fits(nb, nt)) return hipErrorInvalidConfiguration;
     if (a.noise != 0.0)
         hipLaunchKernelGGL((stencil_blk<S, BXG, BY, BZ, T, PZ, true>), dim3((unsigned)nb), dim3(nt), 0, st, (const S *)u,
                            (const S *)v, (S *)un, (S *)vn, a);

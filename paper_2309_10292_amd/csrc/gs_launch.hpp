@@ -39,6 +39,13 @@ inline int next_depth(int64_t left, int T)
     return (int)((left + launches - 1) / launches);
 }
 
+// Whether one launch takes that many workgroups: a grid of the runtime has less than
+// 2^31 of them and less than 2^32 threads.
+inline bool grid_fits(size_t blocks, int lanes)
+{
+    return blocks > 0 && blocks <= 0x7fffffffu && blocks * (size_t)lanes < ((size_t)1 << 32);
+}
+
 struct TileShape {
     int tx, ty;
 };

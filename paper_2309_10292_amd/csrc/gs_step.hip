@@ -286,7 +286,7 @@ static hipError_t launch_tile(const void *u, const void *v, void *un, void *vn, 
     a.nty = (a.ny + TY - 1) / TY;
     const int nzc = (a.nz + a.zc - 1) / a.zc;
     const size_t nb = (size_t)a.ntx * a.nty * nzc;
-    if (nb == 0 || nb > 0x7fffffffu) return hipErrorInvalidConfiguration;
+    if (!grid_fits(nb, 256)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((stencil_tile<S, TX, TY, V, NF, NOISE, LAPLACE>), dim3((unsigned)nb), dim3(256), 0, st,
                        (const S *)u, (const S *)v, (S *)un, (S *)vn, a);
     return hipGetLastError();

@@ -530,7 +530,7 @@ static hipError_t launch_tb_t(const void *u, const void *v, void *un, void *vn, 
     a.nty = (a.ny + TY - 1) / TY;
     const int nzc = (a.nz + a.zc - 1) / a.zc;
     const size_t nb = (size_t)a.ntx * a.nty * nzc;
-    if (nb == 0 || nb > 0x7fffffffu) return hipErrorInvalidConfiguration;
+    if (!grid_fits(nb, NT)) return hipErrorInvalidConfiguration;
     auto go = [&](auto mode) {
         hipLaunchKernelGGL((stencil_tb<S, TXG, TY, T, NT, decltype(mode)::value>), dim3((unsigned)nb), dim3(NT), 0, st,
                            (const S *)u, (const S *)v, (S *)un, (S *)vn, a);

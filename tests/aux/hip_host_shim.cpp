@@ -1,7 +1,7 @@
 // Stand-ins for the HIP runtime calls of the library's host code, so that its launch
 // rules and its reads run on a machine without a GPU: "device" memory is host memory,
-// streams are synchronous. Loaded with global symbols before libgs.so. No kernel may be
-// launched.
+// streams are synchronous, and a kernel's launch does nothing. Loaded with global symbols
+// before libgs.so.
 #include <hip/hip_runtime_api.h>
 
 #include <atomic>
@@ -11,7 +11,9 @@
 
 static int g_cus = 256, g_lanes = 1024; // compute units; lanes that one of them holds
 static const void *g_known;              // memory of the runtime's own
-static std::atomic<int> g_pinned{0}, g_events{0};
+static struct { dim3 grid, block; size_t lds; hipStream_t st; } g_call; // (of the one thread that launches)
+static hipError_t g_error = hipSuccess;
+static std::atomic<int> g_pinned{0}, g_events{0}, g_launches{0};
 
 extern "C" {
 
@@ -19,6 +21,7 @@ void shim_device(int cus, int lanes) { g_cus = cus, g_lanes = lanes; }
 void shim_known(const void *p) { g_known = p; }
 int shim_pinned() { return g_pinned; } // pinned allocations alive
 int shim_events() { return g_events; } // events alive
+int shim_launches() { return g_launches; }
 // Denormals are zero and flushed to zero in the calling thread (and those it starts).
 void shim_flush_denormals(int on) { _mm_setcsr(on ? _mm_getcsr() | 0x8040 : _mm_getcsr() & ~0x8040u); }
 
@@ -67,5 +70,27 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
     return a->type = hipMemoryTypeDevice, hipSuccess;
 }
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t st)
+{
+    g_call = {grid, block, lds, st};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *st)
+{
+    *grid = g_call.grid, *block = g_call.block, *lds = g_call.lds, *st = g_call.st;
+    return hipSuccess;
+}
+// The runtime's limit: less than 2^32 threads in a dimension of the grid.
+hipError_t hipLaunchKernel(const void *, dim3 grid, dim3 block, void **, size_t, hipStream_t)
+{
+    ++g_launches;
+    return g_error = (double)grid.x * block.x < 4294967296.0 ? hipSuccess : hipErrorInvalidConfiguration;
+}
+hipError_t hipGetLastError()
+{
+    const hipError_t e = g_error;
+    return g_error = hipSuccess, e;
+}
+hipError_t hipEventCreate(hipEvent_t *e) { return hipEventCreateWithFlags(e, 0); }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
 }

@@ -194,3 +194,17 @@ def test_fp64_reads_into_memory_of_the_runtime(run, known):
     s.read(*out)
     assert shim.shim_pinned() == 1 and all(np.array_equal(out[f], np.arange(n) + f) for f in range(2))
     """)
+
+
+def test_tune_on_grids_of_more_blocks_than_a_launch_takes(run):
+    """The autotuner passes over the candidates whose launch would have 2^32 threads or more (the block kernel's on
+    a grid of 1.3 G cells) and measures the others."""
+    run("""
+    s = HostSim(2048, 1024, 640, storage="bf16")
+    table, n = (gs.gs_tune_entry * 256)(), ctypes.c_int32()
+    gs.check(L.gs_tune(s.h, 1, ctypes.cast(table, ctypes.c_void_p), 256, ctypes.byref(n)))
+    tried = {(e.tile, e.tblock) for e in table[:n.value]}
+    every = {(tile, T) for tile in range(1, 15) for T in range(1, gs.max_tblock(tile, "bf16") + 1)}
+    # 10.5 M blocks of 8 x 4 x 4 cells in workgroups of 64, 192, 256 and, at four steps, 448 lanes
+    assert every - tried == {(10, 4)}, every - tried
+    """)
