@@ -95,6 +95,10 @@ constexpr size_t k_part = (size_t)256 << 10; // bytes a thread widens at a time
 constexpr int k_parts = (int)(k_slot / k_part);
 constexpr int k_threads = 8;
 constexpr size_t k_min = 448 << 10;          // values of a field from which the ring is used
+// Rings that handles keep between reads, in all (of 8 MB each, which cannot be paged
+// out); a handle beyond that makes one for each read (0.7 ms) and gives it back.
+constexpr int k_kept = 16;
+std::atomic<int> g_rings{0}; // rings there are
 
 // One field in a plain copy.
 gs_status read_plain(const void *dev, int32_t storage, size_t n, double *host, hipStream_t st, int field)
@@ -115,7 +119,7 @@ gs_status read_plain(const void *dev, int32_t storage, size_t n, double *host, h
 
 } // namespace
 
-// The ring, made at the first large read. False where it cannot serve: no memory, or
+// The ring, made at the first large read (or, unless kept, at each). False where it cannot serve: no memory, or
 // a stream of another device than the current one or the ring's.
 bool ReadStage::prepare(hipStream_t st)
 {
@@ -141,15 +145,18 @@ bool ReadStage::prepare(hipStream_t st)
         }
     ring = static_cast<unsigned char *>(p);
     device = now;
+    kept = g_rings.fetch_add(1) < k_kept;
     return true;
 }
 
-ReadStage::~ReadStage()
+void ReadStage::release()
 {
     if (!ring) return;
     Relaxed relaxed;
     for (hipEvent_t e : arrived) (void)hipEventDestroy(e);
     (void)hipHostFree(ring);
+    ring = nullptr;
+    g_rings.fetch_sub(1);
 }
 
 gs_status read_fields(ReadStage &stage, const void *const dev[2], int32_t storage, size_t n, double *const host[2],
@@ -187,6 +194,13 @@ gs_status read_fields(ReadStage &stage, const void *const dev[2], int32_t storag
         return GS_OK;
     }
 
+    struct GiveBack {
+        ReadStage &stage;
+        ~GiveBack()
+        {
+            if (!stage.kept) stage.release();
+        }
+    } give_back{stage};
     constexpr int K = ReadStage::SLOTS;
     const size_t total = chunks * nf;
     auto chunk_bytes = [&](size_t c) { return std::min(k_slot, bytes - c % chunks * k_slot); };

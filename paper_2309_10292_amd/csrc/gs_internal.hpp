@@ -18,18 +18,21 @@ bool aligned(const void *p, size_t a);
 // Validates a problem statement (grid, coefficients, init, tiling fields).
 gs_status validate(const gs_params *p);
 // Pinned staging of a handle's reads: a ring that the first large read makes and the
-// handle gives back. Reads of one handle from several threads take turns.
+// handle gives back, or, where enough other handles keep one, the read itself. Reads of
+// one handle from several threads take turns.
 struct ReadStage {
     static constexpr int SLOTS = 4; // of 2 MB
     std::mutex mu;
     unsigned char *ring = nullptr;
     int device = -1;
+    bool kept = false;
     hipEvent_t arrived[SLOTS] = {};
     ReadStage() = default;
     ReadStage(const ReadStage &) = delete;
     ReadStage &operator=(const ReadStage &) = delete;
-    ~ReadStage();
+    ~ReadStage() { release(); }
     bool prepare(hipStream_t st);
+    void release();
 };
 // Synchronising copies between device fields of `storage` type (u, v) and host FP64;
 // a NULL host skips the field.

@@ -208,3 +208,29 @@ def test_tune_on_grids_of_more_blocks_than_a_launch_takes(run):
     # 10.5 M blocks of 8 x 4 x 4 cells in workgroups of 64, 192, 256 and, at four steps, 448 lanes
     assert every - tried == {(10, 4)}, every - tried
     """)
+
+
+def test_pinned_memory_of_many_handles_is_bounded(run):
+    """Forty simulations that have each read a large field hold 16 rings, and none when they are closed; all of them
+    read what they should, again and again."""
+    run("""
+    n = 64 * 64 * 128
+    def make(i):
+        fields = [aligned(4 * n) for _ in range(2)] * 2
+        for f in range(2):
+            fields[f].view(np.float32)[:] = np.arange(n) % 1000 + i + f
+        return HostSim(64, 64, 128, fields[:2] + [aligned(256), aligned(256)], storage="f32")
+    sims, u, v = [make(i) for i in range(40)], np.empty(n), np.empty(n)
+    for turn in range(2):
+        for i, s in enumerate(sims):
+            s.read(u, v)
+            assert np.array_equal(u, np.arange(n) % 1000 + i) and np.array_equal(v, u + 1)
+            assert shim.shim_pinned() <= 16 and shim.shim_events() == 4 * shim.shim_pinned()
+    assert shim.shim_pinned() == 16
+    sims[3].close()
+    sims[30].read(u, v)
+    assert shim.shim_pinned() == 16 # the place goes to the next that reads
+    for i, s in enumerate(sims):
+        if i != 3: s.close()
+    assert shim.shim_pinned() == 0 and shim.shim_events() == 0
+    """)
