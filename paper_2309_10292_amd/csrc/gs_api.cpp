@@ -52,6 +52,15 @@ size_t storage_bytes(int32_t s)
 
 bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
+int device_cus()
+{
+    int cus = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        (void)hipGetLastError();
+    return cus > 0 ? cus : 256;
+}
+
 // Tile indices: 1..num_tiles() select the single-step z-streaming kernel's
 // shapes; the next num_tb_shapes() indices select the temporally blocked
 // kernel's shapes (any tblock), the next num_blk_shapes() the block
@@ -244,11 +253,12 @@ bool large_grid(const gs_params &p) { return grid_cells(p) >= 64.0 * 1024 * 1024
 // steps), while 88^3 ties and 128 x 106 x 75 loses 15 %. The z-streaming tile is
 // 64 x 10 cells, so what it wastes on narrow rows counts too: 16 x 250 x 250
 // 18.6 -> 7.9 and 16 x 600 x 600 72 -> 31 (16x8x8, one step); 32 x 150 x 200 gains
-// 6 % in FP64 and loses 5 % in BF16 with noise, 24 x 640 x 640 loses 20 %.
+// 6 % in FP64 and loses 5 % in BF16 with noise, 24 x 640 x 640 loses 20 %. The numbers
+// of blocks are per CU of the 256 that this was measured with.
 struct BlockChoice {
     int shape, T;
 };
-BlockChoice default_block(const gs_params &p)
+BlockChoice default_block(const gs_params &p, int cus)
 {
     if (p.zchunk) return BlockChoice{0, 0}; // the caller's z-chunk has no meaning for blocks
     auto up = [](int n, int t) { return (double)((n + t - 1) / t); };
@@ -256,19 +266,19 @@ BlockChoice default_block(const gs_params &p)
         const gs::BlkShape b = gs::blk_shape(shape);
         return up(p.nx, b.bx) * up(p.ny, b.by) * up(p.nz, b.bz);
     };
-    if (blocks(1) <= 512) return BlockChoice{1, blocks(1) <= 400 ? 4 : 3};
-    if (blocks(2) <= 256) return BlockChoice{2, 3};
-    if (blocks(3) <= 256) return BlockChoice{3, 3};
+    if (blocks(1) <= 2 * cus) return BlockChoice{1, 16 * blocks(1) <= 25 * cus ? 4 : 3};
+    if (blocks(2) <= cus) return BlockChoice{2, 3};
+    if (blocks(3) <= cus) return BlockChoice{3, 3};
     const double streamed = 64 * up(p.nx, 64) * 10 * up(p.ny, 10) * p.nz; // cells its tiles cover
     if (grid_cells(p) < 4.0 * 1024 * 1024)
-        return blocks(2) <= 600 || 512 * blocks(2) <= (grid_cells(p) < 600e3 ? 0.63 : 0.45) * streamed ? BlockChoice{2, 2}
+        return 32 * blocks(2) <= 75 * cus || 512 * blocks(2) <= (grid_cells(p) < 600e3 ? 0.63 : 0.45) * streamed ? BlockChoice{2, 2}
                                                                                                       : BlockChoice{0, 0};
     return !large_grid(p) && 1024 * blocks(3) <= 0.3 * streamed ? BlockChoice{3, 1} : BlockChoice{0, 0};
 }
 
-int default_tile(const gs_params &p)
+int default_tile(const gs_params &p, int cus)
 {
-    const BlockChoice b = default_block(p);
+    const BlockChoice b = default_block(p, cus);
     if (b.shape) return first_blk() + b.shape;
     const int tb = gs::num_tiles(); // tiles tb + 1 .. tb + 5 are the blocked shapes 1..5
     if (grid_cells(p) < 4.0 * 1024 * 1024) return tb + 1;
@@ -279,10 +289,10 @@ int default_tile(const gs_params &p)
     return p.tblock <= tile_max_tblock(tile, p.storage) ? tile : tb + 2;
 }
 
-int default_tblock(const gs_params &p, int tile)
+int default_tblock(const gs_params &p, int tile, int cus)
 {
     if (tile <= gs::num_tiles()) return 1;
-    const BlockChoice b = default_block(p);
+    const BlockChoice b = default_block(p, cus);
     if (is_blk_tile(tile)) return tile == first_blk() + b.shape ? b.T : 2;
     int T = 2;
     if (large_grid(p) && p.storage == GS_F64) T = 3;
@@ -351,8 +361,8 @@ int default_zc(const gs_params &p, int tile, int tblock)
 
 // Launch of grids between the block kernel's and 64 M cells when gs_params leaves
 // all of it to the library: the blocked shape, depth and z-chunk of least
-// estimated time per step. A launch of nb workgroups on 256 CUs that hold occ each
-// runs nb / (256 occ) full rounds and a part of one; a round takes
+// estimated time per step. A launch of nb workgroups on CUs that hold occ each
+// runs nb / (CUs occ) full rounds and a part of one; a round takes
 // (zc + 2T - 1) plane times (the chunk, the planes its levels run ahead and one
 // for its start), and a plane of a CU with n workgroups fixed + n each, in us.
 // The constants are least-squares fits over 25 grids of 0.4 to 57 M cells and 14
@@ -374,7 +384,7 @@ struct StreamCost {
 struct StreamChoice {
     int shape, T, zc;
 };
-StreamChoice default_stream(const gs_params &p)
+StreamChoice default_stream(const gs_params &p, int cus)
 {
     static const StreamCost f64[] = {{1, 2, 2, {0.70, 0.84}, {0.55, 0.57}},
                                      {2, 2, 1, {0.96, 1.10}, {0.96, 1.10}},
@@ -402,9 +412,9 @@ StreamChoice default_stream(const gs_params &p)
         const gs::TileShape t = gs::tb_shape(c.shape, c.T);
         const int64_t tiles = (int64_t)((p.nx + t.tx - 1) / t.tx) * ((p.ny + t.ty - 1) / t.ty);
         for (int z = 3; z <= 64 && z <= p.nz; ++z) {
-            const int64_t nb = tiles * ((p.nz + z - 1) / z), full = nb / (256 * c.occ), rest = nb % (256 * c.occ);
+            const int64_t nb = tiles * ((p.nz + z - 1) / z), full = nb / (cus * c.occ), rest = nb % (cus * c.occ);
             double plane = full * (c.fixed[noise] + c.occ * c.each[noise]);
-            if (rest) plane += c.fixed[noise] + (double)((rest + 255) / 256) * c.each[noise];
+            if (rest) plane += c.fixed[noise] + (double)((rest + cus - 1) / cus) * c.each[noise];
             double us = (2.5 + (z + 2 * c.T - 1) * plane) / c.T; // 2.5: a launch
             if (c.shape > gs::num_tb_shapes()) us *= 1.1;
             if (us <= best_us) {
@@ -554,12 +564,13 @@ gs_status gs_init(const gs_params *p, void *u0, void *v0, void *u1, void *v1, vo
     s->step = p->step0;
     s->ws = workspace;
     s->stream = (hipStream_t)hip_stream;
-    s->tile = p->tile ? p->tile : default_tile(*p);
-    s->tblock = p->tblock ? p->tblock : default_tblock(*p, s->tile);
+    const int cus = device_cus();
+    s->tile = p->tile ? p->tile : default_tile(*p, cus);
+    s->tblock = p->tblock ? p->tblock : default_tblock(*p, s->tile, cus);
     s->zc = p->zchunk ? (p->zchunk < p->nz ? p->zchunk : p->nz) : default_zc(*p, s->tile, s->tblock);
     if (p->tile == 0 && p->tblock == 0 && p->zchunk == 0) {
-        if (!large_grid(*p) && !default_block(*p).shape) {
-            const StreamChoice c = default_stream(*p);
+        if (!large_grid(*p) && !default_block(*p, cus).shape) {
+            const StreamChoice c = default_stream(*p, cus);
             s->tile = tb_tile_of(c.shape);
             s->tblock = c.T;
             s->zc = c.zc;

@@ -201,7 +201,7 @@ BatchChoice shape_batch(const gs_batch *b, int shape, int tblock, int32_t n_sims
 // Library choice of tile, steps per launch and z-chunk, before any tuning: the least
 // estimated time per step, for all simulations together so that they share their
 // launches. A launch's items stream (chunk + 2T - 1) planes each, the longest first;
-// n of them on 256 CUs of up to occ workgroups take the longest item if all are
+// n of them on CUs of up to occ workgroups take the longest item if all are
 // resident at once, else their planes over the places and 0.3 of the longest item for
 // the last round, and a plane of a CU with k workgroups takes fixed + k each, in us.
 // The constants are least-squares fits over 48 batches of 4 to 32 grids of 16^3 to
@@ -259,8 +259,9 @@ BatchChoice default_batch(const gs_batch *b, int32_t n_sims, const int32_t *nx, 
                 planes += tiles[(size_t)j] * (nz[j] + (2 * c.T - 1) * parts);
                 longest = std::max(longest, std::min(zc, nz[j]) + 2 * c.T - 1);
             }
-            const double k = std::min((double)c.occ, std::ceil(n / 256));
-            const double span = n <= 256 * k ? longest : std::max((double)longest, planes / (256 * k) + 0.3 * longest);
+            const double k = std::min((double)c.occ, std::ceil(n / b->cus));
+            const double places = b->cus * k;
+            const double span = n <= places ? longest : std::max((double)longest, planes / places + 0.3 * longest);
             const double us = (2.5 + span * (c.fixed[noise] + k * c.each[noise])) / c.T; // 2.5: a launch
             if (c.shape == first.shape && c.T == first.T && zc == first.zc) first_us = us;
             if (us < best_us) {

@@ -15,6 +15,8 @@ gs_status fail(gs_status s, const char *fmt, ...) __attribute__((format(printf, 
 gs_status hip_fail(hipError_t e, const char *what);
 size_t storage_bytes(int32_t storage);
 bool aligned(const void *p, size_t a);
+// Compute units of the current device (256 where the runtime cannot say).
+int device_cus();
 // Validates a problem statement (grid, coefficients, init, tiling fields).
 gs_status validate(const gs_params *p);
 // Pinned staging of a handle's reads: a ring that the first large read makes and the

@@ -1358,16 +1358,16 @@ static int chunk_planes(int nz, size_t cols, size_t slots, int unit)
     return best;
 }
 
-hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a, hipStream_t st)
+hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a, int cus, hipStream_t st)
 {
     if (a.geo.nx % PX != 0 || a.geo.nz < 4) return hipErrorInvalidValue;
     if (nt == 2 && mode != MODE_OUT && (cin == 8 || cin == 32)) {
         ConvArgs b = a;
         const int waves = cin == 8 ? C8_WAVES : C32_WAVES, py = waves * (cin == 8 ? C8_RW : C32_RW);
         const size_t cols = (size_t)(a.geo.nx / PX) * ((a.geo.ny + py - 1) / py) * a.nsamp;
-        // workgroups at once on 256 CUs: three of conv8_kernel a CU (registers), one of
+        // workgroups at once: three of conv8_kernel a CU (registers), one of
         // conv32p_kernel (registers and LDS)
-        b.zc = cin == 8 ? chunk_planes(a.geo.nz, cols, 768, 3) : chunk_planes(a.geo.nz, cols, 256, 4);
+        b.zc = cin == 8 ? chunk_planes(a.geo.nz, cols, 3 * (size_t)cus, 3) : chunk_planes(a.geo.nz, cols, cus, 4);
         const size_t nb = cols * ((a.geo.nz + b.zc - 1) / b.zc);
         if (nb == 0 || nb > 0x7fffffffu) return hipErrorInvalidConfiguration;
         auto go = [&](auto m) {
@@ -1382,7 +1382,7 @@ hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a,
         ConvArgs b = a;
         const int ng = a.geo.nx / 16, tg = ng <= OUT_NG ? ng : OUT_NG - 2;
         const size_t cols = (size_t)((ng + tg - 1) / tg) * ((a.geo.ny + OUT_TY - 1) / OUT_TY) * a.nsamp;
-        b.zc = balanced_zc(a.geo.nz, cols, 256); // one workgroup per CU
+        b.zc = balanced_zc(a.geo.nz, cols, cus); // one workgroup per CU
         const size_t nb = cols * ((a.geo.nz + b.zc - 1) / b.zc);
         if (nb == 0 || nb > 0x7fffffffu) return hipErrorInvalidConfiguration;
         auto go = [&](auto full) {
@@ -1397,10 +1397,10 @@ hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a,
 
 int wgrad_blocks() { return 512; }
 
-hipError_t launch_wgrad_edge(bool first, const WgradArgs &a, float *gW, float *gb, hipStream_t st)
+hipError_t launch_wgrad_edge(bool first, const WgradArgs &a, float *gW, float *gb, int cus, hipStream_t st)
 {
-    // resident at once on 256 CUs: 3 workgroups per CU (LDS), or 4
-    const size_t slots = first ? 768 : 1024;
+    // resident at once: 3 workgroups per CU (LDS), or 4; the partials have room for 1024
+    const size_t slots = std::min<size_t>((first ? 3 : 4) * (size_t)cus, 1024);
     const size_t cols = (size_t)(a.geo.nx / 16) * ((a.geo.ny + WS_RT - 1) / WS_RT) * a.nsamp;
     WgradArgs b = a;
     b.zc = balanced_zc(a.geo.nz, cols, slots * WS_WAVES);

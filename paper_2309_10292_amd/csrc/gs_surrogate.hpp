@@ -43,12 +43,13 @@ struct WgradArgs {
     float *bpart;        // wgrad_blocks() x 32 partial sums of dz (bias gradient)
 };
 
-hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a, hipStream_t st);
+// (cus: compute units of the device)
+hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a, int cus, hipStream_t st);
 int wgrad_blocks();
 hipError_t launch_wgrad(const WgradArgs &a, hipStream_t st); // 32 -> 32 layers
 // Weight and bias gradients of the first layer (8 stored input channels) or the
 // last (8 stored output channels), from the tensors in `a`.
-hipError_t launch_wgrad_edge(bool first, const WgradArgs &a, float *gW, float *gb, hipStream_t st);
+hipError_t launch_wgrad_edge(bool first, const WgradArgs &a, float *gW, float *gb, int cus, hipStream_t st);
 hipError_t launch_wgrad_reduce(const float *part, float *gW, hipStream_t st);
 hipError_t launch_bias_reduce(const float *bpart, int cout, float *gb, hipStream_t st);
 // The samples' (F, k) go with the launch, up to FK_PER_LAUNCH samples at once:

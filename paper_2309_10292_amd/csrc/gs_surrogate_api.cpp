@@ -86,6 +86,7 @@ struct gs_surrogate {
     char *ws;
     Layout L;
     hipStream_t stream;
+    int cus;
     int adam_t;
     int last_batch; // samples of the last loss_grad (gradient present when > 0)
     int last_fwd;   // samples of the last forward pass (predict or loss_grad)
@@ -165,7 +166,7 @@ hipError_t forward(gs_surrogate *s, int32_t nsamp, int io_f64, const void *u, co
         a.bias = P + b_off(l);
         a.zout = keep_pre ? at<uint16_t>(s, s->L.z[l]) : nullptr;
         a.aout = at<uint16_t>(s, s->L.a[l]);
-        e = launch_conv(k_cins[l], 2, keep_pre ? MODE_HIDDEN : MODE_ACT, 0, a, s->stream);
+        e = launch_conv(k_cins[l], 2, keep_pre ? MODE_HIDDEN : MODE_ACT, 0, a, s->cus, s->stream);
         in = a.aout;
     }
     if (e == hipSuccess) {
@@ -179,7 +180,7 @@ hipError_t forward(gs_surrogate *s, int32_t nsamp, int io_f64, const void *u, co
         a.res_v = v;
         a.out_u = uo;
         a.out_v = vo;
-        e = launch_conv(32, 1, MODE_OUT, io_f64, a, s->stream);
+        e = launch_conv(32, 1, MODE_OUT, io_f64, a, s->cus, s->stream);
     }
     return e;
 }
@@ -216,6 +217,7 @@ gs_status gs_surrogate_init(int32_t nx, int32_t ny, int32_t nz, int32_t max_batc
     s->ws = (char *)workspace;
     s->L = L;
     s->stream = (hipStream_t)hip_stream;
+    s->cus = device_cus();
     s->adam_t = 0;
     s->last_batch = 0;
     s->last_fwd = 0;
@@ -307,7 +309,7 @@ gs_status gs_surrogate_loss_grad(gs_surrogate *s, int32_t nsamp, const float *u,
         w.part = wpart;
         w.bpart = cpart;
         if (l == 0 || l == 3) {
-            e = launch_wgrad_edge(l == 0, w, G + w_off(l), G + b_off(l), s->stream);
+            e = launch_wgrad_edge(l == 0, w, G + w_off(l), G + b_off(l), s->cus, s->stream);
         } else {
             e = launch_wgrad(w, s->stream);
             if (e == hipSuccess) e = launch_wgrad_reduce(wpart, G + w_off(l), s->stream);
@@ -321,7 +323,7 @@ gs_status gs_surrogate_loss_grad(gs_surrogate *s, int32_t nsamp, const float *u,
         a.wpack = at<uint16_t>(s, s->L.wd[l]);
         a.zprev = at<uint16_t>(s, s->L.z[l - 1]);
         a.aout = at<uint16_t>(s, s->L.dz[l - 1]);
-        e = launch_conv(couts, 2, MODE_DGRAD, 0, a, s->stream);
+        e = launch_conv(couts, 2, MODE_DGRAD, 0, a, s->cus, s->stream);
         dz = a.aout;
         couts = 32;
     }

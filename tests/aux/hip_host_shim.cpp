@@ -4,16 +4,19 @@
 // before libgs.so.
 #include <hip/hip_runtime_api.h>
 
-#include <atomic>
 #include <stdlib.h>
 #include <string.h>
 #include <xmmintrin.h>
+
+#include <atomic>
+#include <vector>
 
 static int g_cus = 256, g_lanes = 1024; // compute units; lanes that one of them holds
 static const void *g_known;              // memory of the runtime's own
 static struct { dim3 grid, block; size_t lds; hipStream_t st; } g_call; // (of the one thread that launches)
 static hipError_t g_error = hipSuccess;
-static std::atomic<int> g_pinned{0}, g_events{0}, g_launches{0};
+static std::atomic<int> g_pinned{0}, g_events{0};
+static std::vector<unsigned> g_grids; // workgroups of each launch
 
 extern "C" {
 
@@ -21,7 +24,8 @@ void shim_device(int cus, int lanes) { g_cus = cus, g_lanes = lanes; }
 void shim_known(const void *p) { g_known = p; }
 int shim_pinned() { return g_pinned; } // pinned allocations alive
 int shim_events() { return g_events; } // events alive
-int shim_launches() { return g_launches; }
+int shim_launches() { return (int)g_grids.size(); }
+unsigned shim_grid(int i) { return g_grids[i]; }
 // Denormals are zero and flushed to zero in the calling thread (and those it starts).
 void shim_flush_denormals(int on) { _mm_setcsr(on ? _mm_getcsr() | 0x8040 : _mm_getcsr() & ~0x8040u); }
 
@@ -38,6 +42,11 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, in
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
 {
     memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t)
+{
+    memset(d, v, n);
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
@@ -83,7 +92,7 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipSt
 // The runtime's limit: less than 2^32 threads in a dimension of the grid.
 hipError_t hipLaunchKernel(const void *, dim3 grid, dim3 block, void **, size_t, hipStream_t)
 {
-    ++g_launches;
+    g_grids.push_back(grid.x);
     return g_error = (double)grid.x * block.x < 4294967296.0 ? hipSuccess : hipErrorInvalidConfiguration;
 }
 hipError_t hipGetLastError()

@@ -234,3 +234,45 @@ def test_pinned_memory_of_many_handles_is_bounded(run):
         if i != 3: s.close()
     assert shim.shim_pinned() == 0 and shim.shim_events() == 0
     """)
+
+
+def test_launches_fit_the_devices_compute_units(run):
+    """A device with an eighth of the compute units takes, for an eighth of the work, the launch that the whole one
+    takes for all of it: single grids (192 cells of x are whole tiles of every width), batches and the surrogate."""
+    run("""
+    got = []
+    for cus, scale in ((256, 8), (32, 1)):
+        shim.shim_device(cus, 1024)
+        c = []
+        for storage in ("f64", "f32", "bf16"):
+            for noise in (0.0, 1e-3):
+                for ny, nz in ((20, 20), (10, 61), (40, 40), (55, 90), (120, 110), (200, 190)):
+                    c.append(HostSim(192 * scale, ny, nz, storage=storage, noise=noise).config())
+                for sides in ([24, 40], [56, 64, 72], [96, 128, 192], [160]):
+                    c.append(HostBatch(sides * scale, storage=storage, noise=noise).config())
+        got.append(c)
+    differ = [(a, b) for a, b in zip(*got) if a != b]
+    assert not differ, (len(differ), len(got[0]), differ[:5])
+    """)
+
+
+def test_surrogate_launches_fit_the_devices_compute_units(run):
+    """The same for the surrogate's kernels: the workgroups of a prediction of eight samples are eight times those of
+    one on an eighth of the compute units."""
+    run("""
+    nx, ny, nz = 32, 40, 30
+    n = nx * ny * nz
+    grids = []
+    for cus, batch in ((256, 8), (32, 1)):
+        shim.shim_device(cus, 1024)
+        need = int(L.gs_surrogate_workspace_bytes(nx, ny, nz, batch))
+        ws, p, h = aligned(need), np.zeros(60578, np.float32), ctypes.c_void_p()
+        gs.check(L.gs_surrogate_init(nx, ny, nz, batch, p.ctypes.data, ws.ctypes.data, need, None, ctypes.byref(h)))
+        x, fk = [aligned(4 * n * batch) for _ in range(4)], np.full(batch, 0.05)
+        first = shim.shim_launches()
+        gs.check(L.gs_surrogate_predict(h, batch, 1, x[0].ctypes.data, x[1].ctypes.data, fk.ctypes.data, fk.ctypes.data,
+                                        x[2].ctypes.data, x[3].ctypes.data))
+        grids.append([shim.shim_grid(i) for i in range(first, shim.shim_launches())])
+    # the input's packing, and four layers
+    assert len(grids[1]) == 5 and grids[0] == [8 * g for g in grids[1]], grids
+    """)

@@ -45,6 +45,14 @@ def kernels(tmp_path_factory):
     # FP32: three steps in 1024 lanes; one in 768, two workgroups of which share a CU at 80 registers
     (r"10stencil_tbIfLi16ELi50ELi3ELi1024E", 128, 0),
     (r"10stencil_tbIfLi16ELi40ELi1ELi768E", 80, 0),
+    # workgroups per CU that the launch estimates count on: two steps in 256 lanes (FP64 two, the others four) and in
+    # 512 lanes (two), surrogate layers of 8 channels (three; four of the last weight gradient)
+    (r"10stencil_tbIdLi16ELi10ELi2ELi256E", 256, 0),
+    (r"10stencil_tbI(f|DF16_|NS_4bf16E|NS_5bf16cE)Li16ELi10ELi2ELi256E", 128, 2),
+    (r"10stencil_tbI(f|DF16_|NS_4bf16E|NS_5bf16cE)Li(16ELi24|8ELi47|12ELi32)ELi2ELi512E", 128, 2),
+    (r"12conv8_kernel", 168, 0),
+    (r"18wgrad_shift_kernelILb1E", 168, 0),
+    (r"18wgrad_shift_kernelILb0E", 128, 0),
 ])
 def test_registers(kernels, symbol, vgprs, spilled):
     found = {k: v for k, v in kernels.items() if re.search(symbol, k)}
