@@ -145,7 +145,6 @@ struct BatchArgs {
 };
 
 hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b, hipStream_t st);
-int tb_shape_lanes(int shape);
 // Resident workgroups per CU of the batched kernel (at least 1).
 int tb_batch_occupancy(int storage, int T, int shape);
 // Resident workgroups per CU of the single-grid blocked kernel (0 when unknown).

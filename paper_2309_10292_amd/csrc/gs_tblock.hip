@@ -478,6 +478,32 @@ __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb(con
                                       (int)(rest / (uint32_t)a.nty), NOISE ? step_index(a) : 0, lds, pre_lds);
 }
 
+// The shapes: a workgroup of `lanes` lanes takes output tiles of 4 txg cells by
+// rows - 2 T rows at T fused steps, from a level-0 region of (txg + 2) x-groups by
+// `rows` rows. 6 and 7 are for rows that 64 cells cover badly: single grids of one to
+// three steps, and the items of shape 2's batches that the host gives their width.
+struct TbDef {
+    int txg, rows, lanes;
+};
+constexpr int k_tb_shapes = 5, k_tb_narrow = 2, k_tb_depth = 4;
+constexpr TbDef tb_def(int shape)
+{
+    constexpr TbDef d[k_tb_shapes + k_tb_narrow] = {{16, 14, 256},  {16, 28, 512}, {32, 14, 512}, {16, 42, 768},
+                                                    {16, 56, 1024}, {8, 51, 512},  {12, 36, 512}};
+    return d[shape - 1];
+}
+// One workgroup per CU: NT lanes leave 512 / ceil(NT / 256) registers per lane. The
+// deepest fusion whose registers fit that budget (FP64 at four steps spills some tens);
+// batched sweeps take the larger shapes one step less deep; 0: not available.
+template <typename S, bool BATCH> constexpr int tb_max_T_shape(int shape)
+{
+    if (shape > k_tb_shapes) return BATCH ? 0 : 3;
+    const int lanes = tb_def(shape).lanes;
+    if (lanes <= 512) return 4;
+    if (lanes <= 768) return sizeof(S) == 8 ? (BATCH ? 1 : 2) : (BATCH ? 3 : 4);
+    return sizeof(S) == 8 ? (BATCH ? 0 : 1) : (BATCH ? 2 : 3);
+}
+
 // Sweep over many independent simulations: one workgroup per work item (one
 // tile x z-chunk of one simulation), items sorted by decreasing cost, so that
 // the places that fall free last are filled with the cheapest ones. Items are
@@ -491,10 +517,12 @@ __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb(con
 template <typename S, int TXG, int TY, int T, int NT, int NOISE, bool WIDTHS>
 __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb_batch(BatchArgs b)
 {
-    constexpr int TY6 = 51 - 2 * T, TY7 = 36 - 2 * T;
+    constexpr TbDef d6 = tb_def(k_tb_shapes + 1), d7 = tb_def(k_tb_shapes + 2);
+    static_assert(!WIDTHS || (NT == d6.lanes && NT == d7.lanes), "the widths share a launch");
+    constexpr int TY6 = d6.rows - 2 * T, TY7 = d7.rows - 2 * T;
     constexpr int F0 = TbGeom<S, TXG, TY, T, NT>::FIELD;
-    constexpr int F6 = WIDTHS ? TbGeom<S, 8, WIDTHS ? TY6 : 4, WIDTHS ? T : 1, 512>::FIELD : 0;
-    constexpr int F7 = WIDTHS ? TbGeom<S, 12, WIDTHS ? TY7 : 4, WIDTHS ? T : 1, 512>::FIELD : 0;
+    constexpr int F6 = WIDTHS ? TbGeom<S, d6.txg, WIDTHS ? TY6 : 4, WIDTHS ? T : 1, d6.lanes>::FIELD : 0;
+    constexpr int F7 = WIDTHS ? TbGeom<S, d7.txg, WIDTHS ? TY7 : 4, WIDTHS ? T : 1, d7.lanes>::FIELD : 0;
     __shared__ typename Traits<S>::C lds[2 * (F0 > F6 ? (F0 > F7 ? F0 : F7) : (F6 > F7 ? F6 : F7))];
     __shared__ uint4 pre_lds[tb_pre_slots<S, T, NT, NOISE>()];
     const uint32_t r0 = blockIdx.x / (uint32_t)b.slots * (uint32_t)b.slots;
@@ -516,13 +544,28 @@ __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb_bat
     const uint64_t t0 = NOISE ? (b.t_dev ? *b.t_dev + b.t : b.t) : 0;
     if constexpr (WIDTHS) {
         const int width = item_width(w);
-        if (width == 1) return tb_item<S, 8, TY6, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, item_bz(w), t0, lds, pre_lds);
-        if (width == 2) return tb_item<S, 12, TY7, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, item_bz(w), t0, lds, pre_lds);
+        if (width == 1) return tb_item<S, d6.txg, TY6, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, item_bz(w), t0, lds, pre_lds);
+        if (width == 2) return tb_item<S, d7.txg, TY7, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, item_bz(w), t0, lds, pre_lds);
     }
     tb_item<S, TXG, TY, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, WIDTHS ? item_bz(w) : w.bz, t0, lds, pre_lds);
 }
 
 // ------------------------------------------------------------------ launch
+// f(shape, T) as constants, where the kernel exists; else `none`.
+template <typename S, bool BATCH, int SHAPE, int T, typename R, typename F>
+static R with_kernel(int shape, int depth, R none, const F &f)
+{
+    if constexpr (T > k_tb_depth) {
+        return none;
+    } else if constexpr (SHAPE > k_tb_shapes + k_tb_narrow) {
+        return with_kernel<S, BATCH, 1, T + 1>(shape, depth, none, f);
+    } else {
+        if (shape != SHAPE || depth != T) return with_kernel<S, BATCH, SHAPE + 1, T>(shape, depth, none, f);
+        if constexpr (T <= tb_max_T_shape<S, BATCH>(SHAPE)) return f(Phase<SHAPE>{}, Phase<T>{});
+        else return none;
+    }
+}
+
 template <typename S, int TXG, int TY, int T, int NT>
 static hipError_t launch_tb_t(const void *u, const void *v, void *un, void *vn, StepArgs a, hipStream_t st)
 {
@@ -544,70 +587,15 @@ static hipError_t launch_tb_t(const void *u, const void *v, void *un, void *vn, 
     else return go(Phase<NOISE_64>{});
 }
 
-// Shapes per T (output x-groups, rows, lanes): the level-0 region
-// (TXG + 2) x (TY + 2T) fills the workgroup.
-//   shape 1: TXG=16,  256 lanes, region 18 x 14
-//   shape 2: TXG=16,  512 lanes, region 18 x 28
-//   shape 3: TXG=32,  512 lanes, region 34 x 14
-//   shape 4: TXG=16,  768 lanes, region 18 x 42
-//   shape 5: TXG=16, 1024 lanes, region 18 x 56
-//   shape 6: TXG=8,   512 lanes, region 10 x 51 \\ one to three steps, single grids: for
-//   shape 7: TXG=12,  512 lanes, region 14 x 36 / rows that 64 cells cover badly
-// One workgroup per CU: NT lanes leave 512 / ceil(NT / 256) registers per
-// lane. The deepest fusion whose registers fit that budget without spills
-// (batched sweeps take the larger shapes one step less deep):
-template <typename S, int NT, bool BATCH> constexpr int tb_max_T_of()
-{
-    if (NT <= 512) return 4;
-    if (NT <= 768) return sizeof(S) == 8 ? (BATCH ? 1 : 2) : (BATCH ? 3 : 4);
-    return sizeof(S) == 8 ? (BATCH ? 0 : 1) : (BATCH ? 2 : 3);
-}
-constexpr int shape_lanes(int shape) { return shape == 1 ? 256 : shape == 4 ? 768 : shape == 5 ? 1024 : 512; }
-template <typename S, bool BATCH> constexpr int tb_max_T_shape(int shape)
-{
-    return shape <= 3   ? tb_max_T_of<S, 512, BATCH>()
-           : shape == 4 ? tb_max_T_of<S, 768, BATCH>()
-           : shape == 5 ? tb_max_T_of<S, 1024, BATCH>()
-                        : (BATCH ? 0 : 3);
-}
-
-template <typename S, int T>
-static hipError_t dispatch_tb_shape(int shape, const void *u, const void *v, void *un, void *vn, const StepArgs &a,
-                                    hipStream_t st)
-{
-    switch (shape) {
-    case 1: return launch_tb_t<S, 16, 14 - 2 * T, T, 256>(u, v, un, vn, a, st);
-    case 2: return launch_tb_t<S, 16, 28 - 2 * T, T, 512>(u, v, un, vn, a, st);
-    case 3: return launch_tb_t<S, 32, 14 - 2 * T, T, 512>(u, v, un, vn, a, st);
-    case 4:
-        if constexpr (T <= tb_max_T_of<S, 768, false>())
-            return launch_tb_t<S, 16, 42 - 2 * T, T, 768>(u, v, un, vn, a, st);
-        break;
-    case 5:
-        if constexpr (T <= tb_max_T_of<S, 1024, false>())
-            return launch_tb_t<S, 16, 56 - 2 * T, T, 1024>(u, v, un, vn, a, st);
-        break;
-    case 6:
-        if constexpr (T <= 3) return launch_tb_t<S, 8, 51 - 2 * T, T, 512>(u, v, un, vn, a, st);
-        break;
-    case 7:
-        if constexpr (T <= 3) return launch_tb_t<S, 12, 36 - 2 * T, T, 512>(u, v, un, vn, a, st);
-        break;
-    }
-    return hipErrorInvalidValue;
-}
-
 template <typename S>
-hipError_t dispatch_tb_T(int T, int shape, const void *u, const void *v, void *un, void *vn,
-                                const StepArgs &a, hipStream_t st)
+hipError_t dispatch_tb_T(int T, int shape, const void *u, const void *v, void *un, void *vn, const StepArgs &a,
+                         hipStream_t st)
 {
-    switch (T) {
-    case 1: return dispatch_tb_shape<S, 1>(shape, u, v, un, vn, a, st);
-    case 2: return dispatch_tb_shape<S, 2>(shape, u, v, un, vn, a, st);
-    case 3: return dispatch_tb_shape<S, 3>(shape, u, v, un, vn, a, st);
-    case 4: return dispatch_tb_shape<S, 4>(shape, u, v, un, vn, a, st);
-    }
-    return hipErrorInvalidValue;
+    return with_kernel<S, false, 1, 1>(shape, T, hipErrorInvalidValue, [&](auto sh, auto depth) {
+        constexpr TbDef d = tb_def(decltype(sh)::value);
+        constexpr int D = decltype(depth)::value;
+        return launch_tb_t<S, d.txg, d.rows - 2 * D, D, d.lanes>(u, v, un, vn, a, st);
+    });
 }
 
 template <typename S, int TXG, int TY, int T, int NT>
@@ -632,34 +620,14 @@ static hipError_t launch_tb_batch_t(const BatchArgs &b, hipStream_t st)
     else return go(Phase<NOISE_64>{});
 }
 
-template <typename S, int T>
-static hipError_t batch_shape(int shape, const BatchArgs &b, hipStream_t st)
-{
-    switch (shape) {
-    case 1: return launch_tb_batch_t<S, 16, 14 - 2 * T, T, 256>(b, st);
-    case 2: return launch_tb_batch_t<S, 16, 28 - 2 * T, T, 512>(b, st);
-    case 3: return launch_tb_batch_t<S, 32, 14 - 2 * T, T, 512>(b, st);
-    case 4:
-        if constexpr (T <= tb_max_T_of<S, 768, true>()) return launch_tb_batch_t<S, 16, 42 - 2 * T, T, 768>(b, st);
-        break;
-    case 5:
-        if constexpr (T <= tb_max_T_of<S, 1024, true>())
-            return launch_tb_batch_t<S, 16, 56 - 2 * T, T, 1024>(b, st);
-        break;
-    }
-    return hipErrorInvalidValue;
-}
-
 template <typename S>
 hipError_t batch_T(int T, int shape, const BatchArgs &b, hipStream_t st)
 {
-    switch (T) {
-    case 1: return batch_shape<S, 1>(shape, b, st);
-    case 2: return batch_shape<S, 2>(shape, b, st);
-    case 3: return batch_shape<S, 3>(shape, b, st);
-    case 4: return batch_shape<S, 4>(shape, b, st);
-    }
-    return hipErrorInvalidValue;
+    return with_kernel<S, true, 1, 1>(shape, T, hipErrorInvalidValue, [&](auto sh, auto depth) {
+        constexpr TbDef d = tb_def(decltype(sh)::value);
+        constexpr int D = decltype(depth)::value;
+        return launch_tb_batch_t<S, d.txg, d.rows - 2 * D, D, d.lanes>(b, st);
+    });
 }
 
 template <typename S, int TXG, int TY, int T, int NT>
@@ -671,33 +639,14 @@ static int occ_t()
     return n > 0 ? n : 1;
 }
 
-template <typename S, int T>
-static int occ_shape(int shape)
-{
-    switch (shape) {
-    case 1: return occ_t<S, 16, 14 - 2 * T, T, 256>();
-    case 2: return occ_t<S, 16, 28 - 2 * T, T, 512>();
-    case 3: return occ_t<S, 32, 14 - 2 * T, T, 512>();
-    case 4:
-        if constexpr (T <= tb_max_T_of<S, 768, true>()) return occ_t<S, 16, 42 - 2 * T, T, 768>();
-        break;
-    case 5:
-        if constexpr (T <= tb_max_T_of<S, 1024, true>()) return occ_t<S, 16, 56 - 2 * T, T, 1024>();
-        break;
-    }
-    return 1;
-}
-
 template <typename S>
 int occ_T(int T, int shape)
 {
-    switch (T) {
-    case 1: return occ_shape<S, 1>(shape);
-    case 2: return occ_shape<S, 2>(shape);
-    case 3: return occ_shape<S, 3>(shape);
-    case 4: return occ_shape<S, 4>(shape);
-    }
-    return 1;
+    return with_kernel<S, true, 1, 1>(shape, T, 1, [&](auto sh, auto depth) {
+        constexpr TbDef d = tb_def(decltype(sh)::value);
+        constexpr int D = decltype(depth)::value;
+        return occ_t<S, d.txg, d.rows - 2 * D, D, d.lanes>();
+    });
 }
 
 template <typename S, int TXG, int TY, int T, int NT>
@@ -710,39 +659,14 @@ static int occ_single_t(bool noise)
     return e == hipSuccess && n > 0 ? n : 0;
 }
 
-template <typename S, int T>
-static int occ_single_shape(int shape, bool noise)
-{
-    switch (shape) {
-    case 1: return occ_single_t<S, 16, 14 - 2 * T, T, 256>(noise);
-    case 2: return occ_single_t<S, 16, 28 - 2 * T, T, 512>(noise);
-    case 3: return occ_single_t<S, 32, 14 - 2 * T, T, 512>(noise);
-    case 4:
-        if constexpr (T <= tb_max_T_of<S, 768, false>()) return occ_single_t<S, 16, 42 - 2 * T, T, 768>(noise);
-        break;
-    case 5:
-        if constexpr (T <= tb_max_T_of<S, 1024, false>()) return occ_single_t<S, 16, 56 - 2 * T, T, 1024>(noise);
-        break;
-    case 6:
-        if constexpr (T <= 3) return occ_single_t<S, 8, 51 - 2 * T, T, 512>(noise);
-        break;
-    case 7:
-        if constexpr (T <= 3) return occ_single_t<S, 12, 36 - 2 * T, T, 512>(noise);
-        break;
-    }
-    return 0;
-}
-
 template <typename S>
 int occ_single_T(int T, int shape, bool noise)
 {
-    switch (T) {
-    case 1: return occ_single_shape<S, 1>(shape, noise);
-    case 2: return occ_single_shape<S, 2>(shape, noise);
-    case 3: return occ_single_shape<S, 3>(shape, noise);
-    case 4: return occ_single_shape<S, 4>(shape, noise);
-    }
-    return 0;
+    return with_kernel<S, false, 1, 1>(shape, T, 0, [&](auto sh, auto depth) {
+        constexpr TbDef d = tb_def(decltype(sh)::value);
+        constexpr int D = decltype(depth)::value;
+        return occ_single_t<S, d.txg, d.rows - 2 * D, D, d.lanes>(noise);
+    });
 }
 
 // The kernels of a storage type are instantiated in an object of their own
@@ -771,21 +695,13 @@ GS_TB_TYPE(extern, bf16, GS_TB_BATCH)
 GS_TB_TYPE(extern, f16, GS_TB_BATCH)
 GS_TB_TYPE(extern, bf16c, GS_TB_SINGLE)
 
-int num_tb_shapes() { return 5; }
-int num_tb_narrow() { return 2; }
+int num_tb_shapes() { return k_tb_shapes; }
+int num_tb_narrow() { return k_tb_narrow; }
 
 TileShape tb_shape(int shape, int T)
 {
-    switch (shape) {
-    case 1: return TileShape{64, 14 - 2 * T};
-    case 2: return TileShape{64, 28 - 2 * T};
-    case 3: return TileShape{128, 14 - 2 * T};
-    case 4: return TileShape{64, 42 - 2 * T};
-    case 5: return TileShape{64, 56 - 2 * T};
-    case 6: return TileShape{32, 51 - 2 * T};
-    case 7: return TileShape{48, 36 - 2 * T};
-    }
-    return TileShape{0, 0};
+    if (shape < 1 || shape > k_tb_shapes + k_tb_narrow) return TileShape{0, 0};
+    return TileShape{4 * tb_def(shape).txg, tb_def(shape).rows - 2 * T};
 }
 
 template <bool BATCH> static int max_T_for(int shape, int storage)
@@ -814,8 +730,6 @@ hipError_t launch_tblock_batch(int storage, int T, int shape, const BatchArgs &b
     }
     return hipErrorInvalidValue;
 }
-
-int tb_shape_lanes(int shape) { return shape_lanes(shape); }
 
 int tb_occupancy(int storage, int T, int shape, bool noise)
 {
