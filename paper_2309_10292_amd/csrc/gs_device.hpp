@@ -1,7 +1,6 @@
 // Device-side building blocks of the Gray-Scott kernels for gfx950:
-// storage-type conversion, Philox4x32-10 noise, FP64 division by 6, the
-// compensated FP32 Laplacian, and a z-streaming tile of one field (global ->
-// registers -> LDS) shared by the step and Laplacian kernels.
+// storage-type conversion, Philox4x32-10 noise, FP64 division by 6, and the
+// Laplacians and the Euler step that all stencil kernels share.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -140,10 +139,10 @@ __device__ __forceinline__ float noise_term_f32(uint32_t w, float s, float h)
     return __builtin_fmaf((float)(int32_t)w, s, h);
 }
 
-// The FP32 step's coefficients, held in vector registers: on gfx950 an FP32
-// add, multiply or fma whose operands are vector registers or constants issues
-// every 2.5 clocks per SIMD, and every 4.3 with a scalar register among them
-// (measured, two or more waves per SIMD).
+// The FP32 step's coefficients. Most kernels hold them in vector registers: on
+// gfx950 an FP32 add, multiply or fma whose operands are vector registers or
+// constants issues every 2.5 clocks per SIMD, and every 4.3 with a scalar register
+// among them (measured, two or more waves per SIMD).
 struct CoefF32 {
     float Du6, Dv6, F, FK, dt; // Du / 6, Dv / 6
     float ns, nh;              // noise 2^-31, noise 2^-32

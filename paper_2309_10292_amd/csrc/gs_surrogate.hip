@@ -1190,8 +1190,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce(const float *__restrict__ pa
 // Bias gradient: fixed-order fold of the per-workgroup channel sums; 32
 // groups of lanes each sum every 32nd workgroup in order, then lane c adds
 // the 32 group sums of channel c in order.
-__global__ __launch_bounds__(1024) void colsum_reduce(const float *__restrict__ part, int nblk, int cout,
-                                                     float *__restrict__ gb)
+__global__ __launch_bounds__(1024) void colsum_reduce(const float *__restrict__ part, int nblk, float *__restrict__ gb)
 {
     __shared__ double red[32][32];
     const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
@@ -1199,7 +1198,7 @@ __global__ __launch_bounds__(1024) void colsum_reduce(const float *__restrict__ 
     for (int b = g; b < nblk; b += 32) s += part[(size_t)b * 32 + c];
     red[g][c] = s;
     __syncthreads();
-    if (g == 0 && c < cout) {
+    if (g == 0) {
         double t = 0.0;
         for (int i = 0; i < 32; ++i) t += red[i][c];
         gb[c] = (float)t;
@@ -1274,17 +1273,18 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ p, const 
 // weights W'[ci][co][d] = W[co][ci][26 - d] (input channels = co).
 // lo_pairs: input channels cin .. cin + lo_pairs - 1 carry the low parts of
 // channels 0 .. lo_pairs - 1 and take their weights.
-__global__ __launch_bounds__(256) void repack(const float *__restrict__ W, int cout, int cin, int cins, int nt,
-                                              int nch, int dgrad, int lo_pairs, u16 *__restrict__ out)
+__global__ __launch_bounds__(256) void repack(const float *__restrict__ W, int cout, int cin, int cins, int nch,
+                                              int dgrad, int lo_pairs, u16 *__restrict__ out)
 {
-    const int total = nch * nt * 64 * 8;
+    constexpr int NT = 2;
+    const int total = nch * NT * 64 * 8;
     for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-        const int j = e % 8, lane = (e / 8) % 64, t = (e / 512) % nt, c = e / (512 * nt);
+        const int j = e % 8, lane = (e / 8) % 64, t = (e / 512) % NT, c = e / (512 * NT);
         const int k = 32 * c + 8 * (lane / 16) + j;
-        // two tiles: row m of tile t is output channel 8 (m / 4) + 4 t + m % 4, so
-        // that a lane's accumulators of both tiles are 8 consecutive channels
+        // row m of tile t is output channel 8 (m / 4) + 4 t + m % 4, so that a lane's
+        // accumulators of both tiles are 8 consecutive channels
         const int m = lane % 16;
-        const int d = k / cins, kc = k % cins, n = nt == 2 ? 8 * (m / 4) + 4 * t + m % 4 : m;
+        const int d = k / cins, kc = k % cins, n = 8 * (m / 4) + 4 * t + m % 4;
         float w = 0.f;
         if (d < 27) {
             if (!dgrad) {
@@ -1358,10 +1358,10 @@ static int chunk_planes(int nz, size_t cols, size_t slots, int unit)
     return best;
 }
 
-hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a, int cus, hipStream_t st)
+hipError_t launch_conv(int cin, int mode, int io_f64, const ConvArgs &a, int cus, hipStream_t st)
 {
     if (a.geo.nx % PX != 0 || a.geo.nz < 4) return hipErrorInvalidValue;
-    if (nt == 2 && mode != MODE_OUT && (cin == 8 || cin == 32)) {
+    if (mode != MODE_OUT && (cin == 8 || cin == 32)) {
         ConvArgs b = a;
         const int waves = cin == 8 ? C8_WAVES : C32_WAVES, py = waves * (cin == 8 ? C8_RW : C32_RW);
         const size_t cols = (size_t)(a.geo.nx / PX) * ((a.geo.ny + py - 1) / py) * a.nsamp;
@@ -1378,7 +1378,7 @@ hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a,
         };
         return mode == MODE_HIDDEN ? go(IntC<MODE_HIDDEN>{}) : mode == MODE_ACT ? go(IntC<MODE_ACT>{}) : go(IntC<MODE_DGRAD>{});
     }
-    if (cin == 32 && nt == 1 && mode == MODE_OUT) {
+    if (cin == 32 && mode == MODE_OUT) {
         ConvArgs b = a;
         const int ng = a.geo.nx / 16, tg = ng <= OUT_NG ? ng : OUT_NG - 2;
         const size_t cols = (size_t)((ng + tg - 1) / tg) * ((a.geo.ny + OUT_TY - 1) / OUT_TY) * a.nsamp;
@@ -1429,9 +1429,9 @@ hipError_t launch_wgrad_reduce(const float *part, float *gW, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_bias_reduce(const float *bpart, int cout, float *gb, hipStream_t st)
+hipError_t launch_bias_reduce(const float *bpart, float *gb, hipStream_t st)
 {
-    hipLaunchKernelGGL(colsum_reduce, dim3(1), dim3(1024), 0, st, bpart, wgrad_blocks(), cout, gb);
+    hipLaunchKernelGGL(colsum_reduce, dim3(1), dim3(1024), 0, st, bpart, wgrad_blocks(), gb);
     return hipGetLastError();
 }
 
@@ -1471,11 +1471,11 @@ hipError_t launch_repack_out(const float *W, uint16_t *out, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_repack(const float *W, int cout, int cin, int cins, int nt, int nch, int dgrad, int lo_pairs,
-                         uint16_t *out, hipStream_t st)
+hipError_t launch_repack(const float *W, int cout, int cin, int cins, int nch, int dgrad, int lo_pairs, uint16_t *out,
+                         hipStream_t st)
 {
-    const int total = nch * nt * 512;
-    hipLaunchKernelGGL(repack, dim3(grid_cap(total, 256, 1024)), dim3(256), 0, st, W, cout, cin, cins, nt, nch, dgrad,
+    const int total = nch * 2 * 512;
+    hipLaunchKernelGGL(repack, dim3(grid_cap(total, 256, 1024)), dim3(256), 0, st, W, cout, cin, cins, nch, dgrad,
                        lo_pairs, out);
     return hipGetLastError();
 }

@@ -44,14 +44,14 @@ struct WgradArgs {
 };
 
 // (cus: compute units of the device)
-hipError_t launch_conv(int cin, int nt, int mode, int io_f64, const ConvArgs &a, int cus, hipStream_t st);
+hipError_t launch_conv(int cin, int mode, int io_f64, const ConvArgs &a, int cus, hipStream_t st);
 int wgrad_blocks();
 hipError_t launch_wgrad(const WgradArgs &a, hipStream_t st); // 32 -> 32 layers
 // Weight and bias gradients of the first layer (8 stored input channels) or the
 // last (8 stored output channels), from the tensors in `a`.
 hipError_t launch_wgrad_edge(bool first, const WgradArgs &a, float *gW, float *gb, int cus, hipStream_t st);
 hipError_t launch_wgrad_reduce(const float *part, float *gW, hipStream_t st);
-hipError_t launch_bias_reduce(const float *bpart, int cout, float *gb, hipStream_t st);
+hipError_t launch_bias_reduce(const float *bpart, float *gb, hipStream_t st); // 32 channels
 // The samples' (F, k) go with the launch, up to FK_PER_LAUNCH samples at once:
 // no device copy of them to wait for (a prediction at 128^3 lost 35 us to it).
 constexpr int FK_PER_LAUNCH = 64;
@@ -67,8 +67,8 @@ hipError_t launch_adam(float *p, const float *g, float *m, float *v, int n, floa
                        float c1, float c2, hipStream_t st);
 // The output layer's forward weights (conv_out_kernel's order, 6 x 512 values).
 hipError_t launch_repack_out(const float *W, uint16_t *out, hipStream_t st);
-hipError_t launch_repack(const float *W, int cout, int cin, int cins, int nt, int nch, int dgrad, int lo_pairs,
-                         uint16_t *out, hipStream_t st);
+hipError_t launch_repack(const float *W, int cout, int cin, int cins, int nch, int dgrad, int lo_pairs, uint16_t *out,
+                         hipStream_t st);
 
 } // namespace nn
 } // namespace gs

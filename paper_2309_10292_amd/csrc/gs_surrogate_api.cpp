@@ -117,12 +117,12 @@ hipError_t repack_all(gs_surrogate *s)
     const float *P = at<float>(s, s->L.par);
     hipError_t e = hipSuccess;
     for (int l = 0; l < 3 && e == hipSuccess; ++l)
-        e = gs::nn::launch_repack(P + w_off(l), k_chan[l + 1], k_chan[l], k_cins[l], k_nt[l], nchunks(k_cins[l]), 0,
+        e = gs::nn::launch_repack(P + w_off(l), k_chan[l + 1], k_chan[l], k_cins[l], nchunks(k_cins[l]), 0,
                                   l == 0 ? k_lo_pairs : 0, at<uint16_t>(s, s->L.wf[l]), s->stream);
     if (e == hipSuccess) e = gs::nn::launch_repack_out(P + w_off(3), at<uint16_t>(s, s->L.wf[3]), s->stream);
     for (int l = 1; l < 4 && e == hipSuccess; ++l) {
         const int cins = l == 3 ? 8 : 32;
-        e = gs::nn::launch_repack(P + w_off(l), k_chan[l + 1], k_chan[l], cins, 2, nchunks(cins), 1, 0,
+        e = gs::nn::launch_repack(P + w_off(l), k_chan[l + 1], k_chan[l], cins, nchunks(cins), 1, 0,
                                   at<uint16_t>(s, s->L.wd[l]), s->stream);
     }
     return e;
@@ -166,7 +166,7 @@ hipError_t forward(gs_surrogate *s, int32_t nsamp, int io_f64, const void *u, co
         a.bias = P + b_off(l);
         a.zout = keep_pre ? at<uint16_t>(s, s->L.z[l]) : nullptr;
         a.aout = at<uint16_t>(s, s->L.a[l]);
-        e = launch_conv(k_cins[l], 2, keep_pre ? MODE_HIDDEN : MODE_ACT, 0, a, s->cus, s->stream);
+        e = launch_conv(k_cins[l], keep_pre ? MODE_HIDDEN : MODE_ACT, 0, a, s->cus, s->stream);
         in = a.aout;
     }
     if (e == hipSuccess) {
@@ -180,7 +180,7 @@ hipError_t forward(gs_surrogate *s, int32_t nsamp, int io_f64, const void *u, co
         a.res_v = v;
         a.out_u = uo;
         a.out_v = vo;
-        e = launch_conv(32, 1, MODE_OUT, io_f64, a, s->cus, s->stream);
+        e = launch_conv(32, MODE_OUT, io_f64, a, s->cus, s->stream);
     }
     return e;
 }
@@ -313,7 +313,7 @@ gs_status gs_surrogate_loss_grad(gs_surrogate *s, int32_t nsamp, const float *u,
         } else {
             e = launch_wgrad(w, s->stream);
             if (e == hipSuccess) e = launch_wgrad_reduce(wpart, G + w_off(l), s->stream);
-            if (e == hipSuccess) e = launch_bias_reduce(cpart, k_chan[l + 1], G + b_off(l), s->stream);
+            if (e == hipSuccess) e = launch_bias_reduce(cpart, G + b_off(l), s->stream);
         }
         if (l == 0 || e != hipSuccess) break;
         ConvArgs a = {};
@@ -323,7 +323,7 @@ gs_status gs_surrogate_loss_grad(gs_surrogate *s, int32_t nsamp, const float *u,
         a.wpack = at<uint16_t>(s, s->L.wd[l]);
         a.zprev = at<uint16_t>(s, s->L.z[l - 1]);
         a.aout = at<uint16_t>(s, s->L.dz[l - 1]);
-        e = launch_conv(couts, 2, MODE_DGRAD, 0, a, s->cus, s->stream);
+        e = launch_conv(couts, MODE_DGRAD, 0, a, s->cus, s->stream);
         dz = a.aout;
         couts = 32;
     }
