@@ -128,7 +128,7 @@ template <typename S, int TXG, int TY, int T, int NT> struct TbGeom {
 // of the first of the T steps. `lds` holds 2 * TbGeom::FIELD elements and
 // `pre_lds` 4 * NT 16-byte slots where tb_dma() holds (else it is unused).
 // Every lane of the workgroup must call it (it contains barriers).
-template <typename S, int TXG, int TY, int T, int NT, int NOISE, bool UNIT_DT>
+template <typename S, int TXG, int TY, int T, int NT, int NOISE, bool UNIT_DT, bool LINE>
 __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__restrict__ v, S *__restrict__ un,
                                         S *__restrict__ vn, const StepArgs &a, int x0, int y0, int z0, int ze,
                                         uint64_t t0, typename Traits<S>::C *__restrict__ lds,
@@ -411,11 +411,11 @@ __device__ __forceinline__ void tb_tile(const S *__restrict__ u, const S *__rest
         }
     };
 
-    // The straight-line variant needs more registers; it is used where they
-    // fit the budget (up to 512 lanes; FP64 up to 3 levels; not FP32 storage,
+    // The straight-line variant (LINE: not ruled out by the caller) needs more
+    // registers; it is used where they fit the budget (up to 512 lanes; FP64 up to 3 levels; not FP32 storage,
     // whose FP64 sums would spill 40 registers at two levels in 128: 530 against
     // 272 us per step at 512^3 with noise).
-    constexpr bool full_ok = NT <= 512 && (sizeof(S) == 2 || (sizeof(S) == 8 && T <= 3));
+    constexpr bool full_ok = LINE && NT <= 512 && (sizeof(S) == 2 || (sizeof(S) == 8 && T <= 3));
     const int wave_depth = __builtin_amdgcn_readfirstlane(dep);
     if (full_ok && wave_depth == T) {
         for (int i = i0; i <= i_end; i += 3) {
@@ -444,7 +444,7 @@ template <typename S, int T, int NT> constexpr int tb_min_waves()
 
 // The output tile (bx, by) and chunk bz of the grid in `a` by this workgroup;
 // `lds` and `pre_lds` as tb_tile takes them.
-template <typename S, int TXG, int TY, int T, int NT, int NOISE>
+template <typename S, int TXG, int TY, int T, int NT, int NOISE, bool LINE = true>
 __device__ __forceinline__ void tb_item(const S *__restrict__ u, const S *__restrict__ v, S *__restrict__ un,
                                         S *__restrict__ vn, const StepArgs &a, int bx, int by, int bz, uint64_t t0,
                                         typename Traits<S>::C *lds, uint4 *pre_lds)
@@ -454,11 +454,12 @@ __device__ __forceinline__ void tb_item(const S *__restrict__ u, const S *__rest
     // without the dt products.
     if constexpr (sizeof(S) == 8) {
         if (a.dt == 1.0) {
-            tb_tile<S, TXG, TY, T, NT, NOISE, true>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds, pre_lds);
+            tb_tile<S, TXG, TY, T, NT, NOISE, true, LINE>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds,
+                                                          pre_lds);
             return;
         }
     }
-    tb_tile<S, TXG, TY, T, NT, NOISE, false>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds, pre_lds);
+    tb_tile<S, TXG, TY, T, NT, NOISE, false, LINE>(u, v, un, vn, a, bx * (TXG * 4), by * TY, z0, ze, t0, lds, pre_lds);
 }
 
 // LDS-DMA prefetch area of a workgroup (tb_dma), in 16-byte slots.
@@ -504,6 +505,16 @@ template <typename S, bool BATCH> constexpr int tb_max_T_shape(int shape)
     return sizeof(S) == 8 ? (BATCH ? 0 : 1) : (BATCH ? 2 : 3);
 }
 
+// The kernel whose launches of more workgroups than are resident do without straight-line
+// levels: FP64 without noise at three steps in 256 lanes takes 283 registers with them,
+// which let one workgroup into a CU, and 220 without, two (16 grids of 128^3 in chunks of
+// 64 planes: 143 us per step with them, 111 without; 256 items, all resident: 8.3 with
+// them, 9.1 without).
+template <typename S, int T, int NT, int NOISE> constexpr bool tb_packs()
+{
+    return sizeof(S) == 8 && T == 3 && NT == 256 && NOISE == NOISE_OFF;
+}
+
 // Sweep over many independent simulations: one workgroup per work item (one
 // tile x z-chunk of one simulation), items sorted by decreasing cost, so that
 // the places that fall free last are filled with the cheapest ones. Items are
@@ -513,10 +524,12 @@ template <typename S, bool BATCH> constexpr int tb_max_T_shape(int shape)
 // host picks a grid's width), so that one launch covers grids of 80 cells with six
 // tiles and grids of 128 with twelve: 32 grids of 32^3 to 192^3 in FP64, 12 steps,
 // 2.18 -> 2.03 ms. A launch without such items takes the kernel without them (32 x
-// 128^3 FP32 with it: 1.97 -> 2.00 ms).
-template <typename S, int TXG, int TY, int T, int NT, int NOISE, bool WIDTHS>
+// 128^3 FP32 with it: 1.97 -> 2.00 ms). PACKED: without straight-line levels (tb_packs).
+enum { BATCH_PLAIN = 0, BATCH_WIDTHS = 1, BATCH_PACKED = 2 };
+template <typename S, int TXG, int TY, int T, int NT, int NOISE, int FORM>
 __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb_batch(BatchArgs b)
 {
+    constexpr bool WIDTHS = FORM == BATCH_WIDTHS;
     constexpr TbDef d6 = tb_def(k_tb_shapes + 1), d7 = tb_def(k_tb_shapes + 2);
     static_assert(!WIDTHS || (NT == d6.lanes && NT == d7.lanes), "the widths share a launch");
     constexpr int TY6 = d6.rows - 2 * T, TY7 = d7.rows - 2 * T;
@@ -547,7 +560,8 @@ __global__ __launch_bounds__(NT, (tb_min_waves<S, T, NT>())) void stencil_tb_bat
         if (width == 1) return tb_item<S, d6.txg, TY6, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, item_bz(w), t0, lds, pre_lds);
         if (width == 2) return tb_item<S, d7.txg, TY7, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, item_bz(w), t0, lds, pre_lds);
     }
-    tb_item<S, TXG, TY, T, NT, NOISE>(u, v, un, vn, a, w.bx, w.by, WIDTHS ? item_bz(w) : w.bz, t0, lds, pre_lds);
+    tb_item<S, TXG, TY, T, NT, NOISE, FORM != BATCH_PACKED>(u, v, un, vn, a, w.bx, w.by, WIDTHS ? item_bz(w) : w.bz, t0,
+                                                             lds, pre_lds);
 }
 
 // ------------------------------------------------------------------ launch
@@ -606,11 +620,17 @@ static hipError_t launch_tb_batch_t(const BatchArgs &b, hipStream_t st)
     auto go = [&](auto mode) {
         if constexpr (TXG == 16 && NT == 512 && T <= 3) {
             if (b.narrow) {
-                hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value, true>), dim3(grid), dim3(NT), 0, st, b);
+                hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value, BATCH_WIDTHS>), dim3(grid), dim3(NT), 0, st, b);
                 return hipGetLastError();
             }
         }
-        hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value, false>), dim3(grid), dim3(NT), 0, st, b);
+        if constexpr (tb_packs<S, T, NT, decltype(mode)::value>()) {
+            if (b.n_items > b.slots) {
+                hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value, BATCH_PACKED>), dim3(grid), dim3(NT), 0, st, b);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((stencil_tb_batch<S, TXG, TY, T, NT, decltype(mode)::value, BATCH_PLAIN>), dim3(grid), dim3(NT), 0, st, b);
         return hipGetLastError();
     };
     if (b.coef.noise == 0.0) return go(Phase<NOISE_OFF>{});
@@ -634,7 +654,7 @@ template <typename S, int TXG, int TY, int T, int NT>
 static int occ_t()
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb_batch<S, TXG, TY, T, NT, NOISE_OFF, false>, NT, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, stencil_tb_batch<S, TXG, TY, T, NT, NOISE_OFF, BATCH_PLAIN>, NT, 0) != hipSuccess)
         return 1;
     return n > 0 ? n : 1;
 }

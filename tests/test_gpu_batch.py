@@ -124,3 +124,21 @@ def test_batch_library_choice(torch, n, dims, storage, noise, zchunk, want):
                 s.step(8)
                 for got, one in zip(b.read(i), s.read()):
                     assert np.array_equal(got, one), (i, max_abs(got, one))
+
+
+@pytest.mark.parametrize("dt", [1.0, 0.5])
+@pytest.mark.parametrize("n", [4, 5])
+def test_batch_three_steps_in_256_lanes(torch, n, dt):
+    """FP64 without noise in the 256-lane tile: 256 work items of 8 planes, all resident, and 320, whose kernel does
+    without straight-line levels; bit for bit the single grids."""
+    from paper_2309_10292_amd import gs
+    sims = [dict(L=64, F=0.02 + 0.005 * i, k=0.05 + 0.002 * i) for i in range(n)]
+    shared = dict(Du=0.2, Dv=0.1, dt=dt, cube_side=20)
+    with gs.Batch(sims, tile=5, tblock=3, zchunk=8, **shared) as b:
+        b.step(7)
+        got = [b.read(i) for i in range(n)]
+    for i, sm in enumerate(sims):
+        with gs.Sim(64, 64, 64, F=sm["F"], k=sm["k"], tile=2, **shared) as s:
+            s.step(7)
+            u, v = s.read()
+        assert np.array_equal(got[i][0], u) and np.array_equal(got[i][1], v), i

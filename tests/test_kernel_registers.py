@@ -50,6 +50,8 @@ def kernels(tmp_path_factory):
     (r"10stencil_tbIdLi16ELi10ELi2ELi256E", 256, 0),
     (r"10stencil_tbI(f|DF16_|NS_4bf16E|NS_5bf16cE)Li16ELi10ELi2ELi256E", 128, 2),
     (r"10stencil_tbI(f|DF16_|NS_4bf16E|NS_5bf16cE)Li(16ELi24|8ELi47|12ELi32)ELi2ELi512E", 128, 2),
+    # two workgroups of the batches' FP64 kernel of three steps in 256 lanes, where more wait than are resident
+    (r"16stencil_tb_batchIdLi16ELi8ELi3ELi256ELi0ELi2E", 256, 0),
     (r"12conv8_kernel", 168, 0),
     (r"18wgrad_shift_kernelILb1E", 168, 0),
     (r"18wgrad_shift_kernelILb0E", 128, 0),
