@@ -223,12 +223,12 @@ gs_status check(gs_sim *s)
 
 // Library choice of the launch configuration before any tuning (from the
 // MI355X autotuner sweeps at 64^3 .. 1024^3, with and without noise): the
-// temporally blocked kernel at every size. Large grids (>= 64 M cells): FP64
+// temporally blocked kernel above the smallest sizes. Large grids (>= 64 M cells): FP64
 // fuses three steps in the 512-lane 64 x 22 tile; with noise the other
 // storage types fuse two steps in the same tile (the Philox blocks of deeper
 // fusion cost more than the traffic they save); without noise the 16-bit types
 // fuse two steps in the 512-lane tile and FP32 three in the 1024-lane one,
-// where two are bound by HBM (1024^3: 1.64 ms per step against 1.80; 640^3 0.46
+// where two are bound by HBM (1024^3: 1.60 ms per step against 1.88; 640^3 0.44
 // against 0.50), unless its tiles of 50 rows cover the grid worse than those of
 // two steps (512^3: 0.24 against 0.22).
 // Smaller grids take the launch that default_stream estimates fastest (where

@@ -195,8 +195,8 @@ def tile_info(tile: int, storage="f64", tblock: int = 1):
 
 
 def tblock_tiles():
-    """Tile indices of the temporally blocked kernel (the first four tiles
-    select the single-step kernel)."""
+    """Tile indices of the kernels that fuse steps: the temporally blocked one
+    and the block kernel (the first four tiles select the single-step kernel)."""
     return list(range(5, int(load().gs_num_tiles()) + 1))
 
 
